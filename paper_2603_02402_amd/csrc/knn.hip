@@ -43,6 +43,7 @@
 #include "rsc_internal.hpp"
 #include "screen_common.hpp"
 #include "screen_fp32.hpp"
+#include "screen_split.hpp"
 
 namespace rsc {
 
@@ -54,6 +55,13 @@ constexpr int kMaxD = 256;       // exact FP32 path (reduced-precision screens: 
 constexpr int kMaxK = 255;       // exact FP32 path (reduced-precision screens: 63)
 constexpr int kMaxDLowp = 128;
 constexpr int kMaxKLowp = 63;
+// Rows from which the exact search of one matrix orders them (knn_run).
+constexpr int64_t kOrderRows = 16384;
+// Workgroups the split screen asks for before it stops splitting the
+// references: fewer leave CUs idle, more multiply the candidate lists the
+// rerank reads (10k rows: screen + rerank 0.34 ms at 128, 0.47 at 256, 0.74
+// at 512; 50k rows: 2.15 / 2.08 ms at 128 / 256).
+constexpr int64_t kSplitWant = 128;
 constexpr int kEscalateCap = 8192;  // rows handled by the escalation screen
 constexpr int kEscalateSplits = 16;
 constexpr int kEscalateWidth = 64;
@@ -68,6 +76,7 @@ __host__ __device__ inline int norm_rows(int d) { return d <= 128 ? kNormRows : 
 
 __global__ __launch_bounds__(64) void k_norms(const float *__restrict__ R, int64_t nr, int d,
                                               float *__restrict__ nrow, uint32_t *__restrict__ max_norm_bits) {
+    // nrow may be null: only the largest norm is wanted
     __shared__ float buf[kNormBuf];
     const int lane = threadIdx.x;
     const int nrb = norm_rows(d);
@@ -84,7 +93,7 @@ __global__ __launch_bounds__(64) void k_norms(const float *__restrict__ R, int64
             s += x * x;
         }
         nf = (float)s;
-        nrow[r0 + lane] = nf;
+        if (nrow) nrow[r0 + lane] = nf;
     }
     const float m = wave_max(sqrtf(nf));
     if (lane == 0) atomicMax(max_norm_bits, __float_as_uint(m));
@@ -192,6 +201,8 @@ __global__ void k_init_counters(KnnCounters *c) {
         c->max_norm_bits = 0u;
         c->flagged2 = 0;
         c->rescanned = 0;
+        c->query_norm_bits = 0u;
+        c->wide = 0;
     }
 }
 
@@ -214,6 +225,7 @@ __global__ __launch_bounds__(256, W) void k_screen_fp32(ScreenArgs a) {
     // Per-lane queue of keys that beat the lane's threshold (see LaneTopK).
     __shared__ float2 qbuf[kQueueCap * 256];
     constexpr int QG = kScreenWaves * 32;
+    if (a.only_wide && a.kc->wide == 0) return;
     const int tid = threadIdx.x;
     const int wave = tid >> 6, c = tid & 31;
     const int p = blockIdx.y;
@@ -350,6 +362,13 @@ __global__ __launch_bounds__(256) void k_rerank(RerankArgs a) {
     const double xn = sqrt(xx) * (1.0 + 1e-12);
     const double ymax = (double)__uint_as_float(a.counters->max_norm_bits) * (1.0 + 1e-6);
     const bool cosine = a.metric == RSC_COSINE;
+    // units and error bound of the screened keys
+    const bool split = a.split && a.counters->wide == 0;
+    const double kscale = split ? ldexp(1.0, -2 * scr::split_exponent(a.counters)) : 1.0;
+    const double eps_coef = split ? a.split_eps : a.eps_coef;
+    const double cosine_eps = split ? a.split_cosine_eps : a.cosine_eps;
+    const double eps_abs =
+        split ? a.split_abs * fmax((double)__uint_as_float(a.counters->query_norm_bits), ymax) : 0.0;
     // cosine: the query's squared norm summed in dimension order (as every
     // pair's distance below and the oracle compute it)
     double cxx = 0.0;
@@ -429,12 +448,12 @@ __global__ __launch_bounds__(256) void k_rerank(RerankArgs a) {
                 const bool zero = cxx == 0.0 || yy == 0.0;
                 d2 = zero ? 1.0 : __dsub_rn(1.0, __ddiv_rn(sxy, __dmul_rn(__dsqrt_rn(cxx), __dsqrt_rn(yy))));
                 // the screen ranked 2 D - 1 (unit vectors) up to cosine_eps
-                if (!zero) ratio = fmaxf(ratio, (float)(fabs((double)key - (2.0 * d2 - 1.0)) / a.cosine_eps));
+                if (!zero) ratio = fmaxf(ratio, (float)(fabs((double)key * kscale - (2.0 * d2 - 1.0)) / cosine_eps));
             } else {
                 d2 = s2;
                 const double yn = sqrt(yy);
-                const double err_bound = a.eps_coef * (2.0 * xn * yn + yy) + 1e-300;
-                ratio = fmaxf(ratio, (float)(fabs((double)key - (d2 - xx)) / err_bound));
+                const double err_bound = eps_coef * (2.0 * xn * yn + yy) + eps_abs * (2.0 * xn + yn) + 1e-300;
+                ratio = fmaxf(ratio, (float)(fabs((double)key * kscale - (d2 - xx)) / err_bound));
             }
         }
         bitonic_sort64(d2, jj, lane);
@@ -444,7 +463,8 @@ __global__ __launch_bounds__(256) void k_rerank(RerankArgs a) {
     if (lane == 0 && ratio > 0.f) atomicMax(&a.counters->max_ratio_bits, __float_as_uint(ratio));
 
     const int m = a.self_mode ? a.k - 1 : a.k;  // neighbours to certify
-    bool ok = true;
+    // norms whose squares overflow float32 leave the screen no keys: such inputs are scanned exhaustively
+    bool ok = !a.certify || m == 0 || ymax < INFINITY;
     if (a.certify && m > 0 && tau < INFINITY && cosine) {
         // Unit vectors: a rejected reference y had a screened key >= tau, and
         // the key is 2 D_y - 1 up to cosine_eps, so D_y >= (tau + 1 - eps) / 2,
@@ -453,8 +473,8 @@ __global__ __launch_bounds__(256) void k_rerank(RerankArgs a) {
         double dm;
         int jm;
         top.at(m - 1, dm, jm);
-        const double bound = ((double)tau + 1.0 - a.cosine_eps) * 0.5 - 1e-13;
-        ok = dm < bound;
+        const double bound = ((double)tau * kscale + 1.0 - cosine_eps) * 0.5 - 1e-13;
+        ok = ok && dm < bound;
     } else if (a.certify && m > 0 && tau < INFINITY) {
         // A rejected reference y had a screened key >= tau.  If ||y|| > Y =
         // ||x|| + D_m it lies farther than D_m (triangle inequality); else its
@@ -464,9 +484,10 @@ __global__ __launch_bounds__(256) void k_rerank(RerankArgs a) {
         int jm;
         top.at(m - 1, dm, jm);
         const double Y = fmin(ymax, (xn + sqrt(dm)) * (1.0 + 1e-9));
-        const double eps = a.eps_coef * (2.0 * xn * Y + Y * Y);
-        const double bound = (double)tau + xx - eps - 1e-12 * (fabs((double)tau) + xx);
-        ok = dm < bound;
+        const double eps = eps_coef * (2.0 * xn * Y + Y * Y) + eps_abs * (2.0 * xn + Y);
+        const double t = (double)tau * kscale;
+        const double bound = t + xx - eps - 1e-12 * (fabs(t) + xx);
+        ok = ok && dm < bound;
     }
 
     int32_t *oi = a.out_idx + row * a.k;
@@ -624,11 +645,10 @@ int pick_dh(int d) {
     return -1;
 }
 
-// Reference ranges for the main screen: enough workgroups to fill the chip
-// (about 4 per CU) while every range keeps at least 8 blocks.
-int pick_splits(int64_t nq, int64_t nblk, int qg) {
-    const int64_t qblocks = (nq + qg - 1) / qg;
-    const int64_t want = 1024;
+// Reference ranges for the main screen: `want` workgroups to fill the chip
+// while every range keeps at least 8 blocks.
+int pick_splits(int64_t nq, int64_t nblk, int qg, int64_t want) {
+    const int64_t qblocks = std::max<int64_t>((nq + qg - 1) / qg, 1);
     int64_t P = qblocks >= want ? 1 : (want + qblocks - 1) / qblocks;
     P = std::min<int64_t>(P, std::max<int64_t>(1, nblk / 8));
     P = std::min<int64_t>(P, 32);
@@ -637,13 +657,27 @@ int pick_splits(int64_t nq, int64_t nblk, int qg) {
 
 }  // namespace
 
+// Bound on |screened key - (2 D - 1)| for the cosine screen: the key error of
+// unit vectors (eps_coef (2 |x||y| + |y|^2) with norms within 4 units of 1)
+// plus the normalisation: each unit vector is within 2 units of roundoff per
+// element of the exact direction, which moves |y|^2 by at most 4 units and
+// x.y by at most 4 units (doubled in the key), with a margin.
+static double cosine_eps_of(double eps_coef) { return 3.0001 * eps_coef + 16.0 * std::ldexp(1.0, -24); }
+
 // Error bound of the float32 key (the norm enters the MFMA sum or is added
 // after it; norms rounded once from float64): 2 (d + 3) units of roundoff
 // times (2 ||x|| ||y|| + ||y||^2).
 double knn_eps_coefficient(int d) { return 2.0 * (d + 3) * std::ldexp(1.0, -24); }
 
-int knn_prep_fp32(const KnnPlan &p, const float *R, const KnnBuffers &b, const int32_t *blk_sample,
-                  const int64_t *boff, const int64_t *soff, hipStream_t stream) {
+void knn_split_bounds(RerankArgs &ra) {
+    ra.split = 1;
+    ra.split_eps = split_eps_coefficient(ra.d);
+    ra.split_abs = split_abs_coefficient(ra.d);
+    ra.split_cosine_eps = cosine_eps_of(ra.split_eps);
+}
+
+int knn_prep_fp32(const KnnPlan &p, const float *R, const float *Q, const KnnBuffers &b, const int32_t *blk_sample,
+                  const int64_t *boff, const int64_t *soff, const int32_t *ref_map, hipStream_t stream) {
     const int s4 = packed_s4(p.dh);
     ScopedTimer timer("prep_pack", stream);
     hipLaunchKernelGGL(k_init_counters, dim3(1), dim3(64), 0, stream, b.counters);
@@ -655,7 +689,13 @@ int knn_prep_fp32(const KnnPlan &p, const float *R, const KnnBuffers &b, const i
     hipLaunchKernelGGL(k_pack, dim3(g1), dim3(256), 0, stream, R, b.nrow, p.nr, p.d, p.dh, s4,
                        norm_folded(p.dh) ? 1 : 0, p.nblk, reinterpret_cast<f32x4 *>(b.packed), b.norms, blk_sample,
                        boff, soff, nullptr);
-    return launch_status("prep_pack");
+    if (Q && p.nq > 0)
+        hipLaunchKernelGGL(k_norms, dim3((unsigned)((p.nq + norm_rows(p.d) - 1) / norm_rows(p.d))), dim3(kNormRows), 0,
+                           stream, Q, p.nq, p.d, nullptr, &b.counters->query_norm_bits);
+    const int st = launch_status("prep_pack");
+    if (st != RSC_OK) return st;
+    return split_pack(R, b.nrow, p.nr, p.d, p.nblk, b.split, blk_sample, boff, soff, ref_map, p.nr, b.counters,
+                      stream);
 }
 
 int knn_norms(const float *R, int64_t nr, int d, float *nrow, KnnCounters *counters, hipStream_t stream) {
@@ -785,8 +825,11 @@ int knn_plan(int64_t nq, int64_t nr, int d, int k, const rsc_knn_opts *opts, boo
     plan->precision = precision;
     plan->metric = metric;
     plan->resid = resid;
-    plan->splits = pick_splits(nq, plan->nblk,
-                               precision == RSC_FP32 ? kQueriesPerGroup : lowp_queries_per_group(precision, d));
+    plan->ordered = precision == RSC_FP32 && nq == nr && nq >= kOrderRows;
+    // the split screen's workgroups of 8 waves fill a CU each; the others run four of 4 waves
+    plan->splits = precision == RSC_FP32
+                       ? pick_splits(nq, plan->nblk, split_queries_per_group(d, plan->half), kSplitWant)
+                       : pick_splits(nq, plan->nblk, lowp_queries_per_group(precision, d), 1024);
     if (precision == RSC_FP32) {
         // enough (range, half) lists that the m nearest fill each to about half
         const int m = self_mode ? k - 1 : k;
@@ -808,6 +851,7 @@ size_t knn_workspace(const KnnPlan &p, void *ws, KnnBuffers *out) {
         b.nrow = cv.take<float>((size_t)p.nr);
         b.packed = cv.take<float>((size_t)p.nblk * s4 * kWave * 4);
         b.norms = cv.take<float>(norm_folded(p.dh) ? 1 : (size_t)p.nblk * 32);
+        b.split = cv.take<char>(split_packed_bytes(p.d, p.nblk));
     } else {
         b.packed = reinterpret_cast<float *>(cv.take<char>(lowp_packed_bytes(p.precision, p.nblk, p.d)));
         b.norms = cv.take<float>((size_t)p.nblk * 32);
@@ -824,7 +868,7 @@ size_t knn_workspace(const KnnPlan &p, void *ws, KnnBuffers *out) {
         b.rn = cv.take<float>((size_t)p.nr * p.d);
         b.qn = p.self_mode ? b.rn : cv.take<float>((size_t)std::max<int64_t>(p.nq, 1) * p.d);
     }
-    if (!fp32 && p.resid == 0 && p.nq > 0) {
+    if ((fp32 ? p.ordered : p.resid == 0) && p.nq > 0) {
         // spatial order of the queries (perm) and its sort
         b.perm = cv.take<int32_t>((size_t)p.nq);
         b.qcount = cv.take<int32_t>(1);
@@ -857,13 +901,6 @@ int normalize_inputs(const KnnPlan &p, const float *Q, const float *R, const Knn
                            stream, Q, p.nq, p.d, b.qn);
     return launch_status("normalize");
 }
-
-// Bound on |screened key - (2 D - 1)| for the cosine screen: the float32
-// key error of unit vectors (eps_coef (2 |x||y| + |y|^2) with norms within
-// 4 units of 1) plus the normalisation: each unit vector is within 2 units of
-// roundoff per element of the exact direction, which moves |y|^2 by at most
-// 4 units and x.y by at most 4 units (doubled in the key), with a margin.
-double cosine_eps(int d) { return 3.0001 * knn_eps_coefficient(d) + 16.0 * std::ldexp(1.0, -24); }
 
 // Reduced-precision form: screen, then rerank without a certificate.
 int knn_run_lowp(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, float *out_dist,
@@ -966,7 +1003,18 @@ int knn_run(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, 
     const bool cosine = p.metric == RSC_COSINE;
     if (cosine && (st = normalize_inputs(p, Q, R, b, stream)) != RSC_OK) return st;
     const float *Qs = cosine ? b.qn : Q;  // what the screen sees
-    if ((st = knn_prep_fp32(p, cosine ? b.rn : R, b, nullptr, nullptr, nullptr, stream)) != RSC_OK) return st;
+    // One matrix: references and queries in a Morton order, each query group
+    // scanning from its own rows on, so that the lists fill with near keys
+    // first and few later blocks hold a key below any threshold.
+    const bool ordered = p.ordered && p.self_mode && !qlist;
+    if (ordered) {
+        if ((st = query_order_run(Qs, p.nq, p.d, b.order_ws, b.perm, stream)) != RSC_OK) return st;
+        hipLaunchKernelGGL(k_set_i32, dim3(1), dim3(64), 0, stream, b.qcount, (int32_t)p.nq);
+        qlist = b.perm;
+        qcount = b.qcount;
+    }
+    if ((st = knn_prep_fp32(p, cosine ? b.rn : R, p.self_mode ? nullptr : Qs, b, nullptr, nullptr, nullptr,
+                            ordered ? b.perm : nullptr, stream)) != RSC_OK) return st;
     if (p.nq == 0) return RSC_OK;
 
     const double eps_coef = knn_eps_coefficient(p.d);
@@ -985,8 +1033,15 @@ int knn_run(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, 
     sa.P = p.splits;
     sa.cand_idx = b.cand_idx;
     sa.cand_key = b.cand_key;
+    sa.kc = b.counters;
+    ScreenArgs ss = sa;  // the split screen; the FP32 chain takes the inputs it cannot (both see the mark)
+    ss.Ap = b.split;
+    ss.rotate = ordered ? 1 : 0;
+    ss.ref_map = ordered ? b.perm : nullptr;
+    if ((st = split_screen(ss, p.half, "screen_fp32", stream)) != RSC_OK) return st;
+    sa.only_wide = 1;
     const unsigned gq = (unsigned)((p.nq + kQueriesPerGroup - 1) / kQueriesPerGroup);
-    if ((st = screen(p.dh, sa, gq, p.half, false, "screen_fp32", stream)) != RSC_OK) return st;
+    if ((st = screen(p.dh, sa, gq, p.half, false, "screen_wide", stream)) != RSC_OK) return st;
 
     // Each (range, half) list is one candidate group of width `half`.
     RerankArgs ra{};
@@ -1004,7 +1059,7 @@ int knn_run(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, 
     ra.self_mode = p.self_mode ? 1 : 0;
     ra.certify = 1;
     ra.metric = p.metric;
-    ra.cosine_eps = cosine_eps(p.d);
+    ra.cosine_eps = cosine_eps_of(eps_coef);
     ra.cand_idx = b.cand_idx;
     ra.cand_key = b.cand_key;
     ra.eps_coef = eps_coef;
@@ -1013,6 +1068,7 @@ int knn_run(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, 
     ra.flag_count = &b.counters->flagged;
     ra.out_idx = out_idx;
     ra.out_dist = out_dist;
+    knn_split_bounds(ra);
     if ((st = knn_launch_rerank(ra, p.nq, "rerank", stream)) != RSC_OK) return st;
 
     // Escalation: rows that failed, screened again 64 wide over many ranges.
@@ -1021,6 +1077,7 @@ int knn_run(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, 
     se.qlist = b.flag1;
     se.qcount = &b.counters->flagged;
     se.qcap = esc_cap;
+    se.only_wide = 0;
     se.P = (int)std::min<int64_t>(kEscalateSplits, std::max<int64_t>(1, p.nblk));
     se.cand_idx = b.esc_idx;
     se.cand_key = b.esc_key;
@@ -1030,6 +1087,7 @@ int knn_run(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, 
     re.qlist = b.flag1;
     re.qcount = &b.counters->flagged;
     re.qcap = esc_cap;
+    re.split = 0;  // keys of the FP32 chain
     re.S = kEscalateWidth / 2;
     re.KP = kEscalateWidth / 2;
     re.P = 2 * se.P;

@@ -166,6 +166,7 @@ int build_plan(const int64_t *offsets, int S, int d, int k, const Shape &sh, Bat
     int st = knn_plan(N, N, d, k, nullptr, true, &bp.kp);
     if (st != RSC_OK) return st;
     bp.kp.nblk = bp.boff[S];
+    bp.kp.ordered = false;
     bp.kp.splits = kMaxSplits;
     if (sh.half == 32 && bp.kp.half == 16) {  // the wider screen tile
         bp.kp.half = 32;
@@ -522,7 +523,7 @@ int batched_run(const float *X, const int64_t *offsets, int S, int d, int k, int
         return RSC_ERR_WORKSPACE;
     }
     if ((st = upload_plan(bp, b, s)) != RSC_OK) return st;
-    if ((st = knn_prep_fp32(bp.kp, X, b.kb, b.blk_sample, b.boff, b.soff, s)) != RSC_OK) return st;
+    if ((st = knn_prep_fp32(bp.kp, X, nullptr, b.kb, b.blk_sample, b.boff, b.soff, nullptr, s)) != RSC_OK) return st;
     if ((st = screen_only(bp, b, X, s)) != RSC_OK) return st;
     RerankArgs ra{};
     ra.Q = X;
@@ -577,7 +578,7 @@ int batched_autotune(const float *X, const int64_t *offsets, int S, int d, int k
         if ((r = upload_plan(bp, b, s)) != RSC_OK) return r;
         if (!prepared) {
             // the packed references do not depend on the shape
-            if ((r = knn_prep_fp32(bp.kp, X, b.kb, b.blk_sample, b.boff, b.soff, s)) != RSC_OK) return r;
+            if ((r = knn_prep_fp32(bp.kp, X, nullptr, b.kb, b.blk_sample, b.boff, b.soff, nullptr, s)) != RSC_OK) return r;
             if ((r = screen_only(bp, b, X, s)) != RSC_OK) return r;  // warm
             prepared = true;
         }

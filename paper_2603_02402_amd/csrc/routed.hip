@@ -39,7 +39,7 @@ constexpr int kMaxParts = 8192;   // partitions of a probed search (LDS bitmap o
 constexpr int kMaxProbes = 64;    // probes per query (one per lane when sorting)
 constexpr int kTileQ = 32;        // queries per tile (one wave)
 constexpr int kBitmapWords = kMaxParts / 32;
-constexpr int64_t kExactSlack = 131072;  // see exact_plan
+constexpr int64_t kExactSlack = 1024 * 512;  // see exact_plan
 
 struct RoutedCounters {
     int32_t nconf;      // probed rows

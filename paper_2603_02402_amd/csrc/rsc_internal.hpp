@@ -76,7 +76,9 @@ struct KnnCounters {
     uint32_t max_norm_bits;   // float bits of max_j ||y_j||
     int32_t flagged2;         // escalated rows whose second certificate failed
     int32_t rescanned;        // rows recomputed exhaustively
-    int32_t pad[3];
+    uint32_t query_norm_bits; // float bits of the largest query norm (rectangular problem; else 0)
+    int32_t wide;             // nonzero: norms spread too far for the split screen, the FP32 chain runs
+    int32_t pad;
 };
 
 struct KnnPlan {
@@ -89,11 +91,13 @@ struct KnnPlan {
     int precision;         // rsc_precision of the screen
     int metric;            // rsc_metric
     int resid;             // FP8 residual variant: reference partitions (0 = off)
+    bool ordered;          // exact path: room to screen one matrix in a Morton order (knn_run)
 };
 
 struct KnnBuffers {
     KnnCounters *counters;
     float *nrow, *packed, *norms;
+    void *split;      // exact path: references packed for the split FP16 screen
     float *scal;      // FP8 per-dimension scales
     uint32_t *amax;   // FP8 per-dimension absmax bits
     int32_t *cand_idx;
@@ -129,6 +133,11 @@ struct RerankArgs {
     const int32_t *cand_idx;
     const float *cand_key;
     double eps_coef;
+    // keys of the split FP16 screen (times its squared scale, unless the
+    // inputs were marked wide): its error bound in place of eps_coef /
+    // cosine_eps
+    int split;
+    double split_eps, split_abs, split_cosine_eps;
     KnnCounters *counters;
     int32_t *flag_out;   // rows that fail the certificate
     int32_t *flag_count;
@@ -147,10 +156,14 @@ int knn_run(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, 
 
 // Pieces of the exact path reused by the batched form (knn.hip).
 double knn_eps_coefficient(int d);
-// init counters, norms, FP32 packing (optionally per sample: blk_sample,
-// boff, soff device arrays).
-int knn_prep_fp32(const KnnPlan &p, const float *R, const KnnBuffers &b, const int32_t *blk_sample,
-                  const int64_t *boff, const int64_t *soff, hipStream_t stream);
+// init counters, norms, FP32 and split packing (optionally per sample:
+// blk_sample, boff, soff device arrays).  Q: the queries of a rectangular
+// problem (their largest norm enters the split's scale), else null.
+// ref_map: the split packing's slot -> row, or null for row order.
+int knn_prep_fp32(const KnnPlan &p, const float *R, const float *Q, const KnnBuffers &b, const int32_t *blk_sample,
+                  const int64_t *boff, const int64_t *soff, const int32_t *ref_map, hipStream_t stream);
+// The rerank's error bounds for keys of the split screen.
+void knn_split_bounds(RerankArgs &ra);
 int knn_launch_rerank(const RerankArgs &ra, int64_t slots, const char *name, hipStream_t stream);
 // exhaustive float64 rescan of the rows flagged in b (first certificate only
 // when there was no escalation); soff/nsamples restrict each row to its sample.
@@ -171,6 +184,18 @@ int knn_pack_mapped(int dh, const float *R, const float *nrow, int64_t nr, int d
 size_t knn_packed_floats(int dh, int64_t nblk);
 int knn_launch_screen(int dh, const scr::ScreenArgs &a, unsigned gx, int half_width, const char *name,
                       hipStream_t s);
+// Split FP16 screen of the exact path (knn_split.hip).
+size_t split_packed_bytes(int d, int64_t nblk);
+int split_queries_per_group(int d, int half_width);
+// Packs nblk blocks (sample tables as knn_prep_fp32; row_map: the rows of
+// the first nmap packed slots, -1 and the slots past them padded)
+// and marks inputs whose norms spread too far; needs the norms of R.
+int split_pack(const float *R, const float *nrow, int64_t nr, int d, int64_t nblk, void *packed,
+               const int32_t *blk_sample, const int64_t *boff, const int64_t *soff, const int32_t *row_map,
+               int64_t nmap, KnnCounters *counters, hipStream_t stream);
+int split_screen(const scr::ScreenArgs &a, int half_width, const char *name, hipStream_t s);
+double split_eps_coefficient(int d);
+double split_abs_coefficient(int d);
 // Reduced-precision screens (knn_lowp.hip).
 int lowp_steps(int precision, int d);
 int lowp_qb(int precision, int d);
