@@ -52,11 +52,19 @@ __global__ __launch_bounds__(256) void k_qo_bounds(const float *__restrict__ Q, 
             }
         }
     }
+    // one pair of atomics per wave and coordinate: one per thread serialised
+    // 1.5M atomics on six words (295 us at 500K rows)
 #pragma unroll
     for (int t = 0; t < kOrderDims; ++t) {
         if (t < D) {
-            atomicMin(&bounds[2 * t], lo[t]);
-            atomicMax(&bounds[2 * t + 1], hi[t]);
+            for (int o = 32; o > 0; o >>= 1) {
+                lo[t] = min(lo[t], (uint32_t)__shfl_xor((int)lo[t], o, 64));
+                hi[t] = max(hi[t], (uint32_t)__shfl_xor((int)hi[t], o, 64));
+            }
+            if ((threadIdx.x & 63) == 0) {
+                atomicMin(&bounds[2 * t], lo[t]);
+                atomicMax(&bounds[2 * t + 1], hi[t]);
+            }
         }
     }
 }
