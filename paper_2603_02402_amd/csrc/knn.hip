@@ -512,6 +512,309 @@ __global__ __launch_bounds__(256) void k_rerank(RerankArgs a) {
 }
 
 // ---------------------------------------------------------------------------
+// Rerank of short answers (at most 64 neighbours): one group of G lanes per
+// query slot, two queries per wave while 32 lanes hold their answers.
+//
+// Of the P S candidates only those whose screened key can still belong to
+// the m nearest are compared in float64: the m-th smallest key plus twice
+// the key's error bound is an upper bound for the key of any of the m
+// nearest (m candidates have a true key below the m-th smallest plus one
+// bound; a candidate whose key lies above that by more than another bound is
+// farther than all of them).  At k = 15 that leaves about 16 of 32 candidates
+// (of 224 with 7 reference ranges).  The bound on the m-th smallest comes from
+// a bisection on the keys with ballots, to 2^-12 of their range.
+//
+// The survivors' rows come in through LDS, 32 dimensions at a time (16 lanes
+// of 8 bytes per row when the rows allow it, else 32 of 4), then each lane
+// sums its own candidate in dimension order (exact_d2's arithmetic), and the
+// order of the answers is a count of smaller (distance, index) pairs in LDS.
+// More survivors than lanes: pass by pass, against the best so far.
+// ---------------------------------------------------------------------------
+constexpr int kLeanChunk = 32;             // dimensions staged per pass
+constexpr int kLeanLd = kLeanChunk + 2;    // LDS row stride: 8-byte reads of 32 lanes meet 32 bank pairs
+
+template <int G, int KR, int VEC>
+__global__ __launch_bounds__(256) void k_rerank_lean(RerankArgs a) {
+    constexpr int NG = 256 / G;     // groups of the workgroup
+    constexpr int PW = kWave / G;   // groups of a wave
+    constexpr int LPR = kLeanChunk / VEC;  // lanes loading one row's chunk
+    constexpr int RPI = G / LPR;           // rows per load instruction of a group
+    __shared__ __attribute__((aligned(16))) float tile[NG][G * kLeanLd];
+    __shared__ double ed[NG][2 * G];
+    __shared__ int ej[NG][2 * G];
+    __shared__ int sj[NG][2 * G];   // survivors waiting (candidate rows and their keys)
+    __shared__ float sk[NG][2 * G];
+    extern __shared__ float xrow[];  // NG x (d | 1) + 1
+    const int lane = threadIdx.x & (kWave - 1);
+    const int gl = threadIdx.x & (G - 1), g = threadIdx.x / G;
+    const int half = lane / G;       // group of the wave
+    const int64_t slot = (int64_t)blockIdx.x * NG + g;
+    int64_t nslots = a.nq;
+    if (a.qlist) nslots = std::min<int64_t>(std::min<int64_t>(*a.qcount, a.qcap), a.nq);
+    if (slot - half >= nslots) return;  // the wave's first slot
+    const int64_t row = slot < nslots ? (a.qlist ? (int64_t)a.qlist[slot] : slot) : -1;
+    const bool live = row >= 0;
+    auto wave_sync = [&]() {
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+        __builtin_amdgcn_wave_barrier();
+    };
+    // bits of this group in a wave's ballot
+    auto group_ballot = [&](bool v) -> unsigned long long {
+        const unsigned long long b = __ballot(v);
+        return PW == 1 ? b : (b >> (half * G)) & ((1ull << (G & 63)) - 1);
+    };
+
+    const float *x = a.Q + (live ? row : 0) * a.d;
+    float *xs = xrow + g * (a.d | 1);
+    for (int t = gl; t < a.d; t += G) xs[t] = x[t];
+    // ||x||^2 in float64 (only feeds the certificate's margin)
+    double xx = 0.0;
+    for (int t = gl; t < a.d; t += G) xx += (double)x[t] * (double)x[t];
+#pragma unroll
+    for (int o = G / 2; o > 0; o >>= 1) xx += __shfl_xor(xx, o, kWave);
+    const double xn = sqrt(xx) * (1.0 + 1e-12);
+    const double ymax = (double)__uint_as_float(a.counters->max_norm_bits) * (1.0 + 1e-6);
+    const bool cosine = a.metric == RSC_COSINE;
+    const bool split = a.split && a.counters->wide == 0;
+    const double kscale = split ? ldexp(1.0, -2 * scr::split_exponent(a.counters)) : 1.0;
+    const double eps_coef = split ? a.split_eps : a.eps_coef;
+    const double cosine_eps = split ? a.split_cosine_eps : a.cosine_eps;
+    const double eps_abs =
+        split ? a.split_abs * fmax((double)__uint_as_float(a.counters->query_norm_bits), ymax) : 0.0;
+    wave_sync();
+    double cxx = 0.0;  // cosine: the query's squared norm summed in dimension order
+    if (cosine)
+        for (int t = 0; t < a.d; ++t) {
+            const double v = (double)xs[t];
+            cxx = __dadd_rn(cxx, __dmul_rn(v, v));
+        }
+
+    // the candidates: lists of S keys, ascending; tau: the smallest key a full list could have rejected
+    const int m = a.self_mode ? a.k - 1 : a.k;
+    const int total = a.P * a.S;
+    const int64_t cbase = (live ? slot : 0) * a.P * a.KP;
+    float key[KR];
+    int cj[KR];
+    float tau = INFINITY, kmin = INFINITY, kmax = -INFINITY;
+    int nvalid = 0;
+#pragma unroll
+    for (int i = 0; i < KR; ++i) {
+        const int ci = i * G + gl;
+        key[i] = INFINITY;
+        cj[i] = -1;
+        if (live && ci < total) {
+            const int p = ci / a.S, e = ci - p * a.S;
+            const int j = a.cand_idx[cbase + p * a.KP + e];
+            const float v = a.cand_key[cbase + p * a.KP + e];
+            if (e == a.S - 1 && j >= 0) tau = fminf(tau, v);
+            if (j >= 0 && !(a.self_mode && j == row)) {
+                key[i] = v;
+                cj[i] = j;
+                // cosine: the key of a zero row says nothing about its distance
+                if (!(cosine && v == 0.f)) {
+                    kmin = fminf(kmin, v);
+                    kmax = fmaxf(kmax, v);
+                }
+            }
+        }
+        nvalid += __popcll(group_ballot(cj[i] >= 0 && !(cosine && key[i] == 0.f)));
+    }
+#pragma unroll
+    for (int o = G / 2; o > 0; o >>= 1) {
+        tau = fminf(tau, __shfl_xor(tau, o, kWave));
+        kmin = fminf(kmin, __shfl_xor(kmin, o, kWave));
+        kmax = fmaxf(kmax, __shfl_xor(kmax, o, kWave));
+    }
+    // keys up to `cut` may belong to the answer
+    float cut = INFINITY;
+    const double slack =
+        cosine ? 2.0 * cosine_eps : 2.0 * (eps_coef * (2.0 * xn + ymax) * ymax + eps_abs * (2.0 * xn + ymax));
+    if (a.certify && nvalid > m && m > 0 && slack < INFINITY && kmax < INFINITY) {
+        float lo = kmin, hi = kmax;  // at least m keys are <= hi
+        for (int it = 0; it < 12; ++it) {
+            const float mid = 0.5f * lo + 0.5f * hi;
+            int c = 0;
+#pragma unroll
+            for (int i = 0; i < KR; ++i) c += __popcll(group_ballot(key[i] <= mid && !(cosine && key[i] == 0.f)));
+            if (c >= m) hi = mid; else lo = mid;
+        }
+        const double t = (double)hi * kscale;
+        cut = (float)((t + slack + 1e-6 * (fabs(t) + slack)) / kscale);
+    }
+
+    int mb = 0;       // best so far
+    float ratio = 0.f;
+    int waiting = 0;  // survivors in sj / sk (group-uniform)
+    // Distances of the first min(waiting, G) survivors, merged into the best.
+    // Every group of the wave calls this together.
+    auto pass = [&]() {
+        const int nc = min(waiting, G);
+        double s2 = 0.0, yy = 0.0, sxy = 0.0;
+        float yf = 0.f;
+        float *T = tile[g];
+        const int ncw = PW == 1 ? nc : max(nc, __shfl_xor(nc, G & 63, kWave));  // either group's
+        for (int k0 = 0; k0 < a.d; k0 += kLeanChunk) {
+            const int w = min(kLeanChunk, a.d - k0);
+            const int e = (gl % LPR) * VEC;
+            float2 buf[G / RPI / 2];
+#pragma unroll
+            for (int hb = 0; hb < 2; ++hb) {  // the rows in two halves of loads in flight
+                if (hb * (G / 2) >= ncw) break;
+#pragma unroll
+                for (int i = 0; i < G / RPI / 2; ++i) {
+                    const int r = hb * (G / 2) + i * RPI + gl / LPR;
+                    buf[i] = make_float2(0.f, 0.f);
+                    if (r < nc && e < w) {
+                        const float *y = a.R + (int64_t)sj[g][r] * a.d + k0 + e;
+                        if constexpr (VEC == 2)
+                            buf[i] = *reinterpret_cast<const float2 *>(y);
+                        else
+                            buf[i].x = *y;
+                    }
+                }
+                if (hb == 0) wave_sync();  // earlier reads of the tile are done
+#pragma unroll
+                for (int i = 0; i < G / RPI / 2; ++i) {
+                    const int r = hb * (G / 2) + i * RPI + gl / LPR;
+                    if constexpr (VEC == 2)
+                        *reinterpret_cast<float2 *>(&T[r * kLeanLd + e]) = buf[i];
+                    else
+                        T[r * kLeanLd + e] = buf[i].x;
+                }
+            }
+            wave_sync();  // the tile is written
+            if (cosine) {
+                for (int t = 0; t < w; ++t) {
+                    const double y = (double)T[gl * kLeanLd + t];
+                    sxy = __dadd_rn(sxy, __dmul_rn((double)xs[k0 + t], y));
+                    yy = __dadd_rn(yy, __dmul_rn(y, y));
+                }
+            } else {
+                auto step = [&](float xv, float yv) {
+                    const double diff = __dsub_rn((double)xv, (double)yv);
+                    s2 = __dadd_rn(s2, __dmul_rn(diff, diff));
+                    yf = fmaf(yv, yv, yf);
+                };
+                int t = 0;
+                for (; t + 1 < w; t += 2) {
+                    const float2 y = *reinterpret_cast<const float2 *>(&T[gl * kLeanLd + t]);
+                    step(xs[k0 + t], y.x);
+                    step(xs[k0 + t + 1], y.y);
+                }
+                if (t < w) step(xs[k0 + t], T[gl * kLeanLd + t]);
+            }
+        }
+        double d2 = INFINITY;
+        int jj = INT_MAX;
+        if (gl < nc) {
+            jj = sj[g][gl];
+            const double skey = (double)sk[g][gl] * kscale;
+            if (cosine) {
+                // 1 - x.y / (||x|| ||y||); a row of zero norm is at distance 1
+                const bool zero = cxx == 0.0 || yy == 0.0;
+                d2 = zero ? 1.0 : __dsub_rn(1.0, __ddiv_rn(sxy, __dmul_rn(__dsqrt_rn(cxx), __dsqrt_rn(yy))));
+                // the screen ranked 2 D - 1 (unit vectors) up to cosine_eps
+                if (!zero) ratio = fmaxf(ratio, (float)(fabs(skey - (2.0 * d2 - 1.0)) / cosine_eps));
+            } else {
+                d2 = s2;
+                const double yn = sqrt((double)yf);
+                const double err_bound =
+                    eps_coef * (2.0 * xn * yn + (double)yf) + eps_abs * (2.0 * xn + yn) + 1e-300;
+                ratio = fmaxf(ratio, (float)(fabs(skey - (d2 - xx)) / err_bound));
+            }
+        }
+        // the waiting list moves up; ranks among the best so far and the new ones
+        double bd = INFINITY;
+        int bj = INT_MAX;
+        if (gl < mb) {
+            bd = ed[g][gl];
+            bj = ej[g][gl];
+        }
+        const int mj = sj[g][G + gl];
+        const float mk = sk[g][G + gl];
+        wave_sync();
+        sj[g][gl] = mj;
+        sk[g][gl] = mk;
+        if (gl < nc) {
+            ed[g][mb + gl] = d2;
+            ej[g][mb + gl] = jj;
+        }
+        wave_sync();
+        const int ne = mb + nc;
+        const int new_ = PW == 1 ? ne : max(ne, __shfl_xor(ne, G & 63, kWave));
+        int rn = 0, rb = 0;
+        for (int e = 0; e < new_; ++e) {
+            if (e < ne) {
+                const double od = ed[g][e];
+                const int oj = ej[g][e];
+                rn += lex_before(od, oj, d2, jj) ? 1 : 0;
+                rb += lex_before(od, oj, bd, bj) ? 1 : 0;
+            }
+        }
+        wave_sync();
+        if (gl < mb && rb < m) {
+            ed[g][rb] = bd;
+            ej[g][rb] = bj;
+        }
+        if (gl < nc && rn < m) {
+            ed[g][rn] = d2;
+            ej[g][rn] = jj;
+        }
+        mb = min(m, ne);
+        waiting -= nc;
+        wave_sync();
+    };
+#pragma unroll
+    for (int i = 0; i < KR; ++i) {
+        if (i * G >= total) break;
+        const bool in = cj[i] >= 0 && (key[i] <= cut || (cosine && key[i] == 0.f));
+        const unsigned long long b = group_ballot(in);
+        if (in) {
+            const int at = waiting + __popcll(b & ((1ull << gl) - 1));
+            sj[g][at] = cj[i];
+            sk[g][at] = key[i];
+        }
+        waiting += __popcll(b);
+        wave_sync();
+        if (__ballot(waiting >= G) != 0ull) pass();
+    }
+    while (__ballot(waiting > 0) != 0ull) pass();
+
+    ratio = wave_max(ratio);
+    if (lane == 0 && ratio > 0.f && __float_as_uint(ratio) > *(volatile uint32_t *)&a.counters->max_ratio_bits)
+        atomicMax(&a.counters->max_ratio_bits, __float_as_uint(ratio));
+    if (!live) return;
+
+    // the certificate of k_rerank
+    const double dm = m > 0 && mb >= m ? ed[g][m - 1] : (double)INFINITY;
+    bool ok = !a.certify || m == 0 || ymax < INFINITY;
+    if (a.certify && m > 0 && tau < INFINITY) {
+        const double t = (double)tau * kscale;
+        if (cosine) {
+            ok = ok && dm < (t + 1.0 - cosine_eps) * 0.5 - 1e-13;
+        } else {
+            const double Y = fmin(ymax, (xn + sqrt(dm)) * (1.0 + 1e-9));
+            const double eps = eps_coef * (2.0 * xn * Y + Y * Y) + eps_abs * (2.0 * xn + Y);
+            ok = ok && dm < t + xx - eps - 1e-12 * (fabs(t) + xx);
+        }
+    }
+    int32_t *oi = a.out_idx + row * a.k;
+    float *od = a.out_dist + row * a.k;
+    const int off = a.self_mode ? 1 : 0;
+    if (a.self_mode && gl == 0) {
+        oi[0] = (int32_t)row;
+        od[0] = 0.f;
+    }
+    for (int pos = gl; pos < m; pos += G) {
+        const bool have = pos < mb;
+        const double d = have ? ed[g][pos] : (double)INFINITY;
+        oi[off + pos] = have ? ej[g][pos] : -1;
+        od[off + pos] = cosine ? (float)d : (float)sqrt(d);
+    }
+    if (!ok && gl == 0) a.flag_out[atomicAdd(a.flag_count, 1)] = (int32_t)row;
+}
+
+// ---------------------------------------------------------------------------
 // Exhaustive float64 scan of the rows no screen could certify: rows
 // list2[0..count2) and list1[cap..count1).  One wave per row: each step the
 // 64 lanes compute the distances of 64 consecutive references; a step with
@@ -724,14 +1027,37 @@ int knn_launch_screen(int dh, const scr::ScreenArgs &a, unsigned gx, int half_wi
     return screen(dh, a, gx, half_width, false, name, s);
 }
 
+template <int G, int KR>
+void launch_rerank_lean(const RerankArgs &ra, int64_t slots, hipStream_t stream) {
+    constexpr int NG = 256 / G;
+    const dim3 grid((unsigned)((slots + NG - 1) / NG));
+    const size_t lds = ((size_t)NG * (ra.d | 1) + 1) * sizeof(float);
+    // 8-byte row loads need even rows from an 8-byte boundary
+    if (ra.d % 2 == 0 && (reinterpret_cast<uintptr_t>(ra.R) & 7u) == 0)
+        hipLaunchKernelGGL((k_rerank_lean<G, KR, 2>), grid, dim3(256), lds, stream, ra);
+    else
+        hipLaunchKernelGGL((k_rerank_lean<G, KR, 1>), grid, dim3(256), lds, stream, ra);
+}
+
 int knn_launch_rerank(const RerankArgs &ra, int64_t slots, const char *name, hipStream_t stream) {
     ScopedTimer timer(name, stream);
     const dim3 grid((unsigned)((slots + 3) / 4));
-    switch (topm_regs(ra.self_mode ? ra.k - 1 : ra.k)) {
-        case 1: hipLaunchKernelGGL(k_rerank<1>, grid, dim3(256), 0, stream, ra); break;
-        case 2: hipLaunchKernelGGL(k_rerank<2>, grid, dim3(256), 0, stream, ra); break;
-        default: hipLaunchKernelGGL(k_rerank<4>, grid, dim3(256), 0, stream, ra); break;
-    }
+    const int m = ra.self_mode ? ra.k - 1 : ra.k, total = ra.P * ra.S;
+    // two rows per wave while 32 lanes hold the answer and a lane few candidates
+    if (m <= 32 && total <= 32)
+        launch_rerank_lean<32, 1>(ra, slots, stream);
+    else if (m <= 32 && total <= 64)
+        launch_rerank_lean<32, 2>(ra, slots, stream);
+    else if (m <= 32 && total <= 256)
+        launch_rerank_lean<32, 8>(ra, slots, stream);
+    else if (m <= 64 && total <= 512)
+        launch_rerank_lean<64, 8>(ra, slots, stream);
+    else if (m <= 64 && total <= 2048)
+        launch_rerank_lean<64, 32>(ra, slots, stream);
+    else if (m <= 128)
+        hipLaunchKernelGGL(k_rerank<2>, grid, dim3(256), 0, stream, ra);
+    else
+        hipLaunchKernelGGL(k_rerank<4>, grid, dim3(256), 0, stream, ra);
     return launch_status(name);
 }
 
