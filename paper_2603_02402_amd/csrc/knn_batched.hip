@@ -34,6 +34,7 @@
 #include "rsc_internal.hpp"
 #include "screen_common.hpp"
 #include "screen_fp32.hpp"
+#include "screen_split.hpp"
 
 namespace rsc {
 
@@ -45,7 +46,7 @@ struct BatchItem {
     int64_t q0;        // first query row, or (with a row list) first list entry
     int64_t b0, b1;    // packed reference blocks [b0, b1)
     int64_t ref_base;  // reference row of packed row 0 for this sample
-    int32_t nq;        // queries in the tile (<= 128)
+    int32_t nq;        // queries in the tile (at most a workgroup's)
     int32_t p;         // range index the lists are filed under
 };
 
@@ -55,12 +56,16 @@ struct BatchArgs {
     int n_items;
     int32_t *counter;
     const int32_t *rows;  // optional: query i of an item is row rows[q0 + i], filed under slot q0 + i
+    int tile_q;           // FP32 chain over items of more than 128 queries: 128-query tiles per item
 };
 
+// The FP32 chain: the escalation, and whole batches marked wide.  An item's
+// queries are taken 128 at a time.
 template <int DH, int L>
 __global__ __launch_bounds__(256, tile_screen_waves(DH, L)) void k_screen_batched(BatchArgs ba) {
     __shared__ float2 qbuf[kQueueCap * 256];
     __shared__ int item_sh;
+    if (ba.base.only_wide && ba.base.kc->wide == 0) return;
     const int tid = threadIdx.x;
     const int qi = (tid >> 6) * 32 + (tid & 31);  // query of this lane within the tile
     while (true) {
@@ -68,13 +73,48 @@ __global__ __launch_bounds__(256, tile_screen_waves(DH, L)) void k_screen_batche
         __syncthreads();
         const int it = item_sh;
         __syncthreads();  // every wave has read the item before it is overwritten
-        if (it >= ba.n_items) break;
-        const BatchItem I = ba.items[it];
-        const bool live = qi < I.nq;
-        const int64_t slot = live ? I.q0 + qi : -1;
+        if (it >= ba.n_items * ba.tile_q) break;
+        const BatchItem I = ba.items[it / ba.tile_q];
+        const int q = it % ba.tile_q * 128 + qi;
+        const bool live = q < I.nq;
+        const int64_t slot = live ? I.q0 + q : -1;
         const int64_t row = live ? (ba.rows ? (int64_t)ba.rows[slot] : slot) : -1;
         screen_fp32_tile<DH, L>(ba.base, slot, row, I.b0, I.b1, I.p, I.ref_base, qbuf);
     }
+}
+
+// The split screen: rows and references of every sample in the order `rows`;
+// a tile starts its scan at its own blocks (near references first).
+template <int Q, int TC, int L>
+__global__ __launch_bounds__((SplitShape<Q, TC, L>::NW * kWave), (SplitShape<Q, TC, L>::W)) void k_split_batched(
+    BatchArgs ba) {
+    using S = SplitShape<Q, TC, L>;
+    __shared__ __attribute__((aligned(16))) char ring0[S::RING];
+    __shared__ __attribute__((aligned(16))) char ring1[S::RING];
+    __shared__ double qbuf[S::QCAP * S::NW * kWave];
+    __shared__ int item_sh;
+    if (ba.base.kc->wide) return;
+    const int tid = threadIdx.x;
+    const int qi = (tid >> 6) * 32 + (tid & 31);
+    while (true) {
+        if (tid == 0) item_sh = atomicAdd(ba.counter, 1);
+        __syncthreads();
+        const int it = item_sh;
+        __syncthreads();
+        if (it >= ba.n_items) break;
+        const BatchItem I = ba.items[it];
+        const int64_t slot = qi < I.nq ? I.q0 + qi : -1;
+        const int64_t row = slot >= 0 ? (int64_t)ba.rows[slot] : -1;
+        const int span = (int)(I.b1 - I.b0);
+        // packed position of the tile's first query: ref_base = soff - 32 boff
+        const int own = (int)((I.q0 - I.ref_base) / 32 - I.b0);
+        screen_split_tile<Q, TC, L>(ba.base, slot, row, (int)I.b0, 1, span, max(0, min(own, span - 1)), I.p,
+                                    I.ref_base, ring0, ring1, qbuf);
+    }
+}
+
+__global__ void k_set_count(int32_t *p, int32_t v) {
+    if (threadIdx.x == 0) *p = v;
 }
 
 __global__ void k_batch_init(int32_t *counter, int32_t *cand_idx, float *cand_key, int64_t n) {
@@ -175,7 +215,7 @@ int build_plan(const int64_t *offsets, int S, int d, int k, const Shape &sh, Bat
     bp.blk_sample.resize(bp.kp.nblk);
     for (int s = 0; s < S; ++s)
         for (int64_t b = bp.boff[s]; b < bp.boff[s + 1]; ++b) bp.blk_sample[b] = s;
-    constexpr int QG = kScreenWaves * 32;
+    const int QG = split_queries_per_group(d, bp.kp.half);
     std::vector<int> order(S);
     for (int s = 0; s < S; ++s) order[s] = s;
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
@@ -221,6 +261,9 @@ struct BatchBuffers {
     int32_t *counter;
     BatchItem *esc_items;
     int32_t *esc_rows, *esc_count;
+    int32_t *order;   // every sample's rows in the order they are screened
+    void *order_ws;
+    int32_t *order_n;
 };
 
 // Workspace: the exact path's buffers for the concatenated problem, then the
@@ -234,7 +277,7 @@ size_t batch_workspace(const BatchPlan &bp, void *ws, BatchBuffers *out) {
     const size_t base = knn_workspace(widest, nullptr, nullptr);
     knn_workspace(bp.kp, ws, &b.kb);
     Carver cv(ws ? static_cast<char *>(ws) + base : nullptr);
-    constexpr int QG = kScreenWaves * 32;
+    constexpr int QG = kScreenWaves * 32;  // no screen's tile is smaller
     size_t max_items = 0;
     for (int s = 0; s < bp.S; ++s) max_items += (size_t)((bp.soff[s + 1] - bp.soff[s] + QG - 1) / QG) * kMaxSplits;
     b.items = cv.take<BatchItem>(std::max<size_t>(max_items, 1));
@@ -247,11 +290,14 @@ size_t batch_workspace(const BatchPlan &bp, void *ws, BatchBuffers *out) {
     b.esc_items = cv.take<BatchItem>(esc_items);
     b.esc_rows = cv.take<int32_t>(kEscCap);
     b.esc_count = cv.take<int32_t>(1);
+    b.order = cv.take<int32_t>((size_t)bp.kp.nq);
+    b.order_n = cv.take<int32_t>(1);
+    b.order_ws = cv.take<char>(sample_order_workspace(bp.kp.nq));
     if (out) *out = b;
     return base + cv.used;
 }
 
-int device_slots(int dh) {
+int compute_units() {
     static int cus = 0;
     if (cus == 0) {
         int dev = 0;
@@ -259,8 +305,10 @@ int device_slots(int dh) {
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
             cus = 256;
     }
-    return cus * tile_screen_waves(dh, 16);
+    return cus;
 }
+
+int device_slots(int dh) { return compute_units() * tile_screen_waves(dh, 16); }
 
 template <int DH>
 int launch_batched_dh(const BatchArgs &ba, unsigned grid, int half, hipStream_t s) {
@@ -271,11 +319,10 @@ int launch_batched_dh(const BatchArgs &ba, unsigned grid, int half, hipStream_t 
     return launch_status("screen_batched");
 }
 
-int launch_batched(const BatchPlan &bp, const BatchArgs &ba, hipStream_t s, int half = 0,
-                   const char *name = "screen_batched") {
+int launch_batched(const BatchPlan &bp, const BatchArgs &ba, hipStream_t s, int half, const char *name) {
     ScopedTimer timer(name, s);
-    if (half == 0) half = bp.kp.half;
-    const unsigned grid = (unsigned)std::max(1, std::min<int>(device_slots(bp.kp.dh), ba.n_items));
+    const unsigned grid =
+        (unsigned)std::max(1, std::min<int>(device_slots(bp.kp.dh), ba.n_items * std::max(1, ba.tile_q)));
     switch (bp.kp.dh) {
         case 4: return launch_batched_dh<4>(ba, grid, half, s);
         case 8: return launch_batched_dh<8>(ba, grid, half, s);
@@ -286,6 +333,38 @@ int launch_batched(const BatchPlan &bp, const BatchArgs &ba, hipStream_t s, int 
         case 64: return launch_batched_dh<64>(ba, grid, half, s);
         default: set_error("internal: no screen kernel for this dimension"); return RSC_ERR_UNSUPPORTED;
     }
+}
+
+template <int Q, int TC, int L>
+int launch_split_batched(const BatchArgs &ba, hipStream_t s) {
+    using S = SplitShape<Q, TC, L>;
+    const unsigned grid = (unsigned)std::max(1, std::min(compute_units() * S::WGS, ba.n_items));
+    hipLaunchKernelGGL((k_split_batched<Q, TC, L>), dim3(grid), dim3(S::NW * kWave), 0, s, ba);
+    return launch_status("screen_batched");
+}
+
+// The batch's screen: the split screen, then (only where the inputs were
+// marked wide) the FP32 chain over the same items.
+int launch_screen(const BatchPlan &bp, BatchArgs ba, const BatchBuffers &b, hipStream_t s) {
+    int st;
+    {
+        ScopedTimer timer("screen_batched", s);
+        BatchArgs bs = ba;
+        bs.base.Ap = b.kb.split;
+        bs.base.ref_map = b.order;
+        st = RSC_ERR_UNSUPPORTED;
+        const SplitGeom g = split_geom(bp.kp.d);
+#define X(Q, TC)                                                          \
+    if (g.q == Q && g.tc == TC)                                           \
+        st = bp.kp.half == 16 ? launch_split_batched<Q, TC, 16>(bs, s) : launch_split_batched<Q, TC, 32>(bs, s);
+        RSC_SPLIT_GEOMS_128(X)
+#undef X
+        if (st != RSC_OK) return st;
+    }
+    hipLaunchKernelGGL(k_batch_init, dim3(1), dim3(64), 0, s, ba.counter, nullptr, nullptr, (int64_t)0);
+    ba.base.only_wide = 1;
+    ba.tile_q = split_queries_per_group(bp.kp.d, bp.kp.half) / 128;
+    return launch_batched(bp, ba, s, bp.kp.half, "screen_wide");
 }
 
 // Upload the plan's tables into the workspace (synchronises the stream, so
@@ -321,6 +400,9 @@ BatchArgs batch_args(const BatchPlan &bp, const BatchBuffers &b, const float *X)
     ba.items = b.items;
     ba.n_items = (int)bp.items.size();
     ba.counter = b.counter;
+    ba.base.kc = b.kb.counters;
+    ba.rows = b.order;
+    ba.tile_q = 1;
     return ba;
 }
 
@@ -330,7 +412,14 @@ int screen_only(const BatchPlan &bp, const BatchBuffers &b, const float *X, hipS
     hipLaunchKernelGGL(k_batch_init, dim3(g), dim3(256), 0, s, b.counter, b.kb.cand_idx, b.kb.cand_key, ncand);
     int st = launch_status("batch init");
     if (st != RSC_OK) return st;
-    return launch_batched(bp, batch_args(bp, b, X), s);
+    return launch_screen(bp, batch_args(bp, b, X), b, s);
+}
+
+// Row order, norms and packings (they do not depend on the tile shape).
+int prepare(const BatchPlan &bp, const BatchBuffers &b, const float *X, hipStream_t s) {
+    int st = sample_order_run(X, bp.kp.nq, bp.kp.d, b.soff, bp.S, b.order_ws, b.order, s);
+    if (st != RSC_OK) return st;
+    return knn_prep_fp32(bp.kp, X, nullptr, b.kb, b.blk_sample, b.boff, b.soff, b.order, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -478,6 +567,7 @@ int escalate(const BatchPlan &bp, const BatchBuffers &b, const float *X, int32_t
         re.qlist = b.esc_rows;
         re.qcount = b.esc_count;
         re.qcap = c;
+        re.split = 0;  // keys of the FP32 chain
         re.S = kEscHalf;
         re.KP = kEscHalf;
         re.P = 2 * kEscRanges;
@@ -523,11 +613,15 @@ int batched_run(const float *X, const int64_t *offsets, int S, int d, int k, int
         return RSC_ERR_WORKSPACE;
     }
     if ((st = upload_plan(bp, b, s)) != RSC_OK) return st;
-    if ((st = knn_prep_fp32(bp.kp, X, nullptr, b.kb, b.blk_sample, b.boff, b.soff, nullptr, s)) != RSC_OK) return st;
+    if ((st = prepare(bp, b, X, s)) != RSC_OK) return st;
     if ((st = screen_only(bp, b, X, s)) != RSC_OK) return st;
     RerankArgs ra{};
+    hipLaunchKernelGGL(k_set_count, dim3(1), dim3(64), 0, s, b.order_n, (int32_t)bp.kp.nq);
     ra.Q = X;
     ra.nq = bp.kp.nq;
+    ra.qlist = b.order;
+    ra.qcount = b.order_n;
+    ra.qcap = (int)bp.kp.nq;
     ra.R = X;
     ra.d = d;
     ra.k = k;
@@ -544,6 +638,7 @@ int batched_run(const float *X, const int64_t *offsets, int S, int d, int k, int
     ra.flag_count = &b.kb.counters->flagged;
     ra.out_idx = out_idx;
     ra.out_dist = out_dist;
+    knn_split_bounds(ra);
     if ((st = knn_launch_rerank(ra, bp.kp.nq, "rerank", s)) != RSC_OK) return st;
     return escalate(bp, b, X, out_idx, out_dist, ra, s);
 }
@@ -578,7 +673,7 @@ int batched_autotune(const float *X, const int64_t *offsets, int S, int d, int k
         if ((r = upload_plan(bp, b, s)) != RSC_OK) return r;
         if (!prepared) {
             // the packed references do not depend on the shape
-            if ((r = knn_prep_fp32(bp.kp, X, nullptr, b.kb, b.blk_sample, b.boff, b.soff, nullptr, s)) != RSC_OK) return r;
+            if ((r = prepare(bp, b, X, s)) != RSC_OK) return r;
             if ((r = screen_only(bp, b, X, s)) != RSC_OK) return r;  // warm
             prepared = true;
         }

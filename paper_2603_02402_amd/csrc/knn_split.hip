@@ -40,14 +40,14 @@ __global__ __launch_bounds__(256) void k_pack_split(const float *__restrict__ R,
     for (int64_t b = blockIdx.x; b < nblk; b += gridDim.x) {
         // row of packed slot 32 b + i, or -1 (see k_pack)
         auto row_of = [&](int i) -> int64_t {
-            if (row_map) return 32 * b + i < nmap ? row_map[32 * b + i] : -1;
-            int64_t row = 32 * b + i, end = nr;
+            int64_t pos = 32 * b + i, end = row_map ? nmap : nr;
             if (blk_sample) {
                 const int smp = blk_sample[b];
-                row = soff[smp] + 32 * (b - boff[smp]) + i;
+                pos = soff[smp] + 32 * (b - boff[smp]) + i;
                 end = soff[smp + 1];
             }
-            return row < end ? row : -1;
+            if (pos >= end) return -1;
+            return row_map ? row_map[pos] : pos;
         };
         __syncthreads();  // the previous block's rows are consumed
         if (row_map) {

@@ -29,6 +29,7 @@
 #include "rsc_internal.hpp"
 #include "screen_common.hpp"
 #include "screen_fp32.hpp"
+#include "screen_split.hpp"
 
 namespace rsc {
 namespace {
@@ -60,6 +61,7 @@ struct RoutedBuffers {
     int64_t *pblk;
     int32_t *map;
     float *packed, *norms;
+    void *split;
     int32_t *own, *probes, *ccount, *cursor, *qperm, *fall;
     int64_t *coff, *toff;
     int2 *tiles;
@@ -107,6 +109,7 @@ size_t carve_probed(int64_t n, int d, int k, int P, int probes, void *ws, Routed
     b.map = cv.take<int32_t>((size_t)nblk * 32);
     b.packed = cv.take<float>(knn_packed_floats(dh, nblk));
     b.norms = cv.take<float>((size_t)nblk * 32);
+    b.split = cv.take<char>(split_packed_bytes(d, nblk));
     b.own = cv.take<int32_t>(n);
     b.probes = cv.take<int32_t>((size_t)n * probes);
     b.ccount = cv.take<int32_t>(P);
@@ -419,6 +422,7 @@ template <int DH, int L>
 __global__ __launch_bounds__(256, screen_min_waves(DH, L)) void k_screen_routed(RoutedScreenArgs ra) {
     __shared__ float2 qbuf[kQueueCap * 256];
     __shared__ uint32_t bitmap[kScreenWaves][kBitmapWords];
+    if (ra.s.kc->wide == 0) return;  // the split screen answered
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = tid >> 6;
     const int c = lane & 31, h = lane >> 5;
@@ -528,6 +532,140 @@ __global__ __launch_bounds__(256, screen_min_waves(DH, L)) void k_screen_routed(
     }
 }
 
+// The union of a tile's probed partitions, block by block in ascending order,
+// with the lanes whose query probed the block's partition.
+struct ProbeStream {
+    const uint32_t *bm;     // the union (LDS)
+    const int64_t *pblk;
+    const int32_t *pr;      // this lane's sorted probe list
+    int nwords, np;
+    int w = 0, ptr = 0, nextp;
+    uint32_t bits;
+    int64_t b = 0, b1 = 0;  // the next block of the current partition and its end
+    bool active = false;
+
+    __device__ __forceinline__ ProbeStream(const uint32_t *bm_, const int64_t *pblk_, const int32_t *pr_, int nwords_,
+                                           int np_, bool live)
+        : bm(bm_), pblk(pblk_), pr(pr_), nwords(nwords_), np(np_) {
+        nextp = live ? pr[0] : INT_MAX;
+        bits = nwords > 0 ? __builtin_amdgcn_readfirstlane(bm[0]) : 0u;
+    }
+    // The next block and whether this lane's query takes it; false at the end.
+    __device__ __forceinline__ bool next(int64_t &blk, bool &on) {
+        while (b >= b1) {
+            while (bits == 0u) {
+                if (++w >= nwords) return false;
+                bits = __builtin_amdgcn_readfirstlane(bm[w]);
+            }
+            const int p = w * 32 + __builtin_ctz(bits);
+            bits &= bits - 1;
+            // every probe of this query below p has been consumed, so the
+            // query probed p exactly when its next probe is p
+            active = nextp == p;
+            if (active) {
+                ++ptr;
+                nextp = ptr < np ? pr[ptr] : INT_MAX;
+            }
+            b = pblk[p];
+            b1 = pblk[p + 1];
+        }
+        blk = b++;
+        on = active;
+        return true;
+    }
+};
+
+// The same search on the split operands.  Tiles of different waves share no
+// blocks, so each wave streams its own through a pair of LDS buffers by
+// asynchronous loads, the next block's in flight under the current one's
+// MFMAs, without a barrier.
+template <int Q, int TC, int L>
+__global__ __launch_bounds__(256, (SplitStream<Q, TC>::W)) void k_split_routed(RoutedScreenArgs ra) {
+    constexpr int NA = 2 * Q + TC;
+    constexpr int QCAP = 8;
+    __shared__ __attribute__((aligned(16))) char buf0[kScreenWaves * NA * 1024];
+    __shared__ __attribute__((aligned(16))) char buf1[kScreenWaves * NA * 1024];
+    __shared__ double qbuf[QCAP * 256];
+    __shared__ uint32_t bitmap[kScreenWaves][kBitmapWords];
+    if (ra.s.kc->wide) return;
+    const int tid = threadIdx.x;
+    const int lane = tid & (kWave - 1), wave = tid >> 6;
+    const int c = lane & 31, h = lane >> 5;
+    uint32_t *bm = bitmap[wave];
+    double *q = qbuf + tid;
+    const int nwords = (ra.nparts + 31) / 32;
+    const int ntiles = *ra.ntiles;
+    const ScreenArgs &a = ra.s;
+    const float scale = ldexpf(1.f, split_exponent(a.kc));
+    while (true) {
+        int t = 0;
+        if (lane == 0) t = atomicAdd(ra.tile_next, 1);
+        t = __shfl(t, 0, kWave);
+        if (t >= ntiles) break;
+        const int2 tile = ra.tiles[t];
+        const int64_t slot = c < tile.y ? (int64_t)tile.x + c : -1;
+        const int64_t row = slot >= 0 ? (int64_t)ra.qperm[slot] : -1;
+        const int32_t *pr = ra.probes + (row >= 0 ? row : 0) * ra.np;
+        for (int w = lane; w < nwords; w += kWave) bm[w] = 0u;
+        __builtin_amdgcn_wave_barrier();
+        if (row >= 0) {
+            for (int j = h; j < ra.np; j += 2) {
+                const int p = pr[j];
+                if (p != INT_MAX) atomicOr(&bm[p >> 5], 1u << (p & 31));
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");  // the ORs land before the bitmap is read
+        __builtin_amdgcn_wave_barrier();
+
+        SplitQuery<Q, TC> qop;
+        qop.load(a.Q, a.d, row, h, scale);
+        PackTopK<L, QCAP> top;
+        top.init();
+        int64_t union_blocks = 0;
+        ProbeStream stream(bm, ra.pblk, pr, nwords, ra.np, row >= 0);
+        char *const mine0 = buf0 + wave * (NA * 1024), *const mine1 = buf1 + wave * (NA * 1024);
+        auto load = [&](char *buf, int64_t blk) {
+            const char *src = static_cast<const char *>(a.Ap) + blk * (NA * 1024) + lane * 16;
+#pragma unroll
+            for (int s = 0; s < NA; ++s) load_lds16(src + s * 1024, buf + s * 1024);
+        };
+        // `more`: the next block's NA loads are in flight behind this one's
+        auto use = [&](const char *buf, int64_t blk, bool on, bool more) {
+            if (more)
+                __builtin_amdgcn_s_waitcnt(0x0f70 | (NA & 15) | ((NA >> 4) << 14));
+            else
+                __builtin_amdgcn_s_waitcnt(0x0f70);
+            const f16x8 *sl = reinterpret_cast<const f16x8 *>(buf) + lane;
+            f16x8 A[NA];
+#pragma unroll
+            for (int s = TC; s < NA; ++s) A[s] = sl[s * kWave];
+#pragma unroll
+            for (int s = 0; s < TC; ++s) A[s] = sl[s * kWave];
+            f32x16 acc = split_keys<Q, TC>(A, qop);
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[v] = on ? acc[v] : INFINITY;
+            top.offer(acc, (int)(blk * 32) + 4 * h, q, 256);
+            ++union_blocks;
+        };
+        int64_t blk0 = 0, blk1 = 0;
+        bool on0 = false, on1 = false;
+        bool have = stream.next(blk0, on0);
+        if (have) load(mine0, blk0);
+        while (have) {
+            const bool more = stream.next(blk1, on1);
+            if (more) load(mine1, blk1);
+            use(mine0, blk0, on0, more);
+            if (!more) break;
+            have = stream.next(blk0, on0);
+            if (have) load(mine0, blk0);
+            use(mine1, blk1, on1, have);
+        }
+        top.flush(q, 256);
+        if (lane == 0) atomicAdd(ra.screened, (unsigned long long)(union_blocks * 32 * tile.y));
+        if (slot >= 0) top.store(a, slot, 0, h, ra.map);
+    }
+}
+
 int device_slots(int dh) {
     static int cus = 0;
     if (cus == 0) {
@@ -548,8 +686,31 @@ int launch_routed_dh(const RoutedScreenArgs &ra, unsigned grid, int half, hipStr
     return launch_status("screen_routed");
 }
 
-int launch_routed(int dh, const RoutedScreenArgs &ra, int half, int64_t max_tiles, hipStream_t s) {
+template <int Q, int TC>
+int launch_split_routed(const RoutedScreenArgs &ra, int half, int64_t max_tiles, int cus, hipStream_t s) {
+    const unsigned grid = (unsigned)std::max<int64_t>(
+        1, std::min<int64_t>((int64_t)cus * SplitStream<Q, TC>::W, (max_tiles + kScreenWaves - 1) / kScreenWaves));
+    if (half == 16)
+        hipLaunchKernelGGL((k_split_routed<Q, TC, 16>), dim3(grid), dim3(256), 0, s, ra);
+    else
+        hipLaunchKernelGGL((k_split_routed<Q, TC, 32>), dim3(grid), dim3(256), 0, s, ra);
+    return launch_status("screen_routed");
+}
+
+int launch_split(const RoutedScreenArgs &ra, int half, int64_t max_tiles, hipStream_t s) {
     ScopedTimer timer("screen_routed", s);
+    const SplitGeom g = split_geom(ra.s.d);
+    const int cus = device_slots(64) / screen_min_waves(64, 16);
+#define X(Q, TC) \
+    if (g.q == Q && g.tc == TC) return launch_split_routed<Q, TC>(ra, half, max_tiles, cus, s);
+    RSC_SPLIT_GEOMS_128(X)
+#undef X
+    set_error("internal: no split screen for this dimension");
+    return RSC_ERR_UNSUPPORTED;
+}
+
+int launch_routed(int dh, const RoutedScreenArgs &ra, int half, int64_t max_tiles, hipStream_t s) {
+    ScopedTimer timer("screen_wide", s);
     const unsigned grid =
         (unsigned)std::max<int64_t>(1, std::min<int64_t>(device_slots(dh), (max_tiles + kScreenWaves - 1) / kScreenWaves));
     switch (dh) {
@@ -623,6 +784,9 @@ int probed_run(const float *X, int64_t n, int d, int k, const int64_t *offsets, 
         // a partition layout inconsistent with n could overrun the packed
         // array: the pack covers the capacity, which every valid layout fits
         if ((st = knn_pack_mapped(dh, X, b.nrow, n, d, nblk_cap, b.packed, b.norms, b.map, s)) != RSC_OK) return st;
+        if ((st = split_pack(X, b.nrow, n, d, nblk_cap, b.split, nullptr, nullptr, nullptr, b.map, nblk_cap * 32, b.kc,
+                             s)) != RSC_OK)
+            return st;
         hipLaunchKernelGGL(k_sort_probes, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, probe_parts, n, probes, P,
                            b.probes, &b.rc->bad);
         hipLaunchKernelGGL(k_classify, dim3(grid_for(n)), dim3(256), 0, s, n, exact_rows, mass, threshold, b.own,
@@ -672,7 +836,14 @@ int probed_run(const float *X, int64_t n, int d, int k, const int64_t *offsets, 
     ra.tile_next = &b.rc->tile_next;
     ra.map = b.map;
     ra.screened = &b.rc->screened_cells;
-    if (hc.ntiles > 0 && (st = launch_routed(dh, ra, half, hc.ntiles, s)) != RSC_OK) return st;
+    ra.s.kc = b.kc;
+    if (hc.ntiles > 0) {
+        RoutedScreenArgs rs = ra;
+        rs.s.Ap = b.split;
+        if ((st = launch_split(rs, half, hc.ntiles, s)) != RSC_OK) return st;
+        // (only where the inputs were marked wide; the tiles are then all left)
+        if ((st = launch_routed(dh, ra, half, hc.ntiles, s)) != RSC_OK) return st;
+    }
 
     RerankArgs rr{};
     rr.Q = X;
@@ -696,6 +867,7 @@ int probed_run(const float *X, int64_t n, int d, int k, const int64_t *offsets, 
     rr.flag_count = &b.rc->nfall;
     rr.out_idx = out_idx;
     rr.out_dist = out_dist;
+    knn_split_bounds(rr);
     if (hc.nconf > 0 && (st = knn_launch_rerank(rr, hc.nconf, "rerank_probed", s)) != RSC_OK) return st;
     hipLaunchKernelGGL(k_route_uncertified, dim3(64), dim3(256), 0, s, b.rc, b.fall, b.route);
     if ((st = launch_status("probed routes")) != RSC_OK) return st;

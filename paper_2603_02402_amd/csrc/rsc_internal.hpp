@@ -187,8 +187,8 @@ int knn_launch_screen(int dh, const scr::ScreenArgs &a, unsigned gx, int half_wi
 // Split FP16 screen of the exact path (knn_split.hip).
 size_t split_packed_bytes(int d, int64_t nblk);
 int split_queries_per_group(int d, int half_width);
-// Packs nblk blocks (sample tables as knn_prep_fp32; row_map: the rows of
-// the first nmap packed slots, -1 and the slots past them padded)
+// Packs nblk blocks (sample tables as knn_prep_fp32; row_map: the rows at
+// the first nmap positions, -1 and the positions past them padded)
 // and marks inputs whose norms spread too far; needs the norms of R.
 int split_pack(const float *R, const float *nrow, int64_t nr, int d, int64_t nblk, void *packed,
                const int32_t *blk_sample, const int64_t *boff, const int64_t *soff, const int32_t *row_map,
@@ -217,6 +217,11 @@ int lowp_unmap_rows(const KnnPlan &p, const KnnBuffers &b, const int32_t *rmap, 
 // Morton code of their first three coordinates.
 size_t query_order_workspace(int64_t nq);
 int query_order_run(const float *Q, int64_t nq, int d, void *ws, int32_t *perm, hipStream_t s);
+// The same within each of S samples (rows soff[s] .. soff[s+1]-1, device
+// offsets): perm holds every sample's rows at its own positions.
+size_t sample_order_workspace(int64_t n);
+int sample_order_run(const float *X, int64_t n, int d, const int64_t *soff, int S, void *ws, int32_t *perm,
+                     hipStream_t s);
 
 // Batched form (knn_batched.hip).
 size_t batched_workspace_bytes(const int64_t *offsets, int S, int d, int k);

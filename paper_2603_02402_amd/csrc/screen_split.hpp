@@ -186,6 +186,13 @@ struct SplitShape {
     static constexpr int QG = NW * 32;  // queries per workgroup
 };
 
+// Waves per SIMD of a screen whose waves stream blocks of their own, two LDS
+// buffers each (two workgroups of 4 waves per CU while they fit).
+template <int Q, int TC>
+struct SplitStream {
+    static constexpr int W = 2 * Q + TC <= 9 ? 2 : 1;
+};
+
 // One tile of 32 queries per wave over the `span` packed blocks b0 + step i of a
 // range, i from `rot` on and around: every wave of the workgroup calls this
 // together.  slot / row: this lane's output slot and query row (or -1);

@@ -89,3 +89,42 @@ def test_queries_of_another_size(rsc, oracle_mod, factor):
     res = compare_knn(None, np.arange(333), idx, dist, io, do, oracle_mod, 15, self_mode=False,
                       pair_dist=lambda _, i, j: np.sqrt(((Q[i].astype(np.float64) - R[j]) ** 2).sum(1)))
     assert res["exact_rows"] + res["near_tie_rows"] == 333
+
+
+@pytest.mark.parametrize("spread", [1.0, 2.0 ** -20])
+def test_batched_samples(rsc, oracle_mod, spread):
+    """Ragged samples around the tile sizes; with one sample 2^-20 as long as the others the FP32 chain answers."""
+    import torch
+
+    print(f"[split] batched spread={spread}", flush=True)
+    sizes = [15, 16, 31, 33, 255, 256, 257, 700, 2049]
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    X = np.concatenate([synth.mixture(n, d=50, n_clusters=3, seed=n) for n in sizes])
+    X[off[5]:off[7]] *= np.float32(spread)
+    idx, dist = rsc.knn_batched(torch.from_numpy(X).cuda(), off, 15)
+    idx, dist = idx.cpu().numpy(), dist.cpu().numpy()
+    for s in range(len(sizes)):
+        io, _, do = oracle_mod.knn(X[off[s]:off[s + 1]], 15)
+        np.testing.assert_array_equal(idx[off[s]:off[s + 1]] - off[s], io)
+        np.testing.assert_array_equal(dist[off[s]:off[s + 1]], np.asarray(do).astype(np.float32))
+
+
+@pytest.mark.parametrize("spread", [1.0, 2.0 ** -20])
+@pytest.mark.parametrize("d,k", [(50, 15), (9, 5), (64, 20), (100, 40), (128, 15)])
+def test_probed_partitions(rsc, oracle_mod, d, k, spread):
+    import torch
+    from oracle import partition
+
+    print(f"[split] probed d={d} k={k} spread={spread}", flush=True)
+    n, P = 2500, 37
+    X = synth.mixture(n, d=d, n_clusters=5, seed=d)
+    X[::2] *= np.float32(spread)
+    labels = synth.random_labels(n, P, 3)
+    off, perm = partition.inverted_lists(labels, P)
+    pr = synth.random_probes(n, P, 9, 4, own=labels)
+    dev = [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (X, off, perm.astype(np.int32), pr)]
+    idx, dist, route, _ = rsc.knn_probed(dev[0], k, *dev[1:])
+    route = route.cpu().numpy()
+    io, _, do = partition.routed_knn(X, k, off, perm, pr, exact_rows=route != 0)
+    np.testing.assert_array_equal(idx.cpu().numpy(), io)
+    np.testing.assert_array_equal(dist.cpu().numpy(), np.asarray(do).astype(np.float32))
