@@ -67,63 +67,78 @@ constexpr int kEscalateSplits = 16;
 constexpr int kEscalateWidth = 64;
 
 // Squared norms of the reference rows (float64 sum, rounded once) and the
-// largest norm.  One wave per block of norm_rows(d) rows (64 for d <= 128):
-// the rows (contiguous in memory) are copied into LDS with coalesced loads,
-// then lane i sums row i.
+// largest norm.  A workgroup takes norm_rows(d) rows (64 for d <= 128): they
+// are contiguous in memory and come into LDS with coalesced loads, then four
+// lanes sum each row.  Bound by reading the rows; one wave per 64 rows, a lane
+// summing each, kept 5 waves on a CU (245 us at 640k x 50, now 58).
 constexpr int kNormRows = 64;
-constexpr int kNormBuf = kNormRows * 128;  // floats staged per block
-__host__ __device__ inline int norm_rows(int d) { return d <= 128 ? kNormRows : kNormBuf / d; }
+constexpr int kNormThreads = 256;
+constexpr int kNormBuf = kNormRows * 129;  // floats staged per block
+__host__ __device__ inline int norm_rows(int d) { return d <= 128 ? kNormRows : kNormRows * 128 / d; }
 
-__global__ __launch_bounds__(64) void k_norms(const float *__restrict__ R, int64_t nr, int d,
-                                              float *__restrict__ nrow, uint32_t *__restrict__ max_norm_bits) {
+__global__ __launch_bounds__(kNormThreads) void k_norms(const float *__restrict__ R, int64_t nr, int d,
+                                                        float *__restrict__ nrow,
+                                                        uint32_t *__restrict__ max_norm_bits) {
     // nrow may be null: only the largest norm is wanted
     __shared__ float buf[kNormBuf];
-    const int lane = threadIdx.x;
+    __shared__ float wmax[kNormThreads / kWave];
     const int nrb = norm_rows(d);
     const int64_t r0 = (int64_t)blockIdx.x * nrb;
     const int rows = (int)min<int64_t>(nrb, nr - r0);
+    const int ld = d | 1;
     const float *src = R + r0 * d;
-    for (int e = lane; e < rows * d; e += kWave) buf[e] = src[e];
+    for (int e = threadIdx.x; e < rows * d; e += kNormThreads) buf[e / d * ld + e % d] = src[e];
     __syncthreads();
-    float nf = 0.f;
-    if (lane < rows) {
-        double s = 0.0;
-        for (int t = 0; t < d; ++t) {
-            const double x = (double)buf[lane * d + t];
+    const int i = threadIdx.x >> 2, q = threadIdx.x & 3;
+    double s = 0.0;
+    if (i < rows)
+        for (int t = q; t < d; t += 4) {
+            const double x = (double)buf[i * ld + t];
             s += x * x;
         }
-        nf = (float)s;
-        if (nrow) nrow[r0 + lane] = nf;
-    }
+    s += __shfl_xor(s, 1, kWave);
+    s += __shfl_xor(s, 2, kWave);
+    const float nf = (float)s;
+    if (nrow && i < rows && q == 0) nrow[r0 + i] = nf;
     const float m = wave_max(sqrtf(nf));
-    if (lane == 0) atomicMax(max_norm_bits, __float_as_uint(m));
+    if ((threadIdx.x & (kWave - 1)) == 0) wmax[threadIdx.x / kWave] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const uint32_t bits = __float_as_uint(fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3])));
+        // an atomic only where the maximum grows: they all meet in one word
+        if (bits > *(volatile uint32_t *)max_norm_bits) atomicMax(max_norm_bits, bits);
+    }
 }
 
 // Unit-normalised rows for the cosine screen: x / ||x|| with the norm summed
 // in float64 and rounded once to float32, then one float32 division per
 // element (each element within 2 units of roundoff of x_t / ||x||); a row of
-// zero norm stays zero.  One wave per 64 rows, staged through LDS so that the
-// loads and stores are coalesced.
-__global__ __launch_bounds__(64) void k_normalize(const float *__restrict__ X, int64_t n, int d,
-                                                  float *__restrict__ out) {
+// zero norm stays zero.  Rows staged as in k_norms.
+__global__ __launch_bounds__(kNormThreads) void k_normalize(const float *__restrict__ X, int64_t n, int d,
+                                                            float *__restrict__ out) {
     __shared__ float buf[kNormBuf];
-    const int lane = threadIdx.x;
+    __shared__ float norm[kNormRows];
     const int nrb = norm_rows(d);
     const int64_t r0 = (int64_t)blockIdx.x * nrb;
     const int rows = (int)min<int64_t>(nrb, n - r0);
-    for (int e = lane; e < rows * d; e += kWave) buf[e] = X[r0 * d + e];
+    const int ld = d | 1;
+    for (int e = threadIdx.x; e < rows * d; e += kNormThreads) buf[e / d * ld + e % d] = X[r0 * d + e];
     __syncthreads();
-    if (lane < rows) {
-        double s = 0.0;
-        for (int t = 0; t < d; ++t) {
-            const double x = (double)buf[lane * d + t];
+    const int i = threadIdx.x >> 2, q = threadIdx.x & 3;
+    double s = 0.0;
+    if (i < rows)
+        for (int t = q; t < d; t += 4) {
+            const double x = (double)buf[i * ld + t];
             s += x * x;
         }
-        const float nrm = (float)sqrt(s);
-        for (int t = 0; t < d; ++t) buf[lane * d + t] = nrm > 0.f ? buf[lane * d + t] / nrm : 0.f;
-    }
+    s += __shfl_xor(s, 1, kWave);
+    s += __shfl_xor(s, 2, kWave);
+    if (i < rows && q == 0) norm[i] = (float)sqrt(s);
     __syncthreads();
-    for (int e = lane; e < rows * d; e += kWave) out[r0 * d + e] = buf[e];
+    for (int e = threadIdx.x; e < rows * d; e += kNormThreads) {
+        const float nrm = norm[e / d];
+        out[r0 * d + e] = nrm > 0.f ? buf[e / d * ld + e % d] / nrm : 0.f;
+    }
 }
 
 // Packed reference layout for a contraction half-width DH.  Block b holds
@@ -984,8 +999,8 @@ int knn_prep_fp32(const KnnPlan &p, const float *R, const float *Q, const KnnBuf
     const int s4 = packed_s4(p.dh);
     ScopedTimer timer("prep_pack", stream);
     hipLaunchKernelGGL(k_init_counters, dim3(1), dim3(64), 0, stream, b.counters);
-    hipLaunchKernelGGL(k_norms, dim3((unsigned)((p.nr + norm_rows(p.d) - 1) / norm_rows(p.d))), dim3(kNormRows), 0, stream, R,
-                       p.nr, p.d, b.nrow,
+    hipLaunchKernelGGL(k_norms, dim3((unsigned)((p.nr + norm_rows(p.d) - 1) / norm_rows(p.d))), dim3(kNormThreads), 0,
+                       stream, R, p.nr, p.d, b.nrow,
                        &b.counters->max_norm_bits);
     const int64_t tot = p.nblk * s4 * kWave;
     const unsigned g1 = (unsigned)std::min<int64_t>((tot + 255) / 256, 65536);
@@ -993,7 +1008,7 @@ int knn_prep_fp32(const KnnPlan &p, const float *R, const float *Q, const KnnBuf
                        norm_folded(p.dh) ? 1 : 0, p.nblk, reinterpret_cast<f32x4 *>(b.packed), b.norms, blk_sample,
                        boff, soff, nullptr);
     if (Q && p.nq > 0)
-        hipLaunchKernelGGL(k_norms, dim3((unsigned)((p.nq + norm_rows(p.d) - 1) / norm_rows(p.d))), dim3(kNormRows), 0,
+        hipLaunchKernelGGL(k_norms, dim3((unsigned)((p.nq + norm_rows(p.d) - 1) / norm_rows(p.d))), dim3(kNormThreads), 0,
                            stream, Q, p.nq, p.d, nullptr, &b.counters->query_norm_bits);
     const int st = launch_status("prep_pack");
     if (st != RSC_OK) return st;
@@ -1003,9 +1018,8 @@ int knn_prep_fp32(const KnnPlan &p, const float *R, const float *Q, const KnnBuf
 
 int knn_norms(const float *R, int64_t nr, int d, float *nrow, KnnCounters *counters, hipStream_t stream) {
     hipLaunchKernelGGL(k_init_counters, dim3(1), dim3(64), 0, stream, counters);
-    hipLaunchKernelGGL(k_norms, dim3((unsigned)((nr + norm_rows(d) - 1) / norm_rows(d))), dim3(kNormRows), 0, stream, R, nr,
-                       d, nrow,
-                       &counters->max_norm_bits);
+    hipLaunchKernelGGL(k_norms, dim3((unsigned)((nr + norm_rows(d) - 1) / norm_rows(d))), dim3(kNormThreads), 0, stream, R,
+                       nr, d, nrow, &counters->max_norm_bits);
     return launch_status("norms");
 }
 
@@ -1220,10 +1234,10 @@ size_t knn_workspace(const KnnPlan &p, void *ws, KnnBuffers *out) {
 // Cosine metric: the screen's inputs are the unit-normalised rows.
 int normalize_inputs(const KnnPlan &p, const float *Q, const float *R, const KnnBuffers &b, hipStream_t stream) {
     ScopedTimer timer("normalize", stream);
-    hipLaunchKernelGGL(k_normalize, dim3((unsigned)((p.nr + norm_rows(p.d) - 1) / norm_rows(p.d))), dim3(kNormRows), 0, stream,
-                       R, p.nr, p.d, b.rn);
+    hipLaunchKernelGGL(k_normalize, dim3((unsigned)((p.nr + norm_rows(p.d) - 1) / norm_rows(p.d))), dim3(kNormThreads), 0,
+                       stream, R, p.nr, p.d, b.rn);
     if (!p.self_mode && p.nq > 0)
-        hipLaunchKernelGGL(k_normalize, dim3((unsigned)((p.nq + norm_rows(p.d) - 1) / norm_rows(p.d))), dim3(kNormRows), 0,
+        hipLaunchKernelGGL(k_normalize, dim3((unsigned)((p.nq + norm_rows(p.d) - 1) / norm_rows(p.d))), dim3(kNormThreads), 0,
                            stream, Q, p.nq, p.d, b.qn);
     return launch_status("normalize");
 }
