@@ -43,7 +43,7 @@
 #include "rsc_internal.hpp"
 #include "screen_common.hpp"
 #include "screen_fp32.hpp"
-#include "screen_split.hpp"
+#include "screen_split_grid.hpp"
 
 namespace rsc {
 
@@ -55,8 +55,13 @@ constexpr int kMaxD = 256;       // exact FP32 path (reduced-precision screens: 
 constexpr int kMaxK = 255;       // exact FP32 path (reduced-precision screens: 63)
 constexpr int kMaxDLowp = 128;
 constexpr int kMaxKLowp = 63;
-// Rows from which the exact search of one matrix orders them (knn_run).
-constexpr int64_t kOrderRows = 16384;
+// References and query-reference pairs from which the exact search is pruned:
+// ordering them and bounding the segments costs 0.15 ms at 16k rows and 0.9 ms
+// at 1M.  Screen, rerank and order at 16384 rows (20 clusters): 0.41 ms pruned,
+// 0.46 without (in a Morton order); at 10k rows 0.39 against 0.21; rectangular:
+// the pairs of that square.
+constexpr int64_t kPruneRows = 16384;
+constexpr double kPrunePairs = 2.5e8;
 // Workgroups the split screen asks for before it stops splitting the
 // references: fewer leave CUs idle, more multiply the candidate lists the
 // rerank reads (10k rows: screen + rerank 0.34 ms at 128, 0.47 at 256, 0.74
@@ -218,6 +223,7 @@ __global__ void k_init_counters(KnnCounters *c) {
         c->rescanned = 0;
         c->query_norm_bits = 0u;
         c->wide = 0;
+        c->visited = 0ull;
     }
 }
 
@@ -545,6 +551,7 @@ __global__ __launch_bounds__(256) void k_rerank(RerankArgs a) {
 // order of the answers is a count of smaller (distance, index) pairs in LDS.
 // More survivors than lanes: pass by pass, against the best so far.
 // ---------------------------------------------------------------------------
+constexpr int kLeanAnswer = 64;            // neighbours a group of 64 lanes holds
 constexpr int kLeanChunk = 32;             // dimensions staged per pass
 constexpr int kLeanLd = kLeanChunk + 2;    // LDS row stride: 8-byte reads of 32 lanes meet 32 bank pairs
 
@@ -606,7 +613,8 @@ __global__ __launch_bounds__(256) void k_rerank_lean(RerankArgs a) {
 
     // the candidates: lists of S keys, ascending; tau: the smallest key a full list could have rejected
     const int m = a.self_mode ? a.k - 1 : a.k;
-    const int total = a.P * a.S;
+    const int found = a.counts && live ? a.counts[slot] : 0;
+    const int total = a.counts ? min(found, a.KP) : a.P * a.S;
     const int64_t cbase = (live ? slot : 0) * a.P * a.KP;
     float key[KR];
     int cj[KR];
@@ -618,7 +626,7 @@ __global__ __launch_bounds__(256) void k_rerank_lean(RerankArgs a) {
         key[i] = INFINITY;
         cj[i] = -1;
         if (live && ci < total) {
-            const int p = ci / a.S, e = ci - p * a.S;
+            const int p = a.counts ? 0 : ci / a.S, e = ci - p * a.S;
             const int j = a.cand_idx[cbase + p * a.KP + e];
             const float v = a.cand_key[cbase + p * a.KP + e];
             if (e == a.S - 1 && j >= 0) tau = fminf(tau, v);
@@ -781,8 +789,8 @@ __global__ __launch_bounds__(256) void k_rerank_lean(RerankArgs a) {
     };
 #pragma unroll
     for (int i = 0; i < KR; ++i) {
-        if (i * G >= total) break;
-        const bool in = cj[i] >= 0 && (key[i] <= cut || (cosine && key[i] == 0.f));
+        if (__ballot(i * G < total) == 0ull) break;
+        const bool in = cj[i] >= 0 && (a.counts || key[i] <= cut || (cosine && key[i] == 0.f));
         const unsigned long long b = group_ballot(in);
         if (in) {
             const int at = waiting + __popcll(b & ((1ull << gl) - 1));
@@ -826,7 +834,15 @@ __global__ __launch_bounds__(256) void k_rerank_lean(RerankArgs a) {
         oi[off + pos] = have ? ej[g][pos] : -1;
         od[off + pos] = cosine ? (float)d : (float)sqrt(d);
     }
-    if (!ok && gl == 0) a.flag_out[atomicAdd(a.flag_count, 1)] = (int32_t)row;
+    if (found > a.KP) ok = false;
+    if (!ok && gl == 0) {
+        const int pos = atomicAdd(a.flag_count, 1);
+        a.flag_out[pos] = (int32_t)row;
+        if (a.flag_bound && pos < a.flag_cap) {
+            a.flag_bound[pos] = dm;
+            a.flag_found[pos] = 0;
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -995,7 +1011,7 @@ void knn_split_bounds(RerankArgs &ra) {
 }
 
 int knn_prep_fp32(const KnnPlan &p, const float *R, const float *Q, const KnnBuffers &b, const int32_t *blk_sample,
-                  const int64_t *boff, const int64_t *soff, const int32_t *ref_map, hipStream_t stream) {
+                  const int64_t *boff, const int64_t *soff, hipStream_t stream) {
     const int s4 = packed_s4(p.dh);
     ScopedTimer timer("prep_pack", stream);
     hipLaunchKernelGGL(k_init_counters, dim3(1), dim3(64), 0, stream, b.counters);
@@ -1010,10 +1026,7 @@ int knn_prep_fp32(const KnnPlan &p, const float *R, const float *Q, const KnnBuf
     if (Q && p.nq > 0)
         hipLaunchKernelGGL(k_norms, dim3((unsigned)((p.nq + norm_rows(p.d) - 1) / norm_rows(p.d))), dim3(kNormThreads), 0,
                            stream, Q, p.nq, p.d, nullptr, &b.counters->query_norm_bits);
-    const int st = launch_status("prep_pack");
-    if (st != RSC_OK) return st;
-    return split_pack(R, b.nrow, p.nr, p.d, p.nblk, b.split, blk_sample, boff, soff, ref_map, p.nr, b.counters,
-                      stream);
+    return launch_status("prep_pack");
 }
 
 int knn_norms(const float *R, int64_t nr, int d, float *nrow, KnnCounters *counters, hipStream_t stream) {
@@ -1064,9 +1077,9 @@ int knn_launch_rerank(const RerankArgs &ra, int64_t slots, const char *name, hip
         launch_rerank_lean<32, 2>(ra, slots, stream);
     else if (m <= 32 && total <= 256)
         launch_rerank_lean<32, 8>(ra, slots, stream);
-    else if (m <= 64 && total <= 512)
+    else if (m <= kLeanAnswer && total <= 512)
         launch_rerank_lean<64, 8>(ra, slots, stream);
-    else if (m <= 64 && total <= 2048)
+    else if (m <= kLeanAnswer && total <= 2048)
         launch_rerank_lean<64, 32>(ra, slots, stream);
     else if (m <= 128)
         hipLaunchKernelGGL(k_rerank<2>, grid, dim3(256), 0, stream, ra);
@@ -1165,11 +1178,14 @@ int knn_plan(int64_t nq, int64_t nr, int d, int k, const rsc_knn_opts *opts, boo
     plan->precision = precision;
     plan->metric = metric;
     plan->resid = resid;
-    plan->ordered = precision == RSC_FP32 && nq == nr && nq >= kOrderRows;
+    plan->pruned = precision == RSC_FP32 && nr >= kPruneRows && (double)nq * (double)nr >= kPrunePairs;
     // the split screen's workgroups of 8 waves fill a CU each; the others run four of 4 waves
     plan->splits = precision == RSC_FP32
-                       ? pick_splits(nq, plan->nblk, split_queries_per_group(d, plan->half), kSplitWant)
+                       ? pick_splits(nq, plan->nblk, split_queries_per_group(d, plan->half),
+                                     plan->pruned ? kCUs : kSplitWant)
                        : pick_splits(nq, plan->nblk, lowp_queries_per_group(precision, d), 1024);
+    // (two ranges even out tiles of different cost while each CU gets about one)
+    if (plan->pruned && nq < 512 * split_queries_per_group(d, plan->half)) plan->splits = std::max(plan->splits, 2);
     if (precision == RSC_FP32) {
         // enough (range, half) lists that the m nearest fill each to about half
         const int m = self_mode ? k - 1 : k;
@@ -1191,7 +1207,8 @@ size_t knn_workspace(const KnnPlan &p, void *ws, KnnBuffers *out) {
         b.nrow = cv.take<float>((size_t)p.nr);
         b.packed = cv.take<float>((size_t)p.nblk * s4 * kWave * 4);
         b.norms = cv.take<float>(norm_folded(p.dh) ? 1 : (size_t)p.nblk * 32);
-        b.split = cv.take<char>(split_packed_bytes(p.d, p.nblk));
+        // (the pruned screen loads whole segments: the last one may reach past the blocks)
+        b.split = cv.take<char>(split_packed_bytes(p.d, p.nblk + (p.pruned ? spatial_seg_blocks(p.nblk) : 0)));
     } else {
         b.packed = reinterpret_cast<float *>(cv.take<char>(lowp_packed_bytes(p.precision, p.nblk, p.d)));
         b.norms = cv.take<float>((size_t)p.nblk * 32);
@@ -1204,11 +1221,18 @@ size_t knn_workspace(const KnnPlan &p, void *ws, KnnBuffers *out) {
     b.flag2 = cv.take<int32_t>((size_t)std::max<int64_t>(esc_rows, 1));
     b.esc_idx = cv.take<int32_t>((size_t)std::max<int64_t>(esc_rows, 1) * kEscalateSplits * kEscalateWidth);
     b.esc_key = cv.take<float>((size_t)std::max<int64_t>(esc_rows, 1) * kEscalateSplits * kEscalateWidth);
+    b.esc_bound = cv.take<double>((size_t)std::max<int64_t>(esc_rows, 1));
+    b.esc_found = cv.take<int32_t>((size_t)std::max<int64_t>(esc_rows, 1));
     if (p.metric == RSC_COSINE) {
         b.rn = cv.take<float>((size_t)p.nr * p.d);
         b.qn = p.self_mode ? b.rn : cv.take<float>((size_t)std::max<int64_t>(p.nq, 1) * p.d);
     }
-    if ((fp32 ? p.ordered : p.resid == 0) && p.nq > 0) {
+    if (fp32 && p.pruned) {
+        b.qcount = cv.take<int32_t>(1);
+        const size_t need = spatial_carve(p.nq, p.nr, p.d, false, nullptr, nullptr);
+        char *base = cv.take<char>(need);
+        spatial_carve(p.nq, p.nr, p.d, false, base, &b.sp);
+    } else if (!fp32 && p.resid == 0 && p.nq > 0) {
         // spatial order of the queries (perm) and its sort
         b.perm = cv.take<int32_t>((size_t)p.nq);
         b.qcount = cv.take<int32_t>(1);
@@ -1343,18 +1367,28 @@ int knn_run(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, 
     const bool cosine = p.metric == RSC_COSINE;
     if (cosine && (st = normalize_inputs(p, Q, R, b, stream)) != RSC_OK) return st;
     const float *Qs = cosine ? b.qn : Q;  // what the screen sees
-    // One matrix: references and queries in a Morton order, each query group
-    // scanning from its own rows on, so that the lists fill with near keys
-    // first and few later blocks hold a key below any threshold.
-    const bool ordered = p.ordered && p.self_mode && !qlist;
-    if (ordered) {
-        if ((st = query_order_run(Qs, p.nq, p.d, b.order_ws, b.perm, stream)) != RSC_OK) return st;
+    const float *Rs = cosine ? b.rn : R;
+    if ((st = knn_prep_fp32(p, Rs, p.self_mode ? nullptr : Qs, b, nullptr, nullptr, nullptr, stream)) != RSC_OK)
+        return st;
+    // Large problems are screened in a spatial order with its segments' bounds.
+    const bool pruned = p.pruned && !qlist && p.nq > 0;
+    const int32_t *ref_map = nullptr;
+    if (pruned) {
+        if ((st = spatial_refs(Rs, b.nrow, p.nr, p.d, b.sp, b.counters, stream)) != RSC_OK) return st;
+        if (!p.self_mode && (st = spatial_queries(Qs, p.nq, p.nr, p.d, split_queries_per_group(p.d, p.half), b.sp,
+                                                  b.counters, stream)) != RSC_OK)
+            return st;
+        ref_map = b.sp.rperm;
+        qlist = p.self_mode ? b.sp.rperm : b.sp.qperm;
         hipLaunchKernelGGL(k_set_i32, dim3(1), dim3(64), 0, stream, b.qcount, (int32_t)p.nq);
-        qlist = b.perm;
         qcount = b.qcount;
     }
-    if ((st = knn_prep_fp32(p, cosine ? b.rn : R, p.self_mode ? nullptr : Qs, b, nullptr, nullptr, nullptr,
-                            ordered ? b.perm : nullptr, stream)) != RSC_OK) return st;
+    {
+        ScopedTimer timer("pack_split", stream);
+        if ((st = split_pack(Rs, b.nrow, p.nr, p.d, p.nblk, b.split, nullptr, nullptr, nullptr, ref_map, p.nr,
+                             b.counters, stream)) != RSC_OK)
+            return st;
+    }
     if (p.nq == 0) return RSC_OK;
 
     const double eps_coef = knn_eps_coefficient(p.d);
@@ -1376,9 +1410,21 @@ int knn_run(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, 
     sa.kc = b.counters;
     ScreenArgs ss = sa;  // the split screen; the FP32 chain takes the inputs it cannot (both see the mark)
     ss.Ap = b.split;
-    ss.rotate = ordered ? 1 : 0;
-    ss.ref_map = ordered ? b.perm : nullptr;
-    if ((st = split_screen(ss, p.half, "screen_fp32", stream)) != RSC_OK) return st;
+    ss.ref_map = ref_map;
+    if (pruned) {
+        PrunedArgs pa{};
+        pa.s = ss;
+        pa.segments = b.sp.seg_packed;
+        pa.nseg = b.sp.nseg;
+        while ((1 << pa.seg_shift) < b.sp.seg_blocks) ++pa.seg_shift;
+        pa.own = p.self_mode ? nullptr : b.sp.own;
+        pa.eps = split_eps_coefficient(p.d);
+        pa.visited = &b.counters->visited;
+        st = split_screen_pruned(pa, p.half, "screen_fp32", stream);
+    } else {
+        st = split_screen(ss, p.half, "screen_fp32", stream);
+    }
+    if (st != RSC_OK) return st;
     sa.only_wide = 1;
     const unsigned gq = (unsigned)((p.nq + kQueriesPerGroup - 1) / kQueriesPerGroup);
     if ((st = screen(p.dh, sa, gq, p.half, false, "screen_wide", stream)) != RSC_OK) return st;
@@ -1409,32 +1455,76 @@ int knn_run(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, 
     ra.out_idx = out_idx;
     ra.out_dist = out_dist;
     knn_split_bounds(ra);
+    const int esc_cap = (int)std::min<int64_t>(p.nq, kEscalateCap);
+    const bool collect = (p.self_mode ? p.k - 1 : p.k) <= kLeanAnswer;
+    if (collect) {
+        ra.flag_bound = b.esc_bound;
+        ra.flag_found = b.esc_found;
+        ra.flag_cap = esc_cap;
+    }
     if ((st = knn_launch_rerank(ra, p.nq, "rerank", stream)) != RSC_OK) return st;
 
-    // Escalation: rows that failed, screened again 64 wide over many ranges.
-    const int esc_cap = (int)std::min<int64_t>(p.nq, kEscalateCap);
-    ScreenArgs se = sa;
-    se.qlist = b.flag1;
-    se.qcount = &b.counters->flagged;
-    se.qcap = esc_cap;
-    se.only_wide = 0;
-    se.P = (int)std::min<int64_t>(kEscalateSplits, std::max<int64_t>(1, p.nblk));
-    se.cand_idx = b.esc_idx;
-    se.cand_key = b.esc_key;
-    const unsigned ge = (unsigned)((esc_cap + kQueriesPerGroup - 1) / kQueriesPerGroup);
-    if ((st = screen(p.dh, se, ge, kEscalateWidth / 2, true, "screen_escalate", stream)) != RSC_OK) return st;
+    // Escalation of the rows that failed.  The m-th distance found bounds the
+    // true one: a row of a short answer collects every reference whose key
+    // can lie below it and re-ranks those (the answer is then complete).
+    // Rows of longer answers are screened again 64 wide over many ranges, in
+    // the FP32 chain.
     RerankArgs re = ra;
     re.qlist = b.flag1;
     re.qcount = &b.counters->flagged;
     re.qcap = esc_cap;
-    re.split = 0;  // keys of the FP32 chain
-    re.S = kEscalateWidth / 2;
-    re.KP = kEscalateWidth / 2;
-    re.P = 2 * se.P;
     re.cand_idx = b.esc_idx;
     re.cand_key = b.esc_key;
     re.flag_out = b.flag2;
     re.flag_count = &b.counters->flagged2;
+    re.flag_bound = nullptr;
+    if (collect) {
+        CollectArgs ca{};
+        ca.Q = Qs;
+        ca.R = Rs;
+        ca.Q0 = Q;
+        ca.R0 = R;
+        ca.d = p.d;
+        ca.metric = p.metric;
+        ca.rows = b.flag1;
+        ca.nrows = &b.counters->flagged;
+        ca.cap = esc_cap;
+        ca.bound = b.esc_bound;
+        ca.found = b.esc_found;
+        ca.width = kEscalateSplits * kEscalateWidth;
+        ca.out_idx = b.esc_idx;
+        ca.out_key = b.esc_key;
+        ca.packed = b.split;
+        ca.ref_map = ref_map;
+        ca.nr = p.nr;
+        ca.nblk = p.nblk;
+        ca.eps = ra.split_eps;
+        ca.eps_abs = ra.split_abs;
+        ca.cosine_eps = ra.split_cosine_eps;
+        ca.kc = b.counters;
+        {
+            ScopedTimer timer("screen_escalate", stream);
+            if ((st = split_collect(ca, stream)) != RSC_OK) return st;
+        }
+        re.certify = 0;
+        re.P = 1;
+        re.S = re.KP = ca.width;
+        re.counts = b.esc_found;
+    } else {
+        ScreenArgs se = sa;
+        se.qlist = b.flag1;
+        se.qcount = &b.counters->flagged;
+        se.qcap = esc_cap;
+        se.only_wide = 0;
+        se.P = (int)std::min<int64_t>(kEscalateSplits, std::max<int64_t>(1, p.nblk));
+        se.cand_idx = b.esc_idx;
+        se.cand_key = b.esc_key;
+        const unsigned ge = (unsigned)((esc_cap + kQueriesPerGroup - 1) / kQueriesPerGroup);
+        if ((st = screen(p.dh, se, ge, kEscalateWidth / 2, true, "screen_escalate", stream)) != RSC_OK) return st;
+        re.split = 0;
+        re.S = re.KP = kEscalateWidth / 2;
+        re.P = 2 * se.P;
+    }
     if ((st = knn_launch_rerank(re, esc_cap, "rerank_escalate", stream)) != RSC_OK) return st;
     return knn_launch_rescan(p, Q, R, b, esc_cap, out_idx, out_dist, nullptr, 0, stream);
 }

@@ -108,7 +108,7 @@ __global__ __launch_bounds__((SplitShape<Q, TC, L>::NW * kWave), (SplitShape<Q, 
         const int span = (int)(I.b1 - I.b0);
         // packed position of the tile's first query: ref_base = soff - 32 boff
         const int own = (int)((I.q0 - I.ref_base) / 32 - I.b0);
-        screen_split_tile<Q, TC, L>(ba.base, slot, row, (int)I.b0, 1, span, max(0, min(own, span - 1)), I.p,
+        screen_split_tile<Q, TC, L>(ba.base, slot, row, (int)I.b0, span, max(0, min(own, span - 1)), I.p,
                                     I.ref_base, ring0, ring1, qbuf);
     }
 }
@@ -206,7 +206,7 @@ int build_plan(const int64_t *offsets, int S, int d, int k, const Shape &sh, Bat
     int st = knn_plan(N, N, d, k, nullptr, true, &bp.kp);
     if (st != RSC_OK) return st;
     bp.kp.nblk = bp.boff[S];
-    bp.kp.ordered = false;
+    bp.kp.pruned = false;
     bp.kp.splits = kMaxSplits;
     if (sh.half == 32 && bp.kp.half == 16) {  // the wider screen tile
         bp.kp.half = 32;
@@ -419,7 +419,9 @@ int screen_only(const BatchPlan &bp, const BatchBuffers &b, const float *X, hipS
 int prepare(const BatchPlan &bp, const BatchBuffers &b, const float *X, hipStream_t s) {
     int st = sample_order_run(X, bp.kp.nq, bp.kp.d, b.soff, bp.S, b.order_ws, b.order, s);
     if (st != RSC_OK) return st;
-    return knn_prep_fp32(bp.kp, X, nullptr, b.kb, b.blk_sample, b.boff, b.soff, b.order, s);
+    if ((st = knn_prep_fp32(bp.kp, X, nullptr, b.kb, b.blk_sample, b.boff, b.soff, s)) != RSC_OK) return st;
+    return split_pack(X, b.kb.nrow, bp.kp.nr, bp.kp.d, bp.kp.nblk, b.kb.split, b.blk_sample, b.boff, b.soff, b.order,
+                      bp.kp.nr, b.kb.counters, s);
 }
 
 // ---------------------------------------------------------------------------

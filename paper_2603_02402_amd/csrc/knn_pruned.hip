@@ -1,0 +1,11 @@
+// The pruned screen with lists of 16 keys per contraction half.
+
+#include <hip/hip_runtime.h>
+
+#include "screen_split_grid.hpp"
+
+namespace rsc {
+
+template int scr::pruned_launch<16>(const PrunedArgs &, const char *, hipStream_t);
+
+}  // namespace rsc

@@ -108,7 +108,114 @@ __global__ __launch_bounds__(256) void k_pack_split(const float *__restrict__ R,
     if (__ballot(wide) != 0ull && lane == 0) atomicOr(&counters->wide, 1);
 }
 
+// Every reference that can lie within bound[i] of listed row i (Euclidean:
+// squared): its key is at most bound - ||x||^2 plus the key's error bound.  A
+// key passes for little more than the row's m neighbours, so the pass is the
+// bare contraction (8192 rows against 1M: 1.7 ms; 45 rows: 60 us, where
+// screening them again 64 wide over 16 ranges took 4.2 ms).  Work units are
+// (256 listed rows, a range of blocks), enough ranges for every CU.  Inputs
+// marked wide are compared in float64 instead.
+template <int Q, int TC>
+__global__ __launch_bounds__((SplitShape<Q, TC, 16>::NW * kWave), (SplitShape<Q, TC, 16>::W)) void k_split_collect(
+    CollectArgs a) {
+    using S = SplitShape<Q, TC, 16>;
+    __shared__ __attribute__((aligned(16))) char ring0[S::RING];
+    __shared__ __attribute__((aligned(16))) char ring1[S::RING];
+    const int n = min(*a.nrows, a.cap);
+    if (n == 0) return;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6, h = lane >> 5;
+    const bool cosine = a.metric == RSC_COSINE;
+    if (a.kc->wide) {
+        for (int i = 0; i < n; ++i) {
+            const float *x = a.Q0 + (int64_t)a.rows[i] * a.d;
+            const double bound = a.bound[i];
+            double cxx = 0.0;
+            if (cosine)
+                for (int t = 0; t < a.d; ++t) cxx = __dadd_rn(cxx, __dmul_rn((double)x[t], (double)x[t]));
+            for (int64_t j = (int64_t)blockIdx.x * blockDim.x + tid; j < a.nr; j += (int64_t)gridDim.x * blockDim.x) {
+                const float *y = a.R0 + j * a.d;
+                double v;
+                if (cosine) {
+                    double sxy = 0.0, syy = 0.0;
+                    for (int t = 0; t < a.d; ++t) {
+                        sxy = __dadd_rn(sxy, __dmul_rn((double)x[t], (double)y[t]));
+                        syy = __dadd_rn(syy, __dmul_rn((double)y[t], (double)y[t]));
+                    }
+                    v = (cxx == 0.0 || syy == 0.0)
+                            ? 1.0
+                            : __dsub_rn(1.0, __ddiv_rn(sxy, __dmul_rn(__dsqrt_rn(cxx), __dsqrt_rn(syy))));
+                } else {
+                    v = exact_d2(x, y, a.d);
+                }
+                if (!(v <= bound)) continue;
+                const int at = atomicAdd(&a.found[i], 1);
+                if (at < a.width) {
+                    a.out_idx[(int64_t)i * a.width + at] = (int32_t)j;
+                    a.out_key[(int64_t)i * a.width + at] = NAN;  // no screened key
+                }
+            }
+        }
+        return;
+    }
+    const int e = split_exponent(a.kc);
+    const float scale = ldexpf(1.f, e);
+    const double unit = ldexp(1.0, 2 * e);
+    const double ymax = (double)__uint_as_float(a.kc->max_norm_bits) * (1.0 + 1e-6);
+    const double M = fmax((double)__uint_as_float(a.kc->query_norm_bits), ymax);
+    constexpr int QG = S::NW * 32;
+    const int tiles = (n + QG - 1) / QG;
+    const int ranges = (int)min((int64_t)((gridDim.x + tiles - 1) / tiles), a.nblk);
+    const int per = (int)((a.nblk + ranges - 1) / ranges);
+    for (int u = blockIdx.x; u < tiles * ranges; u += gridDim.x) {
+        const int b0 = u % ranges * per, b1 = (int)min(a.nblk, (int64_t)b0 + per);
+        const int i = u / ranges * QG + wave * 32 + (lane & 31);
+        const int64_t row = i < n ? (int64_t)a.rows[i] : -1;
+        SplitQuery<Q, TC> qop;
+        qop.load(a.Q, a.d, row, h, scale);
+        float limit = -INFINITY;
+        if (row >= 0) {
+            const double dm = a.bound[i];
+            double xx = 0.0;
+            for (int t = 0; t < a.d; ++t) xx += (double)a.Q[row * a.d + t] * (double)a.Q[row * a.d + t];
+            const double xn = sqrt(xx) * (1.0 + 1e-12), Y = fmin(ymax, (xn + sqrt(dm)) * (1.0 + 1e-9));
+            const double t = cosine ? 2.0 * dm - 1.0 + a.cosine_eps
+                                    : dm - xx + a.eps * (2.0 * xn * Y + Y * Y) + a.eps_abs * M * (2.0 * xn + Y);
+            limit = (float)((t + 1e-6 * (fabs(t) + (cosine ? 0.0 : 1e-6 * xx))) * unit);
+        }
+        split_stream<Q, TC, S::PH>(
+            static_cast<const char *>(a.packed), max(0, b1 - b0), [&](int j) { return b0 + j; }, ring0, ring1,
+            [&](const f16x8(&A)[2 * Q + TC], int blk) {
+                const f32x16 acc = split_keys<Q, TC>(A, qop);
+                float mn = acc[0];
+#pragma unroll
+                for (int v = 1; v < 16; ++v) mn = fminf(mn, acc[v]);
+                if (__ballot(mn <= limit) == 0ull) return;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int slot = blk * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
+                    if (acc[v] <= limit && slot < a.nr) {
+                        const int at = atomicAdd(&a.found[i], 1);
+                        if (at < a.width) {
+                            a.out_idx[(int64_t)i * a.width + at] = a.ref_map ? a.ref_map[slot] : slot;
+                            a.out_key[(int64_t)i * a.width + at] = acc[v];
+                        } else {
+                            limit = -INFINITY;  // too many: the row is scanned exhaustively
+                        }
+                    }
+                }
+            });
+    }
+}
+
 }  // namespace
+
+int split_collect(const CollectArgs &a, hipStream_t s) {
+    return scr::split_dispatch(scr::split_geom(a.d), [&](auto q, auto tc) {
+        hipLaunchKernelGGL((k_split_collect<q.value, tc.value>), dim3((unsigned)scr::kCUs),
+                           dim3(SplitShape<q.value, tc.value, 16>::NW * kWave), 0, s, a);
+        return launch_status("collect");
+    });
+}
 
 template int scr::split_launch<16>(const scr::ScreenArgs &, const char *, hipStream_t);
 
@@ -140,16 +247,27 @@ int split_screen(const scr::ScreenArgs &a, int half_width, const char *name, hip
     return half_width == 16 ? split_launch<16>(a, name, s) : split_launch<32>(a, name, s);
 }
 
-// Error bound of a split key: per 32x32x16 MFMA two float32 roundings (its
-// two groups of 8 products are summed and added one after the other), per
-// group of 8 the products' truncation below 2^-24 of the group's largest (7
-// units over the high parts' groups by Cauchy-Schwarz, 7 of the norm's
-// group), and 8 units for the operands' split and the dropped low x low
-// products: (2 MFMAs + 22) units of roundoff of (2 ||x|| ||y|| + ||y||^2),
-// doubled for safety.  Operand parts below FP16's smallest step (2^-25 in
-// scaled units) add split_abs * M (2 ||x|| + ||y||), M the largest norm.
+int split_screen_pruned(const PrunedArgs &a, int half_width, const char *name, hipStream_t s) {
+    return half_width == 16 ? scr::pruned_launch<16>(a, name, s) : scr::pruned_launch<32>(a, name, s);
+}
+
+// Error bound of a split key, in units of roundoff u = 2^-24 of S = 2 ||x||
+// ||y|| + ||y||^2, from the structure of v_mfma_f32_32x32x16_f16 (two groups of
+// 8 exact products, each summed with what lies below u of the group's largest
+// product cut off, then added to the accumulator one after the other with
+// rounding to nearest; read off a probe of the instruction):
+//   2 (TC + Q)  the roundings of the tail and the high parts' MFMAs, those of
+//               the low parts before them are 2^-11 of that size (1 for all);
+//   7           the cut-off products: 7 per group, over the groups at most u
+//               (||y||^2 + the sum of |2 x_t y_t|);
+//   8           the split: |x - xh - xl| <= 2^-23 |x| on either side and the
+//               dropped xl yl <= 2^-22 |x y|;
+// with half as much again for safety.  Operand parts below FP16's smallest
+// step (2^-25 in scaled units) add split_abs M (2 ||x|| + ||y||), M the largest
+// norm.
 double split_eps_coefficient(int d) {
-    return 2.0 * (2 * split_geom(d).mfmas() + 22) * std::ldexp(1.0, -24);
+    const scr::SplitGeom g = scr::split_geom(d);
+    return 1.5 * (2 * (g.tc + g.q) + 16) * std::ldexp(1.0, -24);
 }
 double split_abs_coefficient(int d) { return 2.0 * std::sqrt((double)d) * std::ldexp(1.0, -38); }
 

@@ -79,6 +79,7 @@ struct KnnCounters {
     uint32_t query_norm_bits; // float bits of the largest query norm (rectangular problem; else 0)
     int32_t wide;             // nonzero: norms spread too far for the split screen, the FP32 chain runs
     int32_t pad;
+    unsigned long long visited;  // pruned screen: segments screened, over all query tiles
 };
 
 struct KnnPlan {
@@ -91,10 +92,36 @@ struct KnnPlan {
     int precision;         // rsc_precision of the screen
     int metric;            // rsc_metric
     int resid;             // FP8 residual variant: reference partitions (0 = off)
-    bool ordered;          // exact path: room to screen one matrix in a Morton order (knn_run)
+    bool pruned;           // exact path: room for the spatial order and its segments (knn_run)
 };
 
+// Spatial order of a reference matrix and of a query matrix (spatial.hip).
+constexpr int kSegMax = 8192;  // segments of an order
+struct SpatialBuffers {
+    int nseg, seg_blocks;    // segments, packed blocks per segment (a power of two)
+    int32_t *pivot, *rank;
+    float *nearest, *pairs;
+    uint32_t *bounds;
+    void *pivot_packed;
+    uint32_t *key, *rkey, *qkey;  // unsorted; sorted keys of references / queries
+    int32_t *id, *rperm, *qperm;  // rows in order
+    int32_t *own;                 // segment of the references where each query tile belongs
+    float *centre, *radius;
+    void *seg_packed;
+    void *tmp;
+    size_t tmp_bytes;
+};
+int spatial_seg_blocks(int64_t nblk);
+size_t spatial_carve(int64_t nq, int64_t nr, int d, bool square, void *base, SpatialBuffers *out);
+// Orders the references (norms and their maximum known) and bounds the segments.
+int spatial_refs(const float *R, const float *nrow, int64_t nr, int d, const SpatialBuffers &b, KnnCounters *kc,
+                 hipStream_t s);
+// Orders the queries of a rectangular problem and places their tiles of qg.
+int spatial_queries(const float *Q, int64_t nq, int64_t nr, int d, int qg, const SpatialBuffers &b, KnnCounters *kc,
+                    hipStream_t s);
+
 struct KnnBuffers {
+    SpatialBuffers sp;  // pruned exact screen
     KnnCounters *counters;
     float *nrow, *packed, *norms;
     void *split;      // exact path: references packed for the split FP16 screen
@@ -105,6 +132,8 @@ struct KnnBuffers {
     int32_t *flag1, *flag2;
     int32_t *esc_idx;
     float *esc_key;
+    double *esc_bound;  // flagged rows: bound of the m-th distance, candidates collected
+    int32_t *esc_found;
     float *qn, *rn;   // unit-normalised queries / references (cosine metric)
     // FP8 residual variant
     float *cent;          // partition centroids, resid x d
@@ -141,6 +170,14 @@ struct RerankArgs {
     KnnCounters *counters;
     int32_t *flag_out;   // rows that fail the certificate
     int32_t *flag_count;
+    // optional, for the first flag_cap flagged rows: the m-th distance found
+    // (squared if Euclidean), an upper bound of the true one, and a zeroed count
+    double *flag_bound;
+    int32_t *flag_found;
+    int flag_cap;
+    // optional: candidates per slot, in any order and complete (k_split_collect);
+    // more than KP of them flag the row
+    const int32_t *counts;
     int32_t *out_idx;
     float *out_dist;
 };
@@ -156,12 +193,11 @@ int knn_run(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, 
 
 // Pieces of the exact path reused by the batched form (knn.hip).
 double knn_eps_coefficient(int d);
-// init counters, norms, FP32 and split packing (optionally per sample:
+// init counters, norms, FP32 packing (optionally per sample:
 // blk_sample, boff, soff device arrays).  Q: the queries of a rectangular
 // problem (their largest norm enters the split's scale), else null.
-// ref_map: the split packing's slot -> row, or null for row order.
 int knn_prep_fp32(const KnnPlan &p, const float *R, const float *Q, const KnnBuffers &b, const int32_t *blk_sample,
-                  const int64_t *boff, const int64_t *soff, const int32_t *ref_map, hipStream_t stream);
+                  const int64_t *boff, const int64_t *soff, hipStream_t stream);
 // The rerank's error bounds for keys of the split screen.
 void knn_split_bounds(RerankArgs &ra);
 int knn_launch_rerank(const RerankArgs &ra, int64_t slots, const char *name, hipStream_t stream);
@@ -194,6 +230,29 @@ int split_pack(const float *R, const float *nrow, int64_t nr, int d, int64_t nbl
                const int32_t *blk_sample, const int64_t *boff, const int64_t *soff, const int32_t *row_map,
                int64_t nmap, KnnCounters *counters, hipStream_t stream);
 int split_screen(const scr::ScreenArgs &a, int half_width, const char *name, hipStream_t s);
+// All references within a bound of each listed row (knn_split.hip).
+struct CollectArgs {
+    const float *Q, *R;      // as screened (unit rows for the cosine metric)
+    const float *Q0, *R0;    // as given
+    int d, metric;
+    const int32_t *rows, *nrows;  // the listed rows and their count, at most cap
+    int cap;
+    const double *bound;     // per listed row: the m-th distance found (squared if Euclidean)
+    int32_t *found;          // per listed row: references found (zeroed)
+    int width;               // room per listed row
+    int32_t *out_idx;
+    float *out_key;
+    const void *packed;
+    const int32_t *ref_map;
+    int64_t nr, nblk;
+    double eps, eps_abs, cosine_eps;
+    const KnnCounters *kc;
+};
+int split_collect(const CollectArgs &a, hipStream_t s);
+// The pruned screen over a spatial order: own = the segment of each query
+// tile (null: the queries are the references in their order).
+struct PrunedArgs;
+int split_screen_pruned(const PrunedArgs &a, int half_width, const char *name, hipStream_t s);
 double split_eps_coefficient(int d);
 double split_abs_coefficient(int d);
 // Reduced-precision screens (knn_lowp.hip).

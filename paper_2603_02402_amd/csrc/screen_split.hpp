@@ -1,7 +1,7 @@
 // The exact path's distance screen on the 16-bit matrix cores: every float32
 // operand is split into two FP16 parts whose products are accumulated in
 // FP32, so the key keeps (in fact betters) the accuracy of an FP32 chain at
-// a quarter of its matrix-core time.
+// a fifth of its matrix-core time.
 //
 // Split.  With a power-of-two scale a = 2^e that brings the largest row norm
 // M into [2^13, 2^14),
@@ -25,8 +25,9 @@
 // with the operand reads and the minimum of the epilogue beside it; the
 // screen runs at 1.24, and at the same without its selection.  The largest
 // key error against float64 over the candidates falls there from 3.6 to 2.9
-// units of 2^-24 (2 ||x|| ||y|| + ||y||^2), and over 2k to 300k rows from
-// 3.3-5.0 to 2.5-3.2.
+// units of 2^-24 (2 ||x|| ||y|| + ||y||^2), and over 500 to 300k rows from
+// 3.3-5.1 to 2.2-3.2.  (The pruned form of the screen skips most blocks where
+// the data has clusters: screen_split_grid.hpp.)
 //
 // Range.  Rows whose norm lies below 2^-16 M would lose bits to the FP16
 // exponent; prep marks such inputs (KnnCounters::wide) and they take the FP32
@@ -182,6 +183,9 @@ struct SplitShape {
     static constexpr int BLOCK = NA * 1024;
     static constexpr int ROOM = (160 * 1024 / WGS - QBYTES - 512) / (2 * BLOCK);
     static constexpr int PH = ROOM < 1 ? 1 : ROOM > 8 ? 8 : ROOM;  // blocks per phase
+    // the pruned screen's segment list and bitmap take 20 KiB more
+    static constexpr int ROOMP = (160 * 1024 / WGS - QBYTES - 20 * 1024) / (2 * BLOCK);
+    static constexpr int PHP = ROOMP < 1 ? 1 : ROOMP > 8 ? 8 : ROOMP;
     static constexpr int RING = PH * BLOCK;
     static constexpr int QG = NW * 32;  // queries per workgroup
 };
@@ -193,75 +197,81 @@ struct SplitStream {
     static constexpr int W = 2 * Q + TC <= 9 ? 2 : 1;
 };
 
-// One tile of 32 queries per wave over the `span` packed blocks b0 + step i of a
-// range, i from `rot` on and around: every wave of the workgroup calls this
-// together.  slot / row: this lane's output slot and query row (or -1);
-// ref_base: reference row of packed row 0.
-template <int Q, int TC, int L>
-__device__ __forceinline__ void screen_split_tile(const ScreenArgs &a, int64_t slot, int64_t row, int b0, int step,
-                                                  int span, int rot, int p, int64_t ref_base, char *ring0,
-                                                  char *ring1, double *qbuf) {
-    using S = SplitShape<Q, TC, L>;
-    constexpr int PH = S::PH;
-    const int tid = threadIdx.x;
-    const int lane = tid & (kWave - 1), wave = tid >> 6;
-    const int h = lane >> 5;
-    const int qs = blockDim.x, nw = qs / kWave;
-    const char *Ab = static_cast<const char *>(a.Ap);
-
-    // packed block of position i of the scan
-    auto phys = [&](int i) -> int {
-        int j = rot + i;
-        if (j >= span) j -= span;
-        return b0 + step * j;
-    };
+// Streams packed blocks phys(0) .. phys(count - 1) of Ab through the ring of
+// the workgroup and hands each to use(A, block): every wave of the workgroup
+// calls this together.  phys may name any block that exists.
+template <int Q, int TC, int PH, class Phys, class Use>
+__device__ __forceinline__ void split_stream(const char *Ab, int count, Phys phys, char *ring0, char *ring1, Use use) {
+    constexpr int NA = 2 * Q + TC, BLOCK = NA * 1024;
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+    const int nw = blockDim.x / kWave;
     // this wave's share of the asynchronous loads of phase `ph` into `buf`
-    // (positions past the span load the last block again: always in bounds)
+    // (positions past the end load the last block again: always in bounds)
     auto issue = [&](int ph, char *buf) {
 #pragma unroll
-        for (int j = 0; j < (PH * S::NA + 3) / 4; ++j) {
+        for (int j = 0; j < (PH * NA + 3) / 4; ++j) {
             const int i = j * nw + wave;
-            if (i < PH * S::NA) {
-                const int r = i / S::NA, s = i - r * S::NA;
-                const int64_t blk = phys(min(ph * PH + r, span - 1));
-                load_lds16(Ab + blk * S::BLOCK + s * 1024 + lane * 16, buf + i * 1024);
+            if (i < PH * NA) {
+                const int r = i / NA, s = i - r * NA;
+                const int64_t blk = phys(min(ph * PH + r, count - 1));
+                load_lds16(Ab + blk * BLOCK + s * 1024 + lane * 16, buf + i * 1024);
             }
         }
     };
-
-    SplitQuery<Q, TC> qop;
-    qop.load(a.Q, a.d, row, h, ldexpf(1.f, split_exponent(a.kc)));
-    PackTopK<L, S::QCAP> top;
-    top.init();
-    double *q = qbuf + tid;
-
-    const int nph = (span + PH - 1) / PH;
+    const int nph = (count + PH - 1) / PH;
     auto phase = [&](int ph, const char *cur, char *nxt) {
         __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's loads of phase ph landed
         __syncthreads();                      // everyone's landed; phase ph-1 is fully consumed
         if (ph + 1 < nph) issue(ph + 1, nxt);
-        const int n = min(PH, span - ph * PH);
+        const int n = min(PH, count - ph * PH);
 #pragma unroll 1
         for (int r = 0; r < n; ++r) {
             const int blk = phys(ph * PH + r);
-            const f16x8 *sl = reinterpret_cast<const f16x8 *>(cur + r * S::BLOCK) + lane;
-            f16x8 A[S::NA];
+            const f16x8 *sl = reinterpret_cast<const f16x8 *>(cur + r * BLOCK) + lane;
+            f16x8 A[NA];
 #pragma unroll
-            for (int s = TC; s < S::NA; ++s) A[s] = sl[s * kWave];
+            for (int s = TC; s < NA; ++s) A[s] = sl[s * kWave];
 #pragma unroll
             for (int s = 0; s < TC; ++s) A[s] = sl[s * kWave];
             // all operand reads of the block are in flight before its first MFMA
-            if constexpr (S::NA <= 9) __builtin_amdgcn_sched_barrier(0);
-            const f32x16 acc = split_keys<Q, TC>(A, qop);
-            top.offer(acc, (int)(ref_base + (int64_t)blk * 32) + 4 * h, q, qs);
+            if constexpr (NA <= 9) __builtin_amdgcn_sched_barrier(0);
+            use(A, blk);
         }
     };
-    __syncthreads();  // the ring is free (the previous tile is done with it)
+    __syncthreads();  // the ring is free (the previous stream is done with it)
     if (nph > 0) issue(0, ring0);
     for (int ph = 0; ph < nph; ph += 2) {
         phase(ph, ring0, ring1);
         if (ph + 1 < nph) phase(ph + 1, ring1, ring0);
     }
+}
+
+// One tile of 32 queries per wave over the `span` packed blocks from b0 on,
+// starting at the `rot`-th and around: every wave of the workgroup calls this
+// together.  slot / row: this lane's output slot and query row (or -1);
+// ref_base: reference row of packed row 0.
+template <int Q, int TC, int L>
+__device__ __forceinline__ void screen_split_tile(const ScreenArgs &a, int64_t slot, int64_t row, int b0, int span,
+                                                  int rot, int p, int64_t ref_base, char *ring0, char *ring1,
+                                                  double *qbuf) {
+    using S = SplitShape<Q, TC, L>;
+    const int h = (threadIdx.x & (kWave - 1)) >> 5;
+    SplitQuery<Q, TC> qop;
+    qop.load(a.Q, a.d, row, h, ldexpf(1.f, split_exponent(a.kc)));
+    PackTopK<L, S::QCAP> top;
+    top.init();
+    double *q = qbuf + threadIdx.x;
+    const int qs = blockDim.x;
+    split_stream<Q, TC, S::PH>(
+        static_cast<const char *>(a.Ap), span,
+        [&](int i) {  // packed block of position i of the scan
+            int j = rot + i;
+            if (j >= span) j -= span;
+            return b0 + j;
+        },
+        ring0, ring1, [&](const f16x8(&A)[2 * Q + TC], int blk) {
+            top.offer(split_keys<Q, TC>(A, qop), (int)(ref_base + (int64_t)blk * 32) + 4 * h, q, qs);
+        });
     top.flush(q, qs);
     if (slot >= 0) top.store(a, slot, p, h, a.ref_map);
 }

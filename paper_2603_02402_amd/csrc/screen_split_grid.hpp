@@ -5,9 +5,22 @@
 #include "screen_split.hpp"
 
 namespace rsc {
+
+struct PrunedArgs {
+    scr::ScreenArgs s;       // Ap: references packed in the spatial order (ref_map)
+    const void *segments;    // packed segment bounds
+    int nseg, seg_shift;     // segments, log2 of the blocks per segment
+    const int32_t *own;
+    double eps;              // error coefficient of a split key
+    unsigned long long *visited;  // statistics: segments screened, over all tiles
+};
+
 namespace scr {
 
 constexpr int64_t kCUs = 256;  // MI355X
+// Blocks on either side of a tile's own that are screened before the bounds
+// (at least one segment).
+constexpr int kNearBlocks = 8;
 
 // Query slot i of the launch is row i, or row qlist[i] for i < min(*qcount,
 // qcap) when a list is given; lists are filed as by k_screen_fp32, with keys
@@ -25,21 +38,15 @@ __global__ __launch_bounds__((SplitShape<Q, TC, L>::NW * kWave), (SplitShape<Q, 
     const int tid = threadIdx.x;
     const int wave = tid >> 6, c = tid & 31;
     const int p = blockIdx.y;
-    // Range p holds a run of packed blocks, or, with references packed in the
-    // queries' order, the blocks p, p + P, ..: every range gets a share of
-    // every neighbourhood.
-    const int nblk = (int)a.nblk, per = (nblk + a.P - 1) / a.P;
-    const int step = a.rotate ? a.P : 1, b0 = a.rotate ? p : p * per;
-    const int span = a.rotate ? (p < nblk ? (nblk - p + a.P - 1) / a.P : 0) : max(0, min(per, nblk - b0));
+    const int nblk = (int)a.nblk, per = (nblk + a.P - 1) / a.P, b0 = p * per;  // range p: a run of blocks
+    const int span = max(0, min(per, nblk - b0));
     const int64_t nslots = screen_slots(a);
     const int qg = blockDim.x / 2;  // queries of the workgroup
     for (int64_t qblk = blockIdx.x; qblk * qg < nslots; qblk += gridDim.x) {
         const int64_t slot = qblk * qg + wave * 32 + c;
         int64_t row = -1;
         if (slot < nslots) row = a.qlist ? (int64_t)a.qlist[slot] : slot;
-        // near references first: start at the group's own rows
-        const int rot = a.rotate && span > 0 ? min((int)(qblk * (qg / 32) / a.P), span - 1) : 0;
-        screen_split_tile<Q, TC, L>(a, slot < nslots ? slot : -1, row, b0, step, span, rot, p, 0, ring0, ring1, qbuf);
+        screen_split_tile<Q, TC, L>(a, slot < nslots ? slot : -1, row, b0, span, 0, p, 0, ring0, ring1, qbuf);
     }
 }
 
@@ -54,6 +61,177 @@ int split_launch_geom(const ScreenArgs &a, const char *name, hipStream_t s) {
     hipLaunchKernelGGL((k_screen_split<Q, TC, L>), dim3(gx, (unsigned)a.P), dim3(nw * kWave), 0, s, a);
     return launch_status(name);
 }
+
+// The pruned screen.  A tile first screens the segments around its own rows,
+// which gives every query a threshold T (no row beyond the distance T of its
+// current L-th key can enter its list); a contraction with the segments'
+// bounds then tells which segments any query of the tile has within T, and
+// only those are screened.  A skipped row's true key is above the query's
+// threshold of that moment, hence above its final one: exactly what the
+// rerank's certificate assumes of every row outside the lists.
+// A tile whose queries' T differ by more than 2 holds some whose neighbours
+// are elsewhere: when it would visit many blocks (24 per block of bounds: two
+// more passes over those cost less), it screens every query's nearest segment
+// first and bounds again (1M rows: 42.6 -> 32.3 ms).
+// With P ranges, range p holds the segments p, p + P, ..
+template <int Q, int TC, int L>
+__global__ __launch_bounds__((SplitShape<Q, TC, L>::NW * kWave), (SplitShape<Q, TC, L>::W)) void k_split_pruned(
+    PrunedArgs pa) {
+    using S = SplitShape<Q, TC, L>;
+    constexpr int RING = S::PHP * S::BLOCK;
+    constexpr int NWORDS = kSegMax / 32;
+    __shared__ __attribute__((aligned(16))) char ring0[RING];
+    __shared__ __attribute__((aligned(16))) char ring1[RING];
+    __shared__ double qbuf[S::QCAP * S::NW * kWave];
+    __shared__ uint32_t mark[NWORDS];  // segments found by the last pass over the bounds
+    __shared__ uint32_t done[NWORDS];  // segments screened
+    __shared__ int count[NWORDS];
+    __shared__ uint16_t list[kSegMax];
+    __shared__ uint32_t tmin, tmax;    // float bits of the smallest and largest T
+    const ScreenArgs &a = pa.s;
+    if (a.kc->wide) return;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6, h = lane >> 5;
+    const int p = blockIdx.y, P = a.P;
+    const int nblk = (int)a.nblk, nseg = pa.nseg, sh = pa.seg_shift, nw = (nseg + 31) / 32;
+    const int qg = blockDim.x / 2, qs = blockDim.x;
+    const int64_t nslots = screen_slots(a);
+    const int64_t slot = (int64_t)blockIdx.x * qg + wave * 32 + (lane & 31);
+    const int64_t row = slot < nslots ? (a.qlist ? (int64_t)a.qlist[slot] : slot) : -1;
+    const float scale = ldexpf(1.f, split_exponent(a.kc));
+
+    SplitQuery<Q, TC> qop;
+    qop.load(a.Q, a.d, row, h, scale);
+    PackTopK<L, S::QCAP> top;
+    top.init();
+    double *q = qbuf + tid;
+    float xx = 0.f;  // ||a x||^2
+    if (row >= 0)
+        for (int t = h; t < a.d; t += 2) {
+            const float v = a.Q[row * a.d + t] * scale;
+            xx = fmaf(v, v, xx);
+        }
+    xx += __shfl_xor(xx, 32, kWave);
+    // the key's error bound, ||a c|| <= 2^14, with the products of T and r and the rounding of xx
+    const float slack = 1.5f * (float)pa.eps * (2.f * sqrtf(xx) * 16384.f + 268435456.f) + xx * 0x1p-18f;
+
+    // first the range's segments around the tile's rows
+    const int first = pa.own ? pa.own[blockIdx.x] : (int)(((int64_t)blockIdx.x * qg / 32) >> sh);
+    const int last =
+        pa.own ? first : (int)(min((int64_t)nblk - 1, ((int64_t)(blockIdx.x + 1) * qg - 1) / 32) >> sh);
+    const int reach = max(1, kNearBlocks >> sh) * P;
+    const int lo = max(0, first - reach), hi = min(nseg - 1, last + reach);
+    const int near0 = lo + (p + P - lo % P) % P;
+    int total = near0 <= hi ? (hi - near0) / P + 1 : 0;
+    for (int i = tid; i < total; i += qs) list[i] = (uint16_t)(near0 + i * P);
+    for (int w = tid; w < NWORDS; w += qs) done[w] = 0u;
+    if (tid == 0) {
+        tmin = 0xffffffffu;
+        tmax = 0u;
+    }
+    bool final = false;
+    int visited = 0;
+    for (int round = 0;; ++round) {
+        __syncthreads();  // the list is written
+        split_stream<Q, TC, S::PHP>(
+            static_cast<const char *>(a.Ap), total << sh,
+            [&](int i) { return ((int)list[i >> sh] << sh) + (i & ((1 << sh) - 1)); }, ring0, ring1,
+            [&](const f16x8(&A)[2 * Q + TC], int blk) {
+                if (blk < nblk) top.offer(split_keys<Q, TC>(A, qop), blk * 32 + 4 * h, q, qs);
+            });
+        top.flush(q, qs);
+        visited += total;
+        if (final) break;
+        for (int i = tid; i < total; i += qs) atomicOr(&done[list[i] >> 5], 1u << (list[i] & 31));
+
+        // T of each query, over both halves of its list; a query whose lists are not full takes every segment
+        const float thr = fmaxf(top.thr, __shfl_xor(top.thr, 32, kWave));
+        const float T = (float)(_Float16)(sqrtf(fmaxf(thr + xx * 1.00001f, 0.f)) * 1.002f);
+        const bool bounded = T < 30000.f;
+        const float limit = row < 0 ? -INFINITY : bounded ? T * T - xx + slack : INFINITY;
+        if (round == 0 && row >= 0 && h == 0) {
+            atomicMin(&tmin, __float_as_uint(T));
+            atomicMax(&tmax, __float_as_uint(T));
+        }
+        uint32_t mine = 0u;
+        int w = tid + first / 32;  // this thread's word, from the tile's own on and around
+        if (w >= nw) w -= nw;
+        for (bool nearest = false;; nearest = true) {
+            if (h == 1) qop.tail[TC - 1][7] = (_Float16)(bounded && !nearest ? -2.f * T : 0.f);
+            for (int i = tid; i < NWORDS; i += qs) mark[i] = 0u;
+            float best = INFINITY;
+            int at = -1;
+            split_stream<Q, TC, S::PHP>(
+                static_cast<const char *>(pa.segments), nw, [](int i) { return i; }, ring0, ring1,
+                [&](const f16x8(&A)[2 * Q + TC], int blk) {
+                    const f32x16 acc = split_keys<Q, TC>(A, qop);
+                    if (nearest) {
+#pragma unroll
+                        for (int v = 0; v < 16; ++v)
+                            if (acc[v] < best) {
+                                best = acc[v];
+                                at = 32 * blk + 8 * (v >> 2) + 4 * h + (v & 3);
+                            }
+                        return;
+                    }
+                    float mn = acc[0];
+#pragma unroll
+                    for (int v = 1; v < 16; ++v) mn = fminf(mn, acc[v]);
+                    if (__ballot(mn <= limit) == 0ull) return;
+                    uint32_t bits = 0u;
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const unsigned long long b = __ballot(acc[v] <= limit);
+                        const int r = 8 * (v >> 2) + (v & 3);
+                        bits |= ((uint32_t)b != 0u ? 1u : 0u) << r | ((uint32_t)(b >> 32) != 0u ? 1u : 0u) << (r + 4);
+                    }
+                    if (lane == 0) atomicOr(&mark[blk], bits);
+                });
+            if (nearest && row >= 0 && at >= 0) atomicOr(&mark[at >> 5], 1u << (at & 31));
+            __syncthreads();
+            mine = 0u;
+            if (tid < nw) {
+                mine = mark[w] & ~done[w];
+                for (int i = 0; i < 32; ++i)
+                    if (32 * w + i >= nseg || (P > 1 && (32 * w + i) % P != p)) mine &= ~(1u << i);
+                count[tid] = __popc(mine);
+            }
+            __syncthreads();
+            total = 0;
+            for (int i = 0; i < nw; ++i) total += count[i];
+            // (the same for all threads)
+            if (nearest || round > 0 || total << sh <= 24 * nw ||
+                __uint_as_float(tmax) <= 2.f * __uint_as_float(tmin)) {
+                final = !nearest;
+                break;
+            }
+        }
+        int at = 0;
+        for (int i = 0; i < nw; ++i) at += i < tid ? count[i] : 0;
+        while (mine) {
+            list[at++] = (uint16_t)(32 * w + __builtin_ctz(mine));
+            mine &= mine - 1;
+        }
+    }
+    if (row >= 0) top.store(a, slot, p, h, a.ref_map);
+    if (tid == 0) atomicAdd(pa.visited, (unsigned long long)visited);
+}
+
+template <int Q, int TC, int L>
+int pruned_launch_geom(const PrunedArgs &a, const char *name, hipStream_t s) {
+    using S = SplitShape<Q, TC, L>;
+    ScopedTimer timer(name, s);
+    const unsigned gx = (unsigned)((a.s.nq + S::QG - 1) / S::QG);
+    hipLaunchKernelGGL((k_split_pruned<Q, TC, L>), dim3(gx, (unsigned)a.s.P), dim3(S::NW * kWave), 0, s, a);
+    return launch_status(name);
+}
+
+template <int L>
+int pruned_launch(const PrunedArgs &a, const char *name, hipStream_t s) {
+    return split_dispatch(split_geom(a.s.d),
+                          [&](auto q, auto tc) { return pruned_launch_geom<q.value, tc.value, L>(a, name, s); });
+}
+extern template int pruned_launch<16>(const PrunedArgs &, const char *, hipStream_t);
+extern template int pruned_launch<32>(const PrunedArgs &, const char *, hipStream_t);
 
 // One launch with lists of L keys per contraction half.
 template <int L>
