@@ -81,30 +81,81 @@ __global__ void k_init_result(GraphResult *r) {
     }
 }
 
-// Sum over the row's neighbour slots of exp(-g_j * rinv) with g_j =
-// max(0, d_j - rho), in slot order.  The bisection multiplies by the
+// Sum of the memberships at 1 / sigma, added in slot order.  It multiplies by the
 // reciprocal of sigma (one division per step instead of one per slot); the
-// weights themselves divide by sigma as the definition writes them.
+// weights themselves divide by sigma as the definition writes them.  Slots past
+// the row's m hold an infinite gap and add an exact zero.
 template <int KM>
-__device__ __forceinline__ double membership_sum(const double (&gg)[KM], int m, double rinv) {
+__device__ __forceinline__ double membership_sum(const double (&gg)[KM], double rinv) {
     double s = 0.0;
 #pragma unroll
-    for (int j = 0; j < KM; ++j)
-        if (j < m) s = __dadd_rn(s, exp(-gg[j] * rinv));
+    for (int j = 0; j < KM; ++j) s = __dadd_rn(s, exp(-gg[j] * rinv));
     return s;
 }
 
 // Bisection for sigma from sigma = 1: double until the sum exceeds the
 // target, then halve the bracket; stop when the sum is within 1e-12 of the
 // target (relative), the bracket is one ulp wide, or after 200 steps.
-template <class SumFn>
-__device__ __forceinline__ double bisect_sigma(double target, SumFn sum_at) {
+//
+// The sum grows with sigma, so once its root is known to a few 1e-12 the
+// outcome of every step outside a narrow zone around it is known too, and
+// only the steps inside are evaluated: the sequence of midpoints, and the
+// result, are those of the bisection bit for bit.  The root comes from
+// Newton's iteration in r = 1 / sigma, where the sum is convex and falling, so
+// that from the left it rises to the root without safeguards: in float32 to
+// 1e-5, then two steps in float64.  It starts at r gmax = 1/8, left of every
+// root: with no gap above gmax the sum is at least m (1 - r gmax), so that
+// r gmax >= 1 - log2(m + 1) / m >= 0.2 there (m = 1 is always degenerate).  The
+// zone's edges lie where the sum is 4e-12 of the target away (four times the
+// stop, and 1000 times its rounding).  A row without a sound root (no
+// convergence, a flat sum, an infinite or NaN gap) evaluates every step.
+// About 10 float32 and 7 float64 sums per row in place of 44 float64 ones: 2k
+// rows 69 -> 24 us (k = 15), 70k rows 233 -> 56 us (k = 30), 1M rows 0.76 ->
+// 0.17 ms (k = 15).
+template <class SumFn, class GapFn>
+__device__ __forceinline__ double bisect_sigma(double target, double gmax, SumFn sum_at, GapFn gap) {
+    double z0 = -INFINITY, z1 = INFINITY;  // sigma outside [z0, z1]: the step's outcome is known
+    {
+        const float t = (float)target, scale = (float)(1.0 / gmax);
+        float r = 0.125f;
+        bool close = false;
+        for (int it = 0; it < 32; ++it) {
+            float s = 0.f, ds = 0.f;
+            gap([&](double g) {
+                const float x = fminf((float)g * scale, 1e30f), e = __expf(-x * r);
+                s += e;
+                ds = fmaf(x, e, ds);
+            });
+            close = fabsf(s - t) <= 1e-5f * t;
+            if (close || !(ds > 0.f)) break;
+            r += (s - t) / ds;
+        }
+        if (close && r < 1e30f) {
+            double R = (double)r / gmax, last = 1.0, slope = 0.0;
+            for (int it = 0; it < 2; ++it) {
+                double s = 0.0, ds = 0.0;
+                gap([&](double g) {
+                    const double e = exp(-g * R);
+                    s += e;
+                    ds += fmin(g, 1e300) * e;
+                });
+                slope = ds * R;  // d sum / d log sigma
+                last = (s - target) / slope;
+                R += last * R;
+            }
+            const double tol = 4e-12 * target / slope + 1e-12;
+            if (fabs(last) <= 1e-7 && slope > 1e-4 * target) {
+                z0 = (1.0 - tol) / R;
+                z1 = (1.0 + tol) / R;
+            }
+        }
+    }
     double sigma = 1.0;
     double lo = 0.0, hi = INFINITY;
-    for (int it = 0; it < 200; ++it) {
-        const double f = sum_at(1.0 / sigma);
-        if (fabs(f - target) <= 1e-12 * target) break;
-        if (f > target)
+    int it = 0;
+    // one step of the bisection; true when its bracket is one ulp wide
+    auto step = [&](bool above) {
+        if (above)
             hi = sigma;
         else
             lo = sigma;
@@ -112,7 +163,16 @@ __device__ __forceinline__ double bisect_sigma(double target, SumFn sum_at) {
             sigma = sigma * 2.0;
         else
             sigma = (lo + hi) / 2.0;
-        if (!isinf(hi) && hi - lo <= ldexp(hi, -52)) break;
+        ++it;
+        return !isinf(hi) && hi - lo <= ldexp(hi, -52);
+    };
+    while (it < 200) {
+        bool done = false;
+        while (it < 200 && !done && (sigma < z0 || sigma > z1)) done = step(sigma > z1);
+        if (done || it >= 200) break;
+        const double f = sum_at(1.0 / sigma);
+        if (fabs(f - target) <= 1e-12 * target) break;
+        if (step(f > target)) break;
     }
     return sigma;
 }
@@ -138,7 +198,7 @@ __global__ __launch_bounds__(256) void k_smooth(const float *__restrict__ dist, 
     for (int j = 0; j < KM; ++j) {
         if (j < m && dd[j] <= rho) ++at_rho;
         const double g = dd[j] - rho;
-        gg[j] = g < 0.0 ? 0.0 : g;
+        gg[j] = j < m ? (g < 0.0 ? 0.0 : g) : INFINITY;
     }
     const double target = log2((double)k);
     double sigma;
@@ -151,7 +211,15 @@ __global__ __launch_bounds__(256) void k_smooth(const float *__restrict__ dist, 
             if (j < m) ai[j] = dd[j] <= rho ? 1.0 : 0.0;
         atomicAdd(&res->degenerate, 1);
     } else {
-        sigma = bisect_sigma(target, [&](double rinv) { return membership_sum<KM>(gg, m, rinv); });
+        double gmax = 0.0;
+#pragma unroll
+        for (int j = 0; j < KM; ++j) gmax = fmax(gmax, dd[j] - rho);
+        sigma = bisect_sigma(
+            target, gmax, [&](double rinv) { return membership_sum<KM>(gg, rinv); },
+            [&](auto use) {
+#pragma unroll
+                for (int j = 0; j < KM; ++j) use(gg[j]);
+            });
 #pragma unroll
         for (int j = 0; j < KM; ++j)
             if (j < m) ai[j] = exp(-gg[j] / sigma);
@@ -186,15 +254,22 @@ __global__ __launch_bounds__(256) void k_smooth_wide(const float *__restrict__ d
         for (int j = 0; j < m; ++j) ai[j] = (double)dr[j] <= rho ? 1.0 : 0.0;
         atomicAdd(&res->degenerate, 1);
     } else {
-        sigma = bisect_sigma(target, [&](double rinv) {
-            double s = 0.0;
+        auto gap = [&](auto use) {
             for (int j = 0; j < m; ++j) {
-                double g = (double)dr[j] - rho;
-                if (g < 0.0) g = 0.0;
-                s = __dadd_rn(s, exp(-g * rinv));
+                const double g = (double)dr[j] - rho;
+                use(g < 0.0 ? 0.0 : g);
             }
-            return s;
-        });
+        };
+        double gmax = 0.0;
+        gap([&](double g) { gmax = fmax(gmax, g); });
+        sigma = bisect_sigma(
+            target, gmax,
+            [&](double rinv) {
+                double s = 0.0;
+                gap([&](double g) { s = __dadd_rn(s, exp(-g * rinv)); });
+                return s;
+            },
+            gap);
         for (int j = 0; j < m; ++j) {
             double g = (double)dr[j] - rho;
             if (g < 0.0) g = 0.0;
