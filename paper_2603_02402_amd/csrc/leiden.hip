@@ -40,8 +40,12 @@
 // lane and each lane sums the weights of the lanes that share its community
 // (lane broadcasts); a longer row is summed in an open-addressing table of
 // twice its length in global memory (integer atomics, so the sums are exact).
-// Aggregation sorts (new row, new column) keys with a radix sort and adds
-// equal keys with a reduce-by-key.
+// Kernels that only add a row up give it 16 lanes.  Aggregation sorts (new row,
+// new column) keys with a radix sort and adds equal keys with a reduce-by-key.
+//
+// Counters and sums that every vertex adds to are gathered per block first:
+// with one atomic per wave or vertex, waiting for the few addresses took 40 of
+// the 64 ms of 300k vertices (k = 15); gathered, the run takes 24 ms.
 
 #include <hip/hip_runtime.h>
 
@@ -102,6 +106,94 @@ __device__ __forceinline__ int64_t wave_sum64(int64_t x) {
     for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, kWave);
     return x;
 }
+
+// Lanes that share one short row in the kernels that only add a row up: the
+// rows of a k = 15 graph hold about 20 entries, which fill a whole wave to a
+// third (300k rows, one pass: 118 us by whole waves, 34 us by 16 lanes).
+constexpr int kRowLanes = 16;
+__device__ __forceinline__ int64_t row_sum64(int64_t x) {
+    for (int o = kRowLanes / 2; o > 0; o >>= 1) x += __shfl_xor(x, o, kWave);
+    return x;
+}
+
+// Sum over the block, in thread 0 (every thread of the block calls it).
+__device__ __forceinline__ int64_t block_sum64(int64_t x) {
+    __shared__ int64_t part[kBlock / kWave];
+    x = wave_sum64(x);
+    if ((threadIdx.x & (kWave - 1)) == 0) part[threadIdx.x / kWave] = x;
+    __syncthreads();
+    int64_t s = 0;
+    if (threadIdx.x == 0)
+        for (int i = 0; i < kBlock / kWave; ++i) s += part[i];
+    return s;
+}
+
+__device__ __forceinline__ void add64(int64_t *p, int64_t x) {
+    atomicAdd(reinterpret_cast<unsigned long long *>(p), (unsigned long long)x);
+}
+
+// Sums by community, gathered per block before they go to memory.  Atomics on
+// one address are served one after another, about 5 ns each across the chip,
+// and late in a run a few dozen communities hold every vertex.  Each slot is
+// owned by the first community that hashes to it; the others of that slot add
+// to memory directly.
+constexpr int kSumSlots = 128;
+struct BlockSums {
+    int32_t key[kSumSlots];
+    int64_t a[kSumSlots], b[kSumSlots];
+    __device__ void clear() {
+        for (int i = threadIdx.x; i < kSumSlots; i += kBlock) {
+            key[i] = -1;
+            a[i] = b[i] = 0;
+        }
+        __syncthreads();
+    }
+    __device__ void add(int32_t c, int64_t x, int64_t y, int64_t *ga, int64_t *gb) {
+        const uint32_t i = ((uint32_t)c * 0x9E3779B1u) >> 25;  // top 7 bits: kSumSlots = 128
+        int32_t owner = key[i];
+        if (owner == -1) {
+            owner = atomicCAS(&key[i], -1, c);
+            if (owner == -1) owner = c;
+        }
+        const bool here = owner == c;
+        if (x) add64(here ? &a[i] : &ga[c], x);
+        if (y) add64(here ? &b[i] : &gb[c], y);
+    }
+    __device__ void flush(int64_t *ga, int64_t *gb) {
+        __syncthreads();
+        for (int i = threadIdx.x; i < kSumSlots; i += kBlock) {
+            if (a[i]) add64(&ga[key[i]], a[i]);
+            if (b[i]) add64(&gb[key[i]], b[i]);
+        }
+    }
+};
+
+// The same for minima by community: 300k vertices in 50 communities took 871 us
+// of one atomic each, and take 12 us.
+struct BlockMins {
+    int32_t key[kSumSlots], val[kSumSlots];
+    __device__ void clear() {
+        for (int i = threadIdx.x; i < kSumSlots; i += kBlock) {
+            key[i] = -1;
+            val[i] = INT_MAX;
+        }
+        __syncthreads();
+    }
+    __device__ void add(int32_t c, int32_t x, int32_t *g) {
+        const uint32_t i = ((uint32_t)c * 0x9E3779B1u) >> 25;
+        int32_t owner = key[i];
+        if (owner == -1) {
+            owner = atomicCAS(&key[i], -1, c);
+            if (owner == -1) owner = c;
+        }
+        atomicMin(owner == c ? &val[i] : &g[c], x);
+    }
+    __device__ void flush(int32_t *g) {
+        __syncthreads();
+        for (int i = threadIdx.x; i < kSumSlots; i += kBlock)
+            if (key[i] >= 0) atomicMin(&g[key[i]], val[i]);
+    }
+};
 
 // Wave-wide best (largest h, then smallest c); c < 0 marks no candidate.
 __device__ __forceinline__ void wave_best(double &h, int32_t &c) {
@@ -274,7 +366,10 @@ __global__ __launch_bounds__(kBlock) void k_lv_check(const int64_t *__restrict__
         if (ptr[i] > ptr[i + 1]) err |= 4;
     if (blockIdx.x == 0 && threadIdx.x == 0 && (ptr[0] != 0 || ptr[n] != nnz)) err |= 4;
     if (err) atomicOr(&st->error, err);
-    if (wmax) atomicMax(&st->wmax_bits, wmax);
+    for (int o = kWave / 2; o > 0; o >>= 1) wmax = max(wmax, (uint32_t)__shfl_xor((int)wmax, o, kWave));
+    // the maximum only grows, so a stale value costs an atomic and no more
+    if ((threadIdx.x & (kWave - 1)) == 0 && wmax > *(volatile uint32_t *)&st->wmax_bits)
+        atomicMax(&st->wmax_bits, wmax);
 }
 
 // Level 0's graph: the input columns and W = rint(w 2^S) (twice: the level
@@ -314,29 +409,34 @@ __global__ __launch_bounds__(kBlock) void k_lv_fill32(int32_t *__restrict__ a, i
 
 // ---- per level -------------------------------------------------------------
 
-// Degrees k_v (row sums, diagonal once) and 2m.
+// Degrees k_v (row sums, diagonal once) and 2m.  One atomic per block on 2m:
+// one per wave took 3.1 ms of 300k rows, all of it spent waiting in line.
 __global__ __launch_bounds__(kBlock) void k_lv_degree(const int64_t *__restrict__ ptr,
                                                       const int64_t *__restrict__ gw, int64_t N,
                                                       int64_t *__restrict__ kdeg, LeidenState *__restrict__ st) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t waves = (int64_t)gridDim.x * (blockDim.x / kWave);
+    const int sub = threadIdx.x & (kRowLanes - 1);
+    const int64_t rows = (int64_t)gridDim.x * (kBlock / kRowLanes);
     int64_t acc = 0;
-    for (int64_t v = (int64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave; v < N; v += waves) {
+    for (int64_t v = (int64_t)blockIdx.x * (kBlock / kRowLanes) + threadIdx.x / kRowLanes; v < N; v += rows) {
         int64_t s = 0;
-        for (int64_t e = ptr[v] + lane; e < ptr[v + 1]; e += kWave) s += gw[e];
-        s = wave_sum64(s);
-        if (lane == 0) kdeg[v] = s;
+        for (int64_t e = ptr[v] + sub; e < ptr[v + 1]; e += kRowLanes) s += gw[e];
         acc += s;
+        s = row_sum64(s);
+        if (sub == 0) kdeg[v] = s;
     }
-    if (lane == 0 && acc) atomicAdd(&st->two_m, (unsigned long long)acc);
+    acc = block_sum64(acc);
+    if (threadIdx.x == 0 && acc) atomicAdd(&st->two_m, (unsigned long long)acc);
 }
 
 // tot[c] += k_v over the vertices labelled c (tot cleared before).
 __global__ __launch_bounds__(kBlock) void k_lv_tot(const int32_t *__restrict__ lab, const int64_t *__restrict__ kdeg,
                                                    int64_t N, int64_t *__restrict__ tot) {
+    __shared__ BlockSums sums;
+    sums.clear();
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < N; v += stride)
-        if (kdeg[v]) atomicAdd(reinterpret_cast<unsigned long long *>(&tot[lab[v]]), (unsigned long long)kdeg[v]);
+        sums.add(lab[v], kdeg[v], 0, tot, tot);
+    sums.flush(tot, tot);
 }
 
 // One sweep of local moving: Lnext[v] from the labels L at the sweep start.
@@ -348,8 +448,7 @@ __device__ __forceinline__ void move_one(int64_t v, const int64_t *__restrict__ 
                                          const int64_t *__restrict__ gw, const int64_t *__restrict__ kdeg,
                                          const int64_t *__restrict__ tot, const int32_t *__restrict__ L,
                                          int32_t *__restrict__ Lnext, int up, double gamma, double two_m,
-                                         WaveTable *lt, int32_t *__restrict__ hk, int64_t *__restrict__ hv,
-                                         int &moved) {
+                                         WaveTable *lt, int32_t *__restrict__ hk, int64_t *__restrict__ hv) {
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t b = ptr[v], e = ptr[v + 1];
     const int32_t a = L[v];
@@ -388,10 +487,7 @@ __device__ __forceinline__ void move_one(int64_t v, const int64_t *__restrict__ 
         Ka = 0;
     const double stay = gain(Ka, gamma, kv, tot[a] - kv, two_m);
     const int32_t next = (best_c >= 0 && best_h > stay) ? best_c : a;
-    if (lane == 0) {
-        Lnext[v] = next;
-        moved += next != a;
-    }
+    if (lane == 0) Lnext[v] = next;
 }
 
 __global__ __launch_bounds__(kBlock) void k_lv_move(const int64_t *__restrict__ ptr, const int32_t *__restrict__ col,
@@ -399,13 +495,12 @@ __global__ __launch_bounds__(kBlock) void k_lv_move(const int64_t *__restrict__ 
                                                     const int64_t *__restrict__ kdeg, const int64_t *__restrict__ tot,
                                                     const int32_t *__restrict__ L, int32_t *__restrict__ Lnext,
                                                     int up, double gamma, double two_m, int32_t *__restrict__ hk,
-                                                    int64_t *__restrict__ hv, LeidenState *__restrict__ st) {
+                                                    int64_t *__restrict__ hv) {
     __shared__ WaveTable tabs[kBlock / kWave];
     WaveTable *lt = &tabs[threadIdx.x / kWave];
     const int lane = threadIdx.x & (kWave - 1);
     const int half = lane >> 5, sub = lane & 31;
     const int64_t waves = (int64_t)gridDim.x * (blockDim.x / kWave);
-    int moved = 0;
     for (int64_t g = (int64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave; 2 * g < N; g += waves) {
         const int64_t v = 2 * g + half;
         const bool vok = v < N;
@@ -413,9 +508,9 @@ __global__ __launch_bounds__(kBlock) void k_lv_move(const int64_t *__restrict__ 
         const int len = vok ? (int)(ptr[v + 1] - b) : 0;
         const int len0 = __builtin_amdgcn_readlane(len, 0), len1 = __builtin_amdgcn_readlane(len, 32);
         if (len0 > 32 || len1 > 32) {
-            move_one(2 * g, ptr, col, gw, kdeg, tot, L, Lnext, up, gamma, two_m, lt, hk, hv, moved);
+            move_one(2 * g, ptr, col, gw, kdeg, tot, L, Lnext, up, gamma, two_m, lt, hk, hv);
             if (2 * g + 1 < N)
-                move_one(2 * g + 1, ptr, col, gw, kdeg, tot, L, Lnext, up, gamma, two_m, lt, hk, hv, moved);
+                move_one(2 * g + 1, ptr, col, gw, kdeg, tot, L, Lnext, up, gamma, two_m, lt, hk, hv);
             continue;
         }
         const int32_t a = vok ? L[v] : -1;
@@ -459,77 +554,72 @@ __global__ __launch_bounds__(kBlock) void k_lv_move(const int64_t *__restrict__ 
             const double stay = gain(half ? Ka1 : Ka0, gamma, kv, tot[a] - kv, two_m);
             const int32_t next = (best_c >= 0 && best_h > stay) ? best_c : a;
             Lnext[v] = next;
-            moved += next != a;
         }
     }
-    if ((lane & 31) == 0 && moved) atomicAdd(&st->moved, moved);
 }
 
 // After a sweep: the community totals follow the vertices that moved (integer
-// sums, so tot stays exactly the sum of k over each label).
+// sums, so tot stays exactly the sum of k over each label), and the moves are
+// counted, with one atomic per block: counted by the half-waves of k_lv_move
+// they held up its first sweeps by 1.5 of 1.67 ms (300k vertices).
 __global__ __launch_bounds__(kBlock) void k_lv_tot_delta(const int32_t *__restrict__ L,
                                                          const int32_t *__restrict__ Lnext,
                                                          const int64_t *__restrict__ kdeg, int64_t N,
-                                                         int64_t *__restrict__ tot) {
+                                                         int64_t *__restrict__ tot, LeidenState *__restrict__ st) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    int64_t moved = 0;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < N; v += stride) {
         const int32_t a = L[v], b = Lnext[v];
+        if (a == b) continue;
+        ++moved;
         const int64_t kv = kdeg[v];
-        if (a != b && kv) {
-            atomicAdd(reinterpret_cast<unsigned long long *>(&tot[b]), (unsigned long long)kv);
-            atomicAdd(reinterpret_cast<unsigned long long *>(&tot[a]), (unsigned long long)(-kv));
+        if (kv) {
+            add64(&tot[b], kv);
+            add64(&tot[a], -kv);
         }
     }
+    moved = block_sum64(moved);
+    if (threadIdx.x == 0 && moved) atomicAdd(&st->moved, (int32_t)moved);
 }
 
-// Refinement set-up: kin[v] = K(v, C - v) and totC[c] = sum of k over c.
+// Refinement set-up: kin[v] = K(v, C - v).  (The sum of k over each community
+// is tot, as local moving left it.)
 __global__ __launch_bounds__(kBlock) void k_lv_refine_prep(const int64_t *__restrict__ ptr,
                                                            const int32_t *__restrict__ col,
                                                            const int64_t *__restrict__ gw, int64_t N,
-                                                           const int64_t *__restrict__ kdeg,
-                                                           const int32_t *__restrict__ L, int64_t *__restrict__ kin,
-                                                           int64_t *__restrict__ totC) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t waves = (int64_t)gridDim.x * (blockDim.x / kWave);
-    for (int64_t v = (int64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave; v < N; v += waves) {
+                                                           const int32_t *__restrict__ L, int64_t *__restrict__ kin) {
+    const int sub = threadIdx.x & (kRowLanes - 1);
+    const int64_t rows = (int64_t)gridDim.x * (kBlock / kRowLanes);
+    for (int64_t v = (int64_t)blockIdx.x * (kBlock / kRowLanes) + threadIdx.x / kRowLanes; v < N; v += rows) {
         const int32_t c = L[v];
         int64_t s = 0;
-        for (int64_t e = ptr[v] + lane; e < ptr[v + 1]; e += kWave) {
+        for (int64_t e = ptr[v] + sub; e < ptr[v + 1]; e += kRowLanes) {
             const int32_t u = col[e];
             if (u != (int32_t)v && L[u] == c) s += gw[e];
         }
-        s = wave_sum64(s);
-        if (lane == 0) {
-            kin[v] = s;
-            if (kdeg[v]) atomicAdd(reinterpret_cast<unsigned long long *>(&totC[c]), (unsigned long long)kdeg[v]);
-        }
+        s = row_sum64(s);
+        if (sub == 0) kin[v] = s;
     }
 }
 
-// Per round: totR, size and extR = E(R, C - R) by refined label (cleared before).
+// Per round: extR = E(R, C - R) by refined label (cleared before).
 __global__ __launch_bounds__(kBlock) void k_lv_refine_stats(const int64_t *__restrict__ ptr,
                                                             const int32_t *__restrict__ col,
                                                             const int64_t *__restrict__ gw, int64_t N,
-                                                            const int64_t *__restrict__ kdeg,
                                                             const int32_t *__restrict__ L,
                                                             const int32_t *__restrict__ R,
-                                                            int64_t *__restrict__ totR, int32_t *__restrict__ size,
                                                             int64_t *__restrict__ extR) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t waves = (int64_t)gridDim.x * (blockDim.x / kWave);
-    for (int64_t v = (int64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave; v < N; v += waves) {
+    const int sub = threadIdx.x & (kRowLanes - 1);
+    const int64_t rows = (int64_t)gridDim.x * (kBlock / kRowLanes);
+    for (int64_t v = (int64_t)blockIdx.x * (kBlock / kRowLanes) + threadIdx.x / kRowLanes; v < N; v += rows) {
         const int32_t c = L[v], r = R[v];
         int64_t s = 0;
-        for (int64_t e = ptr[v] + lane; e < ptr[v + 1]; e += kWave) {
+        for (int64_t e = ptr[v] + sub; e < ptr[v + 1]; e += kRowLanes) {
             const int32_t u = col[e];
             if (L[u] == c && R[u] != r) s += gw[e];
         }
-        s = wave_sum64(s);
-        if (lane == 0) {
-            if (kdeg[v]) atomicAdd(reinterpret_cast<unsigned long long *>(&totR[r]), (unsigned long long)kdeg[v]);
-            atomicAdd(&size[r], 1);
-            if (s) atomicAdd(reinterpret_cast<unsigned long long *>(&extR[r]), (unsigned long long)s);
-        }
+        s = row_sum64(s);
+        if (sub == 0 && s) add64(&extR[r], s);
     }
 }
 
@@ -583,19 +673,39 @@ __global__ __launch_bounds__(kBlock) void k_lv_refine_propose(
     }
 }
 
+// Applies the proposals.  A proposal to a singleton that itself moves away is
+// dropped; only singletons propose, so prop says which.  totR and size follow
+// the joins (integer sums), which is all that changes them.
 __global__ __launch_bounds__(kBlock) void k_lv_refine_apply(const int32_t *__restrict__ prop,
-                                                            const int32_t *__restrict__ size, int64_t N,
-                                                            int32_t *__restrict__ R, LeidenState *__restrict__ st) {
+                                                            const int64_t *__restrict__ kdeg, int64_t N,
+                                                            int32_t *__restrict__ R, int64_t *__restrict__ totR,
+                                                            int32_t *__restrict__ size, LeidenState *__restrict__ st) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    int joins = 0;
+    int64_t joins = 0;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < N; v += stride) {
         const int32_t t = prop[v];
-        if (t < 0) continue;
-        if (size[t] == 1 && prop[t] >= 0) continue;  // the target singleton moves away
+        if (t < 0 || prop[t] >= 0) continue;
         R[v] = t;
+        add64(&totR[t], kdeg[v]);
+        totR[v] = 0;
+        atomicAdd(&size[t], 1);
+        size[v] = 0;
         ++joins;
     }
-    if (joins) atomicAdd(&st->joins, joins);
+    joins = block_sum64(joins);
+    if (threadIdx.x == 0 && joins) atomicAdd(&st->joins, (int32_t)joins);
+}
+
+// The refinement starts from singletons.
+__global__ __launch_bounds__(kBlock) void k_lv_refine_init(const int64_t *__restrict__ kdeg, int64_t N,
+                                                           int32_t *__restrict__ R, int64_t *__restrict__ totR,
+                                                           int32_t *__restrict__ size) {
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < N; v += stride) {
+        R[v] = (int32_t)v;
+        totR[v] = kdeg[v];
+        size[v] = 1;
+    }
 }
 
 // head[v] = 1 where v is the smallest vertex (the label) of its refined community
@@ -613,11 +723,11 @@ __global__ __launch_bounds__(kBlock) void k_lv_edge_keys(const int64_t *__restri
                                                          const int32_t *__restrict__ R,
                                                          const int32_t *__restrict__ id, uint64_t *__restrict__ key,
                                                          int64_t *__restrict__ val) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t waves = (int64_t)gridDim.x * (blockDim.x / kWave);
-    for (int64_t v = (int64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave; v < N; v += waves) {
+    const int sub = threadIdx.x & (kRowLanes - 1);
+    const int64_t rows = (int64_t)gridDim.x * (kBlock / kRowLanes);
+    for (int64_t v = (int64_t)blockIdx.x * (kBlock / kRowLanes) + threadIdx.x / kRowLanes; v < N; v += rows) {
         const uint64_t a = (uint64_t)(uint32_t)id[R[v]] << 32;
-        for (int64_t e = ptr[v] + lane; e < ptr[v + 1]; e += kWave) {
+        for (int64_t e = ptr[v] + sub; e < ptr[v + 1]; e += kRowLanes) {
             key[e] = a | (uint32_t)id[R[col[e]]];
             val[e] = gw[e];
         }
@@ -659,9 +769,12 @@ __global__ __launch_bounds__(kBlock) void k_lv_rowptr(const uint64_t *__restrict
 __global__ __launch_bounds__(kBlock) void k_lv_minid(const int32_t *__restrict__ L, const int32_t *__restrict__ R,
                                                      const int32_t *__restrict__ id, int64_t N,
                                                      int32_t *__restrict__ minid) {
+    __shared__ BlockMins mins;
+    mins.clear();
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < N; v += stride)
-        atomicMin(&minid[L[v]], id[R[v]]);
+        mins.add(L[v], id[R[v]], minid);
+    mins.flush(minid);
 }
 
 __global__ __launch_bounds__(kBlock) void k_lv_newlabels(const int32_t *__restrict__ L,
@@ -684,9 +797,12 @@ __global__ __launch_bounds__(kBlock) void k_lv_top(const int32_t *__restrict__ R
 
 __global__ __launch_bounds__(kBlock) void k_lv_first(const int32_t *__restrict__ L, const int32_t *__restrict__ top,
                                                      int64_t n, int32_t *__restrict__ first) {
+    __shared__ BlockMins mins;
+    mins.clear();
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
-        atomicMin(&first[L[top[i]]], (int32_t)i);
+        mins.add(L[top[i]], (int32_t)i, first);
+    mins.flush(first);
 }
 
 __global__ __launch_bounds__(kBlock) void k_lv_mark(const int32_t *__restrict__ L, const int32_t *__restrict__ top,
@@ -712,22 +828,22 @@ __global__ __launch_bounds__(kBlock) void k_lv_quality_sums(const int64_t *__res
                                                             const int64_t *__restrict__ gw, int64_t n,
                                                             const int32_t *__restrict__ labels,
                                                             int64_t *__restrict__ in, int64_t *__restrict__ tot) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t waves = (int64_t)gridDim.x * (blockDim.x / kWave);
-    for (int64_t v = (int64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave; v < n; v += waves) {
+    __shared__ BlockSums sums;
+    sums.clear();
+    const int sub = threadIdx.x & (kRowLanes - 1);
+    const int64_t rows = (int64_t)gridDim.x * (kBlock / kRowLanes);
+    for (int64_t v = (int64_t)blockIdx.x * (kBlock / kRowLanes) + threadIdx.x / kRowLanes; v < n; v += rows) {
         const int32_t c = labels[v];
         int64_t s = 0, t = 0;
-        for (int64_t e = ptr[v] + lane; e < ptr[v + 1]; e += kWave) {
+        for (int64_t e = ptr[v] + sub; e < ptr[v + 1]; e += kRowLanes) {
             t += gw[e];
             if (labels[col[e]] == c) s += gw[e];
         }
-        s = wave_sum64(s);
-        t = wave_sum64(t);
-        if (lane == 0) {
-            if (s) atomicAdd(reinterpret_cast<unsigned long long *>(&in[c]), (unsigned long long)s);
-            if (t) atomicAdd(reinterpret_cast<unsigned long long *>(&tot[c]), (unsigned long long)t);
-        }
+        s = row_sum64(s);
+        t = row_sum64(t);
+        if (sub == 0) sums.add(c, s, t, in, tot);
     }
+    sums.flush(in, tot);
 }
 
 // Q = sum over communities in label order of in/2m - (gamma tot/2m) tot/2m (one thread, in order).
@@ -755,7 +871,7 @@ struct LeidenWs {
     LeidenState *st;
     LevelGraph g[2];
     int64_t *w0;  // fixed-point input weights (level 0 keeps them for the modularity)
-    int64_t *kdeg, *tot, *kin, *totC, *totR, *extR;
+    int64_t *kdeg, *tot, *kin, *totR, *extR;
     int32_t *L, *Lnext, *R, *prop, *size, *head, *id, *minid, *top, *first, *mark, *num;
     int32_t *hk;
     int64_t *hv;
@@ -807,7 +923,6 @@ size_t carve_leiden(int64_t n, int64_t nnz, void *base, LeidenWs *out) {
     w.kdeg = cv.take<int64_t>(N);
     w.tot = cv.take<int64_t>(N);
     w.kin = cv.take<int64_t>(N);
-    w.totC = cv.take<int64_t>(N);
     w.totR = cv.take<int64_t>(N);
     w.extR = cv.take<int64_t>(N);
     w.L = cv.take<int32_t>(N);
@@ -843,6 +958,15 @@ size_t carve_leiden(int64_t n, int64_t nnz, void *base, LeidenWs *out) {
 unsigned grid_items(int64_t items) {
     return (unsigned)std::max<int64_t>(1, std::min<int64_t>((items + kBlock - 1) / kBlock, 8192));
 }
+// 16 lanes per row; few enough blocks that one atomic each stays short
+unsigned grid_rows(int64_t rows) {
+    const int64_t per = kBlock / kRowLanes;
+    return (unsigned)std::max<int64_t>(1, std::min<int64_t>((rows + per - 1) / per, 2048));
+}
+// one item per thread, one atomic per block
+unsigned grid_few(int64_t items) {
+    return (unsigned)std::max<int64_t>(1, std::min<int64_t>((items + kBlock - 1) / kBlock, 1024));
+}
 unsigned grid_waves(int64_t waves) {
     return (unsigned)std::max<int64_t>(1, std::min<int64_t>((waves + kBlock / kWave - 1) / (kBlock / kWave), 65536));
 }
@@ -864,7 +988,7 @@ int leiden_run(const int64_t *indptr, const int32_t *indices, const float *weigh
     carve_leiden(n, nnz, ws, &w);
     int st;
     hipLaunchKernelGGL(k_lv_init, dim3(1), dim3(64), 0, s, w.st);
-    hipLaunchKernelGGL(k_lv_check, dim3(grid_items(std::max(n, nnz))), dim3(kBlock), 0, s, indptr, indices, weights, n,
+    hipLaunchKernelGGL(k_lv_check, dim3(grid_few(std::max(n, nnz))), dim3(kBlock), 0, s, indptr, indices, weights, n,
                        nnz, w.st);
     if ((st = launch_status("leiden input check")) != RSC_OK) return st;
     LeidenState hs;
@@ -902,7 +1026,7 @@ int leiden_run(const int64_t *indptr, const int32_t *indices, const float *weigh
     double two_m0 = 0.0;
     for (;;) {
         hipLaunchKernelGGL(k_lv_init, dim3(1), dim3(64), 0, s, w.st);
-        hipLaunchKernelGGL(k_lv_degree, dim3(grid_waves(N)), dim3(kBlock), 0, s, G.ptr, G.w, N, w.kdeg, w.st);
+        hipLaunchKernelGGL(k_lv_degree, dim3(grid_rows(N)), dim3(kBlock), 0, s, G.ptr, G.w, N, w.kdeg, w.st);
         if ((st = launch_status("leiden degrees")) != RSC_OK) return st;
         if ((st = read_back(&hs, w.st, s, "read 2m")) != RSC_OK) return st;
         if (lv == 0) two_m0 = (double)(int64_t)hs.two_m;
@@ -914,15 +1038,15 @@ int leiden_run(const int64_t *indptr, const int32_t *indices, const float *weigh
         // community totals of the level's starting labels; each sweep then
         // moves them along with the vertices that change label
         hipLaunchKernelGGL(k_lv_fill64, dim3(grid_items(N)), dim3(kBlock), 0, s, w.tot, N, (int64_t)0);
-        hipLaunchKernelGGL(k_lv_tot, dim3(grid_items(N)), dim3(kBlock), 0, s, w.L, w.kdeg, N, w.tot);
+        hipLaunchKernelGGL(k_lv_tot, dim3(grid_few(N)), dim3(kBlock), 0, s, w.L, w.kdeg, N, w.tot);
         for (int sweep = 1; sweep <= kMaxSweeps && quiet < 2; ++sweep) {
             {
                 ScopedTimer t("leiden_move", s);
                 hipLaunchKernelGGL(k_lv_init, dim3(1), dim3(64), 0, s, w.st);
                 hipLaunchKernelGGL(k_lv_move, dim3(grid_waves((N + 1) / 2)), dim3(kBlock), 0, s, G.ptr, G.col, G.w, N, w.kdeg,
-                                   w.tot, w.L, w.Lnext, sweep % 2, gamma, two_m, w.hk, w.hv, w.st);
-                hipLaunchKernelGGL(k_lv_tot_delta, dim3(grid_items(N)), dim3(kBlock), 0, s, w.L, w.Lnext, w.kdeg, N,
-                                   w.tot);
+                                   w.tot, w.L, w.Lnext, sweep % 2, gamma, two_m, w.hk, w.hv);
+                hipLaunchKernelGGL(k_lv_tot_delta, dim3(grid_few(N)), dim3(kBlock), 0, s, w.L, w.Lnext, w.kdeg, N,
+                                   w.tot, w.st);
             }
             if ((st = launch_status("leiden local moving")) != RSC_OK) return st;
             ++sweeps;
@@ -937,23 +1061,19 @@ int leiden_run(const int64_t *indptr, const int32_t *indices, const float *weigh
         // 2. refinement
         {
         ScopedTimer t_refine("leiden_refine", s);
-        hipLaunchKernelGGL(k_lv_fill64, dim3(grid_items(N)), dim3(kBlock), 0, s, w.totC, N, (int64_t)0);
-        hipLaunchKernelGGL(k_lv_iota, dim3(grid_items(N)), dim3(kBlock), 0, s, w.R, N);
-        hipLaunchKernelGGL(k_lv_refine_prep, dim3(grid_waves(N)), dim3(kBlock), 0, s, G.ptr, G.col, G.w, N, w.kdeg,
-                           w.L, w.kin, w.totC);
+        hipLaunchKernelGGL(k_lv_refine_init, dim3(grid_items(N)), dim3(kBlock), 0, s, w.kdeg, N, w.R, w.totR, w.size);
+        hipLaunchKernelGGL(k_lv_refine_prep, dim3(grid_rows(N)), dim3(kBlock), 0, s, G.ptr, G.col, G.w, N, w.L, w.kin);
         if ((st = launch_status("leiden refinement set-up")) != RSC_OK) return st;
         for (int round = 1; round <= kMaxRounds; ++round) {
-            hipLaunchKernelGGL(k_lv_fill64, dim3(grid_items(N)), dim3(kBlock), 0, s, w.totR, N, (int64_t)0);
             hipLaunchKernelGGL(k_lv_fill64, dim3(grid_items(N)), dim3(kBlock), 0, s, w.extR, N, (int64_t)0);
-            hipLaunchKernelGGL(k_lv_fill32, dim3(grid_items(N)), dim3(kBlock), 0, s, w.size, N, 0);
-            hipLaunchKernelGGL(k_lv_refine_stats, dim3(grid_waves(N)), dim3(kBlock), 0, s, G.ptr, G.col, G.w, N,
-                               w.kdeg, w.L, w.R, w.totR, w.size, w.extR);
+            hipLaunchKernelGGL(k_lv_refine_stats, dim3(grid_rows(N)), dim3(kBlock), 0, s, G.ptr, G.col, G.w, N, w.L,
+                               w.R, w.extR);
             hipLaunchKernelGGL(k_lv_refine_propose, dim3(grid_waves(N)), dim3(kBlock), 0, s, G.ptr, G.col, G.w, N,
-                               w.kdeg, w.L, w.R, w.kin, w.totC, w.totR, w.size, w.extR, gamma, two_m, w.prop, w.hk,
+                               w.kdeg, w.L, w.R, w.kin, w.tot, w.totR, w.size, w.extR, gamma, two_m, w.prop, w.hk,
                                w.hv);
             hipLaunchKernelGGL(k_lv_init, dim3(1), dim3(64), 0, s, w.st);
-            hipLaunchKernelGGL(k_lv_refine_apply, dim3(grid_items(N)), dim3(kBlock), 0, s, w.prop, w.size, N, w.R,
-                               w.st);
+            hipLaunchKernelGGL(k_lv_refine_apply, dim3(grid_few(N)), dim3(kBlock), 0, s, w.prop, w.kdeg, N, w.R,
+                               w.totR, w.size, w.st);
             if ((st = launch_status("leiden refinement")) != RSC_OK) return st;
             ++rounds;
             if ((st = read_back(&hs, w.st, s, "read joins")) != RSC_OK) return st;
@@ -977,7 +1097,7 @@ int leiden_run(const int64_t *indptr, const int32_t *indices, const float *weigh
         const int64_t K2 = (int64_t)last_id + last_head;
         LevelGraph H = w.g[1 - gi];
         if (M > 0) {
-            hipLaunchKernelGGL(k_lv_edge_keys, dim3(grid_waves(N)), dim3(kBlock), 0, s, G.ptr, G.col, G.w, N, w.R,
+            hipLaunchKernelGGL(k_lv_edge_keys, dim3(grid_rows(N)), dim3(kBlock), 0, s, G.ptr, G.col, G.w, N, w.R,
                                w.id, w.key, w.val);
             if ((st = launch_status("leiden aggregation keys")) != RSC_OK) return st;
             if ((st = hip_status(rocprim::radix_sort_pairs(w.tmp, w.tmp_bytes, (const uint64_t *)w.key, w.key2,
@@ -1000,7 +1120,7 @@ int leiden_run(const int64_t *indptr, const int32_t *indices, const float *weigh
             hipLaunchKernelGGL(k_lv_fill64, dim3(grid_items(K2 + 1)), dim3(kBlock), 0, s, H.ptr, K2 + 1, (int64_t)0);
         }
         hipLaunchKernelGGL(k_lv_fill32, dim3(grid_items(N)), dim3(kBlock), 0, s, w.minid, N, INT_MAX);
-        hipLaunchKernelGGL(k_lv_minid, dim3(grid_items(N)), dim3(kBlock), 0, s, w.L, w.R, w.id, N, w.minid);
+        hipLaunchKernelGGL(k_lv_minid, dim3(std::min(grid_few(N), 256u)), dim3(kBlock), 0, s, w.L, w.R, w.id, N, w.minid);
         hipLaunchKernelGGL(k_lv_newlabels, dim3(grid_items(N)), dim3(kBlock), 0, s, w.L, w.R, w.id, w.minid, N,
                            w.Lnext);
         hipLaunchKernelGGL(k_lv_top, dim3(grid_items(n)), dim3(kBlock), 0, s, w.R, w.id, n, w.top);
@@ -1012,7 +1132,7 @@ int leiden_run(const int64_t *indptr, const int32_t *indices, const float *weigh
     }
     // carry the labels down, number them by first appearance
     hipLaunchKernelGGL(k_lv_fill32, dim3(grid_items(N)), dim3(kBlock), 0, s, w.first, N, INT_MAX);
-    hipLaunchKernelGGL(k_lv_first, dim3(grid_items(n)), dim3(kBlock), 0, s, w.L, w.top, n, w.first);
+    hipLaunchKernelGGL(k_lv_first, dim3(std::min(grid_few(n), 256u)), dim3(kBlock), 0, s, w.L, w.top, n, w.first);
     hipLaunchKernelGGL(k_lv_mark, dim3(grid_items(n)), dim3(kBlock), 0, s, w.L, w.top, w.first, n, w.mark);
     if ((st = launch_status("leiden numbering")) != RSC_OK) return st;
     if ((st = hip_status(rocprim::exclusive_scan(w.tmp, w.tmp_bytes, (const int32_t *)w.mark, w.num, (int32_t)0,
@@ -1034,7 +1154,7 @@ int leiden_run(const int64_t *indptr, const int32_t *indices, const float *weigh
         if (two_m0 > 0.0) {
             hipLaunchKernelGGL(k_lv_fill64, dim3(grid_items(ncomm)), dim3(kBlock), 0, s, w.qin, ncomm, (int64_t)0);
             hipLaunchKernelGGL(k_lv_fill64, dim3(grid_items(ncomm)), dim3(kBlock), 0, s, w.qtot, ncomm, (int64_t)0);
-            hipLaunchKernelGGL(k_lv_quality_sums, dim3(grid_waves(n)), dim3(kBlock), 0, s, indptr, indices, w.w0, n,
+            hipLaunchKernelGGL(k_lv_quality_sums, dim3(grid_rows(n)), dim3(kBlock), 0, s, indptr, indices, w.w0, n,
                                labels, w.qin, w.qtot);
             hipLaunchKernelGGL(k_lv_quality, dim3(1), dim3(64), 0, s, w.qin, w.qtot, ncomm, gamma, two_m0, w.q);
             if ((st = launch_status("leiden modularity")) != RSC_OK) return st;
