@@ -36,16 +36,18 @@
 // Levels end when moving moves nothing (or after 32 levels); the last labels
 // are carried down and numbered by first appearance.
 //
-// Layout: one wave per vertex.  A row of up to 64 entries sits one entry per
-// lane and each lane sums the weights of the lanes that share its community
-// (lane broadcasts); a longer row is summed in an open-addressing table of
-// twice its length in global memory (integer atomics, so the sums are exact).
+// Layout: local moving gives a wave a batch of rows and sums their entries by
+// community in LDS tables; a row of more than 256 entries takes a whole wave,
+// and one with more distinct communities than its LDS table holds an
+// open-addressing table of twice its length in global memory (integer atomics,
+// so the sums are exact).  Refinement takes one wave per vertex.
 // Kernels that only add a row up give it 16 lanes.  Aggregation sorts (new row,
 // new column) keys with a radix sort and adds equal keys with a reduce-by-key.
 //
 // Counters and sums that every vertex adds to are gathered per block first:
 // with one atomic per wave or vertex, waiting for the few addresses took 40 of
-// the 64 ms of 300k vertices (k = 15); gathered, the run takes 24 ms.
+// the 64 ms of 300k vertices (k = 15); gathered, the run took 24 ms, and takes
+// 14.6 ms with the moves by batches and the host reading every fourth count.
 
 #include <hip/hip_runtime.h>
 
@@ -75,10 +77,22 @@ struct LeidenState {
     int32_t error;       // bit 0: column out of range; bit 1: weight negative or not finite; bit 2: bad row pointers
     uint32_t wmax_bits;  // float bits of the largest weight (weights >= 0, so bits order like values)
     unsigned long long two_m;
-    int32_t moved;
-    int32_t joins;
-    int32_t pad[2];
+    int32_t moved[kMaxSweeps];  // vertices moved by each sweep of the level
+    int32_t joins[kMaxRounds];  // joins of each round of its refinement
 };
+
+// Sweeps and rounds are launched four at a time and the host reads their counts
+// afterwards; reading after each left the chip idle for 30 us a time, 6 of 16
+// ms (300k vertices).  What is launched past the end does nothing: a sweep
+// after two quiet ones (whose labels stand in both buffers) and a round after
+// one without joins.
+constexpr int kAhead = 4;
+__device__ __forceinline__ bool moving_ended(const LeidenState *st, int sweep) {
+    return sweep >= 2 && st->moved[sweep - 1] == 0 && st->moved[sweep - 2] == 0;
+}
+__device__ __forceinline__ bool refining_ended(const LeidenState *st, int round) {
+    return round >= 1 && st->joins[round - 1] == 0;
+}
 
 __device__ __forceinline__ double gain(int64_t K, double gamma, int64_t k, int64_t T, double two_m) {
     const double t = __dmul_rn(gamma, (double)k);
@@ -194,6 +208,24 @@ struct BlockMins {
             if (key[i] >= 0) atomicMin(&g[key[i]], val[i]);
     }
 };
+
+// Inclusive sums over the wave's lanes, by DPP: within rows of 16 lanes, then
+// each row's total to the rows after it.
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ int64_t dpp64(int64_t x) {
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(uint64_t)x, kCtrl, kRowMask, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)((uint64_t)x >> 32), kCtrl, kRowMask, 0xf, false);
+    return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
+}
+__device__ __forceinline__ int64_t wave_scan64(int64_t x) {
+    x += dpp64<0x111, 0xf>(x);  // row_shr 1, 2, 4, 8
+    x += dpp64<0x112, 0xf>(x);
+    x += dpp64<0x114, 0xf>(x);
+    x += dpp64<0x118, 0xf>(x);
+    x += dpp64<0x142, 0xa>(x);  // row_bcast 15 into rows 1 and 3
+    x += dpp64<0x143, 0xc>(x);  // row_bcast 31 into rows 2 and 3
+    return x;
+}
 
 // Wave-wide best (largest h, then smallest c); c < 0 marks no candidate.
 __device__ __forceinline__ void wave_best(double &h, int32_t &c) {
@@ -335,14 +367,15 @@ __device__ __forceinline__ void row_groups(int64_t b, int64_t e, WaveTable *lt, 
 
 // ---- input checks and fixed point ----------------------------------------
 
+static_assert(kMaxSweeps <= 64 && kMaxRounds <= 64, "cleared by one wave");
 __global__ void k_lv_init(LeidenState *st) {
     if (threadIdx.x == 0) {
         st->error = 0;
         st->wmax_bits = 0;
         st->two_m = 0;
-        st->moved = 0;
-        st->joins = 0;
     }
+    if (threadIdx.x < kMaxSweeps) st->moved[threadIdx.x] = 0;
+    if (threadIdx.x < kMaxRounds) st->joins[threadIdx.x] = 0;
 }
 
 __global__ __launch_bounds__(kBlock) void k_lv_check(const int64_t *__restrict__ ptr,
@@ -439,11 +472,8 @@ __global__ __launch_bounds__(kBlock) void k_lv_tot(const int32_t *__restrict__ l
     sums.flush(tot, tot);
 }
 
-// One sweep of local moving: Lnext[v] from the labels L at the sweep start.
-// A wave takes two consecutive vertices: when both rows have at most 32
-// entries, each half of the wave holds one row (its weights summed per
-// community by lane broadcasts within the half); otherwise the wave takes
-// the two vertices one after the other, a whole wave per row.
+// One sweep of local moving for one long row, by a whole wave: Lnext[v] from
+// the labels L at the sweep start.
 __device__ __forceinline__ void move_one(int64_t v, const int64_t *__restrict__ ptr, const int32_t *__restrict__ col,
                                          const int64_t *__restrict__ gw, const int64_t *__restrict__ kdeg,
                                          const int64_t *__restrict__ tot, const int32_t *__restrict__ L,
@@ -490,71 +520,164 @@ __device__ __forceinline__ void move_one(int64_t v, const int64_t *__restrict__ 
     if (lane == 0) Lnext[v] = next;
 }
 
+// A batch of consecutive rows of one wave, kBatchEntries entries at most.  Row
+// r's entries [o, o + len) own the slots [2 o, 2 (o + len)), an open-addressing
+// table that is never more than half full.
+constexpr int kBatchRows = 16;
+constexpr int kBatchEntries = 256;
+struct BatchTable {
+    int32_t key[2 * kBatchEntries];
+    unsigned long long val[2 * kBatchEntries];
+    unsigned long long best[kBatchRows];  // largest gain, as an integer of the same order
+    int64_t own[kBatchRows];              // K(v, own community)
+    int32_t cand[kBatchRows];             // smallest community of that gain
+};
+union MoveTable {
+    BatchTable batch;
+    WaveTable row;  // a row longer than a batch
+};
+
+__device__ __forceinline__ unsigned long long ordered(double h) {
+    const uint64_t b = (uint64_t)__double_as_longlong(h + 0.0);
+    return b >> 63 ? ~b : b | 0x8000000000000000ull;
+}
+__device__ __forceinline__ double unordered(unsigned long long o) {
+    return __longlong_as_double((long long)(o >> 63 ? o & 0x7fffffffffffffffull : ~o));
+}
+
+// One sweep of local moving: Lnext[v] from the labels L at the sweep start.  A
+// wave takes `rows` consecutive vertices in batches of as many as fit; an
+// entry sits in one lane whatever its row, so that the lanes are full at any
+// row length.  The entries add their weights into their row's table in LDS;
+// the lane that opened a slot computes its community's gain.  Entries of the
+// row's own community, most of them late in a run, go past the table by a
+// prefix sum over the lanes, whose ends of rows are added up: 23 additions to
+// one address would be served one after another.
+//
+// 300k rows of 23 entries: 110 us while most neighbours are communities of
+// their own and 51 us when few are left (82 MB of rows and 27 MB of gathered
+// labels and totals), against 225 and 170 us of half a wave per row that
+// broadcast each entry to the others (14 instructions, 32 times).  The chain of
+// loads bounds it: rows, columns, labels, totals; loading the columns and
+// labels of a batch together took it from 60 to 51 us, and totals loaded for
+// every entry instead of every slot from 105 back to 115 us.
 __global__ __launch_bounds__(kBlock) void k_lv_move(const int64_t *__restrict__ ptr, const int32_t *__restrict__ col,
-                                                    const int64_t *__restrict__ gw, int64_t N,
+                                                    const int64_t *__restrict__ gw, int64_t N, int rows,
                                                     const int64_t *__restrict__ kdeg, const int64_t *__restrict__ tot,
                                                     const int32_t *__restrict__ L, int32_t *__restrict__ Lnext,
-                                                    int up, double gamma, double two_m, int32_t *__restrict__ hk,
-                                                    int64_t *__restrict__ hv) {
-    __shared__ WaveTable tabs[kBlock / kWave];
-    WaveTable *lt = &tabs[threadIdx.x / kWave];
+                                                    int sweep, double gamma, double two_m, int32_t *__restrict__ hk,
+                                                    int64_t *__restrict__ hv, const LeidenState *__restrict__ st) {
+    if (moving_ended(st, sweep)) return;
+    const int up = sweep % 2 == 0;
+    __shared__ MoveTable tabs[kBlock / kWave];
+    MoveTable *mt = &tabs[threadIdx.x / kWave];
+    BatchTable *bt = &mt->batch;
     const int lane = threadIdx.x & (kWave - 1);
-    const int half = lane >> 5, sub = lane & 31;
-    const int64_t waves = (int64_t)gridDim.x * (blockDim.x / kWave);
-    for (int64_t g = (int64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave; 2 * g < N; g += waves) {
-        const int64_t v = 2 * g + half;
-        const bool vok = v < N;
-        const int64_t b = vok ? ptr[v] : 0;
-        const int len = vok ? (int)(ptr[v + 1] - b) : 0;
-        const int len0 = __builtin_amdgcn_readlane(len, 0), len1 = __builtin_amdgcn_readlane(len, 32);
-        if (len0 > 32 || len1 > 32) {
-            move_one(2 * g, ptr, col, gw, kdeg, tot, L, Lnext, up, gamma, two_m, lt, hk, hv);
-            if (2 * g + 1 < N)
-                move_one(2 * g + 1, ptr, col, gw, kdeg, tot, L, Lnext, up, gamma, two_m, lt, hk, hv);
+    const int64_t v0 = ((int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave) * rows;
+    if (v0 >= N) return;
+    const int count = (int)(N - v0 < rows ? N - v0 : rows);
+    const int64_t p = ptr[v0 + (lane < count ? lane : count)];
+    for (int r0 = 0; r0 < count;) {
+        const int64_t b0 = readlane64(p, r0);
+        const int nr = __builtin_popcountll(__ballot(lane > r0 && lane <= count && p - b0 <= kBatchEntries));
+        if (nr == 0) {
+            move_one(v0 + r0, ptr, col, gw, kdeg, tot, L, Lnext, up, gamma, two_m, &mt->row, hk, hv);
+            ++r0;
             continue;
         }
-        const int32_t a = vok ? L[v] : -1;
-        const int64_t kv = vok ? kdeg[v] : 0;
-        int32_t c = -1;
-        int64_t w = 0;
-        if (sub < len) {
-            const int32_t u = col[b + sub];
-            c = u == (int32_t)v ? -1 : L[u];
-            w = gw[b + sub];
+        const int off = (int)(p - b0);  // of row r in lane r0 + r, in [0, kBatchEntries]
+        const int total = __builtin_amdgcn_readlane(off, r0 + nr);
+        const bool mine = lane < nr;
+        const int64_t v = v0 + r0 + (mine ? lane : 0);
+        // a batch's loads go out together: columns and weights, then labels
+        constexpr int kIter = kBatchEntries / kWave;
+        int32_t ec[kIter];
+        int64_t ew[kIter];
+        int slot[kIter], erow[kIter];  // slot: of the lane that opened it, else -1
+#pragma unroll
+        for (int i = 0; i < kIter; ++i) {
+            const int e = i * kWave + lane;
+            ec[i] = e < total ? col[b0 + e] : -1;
+            ew[i] = e < total ? gw[b0 + e] : 0;
         }
-        // K(v, c) of this lane's community within its half's row
-        const int tmax = len0 > len1 ? len0 : len1;
-        int64_t K = 0;
-        for (int t = 0; t < tmax; ++t) {
-            const int32_t c0 = __builtin_amdgcn_readlane(c, t), c1 = __builtin_amdgcn_readlane(c, 32 + t);
-            const int64_t w0 = readlane64(w, t), w1 = readlane64(w, 32 + t);
-            if ((half ? c1 : c0) == c) K += half ? w1 : w0;
+        const int32_t a = L[v];
+        const int64_t kv = kdeg[v];
+        for (int j = lane; j < 2 * total; j += kWave) {
+            bt->key[j] = -1;
+            bt->val[j] = 0ull;
         }
-        double best_h = 0.0;
-        int32_t best_c = -1;
-        const bool valid = c >= 0;
-        const bool is_a = valid && c == a;
-        if (valid && !is_a && !(up ? c < a : c > a)) {
-            best_h = gain(K, gamma, kv, tot[c], two_m);
-            best_c = c;
+        if (mine) {
+            bt->best[lane] = 0ull;
+            bt->own[lane] = 0;
+            bt->cand[lane] = INT_MAX;
         }
-        for (int o = 16; o > 0; o >>= 1) {  // best within the half
-            const double h2 = __shfl_xor(best_h, o, kWave);
-            const int32_t c2 = __shfl_xor(best_c, o, kWave);
-            if (c2 >= 0 && (best_c < 0 || better(h2, c2, best_h, best_c))) {
-                best_h = h2;
-                best_c = c2;
+#pragma unroll
+        for (int i = 0; i < kIter; ++i) {
+            const int e = i * kWave + lane;
+            int row = 0;
+            if (i * kWave < total)
+                for (int r = 1; r < nr; ++r) row += e >= __builtin_amdgcn_readlane(off, r0 + r);
+            erow[i] = row;
+            ec[i] = ec[i] < 0 || ec[i] == (int32_t)(v0 + r0 + row) ? -1 : L[ec[i]];
+        }
+        lds_wave_sync();
+#pragma unroll
+        for (int i = 0; i < kIter; ++i) {
+            const int e = i * kWave + lane;
+            slot[i] = -1;
+            if (i * kWave >= total) continue;
+            const int row = erow[i];
+            const int64_t w = ew[i];
+            const int o0 = __shfl(off, r0 + row, kWave), o1 = __shfl(off, r0 + row + 1, kWave);
+            const int32_t ra = __shfl(a, row, kWave);
+            const bool in_own = ec[i] == ra && ec[i] >= 0;
+            const int64_t sum = wave_scan64(in_own ? w : 0);
+            const int next = __shfl(row, lane + 1, kWave);
+            if (e < total && (e + 1 == o1 || lane == kWave - 1)) {
+                add64(&bt->own[row], sum);
+                if (lane != kWave - 1 && e + 1 < total) add64(&bt->own[next], -sum);
+            }
+            if (ec[i] >= 0 && !in_own) {
+                const uint32_t size = 2 * (uint32_t)(o1 - o0);
+                uint32_t s = __umulhi((uint32_t)ec[i] * 0x9E3779B1u, size);
+                int32_t prev;
+                for (;;) {
+                    prev = atomicCAS(&bt->key[2 * o0 + s], -1, ec[i]);
+                    if (prev == -1 || prev == ec[i]) break;
+                    s = s + 1 == size ? 0 : s + 1;
+                }
+                atomicAdd(&bt->val[2 * o0 + s], (unsigned long long)w);
+                if (prev == -1) slot[i] = 2 * o0 + (int)s;
             }
         }
-        const uint64_t holders = __ballot(is_a);
-        const uint32_t hold0 = (uint32_t)holders, hold1 = (uint32_t)(holders >> 32);
-        const int64_t Ka0 = hold0 ? readlane64(K, __builtin_ctz(hold0)) : 0;
-        const int64_t Ka1 = hold1 ? readlane64(K, 32 + __builtin_ctz(hold1)) : 0;
-        if (vok && sub == 0) {
-            const double stay = gain(half ? Ka1 : Ka0, gamma, kv, tot[a] - kv, two_m);
-            const int32_t next = (best_c >= 0 && best_h > stay) ? best_c : a;
-            Lnext[v] = next;
+        lds_wave_sync();
+        unsigned long long eh[kIter];
+#pragma unroll
+        for (int i = 0; i < kIter; ++i) {
+            eh[i] = 0ull;
+            if (i * kWave >= total) continue;
+            const int32_t ra = __shfl(a, erow[i], kWave);
+            const int64_t rk = __shfl(kv, erow[i], kWave);
+            if (slot[i] >= 0) {
+                const int64_t K = (int64_t)bt->val[slot[i]];
+                if (up ? ec[i] > ra : ec[i] < ra) {
+                    eh[i] = ordered(gain(K, gamma, rk, tot[ec[i]], two_m));
+                    atomicMax(&bt->best[erow[i]], eh[i]);
+                }
+            }
         }
+        lds_wave_sync();
+#pragma unroll
+        for (int i = 0; i < kIter; ++i)
+            if (eh[i] && eh[i] == bt->best[erow[i]]) atomicMin(&bt->cand[erow[i]], ec[i]);
+        lds_wave_sync();
+        if (mine) {
+            const int32_t c = bt->cand[lane];
+            const double stay = gain(bt->own[lane], gamma, kv, tot[a] - kv, two_m);
+            Lnext[v] = c != INT_MAX && unordered(bt->best[lane]) > stay ? c : a;
+        }
+        lds_wave_sync();
+        r0 += nr;
     }
 }
 
@@ -565,7 +688,9 @@ __global__ __launch_bounds__(kBlock) void k_lv_move(const int64_t *__restrict__ 
 __global__ __launch_bounds__(kBlock) void k_lv_tot_delta(const int32_t *__restrict__ L,
                                                          const int32_t *__restrict__ Lnext,
                                                          const int64_t *__restrict__ kdeg, int64_t N,
-                                                         int64_t *__restrict__ tot, LeidenState *__restrict__ st) {
+                                                         int64_t *__restrict__ tot, int sweep,
+                                                         LeidenState *__restrict__ st) {
+    if (moving_ended(st, sweep)) return;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     int64_t moved = 0;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < N; v += stride) {
@@ -579,7 +704,7 @@ __global__ __launch_bounds__(kBlock) void k_lv_tot_delta(const int32_t *__restri
         }
     }
     moved = block_sum64(moved);
-    if (threadIdx.x == 0 && moved) atomicAdd(&st->moved, (int32_t)moved);
+    if (threadIdx.x == 0 && moved) atomicAdd(&st->moved[sweep], (int32_t)moved);
 }
 
 // Refinement set-up: kin[v] = K(v, C - v).  (The sum of k over each community
@@ -608,7 +733,9 @@ __global__ __launch_bounds__(kBlock) void k_lv_refine_stats(const int64_t *__res
                                                             const int64_t *__restrict__ gw, int64_t N,
                                                             const int32_t *__restrict__ L,
                                                             const int32_t *__restrict__ R,
-                                                            int64_t *__restrict__ extR) {
+                                                            int64_t *__restrict__ extR, int round,
+                                                            const LeidenState *__restrict__ st) {
+    if (refining_ended(st, round)) return;
     const int sub = threadIdx.x & (kRowLanes - 1);
     const int64_t rows = (int64_t)gridDim.x * (kBlock / kRowLanes);
     for (int64_t v = (int64_t)blockIdx.x * (kBlock / kRowLanes) + threadIdx.x / kRowLanes; v < N; v += rows) {
@@ -629,7 +756,9 @@ __global__ __launch_bounds__(kBlock) void k_lv_refine_propose(
     const int64_t *__restrict__ kdeg, const int32_t *__restrict__ L, const int32_t *__restrict__ R,
     const int64_t *__restrict__ kin, const int64_t *__restrict__ totC, const int64_t *__restrict__ totR,
     const int32_t *__restrict__ size, const int64_t *__restrict__ extR, double gamma, double two_m,
-    int32_t *__restrict__ prop, int32_t *__restrict__ hk, int64_t *__restrict__ hv) {
+    int32_t *__restrict__ prop, int32_t *__restrict__ hk, int64_t *__restrict__ hv, int round,
+    const LeidenState *__restrict__ st) {
+    if (refining_ended(st, round)) return;
     __shared__ WaveTable tabs[kBlock / kWave];
     WaveTable *lt = &tabs[threadIdx.x / kWave];
     const int lane = threadIdx.x & (kWave - 1);
@@ -679,7 +808,9 @@ __global__ __launch_bounds__(kBlock) void k_lv_refine_propose(
 __global__ __launch_bounds__(kBlock) void k_lv_refine_apply(const int32_t *__restrict__ prop,
                                                             const int64_t *__restrict__ kdeg, int64_t N,
                                                             int32_t *__restrict__ R, int64_t *__restrict__ totR,
-                                                            int32_t *__restrict__ size, LeidenState *__restrict__ st) {
+                                                            int32_t *__restrict__ size, int round,
+                                                           LeidenState *__restrict__ st) {
+    if (refining_ended(st, round)) return;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     int64_t joins = 0;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < N; v += stride) {
@@ -693,7 +824,7 @@ __global__ __launch_bounds__(kBlock) void k_lv_refine_apply(const int32_t *__res
         ++joins;
     }
     joins = block_sum64(joins);
-    if (threadIdx.x == 0 && joins) atomicAdd(&st->joins, (int32_t)joins);
+    if (threadIdx.x == 0 && joins) atomicAdd(&st->joins[round], (int32_t)joins);
 }
 
 // The refinement starts from singletons.
@@ -1032,29 +1163,33 @@ int leiden_run(const int64_t *indptr, const int32_t *indices, const float *weigh
         if (lv == 0) two_m0 = (double)(int64_t)hs.two_m;
         if (hs.two_m == 0) break;
         const double two_m = (double)(int64_t)hs.two_m;
-        // 1. local moving
+        // 1. local moving.  Rows per wave: a batch's worth, but 8192 waves first
+        // (32 per CU, all that it holds)
+        const int rows = (int)std::max<int64_t>(1, std::min<int64_t>(kBatchRows, N / 8192));
         int64_t moves = 0;
-        int quiet = 0;
         // community totals of the level's starting labels; each sweep then
         // moves them along with the vertices that change label
         hipLaunchKernelGGL(k_lv_fill64, dim3(grid_items(N)), dim3(kBlock), 0, s, w.tot, N, (int64_t)0);
         hipLaunchKernelGGL(k_lv_tot, dim3(grid_few(N)), dim3(kBlock), 0, s, w.L, w.kdeg, N, w.tot);
-        for (int sweep = 1; sweep <= kMaxSweeps && quiet < 2; ++sweep) {
-            {
+        for (int sweep = 0, quiet = 0; sweep < kMaxSweeps && quiet < 2;) {
+            const int from = sweep, to = std::min(sweep + kAhead, kMaxSweeps);
+            for (; sweep < to; ++sweep) {
                 ScopedTimer t("leiden_move", s);
-                hipLaunchKernelGGL(k_lv_init, dim3(1), dim3(64), 0, s, w.st);
-                hipLaunchKernelGGL(k_lv_move, dim3(grid_waves((N + 1) / 2)), dim3(kBlock), 0, s, G.ptr, G.col, G.w, N, w.kdeg,
-                                   w.tot, w.L, w.Lnext, sweep % 2, gamma, two_m, w.hk, w.hv);
+                hipLaunchKernelGGL(k_lv_move, dim3((unsigned)((N + 4 * rows - 1) / (4 * rows))), dim3(kBlock), 0, s,
+                                   G.ptr, G.col, G.w, N, rows, w.kdeg, w.tot, w.L, w.Lnext, sweep, gamma, two_m, w.hk,
+                                   w.hv, w.st);
                 hipLaunchKernelGGL(k_lv_tot_delta, dim3(grid_few(N)), dim3(kBlock), 0, s, w.L, w.Lnext, w.kdeg, N,
-                                   w.tot, w.st);
+                                   w.tot, sweep, w.st);
+                std::swap(w.L, w.Lnext);
             }
             if ((st = launch_status("leiden local moving")) != RSC_OK) return st;
-            ++sweeps;
-            move_bytes += 16 * M + 24 * N;
-            std::swap(w.L, w.Lnext);
             if ((st = read_back(&hs, w.st, s, "read moves")) != RSC_OK) return st;
-            moves += hs.moved;
-            quiet = hs.moved ? 0 : quiet + 1;
+            for (int i = from; i < to && quiet < 2; ++i) {
+                ++sweeps;
+                move_bytes += 16 * M + 24 * N;
+                moves += hs.moved[i];
+                quiet = hs.moved[i] ? 0 : quiet + 1;
+            }
         }
         ++lv;
         if (moves == 0 || lv >= kMaxLevels) break;
@@ -1064,20 +1199,24 @@ int leiden_run(const int64_t *indptr, const int32_t *indices, const float *weigh
         hipLaunchKernelGGL(k_lv_refine_init, dim3(grid_items(N)), dim3(kBlock), 0, s, w.kdeg, N, w.R, w.totR, w.size);
         hipLaunchKernelGGL(k_lv_refine_prep, dim3(grid_rows(N)), dim3(kBlock), 0, s, G.ptr, G.col, G.w, N, w.L, w.kin);
         if ((st = launch_status("leiden refinement set-up")) != RSC_OK) return st;
-        for (int round = 1; round <= kMaxRounds; ++round) {
-            hipLaunchKernelGGL(k_lv_fill64, dim3(grid_items(N)), dim3(kBlock), 0, s, w.extR, N, (int64_t)0);
-            hipLaunchKernelGGL(k_lv_refine_stats, dim3(grid_rows(N)), dim3(kBlock), 0, s, G.ptr, G.col, G.w, N, w.L,
-                               w.R, w.extR);
-            hipLaunchKernelGGL(k_lv_refine_propose, dim3(grid_waves(N)), dim3(kBlock), 0, s, G.ptr, G.col, G.w, N,
-                               w.kdeg, w.L, w.R, w.kin, w.tot, w.totR, w.size, w.extR, gamma, two_m, w.prop, w.hk,
-                               w.hv);
-            hipLaunchKernelGGL(k_lv_init, dim3(1), dim3(64), 0, s, w.st);
-            hipLaunchKernelGGL(k_lv_refine_apply, dim3(grid_few(N)), dim3(kBlock), 0, s, w.prop, w.kdeg, N, w.R,
-                               w.totR, w.size, w.st);
+        for (int round = 0, ended = 0; round < kMaxRounds && !ended;) {
+            const int from = round, to = std::min(round + kAhead, kMaxRounds);
+            for (; round < to; ++round) {
+                hipLaunchKernelGGL(k_lv_fill64, dim3(grid_items(N)), dim3(kBlock), 0, s, w.extR, N, (int64_t)0);
+                hipLaunchKernelGGL(k_lv_refine_stats, dim3(grid_rows(N)), dim3(kBlock), 0, s, G.ptr, G.col, G.w, N,
+                                   w.L, w.R, w.extR, round, w.st);
+                hipLaunchKernelGGL(k_lv_refine_propose, dim3(grid_waves(N)), dim3(kBlock), 0, s, G.ptr, G.col, G.w, N,
+                                   w.kdeg, w.L, w.R, w.kin, w.tot, w.totR, w.size, w.extR, gamma, two_m, w.prop, w.hk,
+                                   w.hv, round, w.st);
+                hipLaunchKernelGGL(k_lv_refine_apply, dim3(grid_few(N)), dim3(kBlock), 0, s, w.prop, w.kdeg, N, w.R,
+                                   w.totR, w.size, round, w.st);
+            }
             if ((st = launch_status("leiden refinement")) != RSC_OK) return st;
-            ++rounds;
             if ((st = read_back(&hs, w.st, s, "read joins")) != RSC_OK) return st;
-            if (!hs.joins) break;
+            for (int i = from; i < to && !ended; ++i) {
+                ++rounds;
+                ended = hs.joins[i] == 0;
+            }
         }
         }
         // 3. aggregation

@@ -3,7 +3,9 @@
 Each graph is a set of disjoint cliques, so the number of communities is known:
 one, as many as the block's table has slots, one more, and far more (where most
 sums go to memory directly); the clique sizes reach rows on both sides of the
-lanes that share a row.  Labels and modularity equal the oracle's.
+lanes that share a row, of the entries that a wave takes at once (256) and of the
+rows that it takes.  Vertices without edges lie between them.  Labels and
+modularity equal the oracle's.
 """
 
 import numpy as np
@@ -15,12 +17,13 @@ import paper_2603_02402_amd as rsc
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("count,size", [(1, 40), (2, 17), (127, 5), (128, 16), (129, 9), (700, 3), (3000, 2), (40, 70)])
+@pytest.mark.parametrize("count,size", [(1, 40), (2, 17), (127, 5), (128, 16), (129, 9), (700, 3), (3000, 2), (40, 70),
+                                        (5, 256), (3, 257), (2, 258), (300, 17)])
 def test_cliques_match_the_oracle(count, size):
     from oracle import leiden as ol
 
     rng = np.random.default_rng(count)
-    n = count * size
+    n = count * size + count // 2
     place = rng.permutation(n)  # a clique's vertices lie anywhere in the order
     w = rng.uniform(0.5, 1.0, (count, size, size)).astype(np.float32)
     w = np.maximum(w, w.transpose(0, 2, 1))
