@@ -59,7 +59,12 @@ constexpr int kMaxKLowp = 63;
 // ordering them and bounding the segments costs 0.15 ms at 16k rows and 0.9 ms
 // at 1M.  Screen, rerank and order at 16384 rows (20 clusters): 0.41 ms pruned,
 // 0.46 without (in a Morton order); at 10k rows 0.39 against 0.21; rectangular:
-// the pairs of that square.
+// the pairs of that square.  The BF16 form's rows (64 candidates a query) take
+// the same path from there: 16.5k rows 1.40 -> 0.72 ms, 40k 2.25 -> 1.02, 500k
+// 44.4 -> 14.6 (100 clusters, with their graph).  Rows without any clusters
+// gain nothing from bounds and pay for the merge of longer lists by two waves
+// per SIMD where the plain BF16 screen has three: 300k rows 30 -> 33 ms, at
+// d = 100 25 -> 38 (200k).
 constexpr int64_t kPruneRows = 16384;
 constexpr double kPrunePairs = 2.5e8;
 // Workgroups the split screen asks for before it stops splitting the
@@ -1178,15 +1183,17 @@ int knn_plan(int64_t nq, int64_t nr, int d, int k, const rsc_knn_opts *opts, boo
     plan->precision = precision;
     plan->metric = metric;
     plan->resid = resid;
-    plan->pruned = precision == RSC_FP32 && nr >= kPruneRows && (double)nq * (double)nr >= kPrunePairs;
+    plan->pruned = (precision == RSC_FP32 || (precision == RSC_BF16 && lowp_ranges == 1)) && nr >= kPruneRows &&
+                   (double)nq * (double)nr >= kPrunePairs;
+    const bool split = precision == RSC_FP32 || plan->pruned;
     // the split screen's workgroups of 8 waves fill a CU each; the others run four of 4 waves
-    plan->splits = precision == RSC_FP32
+    plan->splits = split
                        ? pick_splits(nq, plan->nblk, split_queries_per_group(d, plan->half),
                                      plan->pruned ? kCUs : kSplitWant)
                        : pick_splits(nq, plan->nblk, lowp_queries_per_group(precision, d), 1024);
     // (two ranges even out tiles of different cost while each CU gets about one)
     if (plan->pruned && nq < 512 * split_queries_per_group(d, plan->half)) plan->splits = std::max(plan->splits, 2);
-    if (precision == RSC_FP32) {
+    if (split) {
         // enough (range, half) lists that the m nearest fill each to about half
         const int m = self_mode ? k - 1 : k;
         plan->splits = std::min(32, std::max(plan->splits, (m + plan->half - 1) / plan->half));
@@ -1199,9 +1206,9 @@ int knn_plan(int64_t nq, int64_t nr, int d, int k, const rsc_knn_opts *opts, boo
 size_t knn_workspace(const KnnPlan &p, void *ws, KnnBuffers *out) {
     Carver cv(ws);
     KnnBuffers b{};
-    const bool fp32 = p.precision == RSC_FP32;
+    const bool fp32 = p.precision == RSC_FP32 || p.pruned;  // (the BF16 form's large problems share the path)
     const int s4 = packed_s4(p.dh);
-    const int64_t esc_rows = fp32 ? std::min<int64_t>(p.nq, kEscalateCap) : 0;
+    const int64_t esc_rows = p.precision == RSC_FP32 ? std::min<int64_t>(p.nq, kEscalateCap) : 0;
     b.counters = cv.take<KnnCounters>(1);
     if (fp32) {
         b.nrow = cv.take<float>((size_t)p.nr);
@@ -1223,11 +1230,11 @@ size_t knn_workspace(const KnnPlan &p, void *ws, KnnBuffers *out) {
     b.esc_key = cv.take<float>((size_t)std::max<int64_t>(esc_rows, 1) * kEscalateSplits * kEscalateWidth);
     b.esc_bound = cv.take<double>((size_t)std::max<int64_t>(esc_rows, 1));
     b.esc_found = cv.take<int32_t>((size_t)std::max<int64_t>(esc_rows, 1));
-    if (p.metric == RSC_COSINE) {
+    if (p.metric == RSC_COSINE || (p.precision == RSC_BF16 && p.pruned)) {  // the rows as the screen sees them
         b.rn = cv.take<float>((size_t)p.nr * p.d);
         b.qn = p.self_mode ? b.rn : cv.take<float>((size_t)std::max<int64_t>(p.nq, 1) * p.d);
     }
-    if (fp32 && p.pruned) {
+    if (p.pruned) {
         b.qcount = cv.take<int32_t>(1);
         const size_t need = spatial_carve(p.nq, p.nr, p.d, false, nullptr, nullptr);
         char *base = cv.take<char>(need);
@@ -1264,6 +1271,24 @@ int normalize_inputs(const KnnPlan &p, const float *Q, const float *R, const Knn
         hipLaunchKernelGGL(k_normalize, dim3((unsigned)((p.nq + norm_rows(p.d) - 1) / norm_rows(p.d))), dim3(kNormThreads), 0,
                            stream, Q, p.nq, p.d, b.qn);
     return launch_status("normalize");
+}
+
+__global__ __launch_bounds__(256) void k_round_bf16(const float *__restrict__ X, int64_t n, float *__restrict__ out) {
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
+        out[i] = (float)(__bf16)X[i];
+}
+
+// The BF16 form on the pruned screen: its inputs are the rows rounded to BF16.
+int round_inputs(const KnnPlan &p, const float *Q, const float *R, const KnnBuffers &b, hipStream_t stream) {
+    ScopedTimer timer("prep_lowp", stream);
+    auto run = [&](const float *x, int64_t n, float *out) {
+        const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 8192));
+        hipLaunchKernelGGL(k_round_bf16, dim3(grid), dim3(256), 0, stream, x, n, out);
+    };
+    run(R, p.nr * p.d, b.rn);
+    if (!p.self_mode && p.nq > 0) run(Q, p.nq * p.d, b.qn);
+    return launch_status("round to BF16");
 }
 
 // Reduced-precision form: screen, then rerank without a certificate.
@@ -1361,20 +1386,22 @@ int knn_run(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, 
             set_error("internal: row lists need the FP32 path");
             return RSC_ERR_UNSUPPORTED;
         }
-        return knn_run_lowp(p, Q, R, out_idx, out_dist, b, stream);
+        if (!p.pruned) return knn_run_lowp(p, Q, R, out_idx, out_dist, b, stream);
     }
     int st;
     const bool cosine = p.metric == RSC_COSINE;
+    const bool rounded = p.precision == RSC_BF16;
     if (cosine && (st = normalize_inputs(p, Q, R, b, stream)) != RSC_OK) return st;
-    const float *Qs = cosine ? b.qn : Q;  // what the screen sees
-    const float *Rs = cosine ? b.rn : R;
+    if (rounded && (st = round_inputs(p, cosine ? b.qn : Q, cosine ? b.rn : R, b, stream)) != RSC_OK) return st;
+    const float *Qs = cosine || rounded ? b.qn : Q;  // what the screen sees
+    const float *Rs = cosine || rounded ? b.rn : R;
     if ((st = knn_prep_fp32(p, Rs, p.self_mode ? nullptr : Qs, b, nullptr, nullptr, nullptr, stream)) != RSC_OK)
         return st;
     // Large problems are screened in a spatial order with its segments' bounds.
     const bool pruned = p.pruned && !qlist && p.nq > 0;
     const int32_t *ref_map = nullptr;
     if (pruned) {
-        if ((st = spatial_refs(Rs, b.nrow, p.nr, p.d, b.sp, b.counters, stream)) != RSC_OK) return st;
+        if ((st = spatial_refs(Rs, b.nrow, p.nr, p.d, rounded, b.sp, b.counters, stream)) != RSC_OK) return st;
         if (!p.self_mode && (st = spatial_queries(Qs, p.nq, p.nr, p.d, split_queries_per_group(p.d, p.half), b.sp,
                                                   b.counters, stream)) != RSC_OK)
             return st;
@@ -1386,7 +1413,7 @@ int knn_run(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, 
     {
         ScopedTimer timer("pack_split", stream);
         if ((st = split_pack(Rs, b.nrow, p.nr, p.d, p.nblk, b.split, nullptr, nullptr, nullptr, ref_map, p.nr,
-                             b.counters, stream)) != RSC_OK)
+                             b.counters, stream, rounded)) != RSC_OK)
             return st;
     }
     if (p.nq == 0) return RSC_OK;
@@ -1420,7 +1447,8 @@ int knn_run(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, 
         pa.own = p.self_mode ? nullptr : b.sp.own;
         pa.eps = split_eps_coefficient(p.d);
         pa.visited = &b.counters->visited;
-        st = split_screen_pruned(pa, p.half, "screen_fp32", stream);
+        pa.rounded = rounded;
+        st = split_screen_pruned(pa, p.half, rounded ? "screen_bf16" : "screen_fp32", stream);
     } else {
         st = split_screen(ss, p.half, "screen_fp32", stream);
     }
@@ -1443,7 +1471,7 @@ int knn_run(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, 
     ra.KP = p.half;
     ra.P = 2 * p.splits;
     ra.self_mode = p.self_mode ? 1 : 0;
-    ra.certify = 1;
+    ra.certify = rounded ? 0 : 1;  // (keys of rounded rows bound nothing)
     ra.metric = p.metric;
     ra.cosine_eps = cosine_eps_of(eps_coef);
     ra.cand_idx = b.cand_idx;
@@ -1454,6 +1482,7 @@ int knn_run(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, 
     ra.flag_count = &b.counters->flagged;
     ra.out_idx = out_idx;
     ra.out_dist = out_dist;
+    if (rounded) return knn_launch_rerank(ra, p.nq, "rerank", stream);
     knn_split_bounds(ra);
     const int esc_cap = (int)std::min<int64_t>(p.nq, kEscalateCap);
     const bool collect = (p.self_mode ? p.k - 1 : p.k) <= kLeanAnswer;

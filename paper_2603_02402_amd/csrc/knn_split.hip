@@ -23,8 +23,8 @@ using namespace scr;
 // norm.  One workgroup per block: the rows come in coalesced through LDS and
 // leave as 16-byte stores.  Marks inputs whose norms spread too far (`wide`).
 __global__ __launch_bounds__(256) void k_pack_split(const float *__restrict__ R, const float *__restrict__ nrow,
-                                                    int64_t nr, int d, int Q, int TC, int64_t nblk,
-                                                    f16x8 *__restrict__ Ap, const int32_t *__restrict__ blk_sample,
+                                                    int64_t nr, int d, int Q, int TC, bool one,
+                                                    int64_t nblk, f16x8 *__restrict__ Ap, const int32_t *__restrict__ blk_sample,
                                                     const int64_t *__restrict__ boff,
                                                     const int64_t *__restrict__ soff,
                                                     const int32_t *__restrict__ row_map, int64_t nmap,
@@ -82,12 +82,12 @@ __global__ __launch_bounds__(256) void k_pack_split(const float *__restrict__ R,
                     if (k < 3) {
                         v[e] = row >= 0 ? (k == 0 ? p1 : k == 1 ? p2 : p3) : (_Float16)(k == 0 ? INFINITY : 0.f);
                     } else {
-                        const int t = 16 * Q + (k - 3) / 3;
-                        const float y = t < d ? x[t] : 0.f;
+                        const TailSlot at(k, Q, one);
+                        const float y = at.t < d ? x[at.t] : 0.f;
                         wide |= below && y != 0.f;
                         _Float16 hi, lo;
                         split16(y * scale, hi, lo);
-                        v[e] = (k - 3) % 3 == 2 ? lo : hi;
+                        v[e] = at.part == 2 ? lo : hi;
                     }
                 }
             } else {
@@ -232,11 +232,11 @@ int split_queries_per_group(int d, int half_width) {
 
 int split_pack(const float *R, const float *nrow, int64_t nr, int d, int64_t nblk, void *packed,
                const int32_t *blk_sample, const int64_t *boff, const int64_t *soff, const int32_t *row_map,
-               int64_t nmap, KnnCounters *counters, hipStream_t stream) {
-    const SplitGeom g = split_geom(d);
+               int64_t nmap, KnnCounters *counters, hipStream_t stream, bool rounded) {
+    const SplitGeom g = rounded ? rounded_geom(d) : split_geom(d);
     const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(nblk, 1 << 20));
     hipLaunchKernelGGL(k_pack_split, dim3(grid), dim3(256), 32 * (size_t)(d | 1) * sizeof(float), stream, R, nrow, nr,
-                       d, g.q, g.tc, nblk, static_cast<f16x8 *>(packed), blk_sample, boff, soff, row_map,
+                       d, g.q, g.tc, rounded, nblk, static_cast<f16x8 *>(packed), blk_sample, boff, soff, row_map,
                        nmap, counters);
     return launch_status("pack_split");
 }
@@ -248,6 +248,7 @@ int split_screen(const scr::ScreenArgs &a, int half_width, const char *name, hip
 }
 
 int split_screen_pruned(const PrunedArgs &a, int half_width, const char *name, hipStream_t s) {
+    if (a.rounded) return scr::rounded_launch(a, name, s);
     return half_width == 16 ? scr::pruned_launch<16>(a, name, s) : scr::pruned_launch<32>(a, name, s);
 }
 

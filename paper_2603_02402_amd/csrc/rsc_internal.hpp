@@ -114,8 +114,9 @@ struct SpatialBuffers {
 int spatial_seg_blocks(int64_t nblk);
 size_t spatial_carve(int64_t nq, int64_t nr, int d, bool square, void *base, SpatialBuffers *out);
 // Orders the references (norms and their maximum known) and bounds the segments.
-int spatial_refs(const float *R, const float *nrow, int64_t nr, int d, const SpatialBuffers &b, KnnCounters *kc,
-                 hipStream_t s);
+// rounded: BF16 rows, whose segments are packed as one FP16 part.
+int spatial_refs(const float *R, const float *nrow, int64_t nr, int d, bool rounded, const SpatialBuffers &b,
+                 KnnCounters *kc, hipStream_t s);
 // Orders the queries of a rectangular problem and places their tiles of qg.
 int spatial_queries(const float *Q, int64_t nq, int64_t nr, int d, int qg, const SpatialBuffers &b, KnnCounters *kc,
                     hipStream_t s);
@@ -228,7 +229,7 @@ int split_queries_per_group(int d, int half_width);
 // and marks inputs whose norms spread too far; needs the norms of R.
 int split_pack(const float *R, const float *nrow, int64_t nr, int d, int64_t nblk, void *packed,
                const int32_t *blk_sample, const int64_t *boff, const int64_t *soff, const int32_t *row_map,
-               int64_t nmap, KnnCounters *counters, hipStream_t stream);
+               int64_t nmap, KnnCounters *counters, hipStream_t stream, bool rounded = false);
 int split_screen(const scr::ScreenArgs &a, int half_width, const char *name, hipStream_t s);
 // All references within a bound of each listed row (knn_split.hip).
 struct CollectArgs {

@@ -29,6 +29,10 @@
 // 3.3-5.1 to 2.2-3.2.  (The pruned form of the screen skips most blocks where
 // the data has clusters: screen_split_grid.hpp.)
 //
+// Rounded rows.  The BF16 form sees rows rounded to BF16, whose 8 bits one FP16
+// part holds: its chain is the tail alone, the norm's slots and then one slot
+// per dimension (ONE below; d = 50: 4 MFMAs).
+//
 // Range.  Rows whose norm lies below 2^-16 M would lose bits to the FP16
 // exponent; prep marks such inputs (KnnCounters::wide) and they take the FP32
 // chain of screen_fp32.hpp instead.
@@ -96,6 +100,19 @@ int split_dispatch(const SplitGeom &g, F f) {
     return RSC_ERR_UNSUPPORTED;
 }
 
+// The rounded rows' geometry: three norm slots, one per dimension, and the last
+// one free for a segment's radius.
+inline SplitGeom rounded_geom(int d) { return {0, (d + 4 + 15) / 16}; }
+#define RSC_ROUNDED_CHUNKS(X) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9)
+
+// Dimension of tail slot k >= 3 and which part of it the slot holds (2: the
+// reference's low part, 1: the query's).
+struct TailSlot {
+    int t, part;
+    __device__ __forceinline__ TailSlot(int k, int Q, bool one)
+        : t(one ? k - 3 : 16 * Q + (k - 3) / 3), part(one ? 0 : (k - 3) % 3) {}
+};
+
 // The two FP16 parts of a scaled float32 value.
 __device__ __forceinline__ void split16(float v, _Float16 &hi, _Float16 &lo) {
     hi = (_Float16)v;
@@ -104,7 +121,7 @@ __device__ __forceinline__ void split16(float v, _Float16 &hi, _Float16 &lo) {
 
 // Query operand of one lane (query c = lane % 32, contraction half h): slot
 // 16 s + 8 h + e of chunk s, for -2 a x.
-template <int Q, int TC>
+template <int Q, int TC, bool ONE = false>
 struct SplitQuery {
     f16x8 hi[Q > 0 ? Q : 1], lo[Q > 0 ? Q : 1], tail[TC];
 
@@ -131,10 +148,10 @@ struct SplitQuery {
                 if (k < 3) {
                     if (row >= 0) v = (_Float16)(k == 0 ? 32768.f : k == 1 ? 16.f : 1.f);
                 } else {
-                    const int t = 16 * Q + (k - 3) / 3;
+                    const TailSlot at(k, Q, ONE);
                     _Float16 a, b;
-                    split16(t < d ? m * x[t] : 0.f, a, b);
-                    v = (k - 3) % 3 == 1 ? b : a;
+                    split16(at.t < d ? m * x[at.t] : 0.f, a, b);
+                    v = at.part == 1 ? b : a;
                 }
                 tail[s][e] = v;
             }
@@ -148,8 +165,8 @@ struct SplitQuery {
 // that the partial sums stay near the key's size: only 2 (TC + Q) of the
 // chain's roundings are at full size.  A: the block's operand chunks --
 // tail, high parts, low parts.
-template <int Q, int TC>
-__device__ __forceinline__ f32x16 split_keys(const f16x8 (&A)[2 * Q + TC], const SplitQuery<Q, TC> &b) {
+template <int Q, int TC, bool ONE>
+__device__ __forceinline__ f32x16 split_keys(const f16x8 (&A)[2 * Q + TC], const SplitQuery<Q, TC, ONE> &b) {
     f32x16 acc = f32x16{};
 #pragma unroll
     for (int s = 0; s < Q; ++s) {
@@ -270,7 +287,7 @@ __device__ __forceinline__ void screen_split_tile(const ScreenArgs &a, int64_t s
             return b0 + j;
         },
         ring0, ring1, [&](const f16x8(&A)[2 * Q + TC], int blk) {
-            top.offer(split_keys<Q, TC>(A, qop), (int)(ref_base + (int64_t)blk * 32) + 4 * h, q, qs);
+            top.offer(split_keys(A, qop), (int)(ref_base + (int64_t)blk * 32) + 4 * h, q, qs);
         });
     top.flush(q, qs);
     if (slot >= 0) top.store(a, slot, p, h, a.ref_map);

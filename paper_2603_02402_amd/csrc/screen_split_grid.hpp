@@ -12,6 +12,7 @@ struct PrunedArgs {
     int nseg, seg_shift;     // segments, log2 of the blocks per segment
     const int32_t *own;
     double eps;              // error coefficient of a split key
+    bool rounded;            // BF16 rows: one FP16 part each (lists of 32)
     unsigned long long *visited;  // statistics: segments screened, over all tiles
 };
 
@@ -74,7 +75,9 @@ int split_launch_geom(const ScreenArgs &a, const char *name, hipStream_t s) {
 // more passes over those cost less), it screens every query's nearest segment
 // first and bounds again (1M rows: 42.6 -> 32.3 ms).
 // With P ranges, range p holds the segments p, p + P, ..
-template <int Q, int TC, int L>
+// ONE: the BF16 form's rounded rows, a chain of one product per dimension (500k
+// rows, d = 50: screen 40 -> 9 ms).
+template <int Q, int TC, int L, bool ONE>
 __global__ __launch_bounds__((SplitShape<Q, TC, L>::NW * kWave), (SplitShape<Q, TC, L>::W)) void k_split_pruned(
     PrunedArgs pa) {
     using S = SplitShape<Q, TC, L>;
@@ -99,7 +102,7 @@ __global__ __launch_bounds__((SplitShape<Q, TC, L>::NW * kWave), (SplitShape<Q, 
     const int64_t row = slot < nslots ? (a.qlist ? (int64_t)a.qlist[slot] : slot) : -1;
     const float scale = ldexpf(1.f, split_exponent(a.kc));
 
-    SplitQuery<Q, TC> qop;
+    SplitQuery<Q, TC, ONE> qop;
     qop.load(a.Q, a.d, row, h, scale);
     PackTopK<L, S::QCAP> top;
     top.init();
@@ -136,7 +139,7 @@ __global__ __launch_bounds__((SplitShape<Q, TC, L>::NW * kWave), (SplitShape<Q, 
             static_cast<const char *>(a.Ap), total << sh,
             [&](int i) { return ((int)list[i >> sh] << sh) + (i & ((1 << sh) - 1)); }, ring0, ring1,
             [&](const f16x8(&A)[2 * Q + TC], int blk) {
-                if (blk < nblk) top.offer(split_keys<Q, TC>(A, qop), blk * 32 + 4 * h, q, qs);
+                if (blk < nblk) top.offer(split_keys(A, qop), blk * 32 + 4 * h, q, qs);
             });
         top.flush(q, qs);
         visited += total;
@@ -163,7 +166,7 @@ __global__ __launch_bounds__((SplitShape<Q, TC, L>::NW * kWave), (SplitShape<Q, 
             split_stream<Q, TC, S::PHP>(
                 static_cast<const char *>(pa.segments), nw, [](int i) { return i; }, ring0, ring1,
                 [&](const f16x8(&A)[2 * Q + TC], int blk) {
-                    const f32x16 acc = split_keys<Q, TC>(A, qop);
+                    const f32x16 acc = split_keys(A, qop);
                     if (nearest) {
 #pragma unroll
                         for (int v = 0; v < 16; ++v)
@@ -216,12 +219,12 @@ __global__ __launch_bounds__((SplitShape<Q, TC, L>::NW * kWave), (SplitShape<Q, 
     if (tid == 0) atomicAdd(pa.visited, (unsigned long long)visited);
 }
 
-template <int Q, int TC, int L>
+template <int Q, int TC, int L, bool ONE = false>
 int pruned_launch_geom(const PrunedArgs &a, const char *name, hipStream_t s) {
     using S = SplitShape<Q, TC, L>;
     ScopedTimer timer(name, s);
     const unsigned gx = (unsigned)((a.s.nq + S::QG - 1) / S::QG);
-    hipLaunchKernelGGL((k_split_pruned<Q, TC, L>), dim3(gx, (unsigned)a.s.P), dim3(S::NW * kWave), 0, s, a);
+    hipLaunchKernelGGL((k_split_pruned<Q, TC, L, ONE>), dim3(gx, (unsigned)a.s.P), dim3(S::NW * kWave), 0, s, a);
     return launch_status(name);
 }
 
@@ -232,6 +235,9 @@ int pruned_launch(const PrunedArgs &a, const char *name, hipStream_t s) {
 }
 extern template int pruned_launch<16>(const PrunedArgs &, const char *, hipStream_t);
 extern template int pruned_launch<32>(const PrunedArgs &, const char *, hipStream_t);
+
+// The BF16 form's rows, in lists of 32.
+int rounded_launch(const PrunedArgs &a, const char *name, hipStream_t s);
 
 // One launch with lists of L keys per contraction half.
 template <int L>

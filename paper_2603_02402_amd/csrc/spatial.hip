@@ -180,8 +180,8 @@ __global__ __launch_bounds__((SplitShape<Q, TC, 16>::NW * kWave), (SplitShape<Q,
 // Centre and radius of every segment: rows perm[32 seg_blocks s ..].
 __global__ __launch_bounds__(256) void k_segments(const float *__restrict__ X, int64_t n, int d,
                                                   const int32_t *__restrict__ perm, int rows,
-                                                  const KnnCounters *__restrict__ kc, float *__restrict__ centre,
-                                                  float *__restrict__ radius) {
+                                                  const KnnCounters *__restrict__ kc, bool one,
+                                                  float *__restrict__ centre, float *__restrict__ radius) {
     __shared__ float part[4][256];
     __shared__ float c[256];
     __shared__ float far[4];
@@ -195,7 +195,9 @@ __global__ __launch_bounds__(256) void k_segments(const float *__restrict__ X, i
     }
     __syncthreads();
     for (int t = threadIdx.x; t < d; t += 256) {
-        const float v = (part[0][t] + part[1][t] + part[2][t] + part[3][t]) / (float)m;
+        float v = (part[0][t] + part[1][t] + part[2][t] + part[3][t]) / (float)m;
+        // any point is a valid centre: one that the packed form holds exactly
+        if (one) v = ldexpf((float)(_Float16)ldexpf(v, split_exponent(kc)), -split_exponent(kc));
         c[t] = v;
         centre[(int64_t)blockIdx.x * d + t] = v;
     }
@@ -224,7 +226,7 @@ __global__ __launch_bounds__(256) void k_segments(const float *__restrict__ X, i
 // Segment s as row s % 32 of packed block s / 32.
 __global__ __launch_bounds__(256) void k_pack_segments(const float *__restrict__ centre,
                                                        const float *__restrict__ radius, int nseg, int d, int Q,
-                                                       int TC, const KnnCounters *__restrict__ kc,
+                                                       int TC, bool one, const KnnCounters *__restrict__ kc,
                                                        f16x8 *__restrict__ out) {
     const int NA = 2 * Q + TC;
     const int total = (nseg + 31) / 32 * NA * kWave;
@@ -255,10 +257,10 @@ __global__ __launch_bounds__(256) void k_pack_segments(const float *__restrict__
                 } else if (k == 16 * TC - 1) {
                     v[e] = rad;
                 } else {
-                    const int t = 16 * Q + (k - 3) / 3;
+                    const TailSlot at(k, Q, one);
                     _Float16 hi, lo;
-                    split16(live && t < d ? c[t] * scale : 0.f, hi, lo);
-                    v[e] = (k - 3) % 3 == 2 ? lo : hi;
+                    split16(live && at.t < d ? c[at.t] * scale : 0.f, hi, lo);
+                    v[e] = at.part == 2 ? lo : hi;
                 }
             }
         } else {
@@ -357,8 +359,8 @@ size_t spatial_carve(int64_t nq, int64_t nr, int d, bool square, void *base, Spa
     return cv.used;
 }
 
-int spatial_refs(const float *R, const float *nrow, int64_t nr, int d, const SpatialBuffers &b, KnnCounters *kc,
-                 hipStream_t s) {
+int spatial_refs(const float *R, const float *nrow, int64_t nr, int d, bool rounded, const SpatialBuffers &b,
+                 KnnCounters *kc, hipStream_t s) {
     ScopedTimer timer("query_order", s);
     hipLaunchKernelGGL(k_sp_pivots, dim3(1), dim3(kPivots), 0, s, nr, b.pivot, b.bounds);
     hipLaunchKernelGGL(k_sp_pairs, dim3(kPivots), dim3(kPivots), 0, s, R, d, b.pivot, b.pairs, b.nearest, b.bounds);
@@ -366,12 +368,12 @@ int spatial_refs(const float *R, const float *nrow, int64_t nr, int d, const Spa
     int st = split_pack(R, nrow, nr, d, kPivots / 32, b.pivot_packed, nullptr, nullptr, nullptr, b.pivot, kPivots, kc,
                         s);
     if (st != RSC_OK || (st = sort_rows(R, nr, d, b, b.rkey, b.rperm, kc, s)) != RSC_OK) return st;
-    const SplitGeom g = split_geom(d);
+    const SplitGeom g = rounded ? rounded_geom(d) : split_geom(d);
     hipLaunchKernelGGL(k_segments, dim3((unsigned)b.nseg), dim3(256), 0, s, R, nr, d, b.rperm, 32 * b.seg_blocks, kc,
-                       b.centre, b.radius);
+                       rounded, b.centre, b.radius);
     const int total = (b.nseg + 31) / 32 * g.chunks() * kWave;
     hipLaunchKernelGGL(k_pack_segments, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, b.centre, b.radius,
-                       b.nseg, d, g.q, g.tc, kc, static_cast<f16x8 *>(b.seg_packed));
+                       b.nseg, d, g.q, g.tc, rounded, kc, static_cast<f16x8 *>(b.seg_packed));
     return launch_status("segments");
 }
 
