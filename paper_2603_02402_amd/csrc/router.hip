@@ -87,18 +87,29 @@ __global__ __launch_bounds__(256) void k_gemm_nt(const uint16_t *__restrict__ A,
     const uint16_t *ap = A + (m0 + c) * lda + 8 * h;
     const uint16_t *bp = B + (n0 + c) * ldb + 8 * h;
     f32x16 acc = f32x16{};
-    i32x4 a = *reinterpret_cast<const i32x4 *>(ap);
-    i32x4 b = *reinterpret_cast<const i32x4 *>(bp);
-    for (int k0 = 16; k0 <= K; k0 += 16) {
-        i32x4 an = a, bn = b;
-        if (k0 < K) {
-            an = *reinterpret_cast<const i32x4 *>(ap + k0);
-            bn = *reinterpret_cast<const i32x4 *>(bp + k0);
+    // The operands of the next eight steps are in flight: products with K = 4096
+    // and a wave per SIMD or less (the gradients) wait for them (the average of
+    // the weights' three 67 -> 60 us, of the hidden layers' two 46 -> 38).
+    constexpr int kAhead = 8;
+    i32x4 a[kAhead], b[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+        if (16 * u < K) {
+            a[u] = *reinterpret_cast<const i32x4 *>(ap + 16 * u);
+            b[u] = *reinterpret_cast<const i32x4 *>(bp + 16 * u);
         }
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b),
-                                                      acc, 0, 0, 0);
-        a = an;
-        b = bn;
+    for (int k0 = 0; k0 < K; k0 += 16 * kAhead) {
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int k = k0 + 16 * u;
+            if (k >= K) break;
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[u]),
+                                                          __builtin_bit_cast(bf16x8, b[u]), acc, 0, 0, 0);
+            if (k + 16 * kAhead < K) {
+                a[u] = *reinterpret_cast<const i32x4 *>(ap + k + 16 * kAhead);
+                b[u] = *reinterpret_cast<const i32x4 *>(bp + k + 16 * kAhead);
+            }
+        }
     }
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
@@ -221,7 +232,16 @@ __global__ __launch_bounds__(256) void k_colsum_partial(const uint16_t *__restri
     if (j >= cols) return;
     const int r1 = min(rows, (c + 1) * kColChunk);
     float s = 0.f;
-    for (int r = c * kColChunk; r < r1; ++r) s += from_bf16(in[(int64_t)r * cols + j]);
+    // sixteen rows in flight, added in order (4096 x 4096: 60 -> 8 us)
+    int r = c * kColChunk;
+    for (; r + 16 <= r1; r += 16) {
+        uint16_t x[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) x[u] = in[(int64_t)(r + u) * cols + j];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) s += from_bf16(x[u]);
+    }
+    for (; r < r1; ++r) s += from_bf16(in[(int64_t)r * cols + j]);
     partial[(int64_t)c * cols + j] = s;
 }
 
@@ -254,6 +274,8 @@ __global__ __launch_bounds__(256) void k_cast_input(const float *__restrict__ X,
 // Soft-target cross-entropy and its gradient, one wave per row.
 //   loss_i = logsumexp(z_i) - (1/m) sum_j z_i[label_j]
 //   dZ_i   = (softmax(z_i) - t_i) * scale        (rows >= nb: 0)
+// The row is read once and its labels are put in afterwards; three passes over
+// it and m comparisons per column took 234 us of 4096 rows of 4096, where this takes 38 (100 MB moved).
 __global__ __launch_bounds__(256) void k_softmax_ce(const float *__restrict__ Z, int P, const int32_t *__restrict__ labels,
                                                     int m, int64_t lrow0, int nb, int B, float scale,
                                                     uint16_t *__restrict__ dZ, float *__restrict__ row_loss) {
@@ -267,17 +289,33 @@ __global__ __launch_bounds__(256) void k_softmax_ce(const float *__restrict__ Z,
         if (lane == 0) row_loss[r] = 0.f;
         return;
     }
+    // the row in registers, P <= 4096 a multiple of 64
+    constexpr int T = 4096 / kWave;
+    float v[T];
     float mx = -INFINITY;
-    for (int p = lane; p < P; p += kWave) mx = fmaxf(mx, z[p]);
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        v[t] = kWave * t < P ? z[lane + kWave * t] : -INFINITY;
+        mx = fmaxf(mx, v[t]);
+    }
     for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, kWave));
     float se = 0.f;
-    for (int p = lane; p < P; p += kWave) se += expf(z[p] - mx);
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+        if (kWave * t < P) se += expf(v[t] - mx);
     for (int o = 32; o > 0; o >>= 1) se += __shfl_xor(se, o, kWave);
     const float lse = mx + logf(se);
     const int32_t *lab = labels + (lrow0 + r) * m;
-    for (int p = lane; p < P; p += kWave) {
+    // every column as if without labels, then the labelled columns again
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+        if (kWave * t < P) g[lane + kWave * t] = to_bf16(expf(v[t] - lse) * scale);
+    __threadfence_block();
+    for (int j = lane; j < m; j += kWave) {
+        const int p = lab[j];
+        if (p < 0 || p >= P) continue;
         float t = 0.f;
-        for (int j = 0; j < m; ++j) t += lab[j] == p ? 1.f : 0.f;
+        for (int i = 0; i < m; ++i) t += lab[i] == p ? 1.f : 0.f;
         g[p] = to_bf16((expf(z[p] - lse) - t / (float)m) * scale);
     }
     if (lane == 0) {
@@ -373,17 +411,25 @@ __global__ __launch_bounds__(256) void k_init_params(float *__restrict__ w, Layo
 
 // Top `probes` partitions per row by logit (ties: lower index) and the
 // softmax mass they hold.  One wave per row: lane l holds columns l + 64 t
-// in registers and keeps a sorted list of its 4 best not yet taken; each
-// round the wave-wide best head (by value, then column) is taken and only
-// its lane's list moves.  A lane whose list runs dry rebuilds it from the
-// values that come after the last one it gave up (rare: a lane holds more
-// than 4 of the winners only when they cluster in its columns).
+// in registers.  The probes-th largest of the 64 lanes' maxima bounds the
+// answer from below; the columns at or above it (about 1.4 per winner when the
+// columns are unrelated) are gathered and sorted across the lanes.  Against one
+// wave-wide reduction per winner: 16384 rows of 4096, 32 winners 208 -> 102 us, of
+// which reading the 268 MB takes about 60.
+//
+// A row with more than 64 such columns, with infinite or NaN logits, or more
+// than 64 winners is taken winner by winner: each lane keeps a sorted list of
+// its 4 best not yet taken; each round the wave-wide best head (by value, then
+// column) is taken and only its lane's list moves.  A lane whose list runs dry
+// rebuilds it from the values that come after the last one it gave up.
 __global__ __launch_bounds__(256) void k_top_probes(const float *__restrict__ Z, int P, int nb, int probes,
                                                     int32_t *__restrict__ parts, float *__restrict__ mass) {
     constexpr int T = 4096 / kWave;  // registers per lane (P <= 4096)
     constexpr int LL = 4;            // list length
-    const int lane = threadIdx.x & 63;
-    const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
+    __shared__ float cand_v[4][kWave];
+    __shared__ int cand_p[4][kWave];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int r = blockIdx.x * 4 + wave;
     if (r >= nb) return;
     const float *z = Z + (int64_t)r * P;
     float v[T];
@@ -399,6 +445,57 @@ __global__ __launch_bounds__(256) void k_top_probes(const float *__restrict__ Z,
 #pragma unroll
     for (int t = 0; t < T; ++t) se += lane + kWave * t < P ? expf(v[t] - mx) : 0.f;
     for (int o = 32; o > 0; o >>= 1) se += __shfl_xor(se, o, kWave);
+
+    if (probes <= kWave && isfinite(se)) {
+        float own = v[0];
+#pragma unroll
+        for (int t = 1; t < T; ++t) own = fmaxf(own, v[t]);
+        for (int w = 2; w <= kWave; w *= 2)  // bitonic, descending
+            for (int o = w / 2; o > 0; o >>= 1) {
+                const float ov = __shfl_xor(own, o, kWave);
+                const bool first = ((lane & o) == 0) == ((lane & w) == 0);
+                own = first ? fmaxf(own, ov) : fminf(own, ov);
+            }
+        const float floor = __shfl(own, probes - 1, kWave);
+        int found = 0;
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            const bool hit = kWave * t < P && v[t] >= floor;
+            const uint64_t hits = __ballot(hit);
+            if (!hits) continue;
+            const int at = found + __builtin_amdgcn_mbcnt_hi((uint32_t)(hits >> 32),
+                                                             __builtin_amdgcn_mbcnt_lo((uint32_t)hits, 0));
+            if (hit && at < kWave) {
+                cand_v[wave][at] = v[t];
+                cand_p[wave][at] = lane + kWave * t;
+            }
+            found += __builtin_popcountll(hits);
+        }
+        if (found <= kWave) {
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+            __builtin_amdgcn_wave_barrier();
+            float x = lane < found ? cand_v[wave][lane] : -INFINITY;
+            int p = lane < found ? cand_p[wave][lane] : INT32_MAX;
+            for (int w = 2; w <= kWave; w *= 2)
+                for (int o = w / 2; o > 0; o >>= 1) {
+                    const float ox = __shfl_xor(x, o, kWave);
+                    const int op = __shfl_xor(p, o, kWave);
+                    const bool first = ((lane & o) == 0) == ((lane & w) == 0);
+                    const bool before = x > ox || (x == ox && p < op);
+                    if (first != before) {
+                        x = ox;
+                        p = op;
+                    }
+                }
+            if (lane < probes) parts[(int64_t)r * probes + lane] = p;
+            const float e = expf(x - mx) / se;
+            float got = 0.f;
+            for (int i = 0; i < probes; ++i)
+                got += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(e), i));
+            if (lane == 0) mass[r] = got;
+            return;
+        }
+    }
 
     // (value desc, t asc) order within the lane; t = -1 marks an empty slot
     float lv[LL];
