@@ -1191,6 +1191,16 @@ int knn_plan(int64_t nq, int64_t nr, int d, int k, const rsc_knn_opts *opts, boo
                        ? pick_splits(nq, plan->nblk, split_queries_per_group(d, plan->half),
                                      plan->pruned ? kCUs : kSplitWant)
                        : pick_splits(nq, plan->nblk, lowp_queries_per_group(precision, d), 1024);
+    // A tile of foreign queries spans several clusters where the queries are
+    // sparser than the references, and costs up to ten times another.  Few tiles
+    // take as many ranges as keep one workgroup per CU (5000 queries of 400k
+    // rows: 12 ranges 0.98 ms, 13 1.45); more of them even out in a second and
+    // third round (20k queries: 2.42 ms in 4 ranges, 1.99 in 7).
+    if (plan->pruned && !self_mode) {
+        const int64_t qg = split_queries_per_group(d, plan->half), tiles = std::max<int64_t>(1, (nq + qg - 1) / qg);
+        const int64_t P = 4 * tiles <= kCUs ? kCUs / tiles : (576 + tiles / 2) / tiles;
+        plan->splits = (int)std::max<int64_t>(1, std::min<int64_t>(32, P));
+    }
     // (two ranges even out tiles of different cost while each CU gets about one)
     if (plan->pruned && nq < 512 * split_queries_per_group(d, plan->half)) plan->splits = std::max(plan->splits, 2);
     if (split) {
