@@ -411,6 +411,7 @@ struct RoutedScreenArgs {
     int np;
     int nparts;
     const int32_t *qperm;        // probed rows grouped by own partition
+    const int32_t *own;          // each row's own partition
     const int2 *tiles;           // (first slot, queries)
     const int32_t *ntiles;
     int32_t *tile_next;
@@ -532,136 +533,200 @@ __global__ __launch_bounds__(256, screen_min_waves(DH, L)) void k_screen_routed(
     }
 }
 
-// The union of a tile's probed partitions, block by block in ascending order,
-// with the lanes whose query probed the block's partition.
-struct ProbeStream {
-    const uint32_t *bm;     // the union (LDS)
+// The union of a workgroup's probed partitions, block by block, in ascending
+// order from partition p0 around.  The same for every lane; the next
+// partition's blocks are read ahead.
+struct ProbeUnion {
+    const uint32_t *bm;  // the union (LDS)
     const int64_t *pblk;
-    const int32_t *pr;      // this lane's sorted probe list
-    int nwords, np;
-    int w = 0, ptr = 0, nextp;
+    int nwords, w, p0, left;
     uint32_t bits;
-    int64_t b = 0, b1 = 0;  // the next block of the current partition and its end
-    bool active = false;
+    int p = -1, b = 0, b1 = 0;     // the current partition, its next block and its end
+    int np = -1, nb = 0, nb1 = 0;  // the one after (np < 0: none)
 
-    __device__ __forceinline__ ProbeStream(const uint32_t *bm_, const int64_t *pblk_, const int32_t *pr_, int nwords_,
-                                           int np_, bool live)
-        : bm(bm_), pblk(pblk_), pr(pr_), nwords(nwords_), np(np_) {
-        nextp = live ? pr[0] : INT_MAX;
-        bits = nwords > 0 ? __builtin_amdgcn_readfirstlane(bm[0]) : 0u;
+    __device__ __forceinline__ ProbeUnion(const uint32_t *bm_, const int64_t *pblk_, int nwords_, int p0_)
+        : bm(bm_), pblk(pblk_), nwords(nwords_), w(p0_ >> 5), p0(p0_), left(nwords_) {
+        bits = __builtin_amdgcn_readfirstlane(bm[w]) & (~0u << (p0 & 31));
+        ahead();
     }
-    // The next block and whether this lane's query takes it; false at the end.
-    __device__ __forceinline__ bool next(int64_t &blk, bool &on) {
-        while (b >= b1) {
-            while (bits == 0u) {
-                if (++w >= nwords) return false;
-                bits = __builtin_amdgcn_readfirstlane(bm[w]);
-            }
-            const int p = w * 32 + __builtin_ctz(bits);
-            bits &= bits - 1;
-            // every probe of this query below p has been consumed, so the
-            // query probed p exactly when its next probe is p
-            active = nextp == p;
-            if (active) {
-                ++ptr;
-                nextp = ptr < np ? pr[ptr] : INT_MAX;
-            }
-            b = pblk[p];
-            b1 = pblk[p + 1];
+    __device__ __forceinline__ void ahead() {
+        np = -1;
+        while (bits == 0u) {
+            if (left == 0) return;
+            --left;
+            w = w + 1 == nwords ? 0 : w + 1;
+            bits = __builtin_amdgcn_readfirstlane(bm[w]);
+            if (left == 0) bits &= ~(~0u << (p0 & 31));  // back at p0's word: what lies before it
         }
-        blk = b++;
-        on = active;
+        np = w * 32 + __builtin_ctz(bits);
+        bits &= bits - 1;
+        nb = (int)pblk[np];
+        nb1 = (int)pblk[np + 1];
+    }
+    // Steps to the next block b - 1 of partition p; false at the end.
+    __device__ __forceinline__ bool next() {
+        while (b >= b1) {
+            if (np < 0) return false;
+            p = np;
+            b = nb;
+            b1 = nb1;
+            ahead();
+        }
+        ++b;
         return true;
     }
 };
 
-// The same search on the split operands.  Tiles of different waves share no
-// blocks, so each wave streams its own through a pair of LDS buffers by
-// asynchronous loads, the next block's in flight under the current one's
-// MFMAs, without a barrier.
+// A query's sorted probe list from partition p0 around: `place` is its next
+// entry's place in that order, and the entry after is read ahead.
+struct ProbeWalk {
+    const int32_t *pr;
+    int np, p0, parts, from, ptr, seen = 0;
+    int place, after;
+
+    __device__ __forceinline__ ProbeWalk(const int32_t *pr_, int np_, int p0_, int parts_, bool live)
+        : pr(pr_), np(np_), p0(p0_), parts(parts_), from(0) {
+        if (live)
+            while (from < np && pr[from] < p0) ++from;
+        ptr = from;
+        if (!live) seen = np;
+        place = fetch();
+        after = fetch();
+    }
+    __device__ __forceinline__ int fetch() {
+        while (seen < np) {
+            ++seen;
+            if (ptr == np) ptr = 0;
+            const int p = pr[ptr++];
+            if (p != INT_MAX) return p >= p0 ? p - p0 : p - p0 + parts;
+        }
+        return INT_MAX;
+    }
+    // Whether partition p (places ascending from call to call) is in the list;
+    // entries before it are passed over (more than one past empty partitions).
+    __device__ __forceinline__ bool has(int p) {
+        const int at = p >= p0 ? p - p0 : p - p0 + parts;
+        while (place < at) {
+            place = after;
+            after = fetch();
+        }
+        return place == at;
+    }
+};
+
+// Its workgroups: two of 4 waves per CU while their rings hold a few blocks,
+// one of 8 beyond (or 4, where registers allow a wave per SIMD).
 template <int Q, int TC, int L>
-__global__ __launch_bounds__(256, (SplitStream<Q, TC>::W)) void k_split_routed(RoutedScreenArgs ra) {
-    constexpr int NA = 2 * Q + TC;
-    constexpr int QCAP = 8;
-    __shared__ __attribute__((aligned(16))) char buf0[kScreenWaves * NA * 1024];
-    __shared__ __attribute__((aligned(16))) char buf1[kScreenWaves * NA * 1024];
-    __shared__ double qbuf[QCAP * 256];
-    __shared__ uint32_t bitmap[kScreenWaves][kBitmapWords];
+struct RoutedShape {
+    using S = SplitShape<Q, TC, L>;
+    static constexpr int WGS = S::NA <= 9 ? 2 : 1;
+    static constexpr int NW = WGS == 2 ? 4 : S::NW;
+    static constexpr int W = NW * WGS / 4;  // waves per SIMD
+    static constexpr int ROOM = (160 * 1024 / WGS - S::QCAP * NW * kWave * 8 - 1024) / (2 * S::BLOCK);
+    static constexpr int PH = ROOM < 1 ? 1 : ROOM > 8 ? 8 : ROOM;  // blocks per phase
+};
+
+// The same search on the split operands.  A workgroup takes a tile per wave,
+// consecutive in the queries' order, whose probes are much the same: the blocks
+// of their union pass through an LDS ring once for all of them, and a wave
+// sits out the partitions none of its queries probed (300k rows, 48 of 512
+// partitions of 18 blocks: a query probes 968 blocks, a tile 1180, four tiles
+// 1518, eight 1769).  Streamed by each wave on its own, the blocks came from L2
+// at 8 TB/s, which bounded it: 9.26 ms, now 6.86.  What bounds it now is the
+// waves' wait for each other at the phases, as they sit out different blocks
+// (one workgroup of 8 waves 7.3 ms), and the filling of the lists.
+template <int Q, int TC, int L>
+__global__ __launch_bounds__((RoutedShape<Q, TC, L>::NW * kWave), (RoutedShape<Q, TC, L>::W)) void k_split_routed(
+    RoutedScreenArgs ra) {
+    using S = SplitShape<Q, TC, L>;
+    using RS = RoutedShape<Q, TC, L>;
+    constexpr int NA = S::NA, PH = RS::PH, RING = PH * S::BLOCK;
+    __shared__ __attribute__((aligned(16))) char ring0[RING];
+    __shared__ __attribute__((aligned(16))) char ring1[RING];
+    __shared__ double qbuf[S::QCAP * RS::NW * kWave];
+    __shared__ uint32_t bm[kBitmapWords];
+    __shared__ int first;
     if (ra.s.kc->wide) return;
-    const int tid = threadIdx.x;
-    const int lane = tid & (kWave - 1), wave = tid >> 6;
+    constexpr int qs = RS::NW * kWave, nw = RS::NW;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
     const int c = lane & 31, h = lane >> 5;
-    uint32_t *bm = bitmap[wave];
     double *q = qbuf + tid;
     const int nwords = (ra.nparts + 31) / 32;
     const int ntiles = *ra.ntiles;
     const ScreenArgs &a = ra.s;
     const float scale = ldexpf(1.f, split_exponent(a.kc));
     while (true) {
-        int t = 0;
-        if (lane == 0) t = atomicAdd(ra.tile_next, 1);
-        t = __shfl(t, 0, kWave);
-        if (t >= ntiles) break;
-        const int2 tile = ra.tiles[t];
+        __syncthreads();  // the last tiles are done with the union and the ring
+        if (tid == 0) first = atomicAdd(ra.tile_next, nw);
+        for (int w = tid; w < nwords; w += qs) bm[w] = 0u;
+        __syncthreads();
+        const int t = first + wave;
+        if (first >= ntiles) break;
+        const int2 tile = t < ntiles ? ra.tiles[t] : int2{0, 0};
         const int64_t slot = c < tile.y ? (int64_t)tile.x + c : -1;
         const int64_t row = slot >= 0 ? (int64_t)ra.qperm[slot] : -1;
         const int32_t *pr = ra.probes + (row >= 0 ? row : 0) * ra.np;
-        for (int w = lane; w < nwords; w += kWave) bm[w] = 0u;
-        __builtin_amdgcn_wave_barrier();
         if (row >= 0) {
             for (int j = h; j < ra.np; j += 2) {
                 const int p = pr[j];
                 if (p != INT_MAX) atomicOr(&bm[p >> 5], 1u << (p & 31));
             }
         }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");  // the ORs land before the bitmap is read
-        __builtin_amdgcn_wave_barrier();
-
         SplitQuery<Q, TC> qop;
         qop.load(a.Q, a.d, row, h, scale);
-        PackTopK<L, QCAP> top;
+        PackTopK<L, S::QCAP> top;
         top.init();
+        __syncthreads();  // the union is complete
+
+        // the queries' own partition first: their lists fill with near rows, which
+        // keeps most of the others out (8.2 -> 7.3 ms)
+        const int p0 = __builtin_amdgcn_readfirstlane(ra.own[ra.qperm[ra.tiles[first].x]]);
+        ProbeUnion loads(bm, ra.pblk, nwords, p0), uses(bm, ra.pblk, nwords, p0);
+        auto issue = [&](char *buf) {
+            int n = 0;
+            for (; n < PH && loads.next(); ++n) {
+                const char *src = static_cast<const char *>(a.Ap) + (int64_t)(loads.b - 1) * S::BLOCK + lane * 16;
+                for (int s = wave; s < NA; s += nw) load_lds16(src + s * 1024, buf + (n * NA + s) * 1024);
+            }
+            return n;
+        };
+        ProbeWalk walk(pr, ra.np, p0, ra.nparts, row >= 0);
+        int at = -1;
+        bool on = false, any = false;
         int64_t union_blocks = 0;
-        ProbeStream stream(bm, ra.pblk, pr, nwords, ra.np, row >= 0);
-        char *const mine0 = buf0 + wave * (NA * 1024), *const mine1 = buf1 + wave * (NA * 1024);
-        auto load = [&](char *buf, int64_t blk) {
-            const char *src = static_cast<const char *>(a.Ap) + blk * (NA * 1024) + lane * 16;
+        auto phase = [&](int n, const char *cur, char *nxt) {
+            __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's loads of the phase landed
+            __syncthreads();                      // everyone's landed; the phase before is consumed
+            const int ahead = issue(nxt);
+#pragma unroll 1
+            for (int r = 0; r < n; ++r) {
+                uses.next();
+                if (uses.p != at) {
+                    at = uses.p;
+                    on = walk.has(at);
+                    any = __ballot(on) != 0ull;
+                }
+                if (!any) continue;
+                const f16x8 *sl = reinterpret_cast<const f16x8 *>(cur + r * S::BLOCK) + lane;
+                f16x8 A[NA];
 #pragma unroll
-            for (int s = 0; s < NA; ++s) load_lds16(src + s * 1024, buf + s * 1024);
+                for (int s = TC; s < NA; ++s) A[s] = sl[s * kWave];
+#pragma unroll
+                for (int s = 0; s < TC; ++s) A[s] = sl[s * kWave];
+                f32x16 acc = split_keys(A, qop);
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[v] = on ? acc[v] : INFINITY;
+                top.offer(acc, (uses.b - 1) * 32 + 4 * h, q, qs);
+                ++union_blocks;
+            }
+            return ahead;
         };
-        // `more`: the next block's NA loads are in flight behind this one's
-        auto use = [&](const char *buf, int64_t blk, bool on, bool more) {
-            if (more)
-                __builtin_amdgcn_s_waitcnt(0x0f70 | (NA & 15) | ((NA >> 4) << 14));
-            else
-                __builtin_amdgcn_s_waitcnt(0x0f70);
-            const f16x8 *sl = reinterpret_cast<const f16x8 *>(buf) + lane;
-            f16x8 A[NA];
-#pragma unroll
-            for (int s = TC; s < NA; ++s) A[s] = sl[s * kWave];
-#pragma unroll
-            for (int s = 0; s < TC; ++s) A[s] = sl[s * kWave];
-            f32x16 acc = split_keys<Q, TC>(A, qop);
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[v] = on ? acc[v] : INFINITY;
-            top.offer(acc, (int)(blk * 32) + 4 * h, q, 256);
-            ++union_blocks;
-        };
-        int64_t blk0 = 0, blk1 = 0;
-        bool on0 = false, on1 = false;
-        bool have = stream.next(blk0, on0);
-        if (have) load(mine0, blk0);
-        while (have) {
-            const bool more = stream.next(blk1, on1);
-            if (more) load(mine1, blk1);
-            use(mine0, blk0, on0, more);
-            if (!more) break;
-            have = stream.next(blk0, on0);
-            if (have) load(mine0, blk0);
-            use(mine1, blk1, on1, have);
+        for (int n = issue(ring0); n > 0;) {
+            n = phase(n, ring0, ring1);
+            if (n > 0) n = phase(n, ring1, ring0);
         }
-        top.flush(q, 256);
-        if (lane == 0) atomicAdd(ra.screened, (unsigned long long)(union_blocks * 32 * tile.y));
+        top.flush(q, qs);
+        if (lane == 0 && tile.y > 0) atomicAdd(ra.screened, (unsigned long long)(union_blocks * 32 * tile.y));
         if (slot >= 0) top.store(a, slot, 0, h, ra.map);
     }
 }
@@ -686,14 +751,12 @@ int launch_routed_dh(const RoutedScreenArgs &ra, unsigned grid, int half, hipStr
     return launch_status("screen_routed");
 }
 
-template <int Q, int TC>
-int launch_split_routed(const RoutedScreenArgs &ra, int half, int64_t max_tiles, int cus, hipStream_t s) {
-    const unsigned grid = (unsigned)std::max<int64_t>(
-        1, std::min<int64_t>((int64_t)cus * SplitStream<Q, TC>::W, (max_tiles + kScreenWaves - 1) / kScreenWaves));
-    if (half == 16)
-        hipLaunchKernelGGL((k_split_routed<Q, TC, 16>), dim3(grid), dim3(256), 0, s, ra);
-    else
-        hipLaunchKernelGGL((k_split_routed<Q, TC, 32>), dim3(grid), dim3(256), 0, s, ra);
+template <int Q, int TC, int L>
+int launch_split_routed(const RoutedScreenArgs &ra, int64_t max_tiles, int cus, hipStream_t s) {
+    using RS = RoutedShape<Q, TC, L>;
+    const unsigned grid =
+        (unsigned)std::max<int64_t>(1, std::min<int64_t>((int64_t)cus * RS::WGS, (max_tiles + RS::NW - 1) / RS::NW));
+    hipLaunchKernelGGL((k_split_routed<Q, TC, L>), dim3(grid), dim3(RS::NW * kWave), 0, s, ra);
     return launch_status("screen_routed");
 }
 
@@ -702,7 +765,9 @@ int launch_split(const RoutedScreenArgs &ra, int half, int64_t max_tiles, hipStr
     const SplitGeom g = split_geom(ra.s.d);
     const int cus = device_slots(64) / screen_min_waves(64, 16);
 #define X(Q, TC) \
-    if (g.q == Q && g.tc == TC) return launch_split_routed<Q, TC>(ra, half, max_tiles, cus, s);
+    if (g.q == Q && g.tc == TC)                                         \
+        return half == 16 ? launch_split_routed<Q, TC, 16>(ra, max_tiles, cus, s) \
+                          : launch_split_routed<Q, TC, 32>(ra, max_tiles, cus, s);
     RSC_SPLIT_GEOMS_128(X)
 #undef X
     set_error("internal: no split screen for this dimension");
@@ -831,6 +896,7 @@ int probed_run(const float *X, int64_t n, int d, int k, const int64_t *offsets, 
     ra.np = probes;
     ra.nparts = P;
     ra.qperm = b.qperm;
+    ra.own = b.own;
     ra.tiles = b.tiles;
     ra.ntiles = &b.rc->ntiles;
     ra.tile_next = &b.rc->tile_next;

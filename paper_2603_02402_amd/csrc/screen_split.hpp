@@ -207,13 +207,6 @@ struct SplitShape {
     static constexpr int QG = NW * 32;  // queries per workgroup
 };
 
-// Waves per SIMD of a screen whose waves stream blocks of their own, two LDS
-// buffers each (two workgroups of 4 waves per CU while they fit).
-template <int Q, int TC>
-struct SplitStream {
-    static constexpr int W = 2 * Q + TC <= 9 ? 2 : 1;
-};
-
 // Streams packed blocks phys(0) .. phys(count - 1) of Ab through the ring of
 // the workgroup and hands each to use(A, block): every wave of the workgroup
 // calls this together.  phys may name any block that exists.
