@@ -83,11 +83,11 @@ typedef enum { RSC_EUCLIDEAN = 0, RSC_COSINE = 1 } rsc_metric;
 
 /*
  * Options of the screening stage.  A zero-initialised struct (or NULL)
- * selects the default: FP32 screen of width 32 (64 for k > 16) followed by
- * the exactness certificate and rescan, i.e. the exact result.
+ * selects the default: screen at FP32 accuracy of width 32 (64 for k > 16), then
+ * the exactness certificate and its fallbacks, i.e. the exact result.
  *   precision  arithmetic of the distance screen on the matrix cores:
  *              RSC_FP32      exact result (certified, see rsc_knn);
- *              RSC_BF16      BF16 operands, FP32 accumulation;
+ *              RSC_BF16      operands rounded to BF16, FP32 accumulation;
  *              RSC_FP8_E4M3  OCP e4m3 operands with per-dimension absmax
  *                            scaling (s_t = max|y_t| / 448), FP32 accumulation.
  *              The reduced-precision forms keep the `screen` (default 64)
@@ -124,7 +124,7 @@ typedef struct {
 
 /* Counters a kNN call leaves in its workspace (read with rsc_knn_read_stats). */
 typedef struct {
-    int64_t escalated_rows; /* rows the first screen could not certify (screened again, wider) */
+    int64_t escalated_rows; /* rows the first screen could not certify (searched again) */
     int64_t rescanned_rows; /* rows no screen could certify (recomputed exhaustively in float64) */
     float max_err_ratio;    /* largest |screened key - exact key| / certificate bound seen */
     float max_ref_norm;     /* max_j ||y_j|| over the references, float32 */

@@ -1054,11 +1054,6 @@ int knn_pack_mapped(int dh, const float *R, const float *nrow, int64_t nr, int d
 
 size_t knn_packed_floats(int dh, int64_t nblk) { return (size_t)nblk * packed_s4(dh) * kWave * 4; }
 
-int knn_launch_screen(int dh, const scr::ScreenArgs &a, unsigned gx, int half_width, const char *name,
-                      hipStream_t s) {
-    return screen(dh, a, gx, half_width, false, name, s);
-}
-
 template <int G, int KR>
 void launch_rerank_lean(const RerankArgs &ra, int64_t slots, hipStream_t stream) {
     constexpr int NG = 256 / G;

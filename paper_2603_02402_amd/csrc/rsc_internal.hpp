@@ -219,8 +219,6 @@ int knn_norms(const float *R, int64_t nr, int d, float *nrow, KnnCounters *count
 int knn_pack_mapped(int dh, const float *R, const float *nrow, int64_t nr, int d, int64_t nblk, float *packed,
                     float *norms, const int32_t *row_map, hipStream_t stream);
 size_t knn_packed_floats(int dh, int64_t nblk);
-int knn_launch_screen(int dh, const scr::ScreenArgs &a, unsigned gx, int half_width, const char *name,
-                      hipStream_t s);
 // Split FP16 screen of the exact path (knn_split.hip).
 size_t split_packed_bytes(int d, int64_t nblk);
 int split_queries_per_group(int d, int half_width);
