@@ -8,8 +8,8 @@ Default workload: n = 1,000,000 cells, d = 50 PCA-like components, k = 15,
 100-cluster Gaussian mixture with Zipf(1.1) cluster sizes and 1/i variance
 decay (a synthetic stand-in for a PCA embedding of a 10x dataset).
 
-Prints ONE JSON line.  ``roofline`` covers the dominant kernel (the FP32
-MFMA screen) with its duration measured by HIP events recorded by the
+Prints ONE JSON line.  ``roofline`` covers the dominant kernel (the pruned
+split-FP16 MFMA screen) with its duration measured by HIP events recorded by the
 library on the launch stream over the timed region.  ``cpu_baseline`` times
 the FP64 CPU oracle on a bounded sample of query rows of the same workload.
 """
@@ -30,8 +30,8 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 METRIC = "kNN graph cells/s (d=50,k=15): plain vs BF16+rerank vs routed, recall@15≥0.99"
-PEAK_FP32_TFLOPS = 157.3  # MI355X dense FP32 matrix
 PEAK_HBM_GBS = 8000.0
+PEAK_FP16_TFLOPS = 2516.6  # MI355X dense FP16 / BF16 matrix
 
 WORKLOADS = {
     "plain_1m": dict(n=1_000_000, clusters=100, law="zipf", seed=1,
@@ -118,7 +118,7 @@ def graph_gbs(kernels: dict, n: int, k: int, nnz: int) -> dict:
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "screen_fp32_plain_1m_traffic.json")
 # the sources that define the screen kernel (and so its traffic)
 SCREEN_SOURCES = [os.path.join(ROOT, "paper_2603_02402_amd", "csrc", f)
-                  for f in ("knn.hip", "screen_fp32.hpp", "screen_common.hpp")]
+                  for f in ("knn.hip", "spatial.hip", "screen_split.hpp", "screen_split_grid.hpp", "screen_common.hpp")]
 
 
 def screen_source_hash() -> str:
@@ -128,6 +128,28 @@ def screen_source_hash() -> str:
     for f in SCREEN_SOURCES:
         h.update(open(f, "rb").read())
     return h.hexdigest()
+
+
+def split_mfmas(d: int) -> int:
+    """FP16 MFMAs (32 x 32 x 16) of the split screen per 32 x 32 keys, from its
+    geometries (three per 16 full dimensions, one or two for the rest)."""
+    for q, tc in [(q, tc) for q in range(4) for tc in (1, 2)] + [(q, 1) for q in (4, 5, 6, 7, 8, 10, 12, 14, 16)]:
+        if d <= 16 * q + (16 * tc - 3) // 3:
+            return 3 * q + tc
+    return 0
+
+
+def screened_pairs(ws, n: int):
+    """Query-reference pairs the pruned screen of the last call multiplied out:
+    segments visited (summed over tiles of 256 queries) times their rows."""
+    import torch
+
+    blocks = (n + 31) // 32
+    seg = 1
+    while (blocks + seg - 1) // seg > 8192:
+        seg *= 2
+    visited = int(ws.buf[32:40].view(torch.int64)[0])
+    return visited * seg * 32 * 256
 
 
 def measured_traffic():
@@ -279,10 +301,13 @@ def precision_forms(args, rsc) -> dict:
         ms, scr, g = timed_form(rsc, Xt, k, prec, args.form_steps, 1, ws, fo)
         rec = recall_at_k(fo[1], ex[1], k)
         we = weight_error(g, g_exact, n)
+        work = 2.0 * d * n * n
+        if prec == rsc.RSC_BF16:  # pruned: what its MFMAs of 16 slots did
+            work = screened_pairs(ws, n) * 32.0 * ((d + 19) // 16)
         res[name] = {"cells_per_s": round(n / (ms / 1e3), 1), "ms_per_step": round(ms, 2),
                      "screen_ms": round(scr, 2), "recall@15": round(rec, 5),
                      "screen_tflops_algorithmic": round(2 * d * n * n / (scr / 1e3) / 1e12, 2),
-                     "screen_frac_of_peak": round(2 * d * n * n / (scr / 1e3) / 1e12 / peak, 4),
+                     "screen_frac_of_peak": round(work / (scr / 1e3) / 1e12 / peak, 4),
                      "weight_error_on_common_entries": we,
                      "meets_recall_0.99": rec >= 0.99}
     # the FP8 residual variant (a separately labelled form): 1024 k-means
@@ -336,9 +361,9 @@ def cosine_form(args, rsc, Xt, ws, out) -> dict:
             kern[name] = round(tot / cnt, 4)
     scr = kern.get("screen_fp32")
     return {"workload": "same cells as the plain line (n=1,000,000, d=50, k=15), distance 1 - cos",
-            "form": "exact cosine (FP32 MFMA screen on unit rows, FP64 rerank + certificate)",
+            "form": "exact cosine (split FP16 MFMA screen on unit rows, FP64 rerank + certificate)",
             "cells_per_s": round(n / (ms / 1e3), 1), "ms_per_step": round(ms, 2), "kernel_ms": kern,
-            "screen_frac_of_fp32_peak": round(2 * d * n * n / (scr / 1e3) / 1e12 / PEAK_FP32_TFLOPS, 4) if scr else None,
+            "screened_pairs_of_all": round(screened_pairs(ws, n) / (n * n), 5) if scr else None,
             "escalated_rows": stats["escalated_rows"], "rescanned_rows": stats["rescanned_rows"],
             "max_err_ratio": round(stats["max_err_ratio"], 4), "nnz": int(g.nnz)}
 
@@ -748,7 +773,8 @@ def batched_form(args, rsc) -> dict:
     return {"workload": f"64 samples, {n} cells, sizes log-uniform in [2000, 200000] (seed 4), d=50, k=15",
             "cells_per_s": round(n / (ms / 1e3), 1), "ms_per_step": round(ms, 2), "screen_ms": round(scr, 2),
             "screen_tflops": round(flops / (scr / 1e3) / 1e12, 2),
-            "screen_frac_of_fp32_peak": round(flops / (scr / 1e3) / 1e12 / PEAK_FP32_TFLOPS, 4),
+            "screen_frac_of_fp16_peak": round(flops / (2 * d) * 32 * split_mfmas(d) / (scr / 1e3) / 1e12
+                                              / PEAK_FP16_TFLOPS, 4),  # 16 slots per issued MFMA
             "autotune_choice": list(table)[chosen] if 0 <= chosen < len(table) else None,
             "autotune_screen_ms": {kk: round(v, 2) for kk, v in table.items()},
             "escalated_rows": stats["escalated_rows"], "rescanned_rows": stats["rescanned_rows"], "nnz": int(g.nnz),
@@ -1050,15 +1076,19 @@ def main() -> int:
         if cnt:
             kernels[name] = round(tot / cnt, 4)
     screen_ms = kernels.get("screen_fp32")
-    flops = 2.0 * d * n * n
     roofline = None
+    pairs = screened_pairs(ws, n) if screen_ms and n >= 16384 else float(n) * n
     if screen_ms:
+        flops = pairs * 32.0 * split_mfmas(d)  # issued: 16 slots an MFMA
         achieved = flops / (screen_ms / 1e3) / 1e12
-        roofline = {"bound": "mfma", "achieved": round(achieved, 2), "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
-                    "frac": round(achieved / PEAK_FP32_TFLOPS, 4),
+        roofline = {"bound": "mfma", "achieved": round(achieved, 2), "peak": PEAK_FP16_TFLOPS, "unit": "TFLOP/s",
+                    "frac": round(achieved / PEAK_FP16_TFLOPS, 4),
                     "traffic": measured_traffic() if args.workload == "plain_1m" and k == 15 else None,
-                    "kernel": "k_screen_fp32 (FP32 MFMA 32x32x2 distance screen + per-query top-32 heap)",
-                    "work_per_launch": f"2*d*n^2 = {flops:.3e} flop (d={d}, n={n})"}
+                    "kernel": ("k_split_pruned (segments outside every query's reach skipped; " if n >= 16384 else
+                               "k_screen_split (") + "split FP16 MFMA 32x32x16 distance screen + per-query top-32 lists)",
+                    "screened_pairs": pairs, "screened_pairs_of_all": round(pairs / (float(n) * n), 5),
+                    "work_per_launch": f"{split_mfmas(d)} MFMAs of 16 slots per 32 x 32 screened pairs = "
+                                       f"{flops:.3e} flop issued; all pairs: 2*d*n^2 = {2.0 * d * n * n:.3e} (d={d}, n={n})"}
 
     graph = graph_gbs(kernels, n, k, int(g.nnz))
 
