@@ -1134,7 +1134,7 @@ def main() -> int:
         "vs_baseline": None,
         "dtype": "fp32",
         "data": "synthetic",
-        "config": {"workload": w["desc"], "form": "plain exact (FP32 MFMA screen, FP64 rerank + certificate)",
+        "config": {"workload": w["desc"], "form": "plain exact (split FP16 MFMA screen at FP32 accuracy, FP64 rerank + certificate)",
                    "n": n, "d": d, "k": k, "nnz": int(g.nnz), "escalated_rows": stats["escalated_rows"],
                    "rescanned_rows": stats["rescanned_rows"],
                    "max_err_ratio": round(stats["max_err_ratio"], 4)},

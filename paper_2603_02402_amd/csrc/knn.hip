@@ -1070,13 +1070,20 @@ int knn_launch_rerank(const RerankArgs &ra, int64_t slots, const char *name, hip
     ScopedTimer timer(name, stream);
     const dim3 grid((unsigned)((slots + 3) / 4));
     const int m = ra.self_mode ? ra.k - 1 : ra.k, total = ra.P * ra.S;
-    // two rows per wave while 32 lanes hold the answer and a lane few candidates
+    // two rows per wave while 32 lanes hold the answer and a lane few candidates;
+    // candidates per lane in steps, as every pass over them counts all (128 in
+    // 4 registers for 8: 70k rows, k = 30 230 -> 199 us; in 2 for 8: 300k rows,
+    // k = 48 1.73 -> 1.43 ms)
     if (m <= 32 && total <= 32)
         launch_rerank_lean<32, 1>(ra, slots, stream);
     else if (m <= 32 && total <= 64)
         launch_rerank_lean<32, 2>(ra, slots, stream);
+    else if (m <= 32 && total <= 128)
+        launch_rerank_lean<32, 4>(ra, slots, stream);
     else if (m <= 32 && total <= 256)
         launch_rerank_lean<32, 8>(ra, slots, stream);
+    else if (m <= kLeanAnswer && total <= 128)
+        launch_rerank_lean<64, 2>(ra, slots, stream);
     else if (m <= kLeanAnswer && total <= 512)
         launch_rerank_lean<64, 8>(ra, slots, stream);
     else if (m <= kLeanAnswer && total <= 2048)

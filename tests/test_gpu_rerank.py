@@ -51,6 +51,15 @@ def test_answer_and_list_sizes(rsc, oracle_mod, n, d, k):
     same(rsc, oracle_mod, synth.mixture(n, d=d, n_clusters=4, seed=n + d + k), k)
 
 
+# 600 rows: two ranges, 128 candidates in lists of 32; 257: one range, 64
+@pytest.mark.parametrize("n", [257, 600])
+@pytest.mark.parametrize("k", [17, 32, 33, 34, 40, 64])
+@pytest.mark.parametrize("metric", ["euclidean", "cosine"])
+def test_candidates_per_lane(rsc, oracle_mod, n, k, metric):
+    print(f"[rerank] n={n} k={k} {metric}", flush=True)
+    same(rsc, oracle_mod, synth.mixture(n, d=50, n_clusters=4, seed=n + k), k, metric=metric)
+
+
 @pytest.mark.parametrize("shift", [1, 2, 3])
 @pytest.mark.parametrize("d", [49, 50])
 def test_unaligned_rows(rsc, oracle_mod, d, shift):
