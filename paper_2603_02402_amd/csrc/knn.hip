@@ -1410,7 +1410,14 @@ int knn_run(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, 
     if ((st = knn_prep_fp32(p, Rs, p.self_mode ? nullptr : Qs, b, nullptr, nullptr, nullptr, stream)) != RSC_OK)
         return st;
     // Large problems are screened in a spatial order with its segments' bounds.
-    const bool pruned = p.pruned && !qlist && p.nq > 0;
+    // (Under stream capture the exact path screens every pair instead: the
+    // order's library sort clears its counters by memset above a size of its own,
+    // and memset nodes have given wrong results on replays.  The BF16 form
+    // always sorted.)
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    const bool captured = p.pruned && !rounded && hipStreamIsCapturing(stream, &capture) == hipSuccess &&
+                          capture != hipStreamCaptureStatusNone;
+    const bool pruned = p.pruned && !captured && !qlist && p.nq > 0;
     const int32_t *ref_map = nullptr;
     if (pruned) {
         if ((st = spatial_refs(Rs, b.nrow, p.nr, p.d, rounded, b.sp, b.counters, stream)) != RSC_OK) return st;
