@@ -89,7 +89,9 @@ __host__ __device__ inline int norm_rows(int d) { return d <= 128 ? kNormRows : 
 __global__ __launch_bounds__(kNormThreads) void k_norms(const float *__restrict__ R, int64_t nr, int d,
                                                         float *__restrict__ nrow,
                                                         uint32_t *__restrict__ max_norm_bits) {
-    // nrow may be null: only the largest norm is wanted
+    // nrow may be null: only the largest norm is wanted.  A row with an infinite or
+    // NaN value has such a norm, which packing takes for no row, and stays out of
+    // the largest (a finite row whose norm overflows float32 does enter it).
     __shared__ float buf[kNormBuf];
     __shared__ float wmax[kNormThreads / kWave];
     const int nrb = norm_rows(d);
@@ -110,7 +112,7 @@ __global__ __launch_bounds__(kNormThreads) void k_norms(const float *__restrict_
     s += __shfl_xor(s, 2, kWave);
     const float nf = (float)s;
     if (nrow && i < rows && q == 0) nrow[r0 + i] = nf;
-    const float m = wave_max(sqrtf(nf));
+    const float m = wave_max(s < INFINITY ? sqrtf(nf) : 0.f);
     if ((threadIdx.x & (kWave - 1)) == 0) wmax[threadIdx.x / kWave] = m;
     __syncthreads();
     if (threadIdx.x == 0) {

@@ -19,8 +19,8 @@ using namespace scr;
 // Packed block b of NA = 2 Q + TC chunks: chunk s, lane (c, h) holds the 8
 // slots 16 s + 8 h .. of row 32 b + c -- first the tail (norm parts, then
 // (h, h, l) triples of dimensions 16 Q ..), then the high and the low parts
-// of dimensions 0 .. 16 Q - 1.  Rows past the end: zeros and an infinite
-// norm.  One workgroup per block: the rows come in coalesced through LDS and
+// of dimensions 0 .. 16 Q - 1.  Rows past the end, and rows with an infinite or
+// NaN value: zeros and an infinite norm.  One workgroup per block: the rows come in coalesced through LDS and
 // leave as 16-byte stores.  Marks inputs whose norms spread too far (`wide`).
 __global__ __launch_bounds__(256) void k_pack_split(const float *__restrict__ R, const float *__restrict__ nrow,
                                                     int64_t nr, int d, int Q, int TC, bool one,
@@ -65,8 +65,8 @@ __global__ __launch_bounds__(256) void k_pack_split(const float *__restrict__ R,
         }
         __syncthreads();
         const int64_t row = row_of(c);
-        const float n2 = row >= 0 ? nrow[row] : 0.f;
-        const bool below = row >= 0 && n2 < small;
+        const float n2 = row >= 0 ? nrow[row] : INFINITY;
+        const bool live = n2 < INFINITY, below = n2 < small;
         const float *x = rows + c * ld;
         for (int s = threadIdx.x >> 6; s < NA; s += 4) {
             f16x8 v;
@@ -80,10 +80,10 @@ __global__ __launch_bounds__(256) void k_pack_split(const float *__restrict__ R,
                 for (int e = 0; e < 8; ++e) {
                     const int k = 16 * s + 8 * h + e;
                     if (k < 3) {
-                        v[e] = row >= 0 ? (k == 0 ? p1 : k == 1 ? p2 : p3) : (_Float16)(k == 0 ? INFINITY : 0.f);
+                        v[e] = live ? (k == 0 ? p1 : k == 1 ? p2 : p3) : (_Float16)(k == 0 ? INFINITY : 0.f);
                     } else {
                         const TailSlot at(k, Q, one);
-                        const float y = at.t < d ? x[at.t] : 0.f;
+                        const float y = live && at.t < d ? x[at.t] : 0.f;
                         wide |= below && y != 0.f;
                         _Float16 hi, lo;
                         split16(y * scale, hi, lo);
@@ -95,7 +95,7 @@ __global__ __launch_bounds__(256) void k_pack_split(const float *__restrict__ R,
                 const int t0 = 16 * (low ? s - TC - Q : s - TC) + 8 * h;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    const float y = t0 + e < d ? x[t0 + e] : 0.f;
+                    const float y = live && t0 + e < d ? x[t0 + e] : 0.f;
                     wide |= below && y != 0.f;
                     _Float16 hi, lo;
                     split16(y * scale, hi, lo);

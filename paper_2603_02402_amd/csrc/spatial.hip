@@ -12,7 +12,8 @@
 // once in 170 draws; the pass costs 16 blocks per query block.
 //
 // Segments.  seg_blocks consecutive packed blocks of the order have a centre
-// (float32 mean) and a radius no row exceeds.  They are packed like rows
+// (float32 mean) and a radius no row exceeds; rows with an infinite or NaN value
+// are in no answer and left out of both.  They are packed like rows
 // (their "norm" is ||c||^2 - r^2, and the tail's last slot holds r), so that
 // the split screen's contraction with a query whose own last slot holds -2 T
 // gives d(x, c)^2 - ||x||^2 - r^2 - 2 T r: above T^2 - ||x||^2 exactly when
@@ -74,7 +75,7 @@ __global__ __launch_bounds__(kPivots) void k_sp_pairs(const float *__restrict__ 
         for (int w = 1; w < kPivots / kWave; ++w) m = fminf(m, best[w]);
         nearest[i] = m;
     }
-    if (j < 3 && j < d) {
+    if (j < 3 && j < d && fabsf(x[j]) < INFINITY) {
         atomicMin(&bounds[2 * j], ordered_bits(x[j]));
         atomicMax(&bounds[2 * j + 1], ordered_bits(x[j]));
     }
@@ -190,7 +191,10 @@ __global__ __launch_bounds__(256) void k_segments(const float *__restrict__ X, i
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
     for (int t = lane; t < d; t += kWave) {
         float s = 0.f;
-        for (int r = wave; r < m; r += 4) s += X[(int64_t)perm[r0 + r] * d + t];
+        for (int r = wave; r < m; r += 4) {
+            const float v = X[(int64_t)perm[r0 + r] * d + t];
+            s += fabsf(v) < INFINITY ? v : 0.f;
+        }
         part[wave][t] = s;
     }
     __syncthreads();
@@ -211,7 +215,7 @@ __global__ __launch_bounds__(256) void k_segments(const float *__restrict__ X, i
             s = fmaf(e, e, s);
         }
         for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, kWave);
-        worst = fmaxf(worst, s);
+        if (s < INFINITY) worst = fmaxf(worst, s);
     }
     if (lane == 0) far[wave] = worst;
     __syncthreads();
