@@ -1503,8 +1503,13 @@ int knn_run(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, 
     ra.flag_count = &b.counters->flagged;
     ra.out_idx = out_idx;
     ra.out_dist = out_dist;
-    if (rounded) return knn_launch_rerank(ra, p.nq, "rerank", stream);
     knn_split_bounds(ra);
+    if (rounded) {
+        // no certificate: the error statistic is relative, as in knn_run_lowp
+        ra.eps_coef = ra.cosine_eps = ra.split_eps = ra.split_cosine_eps = 1.0;
+        ra.split_abs = 0.0;
+        return knn_launch_rerank(ra, p.nq, "rerank", stream);
+    }
     const int esc_cap = (int)std::min<int64_t>(p.nq, kEscalateCap);
     const bool collect = (p.self_mode ? p.k - 1 : p.k) <= kLeanAnswer;
     if (collect) {

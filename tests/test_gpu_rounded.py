@@ -58,3 +58,18 @@ def test_recall(k):
         want, _ = rsc.knn(X, k, metric=metric)
         hit = (idx[:, :, None] == want[:, None, :]).any(2).double().mean().item()
         assert hit > 0.999
+
+
+@pytest.mark.parametrize("metric", [rsc.RSC_EUCLIDEAN, rsc.RSC_COSINE])
+@pytest.mark.parametrize("spread", [1.0, 2.0 ** -20])
+def test_error_statistic(metric, spread):
+    """The statistic is the relative error of a screened key, |key - d^2 + x^2| over 2 |x| |y| + |y|^2 (cosine: the
+    error itself).  Rounding both rows to BF16 moves a key by at most 2^-9 of each term: 2 (2^-9 + 2^-9) |x| |y| and
+    2 2^-9 |y|^2, so it stays below 2^-7 (cosine: below twice that of 3 terms), and it is not zero."""
+    X = rows(20000, 50, 20, seed=6)[0]
+    X = 40 * (X + 0.01 * torch.randn(X.shape, generator=torch.Generator("cuda").manual_seed(7), device="cuda"))
+    X[::7] *= spread
+    ws = rsc.Workspace("cuda")
+    rsc.knn(X, 15, precision=rsc.RSC_BF16, metric=metric, workspace=ws)
+    ratio = rsc.read_knn_stats(ws)["max_err_ratio"]
+    assert 2.0 ** -16 < ratio < (2.0 ** -7 if metric == rsc.RSC_EUCLIDEAN else 2.0 ** -5)
