@@ -126,7 +126,8 @@ typedef struct {
 typedef struct {
     int64_t escalated_rows; /* rows the first screen could not certify (searched again) */
     int64_t rescanned_rows; /* rows no screen could certify (recomputed exhaustively in float64) */
-    float max_err_ratio;    /* largest |screened key - exact key| / certificate bound seen */
+    float max_err_ratio;    /* largest |screened key - exact key| / certificate bound seen (reduced precision,
+                               which has no certificate: over 2 |x||y| + |y|^2, or 1 for the cosine) */
     float max_ref_norm;     /* max_j ||y_j|| over the references, float32 */
 } rsc_knn_stats;
 
@@ -148,6 +149,8 @@ size_t rsc_knn_workspace_bytes(int64_t n_query, int64_t n_ref, int32_t d, int32_
  * re-ranked with float64 distances, and rows whose screen cannot be proved
  * to contain the true neighbours are recomputed exhaustively, so the result
  * is exact for every row.
+ * The search forms (rsc_knn, rsc_knn_opt, rsc_knn_ex; not fp8_residual, which
+ * reads back) may be recorded into a HIP graph: they enqueue kernels alone.
  */
 int rsc_knn(const float *X, int64_t n, int32_t d, int32_t k, int32_t *out_idx, float *out_dist, void *workspace,
             size_t workspace_bytes, void *stream);

@@ -1412,10 +1412,8 @@ int knn_run(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, 
     if ((st = knn_prep_fp32(p, Rs, p.self_mode ? nullptr : Qs, b, nullptr, nullptr, nullptr, stream)) != RSC_OK)
         return st;
     // Large problems are screened in a spatial order with its segments' bounds.
-    // (Under stream capture the exact path screens every pair instead: the
-    // order's library sort clears its counters by memset above a size of its own,
-    // and memset nodes have given wrong results on replays.  The BF16 form
-    // always sorted.)
+    // (Under stream capture the exact path screens every pair instead; the BF16
+    // form, which has no certificate, sorts in pieces that record kernels alone.)
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     const bool captured = p.pruned && !rounded && hipStreamIsCapturing(stream, &capture) == hipSuccess &&
                           capture != hipStreamCaptureStatusNone;

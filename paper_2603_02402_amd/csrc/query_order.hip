@@ -13,12 +13,11 @@
 
 #include <hip/hip_runtime.h>
 
-#include <rocprim/device/device_radix_sort.hpp>
-
 #include <algorithm>
 #include <cstdint>
 
 #include "morton.hpp"
+#include "order_sort.hpp"
 #include "rsc_internal.hpp"
 
 namespace rsc {
@@ -120,10 +119,8 @@ struct OrderWs {
 template <class Key>
 size_t carve_order(int64_t nq, int bits, void *base, OrderWs<Key> *out) {
     const size_t m = (size_t)std::max<int64_t>(nq, 1);
-    size_t tmp = 0;
-    if (rocprim::radix_sort_pairs(nullptr, tmp, (const Key *)nullptr, (Key *)nullptr, (const int32_t *)nullptr,
-                                  (int32_t *)nullptr, m, 0, bits, (hipStream_t)0) != hipSuccess)
-        return 0;
+    const size_t tmp = order_sort_bytes<Key>((int64_t)m, bits);
+    if (!tmp) return 0;
     Carver cv(base);
     OrderWs<Key> w{};
     w.bounds = cv.take<uint32_t>(2 * kOrderDims);
@@ -131,7 +128,7 @@ size_t carve_order(int64_t nq, int bits, void *base, OrderWs<Key> *out) {
     w.key2 = cv.take<Key>(m);
     w.row = cv.take<int32_t>(m);
     w.tmp_bytes = tmp;
-    w.tmp = cv.take<char>(tmp ? tmp : 1);
+    w.tmp = cv.take<char>(tmp);
     if (out) *out = w;
     return cv.used;
 }
@@ -153,9 +150,7 @@ int order_run(const float *Q, int64_t nq, int d, const int64_t *soff, int S, int
     hipLaunchKernelGGL(k_qo_keys<Key>, dim3(g), dim3(256), 0, s, Q, nq, d, D, w.bounds, w.key, w.row, soff, S);
     int st = launch_status("query order keys");
     if (st != RSC_OK) return st;
-    return hip_status(rocprim::radix_sort_pairs(w.tmp, w.tmp_bytes, (const Key *)w.key, w.key2,
-                                                (const int32_t *)w.row, perm, (size_t)nq, 0, bits, s),
-                      "sort of the query order");
+    return order_sort<Key>(w.tmp, w.tmp_bytes, w.key, w.key2, w.row, perm, nq, bits, "sort of the query order", s);
 }
 
 constexpr int kCodeBits = kOrderDims * kOrderBits;

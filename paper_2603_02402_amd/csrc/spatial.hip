@@ -21,12 +21,11 @@
 
 #include <hip/hip_runtime.h>
 
-#include <rocprim/device/device_radix_sort.hpp>
-
 #include <algorithm>
 #include <cmath>
 
 #include "morton.hpp"
+#include "order_sort.hpp"
 #include "rsc_internal.hpp"
 #include "screen_common.hpp"
 #include "screen_split.hpp"
@@ -281,7 +280,8 @@ __global__ __launch_bounds__(256) void k_pack_segments(const float *__restrict__
     }
 }
 
-// Segment of the references where the middle query of each tile belongs.
+// Segment of the references where the middle query of each tile belongs (some
+// segment, where the keys are sorted in pieces).
 __global__ __launch_bounds__(256) void k_sp_own(const uint32_t *__restrict__ qkey, int64_t nq, int qg, int tiles,
                                                 const uint32_t *__restrict__ rkey, int64_t nr, int rows,
                                                 int32_t *__restrict__ own) {
@@ -294,15 +294,6 @@ __global__ __launch_bounds__(256) void k_sp_own(const uint32_t *__restrict__ qke
         if (rkey[mid] < k) lo = mid + 1; else hi = mid;
     }
     own[i] = (int32_t)(min(lo, nr - 1) / rows);
-}
-
-size_t sort_bytes(int64_t n) {
-    size_t tmp = 0;
-    if (rocprim::radix_sort_pairs(nullptr, tmp, (const uint32_t *)nullptr, (uint32_t *)nullptr,
-                                  (const int32_t *)nullptr, (int32_t *)nullptr, (size_t)n, 0, kKeyBits,
-                                  (hipStream_t)0) != hipSuccess)
-        return 0;
-    return tmp;
 }
 
 int sort_rows(const float *X, int64_t n, int d, const SpatialBuffers &b, uint32_t *sorted, int32_t *perm,
@@ -318,10 +309,8 @@ int sort_rows(const float *X, int64_t n, int d, const SpatialBuffers &b, uint32_
 #undef X_
     int st = launch_status("spatial keys");
     if (st != RSC_OK) return st;
-    size_t tmp_bytes = b.tmp_bytes;
-    return hip_status(rocprim::radix_sort_pairs(b.tmp, tmp_bytes, (const uint32_t *)b.key, sorted,
-                                                (const int32_t *)b.id, perm, (size_t)n, 0, kKeyBits, s),
-                      "sort of the spatial order");
+    return order_sort<uint32_t>(b.tmp, b.tmp_bytes, b.key, sorted, b.id, perm, n, kKeyBits, "sort of the spatial order",
+                                s);
 }
 
 }  // namespace
@@ -357,7 +346,7 @@ size_t spatial_carve(int64_t nq, int64_t nr, int d, bool square, void *base, Spa
     b.centre = cv.take<float>((size_t)b.nseg * d);
     b.radius = cv.take<float>((size_t)b.nseg);
     b.seg_packed = cv.take<char>(split_packed_bytes(d, (b.nseg + 31) / 32));
-    b.tmp_bytes = sort_bytes((int64_t)most);
+    b.tmp_bytes = order_sort_bytes<uint32_t>((int64_t)most, kKeyBits);
     b.tmp = cv.take<char>(std::max<size_t>(b.tmp_bytes, 1));
     if (out) *out = b;
     return cv.used;
