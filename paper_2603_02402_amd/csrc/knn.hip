@@ -621,7 +621,8 @@ __global__ __launch_bounds__(256) void k_rerank_lean(RerankArgs a) {
     // the candidates: lists of S keys, ascending; tau: the smallest key a full list could have rejected
     const int m = a.self_mode ? a.k - 1 : a.k;
     const int found = a.counts && live ? a.counts[slot] : 0;
-    const int total = a.counts ? min(found, a.KP) : a.P * a.S;
+    // (a row with more than its room is scanned exhaustively: none of its entries are taken, or need be written)
+    const int total = a.counts ? (found <= a.KP ? found : 0) : a.P * a.S;
     const int64_t cbase = (live ? slot : 0) * a.P * a.KP;
     float key[KR];
     int cj[KR];
@@ -1534,9 +1535,6 @@ int knn_run(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, 
     if (collect) {
         CollectArgs ca{};
         ca.Q = Qs;
-        ca.R = Rs;
-        ca.Q0 = Q;
-        ca.R0 = R;
         ca.d = p.d;
         ca.metric = p.metric;
         ca.rows = b.flag1;
@@ -1554,6 +1552,11 @@ int knn_run(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, 
         ca.eps = ra.split_eps;
         ca.eps_abs = ra.split_abs;
         ca.cosine_eps = ra.split_cosine_eps;
+        ca.packed32 = b.packed;
+        ca.norms32 = b.norms;
+        ca.dh = p.dh;
+        ca.fp32_eps = ra.eps_coef;
+        ca.fp32_cosine_eps = ra.cosine_eps;
         ca.kc = b.counters;
         {
             ScopedTimer timer("screen_escalate", stream);

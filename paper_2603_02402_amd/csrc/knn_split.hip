@@ -8,6 +8,7 @@
 
 #include "rsc_internal.hpp"
 #include "screen_common.hpp"
+#include "screen_fp32.hpp"
 #include "screen_split_grid.hpp"
 
 namespace rsc {
@@ -108,13 +109,88 @@ __global__ __launch_bounds__(256) void k_pack_split(const float *__restrict__ R,
     if (__ballot(wide) != 0ull && lane == 0) atomicOr(&counters->wide, 1);
 }
 
+// Largest key (times `unit`) of a reference that can lie within dm of row `row`:
+// the key's error bound added; Y bounds the norm of such a reference.
+__device__ __forceinline__ float key_limit(const CollectArgs &a, double dm, int64_t row, double ymax, double M, double eps,
+                                           double eps_abs, double cosine_eps, double unit) {
+    const bool cosine = a.metric == RSC_COSINE;
+    double xx = 0.0;
+    for (int t = 0; t < a.d; ++t) xx += (double)a.Q[row * a.d + t] * (double)a.Q[row * a.d + t];
+    const double xn = sqrt(xx) * (1.0 + 1e-12), Y = fmin(ymax, (xn + sqrt(dm)) * (1.0 + 1e-9));
+    const double t = cosine ? 2.0 * dm - 1.0 + cosine_eps
+                            : dm - xx + eps * (2.0 * xn * Y + Y * Y) + eps_abs * M * (2.0 * xn + Y);
+    return (float)((t + 1e-6 * (fabs(t) + (cosine ? 0.0 : 1e-6 * xx))) * unit);
+}
+
+// Files a reference under listed row i.
+__device__ __forceinline__ void file(const CollectArgs &a, int i, int32_t ref, float key, float &limit) {
+    const int at = atomicAdd(&a.found[i], 1);
+    if (at < a.width) {
+        a.out_idx[(int64_t)i * a.width + at] = ref;
+        a.out_key[(int64_t)i * a.width + at] = key;
+    } else {
+        limit = -INFINITY;  // too many: the row is scanned exhaustively
+    }
+}
+
+// The collection on inputs marked wide, in the FP32 chain's keys: the wave's 32
+// listed rows (this lane's: entry i, row `row` or -1) against packed blocks
+// [b0, b1).  Four blocks share a reading of the query's values.  8192 rows
+// against 100k x 50: 2.2 ms, where comparing each pair in float64 took 174.
+__device__ __forceinline__ void collect_wide(const CollectArgs &a, int i, int64_t row, int b0, int b1) {
+    const int lane = threadIdx.x & (kWave - 1), h = lane >> 5;
+    const int folded = norm_folded(a.dh) ? 1 : 0, S4 = packed_s4(a.dh), steps = a.dh + folded;
+    const double ymax = (double)__uint_as_float(a.kc->max_norm_bits) * (1.0 + 1e-6);
+    // keys that could leave float32's range bound nothing: every listed row is scanned exhaustively
+    if (!(fmax(ymax, (double)__uint_as_float(a.kc->query_norm_bits)) < 0x1p62)) {
+        if (row >= 0 && b0 == 0 && h == 0) a.found[i] = a.width + 1;
+        return;
+    }
+    float limit =
+        row >= 0 ? key_limit(a, a.bound[i], row, ymax, 0.0, a.fp32_eps, 0.0, a.fp32_cosine_eps, 1.0) + 0x1p-140f : -INFINITY;
+    const float *x = a.Q + (row >= 0 ? row : 0) * a.d;
+    const f32x4 *A = static_cast<const f32x4 *>(a.packed32) + lane;
+    constexpr int NB = 4;
+    for (int b = b0; b < b1; b += NB) {
+        f32x16 acc[NB] = {};
+        for (int s4 = 0; s4 < S4; ++s4) {
+            float q[4];
+            f32x4 y[NB];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int s = 4 * s4 + u, t = h * a.dh + s - folded;
+                q[u] = 0.f;
+                if (folded && s == 0)
+                    q[u] = h == 0 ? 1.f : 0.f;
+                else if (s < steps && t < a.d)
+                    q[u] = -2.f * x[t];
+            }
+#pragma unroll
+            for (int j = 0; j < NB; ++j) y[j] = A[((int64_t)min(b + j, b1 - 1) * S4 + s4) * kWave];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int j = 0; j < NB; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(y[j][u], q[u], acc[j], 0, 0, 0);
+        }
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            if (b + j >= b1) break;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const float key = folded ? acc[j][v] : acc[j][v] + a.norms32[(int64_t)(b + j) * 32 + h * 16 + v];
+                const int ref = (b + j) * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
+                if (key <= limit && ref < a.nr) file(a, i, ref, key, limit);
+            }
+        }
+    }
+}
+
 // Every reference that can lie within bound[i] of listed row i (Euclidean:
 // squared): its key is at most bound - ||x||^2 plus the key's error bound.  A
 // key passes for little more than the row's m neighbours, so the pass is the
 // bare contraction (8192 rows against 1M: 1.7 ms; 45 rows: 60 us, where
 // screening them again 64 wide over 16 ranges took 4.2 ms).  Work units are
-// (256 listed rows, a range of blocks), enough ranges for every CU.  Inputs
-// marked wide are compared in float64 instead.
+// (256 listed rows, a range of blocks), enough ranges for every CU.
 template <int Q, int TC>
 __global__ __launch_bounds__((SplitShape<Q, TC, 16>::NW * kWave), (SplitShape<Q, TC, 16>::W)) void k_split_collect(
     CollectArgs a) {
@@ -124,36 +200,15 @@ __global__ __launch_bounds__((SplitShape<Q, TC, 16>::NW * kWave), (SplitShape<Q,
     const int n = min(*a.nrows, a.cap);
     if (n == 0) return;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6, h = lane >> 5;
-    const bool cosine = a.metric == RSC_COSINE;
+    constexpr int QG = S::NW * 32;
+    const int tiles = (n + QG - 1) / QG;
+    const int ranges = (int)min((int64_t)((gridDim.x + tiles - 1) / tiles), a.nblk);
+    const int per = (int)((a.nblk + ranges - 1) / ranges);
     if (a.kc->wide) {
-        for (int i = 0; i < n; ++i) {
-            const float *x = a.Q0 + (int64_t)a.rows[i] * a.d;
-            const double bound = a.bound[i];
-            double cxx = 0.0;
-            if (cosine)
-                for (int t = 0; t < a.d; ++t) cxx = __dadd_rn(cxx, __dmul_rn((double)x[t], (double)x[t]));
-            for (int64_t j = (int64_t)blockIdx.x * blockDim.x + tid; j < a.nr; j += (int64_t)gridDim.x * blockDim.x) {
-                const float *y = a.R0 + j * a.d;
-                double v;
-                if (cosine) {
-                    double sxy = 0.0, syy = 0.0;
-                    for (int t = 0; t < a.d; ++t) {
-                        sxy = __dadd_rn(sxy, __dmul_rn((double)x[t], (double)y[t]));
-                        syy = __dadd_rn(syy, __dmul_rn((double)y[t], (double)y[t]));
-                    }
-                    v = (cxx == 0.0 || syy == 0.0)
-                            ? 1.0
-                            : __dsub_rn(1.0, __ddiv_rn(sxy, __dmul_rn(__dsqrt_rn(cxx), __dsqrt_rn(syy))));
-                } else {
-                    v = exact_d2(x, y, a.d);
-                }
-                if (!(v <= bound)) continue;
-                const int at = atomicAdd(&a.found[i], 1);
-                if (at < a.width) {
-                    a.out_idx[(int64_t)i * a.width + at] = (int32_t)j;
-                    a.out_key[(int64_t)i * a.width + at] = NAN;  // no screened key
-                }
-            }
+        for (int u = blockIdx.x; u < tiles * ranges; u += gridDim.x) {
+            const int b0 = u % ranges * per, b1 = (int)min(a.nblk, (int64_t)b0 + per);
+            const int i = u / ranges * QG + wave * 32 + (lane & 31);
+            collect_wide(a, i, i < n ? (int64_t)a.rows[i] : -1, b0, b1);
         }
         return;
     }
@@ -162,26 +217,13 @@ __global__ __launch_bounds__((SplitShape<Q, TC, 16>::NW * kWave), (SplitShape<Q,
     const double unit = ldexp(1.0, 2 * e);
     const double ymax = (double)__uint_as_float(a.kc->max_norm_bits) * (1.0 + 1e-6);
     const double M = fmax((double)__uint_as_float(a.kc->query_norm_bits), ymax);
-    constexpr int QG = S::NW * 32;
-    const int tiles = (n + QG - 1) / QG;
-    const int ranges = (int)min((int64_t)((gridDim.x + tiles - 1) / tiles), a.nblk);
-    const int per = (int)((a.nblk + ranges - 1) / ranges);
     for (int u = blockIdx.x; u < tiles * ranges; u += gridDim.x) {
         const int b0 = u % ranges * per, b1 = (int)min(a.nblk, (int64_t)b0 + per);
         const int i = u / ranges * QG + wave * 32 + (lane & 31);
         const int64_t row = i < n ? (int64_t)a.rows[i] : -1;
         SplitQuery<Q, TC> qop;
         qop.load(a.Q, a.d, row, h, scale);
-        float limit = -INFINITY;
-        if (row >= 0) {
-            const double dm = a.bound[i];
-            double xx = 0.0;
-            for (int t = 0; t < a.d; ++t) xx += (double)a.Q[row * a.d + t] * (double)a.Q[row * a.d + t];
-            const double xn = sqrt(xx) * (1.0 + 1e-12), Y = fmin(ymax, (xn + sqrt(dm)) * (1.0 + 1e-9));
-            const double t = cosine ? 2.0 * dm - 1.0 + a.cosine_eps
-                                    : dm - xx + a.eps * (2.0 * xn * Y + Y * Y) + a.eps_abs * M * (2.0 * xn + Y);
-            limit = (float)((t + 1e-6 * (fabs(t) + (cosine ? 0.0 : 1e-6 * xx))) * unit);
-        }
+        float limit = row >= 0 ? key_limit(a, a.bound[i], row, ymax, M, a.eps, a.eps_abs, a.cosine_eps, unit) : -INFINITY;
         split_stream<Q, TC, S::PH>(
             static_cast<const char *>(a.packed), max(0, b1 - b0), [&](int j) { return b0 + j; }, ring0, ring1,
             [&](const f16x8(&A)[2 * Q + TC], int blk) {
@@ -193,15 +235,7 @@ __global__ __launch_bounds__((SplitShape<Q, TC, 16>::NW * kWave), (SplitShape<Q,
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     const int slot = blk * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
-                    if (acc[v] <= limit && slot < a.nr) {
-                        const int at = atomicAdd(&a.found[i], 1);
-                        if (at < a.width) {
-                            a.out_idx[(int64_t)i * a.width + at] = a.ref_map ? a.ref_map[slot] : slot;
-                            a.out_key[(int64_t)i * a.width + at] = acc[v];
-                        } else {
-                            limit = -INFINITY;  // too many: the row is scanned exhaustively
-                        }
-                    }
+                    if (acc[v] <= limit && slot < a.nr) file(a, i, a.ref_map ? a.ref_map[slot] : slot, acc[v], limit);
                 }
             });
     }

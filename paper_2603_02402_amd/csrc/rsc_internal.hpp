@@ -231,8 +231,7 @@ int split_pack(const float *R, const float *nrow, int64_t nr, int d, int64_t nbl
 int split_screen(const scr::ScreenArgs &a, int half_width, const char *name, hipStream_t s);
 // All references within a bound of each listed row (knn_split.hip).
 struct CollectArgs {
-    const float *Q, *R;      // as screened (unit rows for the cosine metric)
-    const float *Q0, *R0;    // as given
+    const float *Q;          // as screened (unit rows for the cosine metric)
     int d, metric;
     const int32_t *rows, *nrows;  // the listed rows and their count, at most cap
     int cap;
@@ -245,6 +244,11 @@ struct CollectArgs {
     const int32_t *ref_map;
     int64_t nr, nblk;
     double eps, eps_abs, cosine_eps;
+    // inputs marked wide: the references packed for the FP32 chain (row order) and its keys' error bounds
+    const void *packed32;
+    const float *norms32;
+    int dh;
+    double fp32_eps, fp32_cosine_eps;
     const KnnCounters *kc;
 };
 int split_collect(const CollectArgs &a, hipStream_t s);
