@@ -61,12 +61,15 @@ constexpr int kMaxKLowp = 63;
 // 0.46 without (in a Morton order); at 10k rows 0.39 against 0.21; rectangular:
 // the pairs of that square.  The BF16 form's rows (64 candidates a query) take
 // the same path from there: 16.5k rows 1.40 -> 0.72 ms, 40k 2.25 -> 1.02, 500k
-// 44.4 -> 14.6 (100 clusters, with their graph).  Rows without any clusters
-// gain nothing from bounds and pay for the merge of longer lists by two waves
-// per SIMD where the plain BF16 screen has three: 300k rows 30 -> 33 ms, at
-// d = 100 25 -> 38 (200k).
+// 44.4 -> 14.6 (100 clusters, with their graph).  Rows without clusters gain
+// nothing from bounds; the BF16 form finds that out (knn_run_rounded).
 constexpr int64_t kPruneRows = 16384;
 constexpr double kPrunePairs = 2.5e8;
+// Foreign queries from which the BF16 form is pruned: fewer do not pay for ordering
+// the references.  In ms, plain and pruned, rows in 100 clusters: 2500 queries of
+// 100k rows 0.89, 1.05; 3500 1.24, 1.10; 3500 of 500k 2.27, 2.71; 5000 2.70, 2.70;
+// 5000 of 1M 3.97, 4.82; 8000 5.01, 4.72.
+inline int64_t prune_queries_bf16(int64_t nr) { return std::max<int64_t>(3000, 2500 + nr / 200); }
 // Workgroups the split screen asks for before it stops splitting the
 // references: fewer leave CUs idle, more multiply the candidate lists the
 // rerank reads (10k rows: screen + rerank 0.34 ms at 128, 0.47 at 256, 0.74
@@ -230,6 +233,9 @@ __global__ void k_init_counters(KnnCounters *c) {
         c->rescanned = 0;
         c->query_norm_bits = 0u;
         c->wide = 0;
+        c->verdict = 0;
+        c->sampled = 0;
+        c->sampled_segments = 0ull;
         c->visited = 0ull;
     }
 }
@@ -391,7 +397,7 @@ __global__ __launch_bounds__(256) void k_rerank(RerankArgs a) {
     const double ymax = (double)__uint_as_float(a.counters->max_norm_bits) * (1.0 + 1e-6);
     const bool cosine = a.metric == RSC_COSINE;
     // units and error bound of the screened keys
-    const bool split = a.split && a.counters->wide == 0;
+    const bool split = a.split && a.counters->wide == 0 && a.counters->verdict != kPlain;
     const double kscale = split ? ldexp(1.0, -2 * scr::split_exponent(a.counters)) : 1.0;
     const double eps_coef = split ? a.split_eps : a.eps_coef;
     const double cosine_eps = split ? a.split_cosine_eps : a.cosine_eps;
@@ -604,7 +610,7 @@ __global__ __launch_bounds__(256) void k_rerank_lean(RerankArgs a) {
     const double xn = sqrt(xx) * (1.0 + 1e-12);
     const double ymax = (double)__uint_as_float(a.counters->max_norm_bits) * (1.0 + 1e-6);
     const bool cosine = a.metric == RSC_COSINE;
-    const bool split = a.split && a.counters->wide == 0;
+    const bool split = a.split && a.counters->wide == 0 && a.counters->verdict != kPlain;
     const double kscale = split ? ldexp(1.0, -2 * scr::split_exponent(a.counters)) : 1.0;
     const double eps_coef = split ? a.split_eps : a.eps_coef;
     const double cosine_eps = split ? a.split_cosine_eps : a.cosine_eps;
@@ -1018,6 +1024,13 @@ void knn_split_bounds(RerankArgs &ra) {
     ra.split_cosine_eps = cosine_eps_of(ra.split_eps);
 }
 
+// The largest norm of a rectangular problem's queries.
+static int query_norms(const KnnPlan &p, const float *Q, const KnnBuffers &b, hipStream_t stream) {
+    hipLaunchKernelGGL(k_norms, dim3((unsigned)((p.nq + norm_rows(p.d) - 1) / norm_rows(p.d))), dim3(kNormThreads), 0,
+                       stream, Q, p.nq, p.d, nullptr, &b.counters->query_norm_bits);
+    return launch_status("query norms");
+}
+
 int knn_prep_fp32(const KnnPlan &p, const float *R, const float *Q, const KnnBuffers &b, const int32_t *blk_sample,
                   const int64_t *boff, const int64_t *soff, hipStream_t stream) {
     const int s4 = packed_s4(p.dh);
@@ -1031,9 +1044,7 @@ int knn_prep_fp32(const KnnPlan &p, const float *R, const float *Q, const KnnBuf
     hipLaunchKernelGGL(k_pack, dim3(g1), dim3(256), 0, stream, R, b.nrow, p.nr, p.d, p.dh, s4,
                        norm_folded(p.dh) ? 1 : 0, p.nblk, reinterpret_cast<f32x4 *>(b.packed), b.norms, blk_sample,
                        boff, soff, nullptr);
-    if (Q && p.nq > 0)
-        hipLaunchKernelGGL(k_norms, dim3((unsigned)((p.nq + norm_rows(p.d) - 1) / norm_rows(p.d))), dim3(kNormThreads), 0,
-                           stream, Q, p.nq, p.d, nullptr, &b.counters->query_norm_bits);
+    if (Q && p.nq > 0) return query_norms(p, Q, b, stream);
     return launch_status("prep_pack");
 }
 
@@ -1190,6 +1201,7 @@ int knn_plan(int64_t nq, int64_t nr, int d, int k, const rsc_knn_opts *opts, boo
     plan->resid = resid;
     plan->pruned = (precision == RSC_FP32 || (precision == RSC_BF16 && lowp_ranges == 1)) && nr >= kPruneRows &&
                    (double)nq * (double)nr >= kPrunePairs;
+    if (precision == RSC_BF16 && !self_mode && nq < prune_queries_bf16(nr)) plan->pruned = false;
     const bool split = precision == RSC_FP32 || plan->pruned;
     // the split screen's workgroups of 8 waves fill a CU each; the others run four of 4 waves
     plan->splits = split
@@ -1218,10 +1230,16 @@ int knn_plan(int64_t nq, int64_t nr, int d, int k, const rsc_knn_opts *opts, boo
     return RSC_OK;
 }
 
+// Query tiles of the pruned screen.
+static int64_t query_tiles(const KnnPlan &p) {
+    const int64_t qg = split_queries_per_group(p.d, p.half);
+    return (p.nq + qg - 1) / qg;
+}
+
 size_t knn_workspace(const KnnPlan &p, void *ws, KnnBuffers *out) {
     Carver cv(ws);
     KnnBuffers b{};
-    const bool fp32 = p.precision == RSC_FP32 || p.pruned;  // (the BF16 form's large problems share the path)
+    const bool fp32 = p.precision == RSC_FP32, rounded = !fp32 && p.pruned;
     const int s4 = packed_s4(p.dh);
     const int64_t esc_rows = p.precision == RSC_FP32 ? std::min<int64_t>(p.nq, kEscalateCap) : 0;
     b.counters = cv.take<KnnCounters>(1);
@@ -1231,6 +1249,12 @@ size_t knn_workspace(const KnnPlan &p, void *ws, KnnBuffers *out) {
         b.norms = cv.take<float>(norm_folded(p.dh) ? 1 : (size_t)p.nblk * 32);
         // (the pruned screen loads whole segments: the last one may reach past the blocks)
         b.split = cv.take<char>(split_packed_bytes(p.d, p.nblk + (p.pruned ? spatial_seg_blocks(p.nblk) : 0)));
+    } else if (rounded) {
+        b.nrow = cv.take<float>((size_t)p.nr);
+        // one or the other screen's packing
+        b.split = cv.take<char>(std::max(rounded_packed_bytes(p.d, p.nblk + spatial_seg_blocks(p.nblk)),
+                                         lowp_packed_bytes(p.precision, p.nblk, p.d)));
+        b.packed = static_cast<float *>(b.split);
     } else {
         b.packed = reinterpret_cast<float *>(cv.take<char>(lowp_packed_bytes(p.precision, p.nblk, p.d)));
         b.norms = cv.take<float>((size_t)p.nblk * 32);
@@ -1245,7 +1269,7 @@ size_t knn_workspace(const KnnPlan &p, void *ws, KnnBuffers *out) {
     b.esc_key = cv.take<float>((size_t)std::max<int64_t>(esc_rows, 1) * kEscalateSplits * kEscalateWidth);
     b.esc_bound = cv.take<double>((size_t)std::max<int64_t>(esc_rows, 1));
     b.esc_found = cv.take<int32_t>((size_t)std::max<int64_t>(esc_rows, 1));
-    if (p.metric == RSC_COSINE || (p.precision == RSC_BF16 && p.pruned)) {  // the rows as the screen sees them
+    if (p.metric == RSC_COSINE || rounded) {  // the rows as the screen sees them
         b.rn = cv.take<float>((size_t)p.nr * p.d);
         b.qn = p.self_mode ? b.rn : cv.take<float>((size_t)std::max<int64_t>(p.nq, 1) * p.d);
     }
@@ -1304,6 +1328,121 @@ int round_inputs(const KnnPlan &p, const float *Q, const float *R, const KnnBuff
     run(R, p.nr * p.d, b.rn);
     if (!p.self_mode && p.nq > 0) run(Q, p.nq * p.d, b.qn);
     return launch_status("round to BF16");
+}
+
+// The row count on the device; spatial order of a pruned problem's references (and of foreign queries).
+int order_rows(const KnnPlan &p, const float *Qs, const float *Rs, const KnnBuffers &b, hipStream_t stream) {
+    int st;
+    hipLaunchKernelGGL(k_set_i32, dim3(1), dim3(64), 0, stream, b.qcount, (int32_t)p.nq);
+    if ((st = launch_status("set query count")) != RSC_OK) return st;
+    if ((st = spatial_refs(Rs, b.nrow, p.nr, p.d, p.precision == RSC_BF16, b.sp, b.counters, stream)) != RSC_OK) return st;
+    if (p.self_mode) return RSC_OK;
+    return spatial_queries(Qs, p.nq, p.nr, p.d, split_queries_per_group(p.d, p.half), b.sp, b.counters, stream);
+}
+
+PrunedArgs pruned_args(const KnnPlan &p, const ScreenArgs &s, const KnnBuffers &b) {
+    PrunedArgs pa{};
+    pa.s = s;
+    pa.segments = b.sp.seg_packed;
+    pa.nseg = b.sp.nseg;
+    while ((1 << pa.seg_shift) < b.sp.seg_blocks) ++pa.seg_shift;
+    pa.own = p.self_mode ? nullptr : b.sp.own;
+    pa.eps = split_eps_coefficient(p.d);
+    pa.counters = b.counters;
+    pa.rounded = p.precision == RSC_BF16;
+    return pa;
+}
+
+// The BF16 form from kPruneRows references on: the pruned screen over rounded
+// rows, or, where it finds that bounds do not help or the norms spread too far,
+// the plain BF16 screen over the same order (its launches end at once unless that
+// is so).  Rerank without a certificate.  Rows without clusters, in ms, in a plain
+// screen of Morton order / pruned / by verdict: 300k rows, d = 50: 30.0 / 33.9 /
+// 26.4; 200k, d = 100: 24.7 / 38.3 / 23.3; 40k, d = 50: 2.53 / 2.63 / 1.92; 24,000
+// queries of 500k rows: 7.0 / 10.2 / 7.4.
+int knn_run_rounded(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, float *out_dist,
+                    const KnnBuffers &b, hipStream_t stream) {
+    int st;
+    const bool cosine = p.metric == RSC_COSINE;
+    if (cosine && (st = normalize_inputs(p, Q, R, b, stream)) != RSC_OK) return st;
+    if ((st = round_inputs(p, cosine ? b.qn : Q, cosine ? b.rn : R, b, stream)) != RSC_OK) return st;
+    if ((st = knn_norms(b.rn, p.nr, p.d, b.nrow, b.counters, stream)) != RSC_OK) return st;
+    if (!p.self_mode && (st = query_norms(p, b.qn, b, stream)) != RSC_OK) return st;
+    if ((st = order_rows(p, b.qn, b.rn, b, stream)) != RSC_OK) return st;
+    {
+        ScopedTimer timer("pack_split", stream);
+        if ((st = split_pack(b.rn, b.nrow, p.nr, p.d, p.nblk, b.split, nullptr, nullptr, nullptr, b.sp.rperm, p.nr,
+                             b.counters, stream, true)) != RSC_OK)
+            return st;
+    }
+    ScreenArgs sa{};
+    sa.Q = b.qn;
+    sa.nq = p.nq;
+    sa.qlist = p.self_mode ? b.sp.rperm : b.sp.qperm;
+    sa.qcount = b.qcount;
+    sa.qcap = (int)p.nq;
+    sa.Ap = b.split;
+    sa.nblk = p.nblk;
+    sa.d = p.d;
+    sa.P = p.splits;
+    sa.cand_idx = b.cand_idx;
+    sa.cand_key = b.cand_key;
+    sa.kc = b.counters;
+    {
+        ScopedTimer timer("screen_bf16", stream);
+        ScreenArgs ss = sa;
+        ss.ref_map = b.sp.rperm;
+        PrunedArgs pa = pruned_args(p, ss, b);
+        // Whether bounds help is sampled where that pays: with fewer than 256 blocks
+        // to a range a tile has screened most of them by the time the samples know
+        // (16.5k rows without clusters, 4 ranges of 129: 1.12 ms pruned, 1.23 with the
+        // verdict; 25k, 3 of 260: 1.71, 1.38); foreign queries in one round of
+        // workgroups the same (16,384 of 500k rows: 5.09 and 5.20; 24,000: 10.1 and
+        // 7.4); at 9 steps the plain screen has one workgroup per CU and gains nothing
+        // (d = 128, 200k rows: 44.6 pruned, 46.4 plain; d = 126: 44.6, 25.1).
+        // Foreign queries' tiles span several clusters, but their lists settle early:
+        // 24,000 of 500k rows in 100 clusters 4.8 ms pruned, 6.0 plain.
+        const int64_t tiles = query_tiles(p);
+        if (p.nblk / p.splits >= 256 && lowp_steps(p.precision, p.d) <= 8 && (p.self_mode || 4 * tiles > scr::kCUs)) {
+            pa.samples = (int)std::min<int64_t>(scr::kSampleTiles, tiles);
+            pa.plain_over = (int)((p.self_mode ? 0.55 : 0.95) * b.sp.nseg / p.splits);
+        }
+        if ((st = split_screen_pruned(pa, p.half, "screen_bf16_pruned", stream)) != RSC_OK) return st;
+        // (as in knn_run_lowp, references in the queries' order for a single range of one matrix)
+        const int32_t *rmap = p.self_mode && p.splits == 1 ? b.sp.rperm : nullptr;
+        if ((st = lowp_prepare(p, b.qn, b.rn, b.packed, nullptr, nullptr, nullptr, rmap, stream, b.counters)) != RSC_OK)
+            return st;
+        sa.only_plain = 1;
+        sa.rotate = rmap ? 1 : 0;
+        const int plain_qg = lowp_queries_per_group(p.precision, p.d);
+        if ((st = lowp_screen(p, sa, (unsigned)((p.nq + plain_qg - 1) / plain_qg), stream)) != RSC_OK) return st;
+        if (rmap && (st = lowp_unmap_rows(p, b, rmap, stream, b.counters)) != RSC_OK) return st;
+    }
+    RerankArgs ra{};
+    ra.Q = Q;
+    ra.nq = p.nq;
+    ra.qlist = sa.qlist;
+    ra.qcount = sa.qcount;
+    ra.qcap = sa.qcap;
+    ra.R = R;
+    ra.d = p.d;
+    ra.k = p.k;
+    ra.S = p.half;
+    ra.KP = p.half;
+    ra.P = 2 * p.splits;
+    ra.self_mode = p.self_mode ? 1 : 0;
+    ra.certify = 0;
+    ra.metric = p.metric;
+    ra.cand_idx = b.cand_idx;
+    ra.cand_key = b.cand_key;
+    ra.counters = b.counters;
+    ra.flag_out = b.flag1;
+    ra.flag_count = &b.counters->flagged;
+    ra.out_idx = out_idx;
+    ra.out_dist = out_dist;
+    ra.split = 1;  // (keys times the squared scale, unless marked)
+    ra.eps_coef = ra.cosine_eps = ra.split_eps = ra.split_cosine_eps = 1.0;
+    return knn_launch_rerank(ra, p.nq, "rerank", stream);
 }
 
 // Reduced-precision form: screen, then rerank without a certificate.
@@ -1401,39 +1540,33 @@ int knn_run(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, 
             set_error("internal: row lists need the FP32 path");
             return RSC_ERR_UNSUPPORTED;
         }
-        if (!p.pruned) return knn_run_lowp(p, Q, R, out_idx, out_dist, b, stream);
+        return p.pruned ? knn_run_rounded(p, Q, R, out_idx, out_dist, b, stream)
+                        : knn_run_lowp(p, Q, R, out_idx, out_dist, b, stream);
     }
     int st;
     const bool cosine = p.metric == RSC_COSINE;
-    const bool rounded = p.precision == RSC_BF16;
     if (cosine && (st = normalize_inputs(p, Q, R, b, stream)) != RSC_OK) return st;
-    if (rounded && (st = round_inputs(p, cosine ? b.qn : Q, cosine ? b.rn : R, b, stream)) != RSC_OK) return st;
-    const float *Qs = cosine || rounded ? b.qn : Q;  // what the screen sees
-    const float *Rs = cosine || rounded ? b.rn : R;
+    const float *Qs = cosine ? b.qn : Q;  // what the screen sees
+    const float *Rs = cosine ? b.rn : R;
     if ((st = knn_prep_fp32(p, Rs, p.self_mode ? nullptr : Qs, b, nullptr, nullptr, nullptr, stream)) != RSC_OK)
         return st;
     // Large problems are screened in a spatial order with its segments' bounds.
-    // (Under stream capture the exact path screens every pair instead; the BF16
-    // form, which has no certificate, sorts in pieces that record kernels alone.)
+    // (Under stream capture every pair is screened instead.)
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    const bool captured = p.pruned && !rounded && hipStreamIsCapturing(stream, &capture) == hipSuccess &&
+    const bool captured = p.pruned && hipStreamIsCapturing(stream, &capture) == hipSuccess &&
                           capture != hipStreamCaptureStatusNone;
     const bool pruned = p.pruned && !captured && !qlist && p.nq > 0;
     const int32_t *ref_map = nullptr;
     if (pruned) {
-        if ((st = spatial_refs(Rs, b.nrow, p.nr, p.d, rounded, b.sp, b.counters, stream)) != RSC_OK) return st;
-        if (!p.self_mode && (st = spatial_queries(Qs, p.nq, p.nr, p.d, split_queries_per_group(p.d, p.half), b.sp,
-                                                  b.counters, stream)) != RSC_OK)
-            return st;
+        if ((st = order_rows(p, Qs, Rs, b, stream)) != RSC_OK) return st;
         ref_map = b.sp.rperm;
         qlist = p.self_mode ? b.sp.rperm : b.sp.qperm;
-        hipLaunchKernelGGL(k_set_i32, dim3(1), dim3(64), 0, stream, b.qcount, (int32_t)p.nq);
         qcount = b.qcount;
     }
     {
         ScopedTimer timer("pack_split", stream);
         if ((st = split_pack(Rs, b.nrow, p.nr, p.d, p.nblk, b.split, nullptr, nullptr, nullptr, ref_map, p.nr,
-                             b.counters, stream, rounded)) != RSC_OK)
+                             b.counters, stream)) != RSC_OK)
             return st;
     }
     if (p.nq == 0) return RSC_OK;
@@ -1459,16 +1592,7 @@ int knn_run(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, 
     ss.Ap = b.split;
     ss.ref_map = ref_map;
     if (pruned) {
-        PrunedArgs pa{};
-        pa.s = ss;
-        pa.segments = b.sp.seg_packed;
-        pa.nseg = b.sp.nseg;
-        while ((1 << pa.seg_shift) < b.sp.seg_blocks) ++pa.seg_shift;
-        pa.own = p.self_mode ? nullptr : b.sp.own;
-        pa.eps = split_eps_coefficient(p.d);
-        pa.visited = &b.counters->visited;
-        pa.rounded = rounded;
-        st = split_screen_pruned(pa, p.half, rounded ? "screen_bf16" : "screen_fp32", stream);
+        st = split_screen_pruned(pruned_args(p, ss, b), p.half, "screen_fp32", stream);
     } else {
         st = split_screen(ss, p.half, "screen_fp32", stream);
     }
@@ -1491,7 +1615,7 @@ int knn_run(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, 
     ra.KP = p.half;
     ra.P = 2 * p.splits;
     ra.self_mode = p.self_mode ? 1 : 0;
-    ra.certify = rounded ? 0 : 1;  // (keys of rounded rows bound nothing)
+    ra.certify = 1;
     ra.metric = p.metric;
     ra.cosine_eps = cosine_eps_of(eps_coef);
     ra.cand_idx = b.cand_idx;
@@ -1503,12 +1627,6 @@ int knn_run(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, 
     ra.out_idx = out_idx;
     ra.out_dist = out_dist;
     knn_split_bounds(ra);
-    if (rounded) {
-        // no certificate: the error statistic is relative, as in knn_run_lowp
-        ra.eps_coef = ra.cosine_eps = ra.split_eps = ra.split_cosine_eps = 1.0;
-        ra.split_abs = 0.0;
-        return knn_launch_rerank(ra, p.nq, "rerank", stream);
-    }
     const int esc_cap = (int)std::min<int64_t>(p.nq, kEscalateCap);
     const bool collect = (p.self_mode ? p.k - 1 : p.k) <= kLeanAnswer;
     if (collect) {

@@ -93,7 +93,8 @@ __device__ inline float e4m3_value(uint32_t code) {
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_pack_bf16(const float *__restrict__ R, int64_t nr, int d, int KS,
                                                    int64_t nblk, const int32_t *__restrict__ rmap,
-                                                   i32x4 *__restrict__ Ap) {
+                                                   i32x4 *__restrict__ Ap, const KnnCounters *__restrict__ gate) {
+    if (gate && gate->wide == 0 && gate->verdict != kPlain) return;
     const int64_t total = nblk * KS * kWave;
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
          e += (int64_t)gridDim.x * blockDim.x) {
@@ -439,7 +440,9 @@ __device__ __noinline__ ResidCodes<KS> resid_query_codes(const float *__restrict
 // Candidate lists hold packed slots: turn them into row ids through the
 // packing's row map (slots past the rows, never entered, and -1 stay).
 __global__ __launch_bounds__(256) void k_rows_unmap(int32_t *__restrict__ cand, int64_t count,
-                                                    const int32_t *__restrict__ rmap, int64_t nr) {
+                                                    const int32_t *__restrict__ rmap, int64_t nr,
+                                                    const KnnCounters *__restrict__ gate) {
+    if (gate && gate->wide == 0 && gate->verdict != kPlain) return;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count;
          i += (int64_t)gridDim.x * blockDim.x) {
         const int32_t v = cand[i];
@@ -522,6 +525,8 @@ __global__ __launch_bounds__(256, 3) void k_screen_lowp(ScreenArgs a) {
     const int lane = tid & (kWave - 1), wave = tid >> 6;
     const int h = lane >> 5, c = lane & 31;
     const int p = blockIdx.y;
+    if constexpr (PREC == RSC_BF16)
+        if (a.only_plain && a.kc->wide == 0 && a.kc->verdict != kPlain) return;  // the pruned screen answered
     const int64_t blk_per = (a.nblk + a.P - 1) / a.P;
     const int64_t blk0 = (int64_t)p * blk_per;
     const int64_t blk1 = std::min<int64_t>(a.nblk, blk0 + blk_per);
@@ -742,14 +747,14 @@ size_t lowp_packed_bytes(int precision, int64_t nblk, int d) {
 }
 
 int lowp_prepare(const KnnPlan &p, const float *Q, const float *R, void *packed, float *norms, float *scal,
-                 uint32_t *amax, const int32_t *rmap, hipStream_t stream) {
+                 uint32_t *amax, const int32_t *rmap, hipStream_t stream, const KnnCounters *gate) {
     const int ks = lowp_steps(p.precision, p.d);
     const int64_t tot = p.nblk * ks * kWave;
-    const unsigned g1 = (unsigned)std::min<int64_t>((tot + 255) / 256, 65536);
+    const unsigned g1 = (unsigned)std::min<int64_t>((tot + 255) / 256, gate ? 2048 : 65536);  // (gated: most often idle)
     ScopedTimer timer("prep_pack", stream);
     if (p.precision == RSC_BF16) {
         hipLaunchKernelGGL(k_pack_bf16, dim3(g1), dim3(256), 0, stream, R, p.nr, p.d, ks, p.nblk, rmap,
-                           static_cast<i32x4 *>(packed));
+                           static_cast<i32x4 *>(packed), gate);
         return launch_status("pack_bf16");
     }
     // FP8: per-dimension absmax of references (and of queries when distinct)
@@ -800,10 +805,11 @@ int lowp_prepare_resid(const KnnPlan &p, const float *R, const KnnBuffers &b, hi
     return launch_status("pack_fp8_resid");
 }
 
-int lowp_unmap_rows(const KnnPlan &p, const KnnBuffers &b, const int32_t *rmap, hipStream_t stream) {
+int lowp_unmap_rows(const KnnPlan &p, const KnnBuffers &b, const int32_t *rmap, hipStream_t stream,
+                    const KnnCounters *gate) {
     const int64_t count = p.nq * p.splits * p.screen;
-    const unsigned g = (unsigned)std::min<int64_t>((count + 255) / 256, 65536);
-    hipLaunchKernelGGL(k_rows_unmap, dim3(g), dim3(256), 0, stream, b.cand_idx, count, rmap, p.nr);
+    const unsigned g = (unsigned)std::min<int64_t>((count + 255) / 256, gate ? 2048 : 65536);
+    hipLaunchKernelGGL(k_rows_unmap, dim3(g), dim3(256), 0, stream, b.cand_idx, count, rmap, p.nr, gate);
     return launch_status("rows_unmap");
 }
 
@@ -817,16 +823,17 @@ int lowp_unmap(const KnnPlan &p, const KnnBuffers &b, hipStream_t stream) {
 int lowp_screen(const KnnPlan &p, const scr::ScreenArgs &a, unsigned gx, hipStream_t s) {
     const int ks = lowp_steps(p.precision, p.d);
     if (p.precision == RSC_BF16) {
+        const char *name = a.only_plain ? "screen_bf16_plain" : "screen_bf16";
         switch (ks) {
-            case 1: return launch_lowp<RSC_BF16, 1, 32, kLowpQB>(a, gx, "screen_bf16", s);
-            case 2: return launch_lowp<RSC_BF16, 2, 32, kLowpQB>(a, gx, "screen_bf16", s);
-            case 3: return launch_lowp<RSC_BF16, 3, 32, kLowpQB>(a, gx, "screen_bf16", s);
-            case 4: return launch_lowp<RSC_BF16, 4, 32, kLowpQB>(a, gx, "screen_bf16", s);
-            case 5: return launch_lowp<RSC_BF16, 5, 32, kLowpQB>(a, gx, "screen_bf16", s);
-            case 6: return launch_lowp<RSC_BF16, 6, 32, kLowpQB>(a, gx, "screen_bf16", s);
-            case 7: return launch_lowp<RSC_BF16, 7, 32, kLowpQB>(a, gx, "screen_bf16", s);
-            case 8: return launch_lowp<RSC_BF16, 8, 32, kLowpQB>(a, gx, "screen_bf16", s);
-            case 9: return launch_lowp<RSC_BF16, 9, 32, kLowpQB>(a, gx, "screen_bf16", s);
+            case 1: return launch_lowp<RSC_BF16, 1, 32, kLowpQB>(a, gx, name, s);
+            case 2: return launch_lowp<RSC_BF16, 2, 32, kLowpQB>(a, gx, name, s);
+            case 3: return launch_lowp<RSC_BF16, 3, 32, kLowpQB>(a, gx, name, s);
+            case 4: return launch_lowp<RSC_BF16, 4, 32, kLowpQB>(a, gx, name, s);
+            case 5: return launch_lowp<RSC_BF16, 5, 32, kLowpQB>(a, gx, name, s);
+            case 6: return launch_lowp<RSC_BF16, 6, 32, kLowpQB>(a, gx, name, s);
+            case 7: return launch_lowp<RSC_BF16, 7, 32, kLowpQB>(a, gx, name, s);
+            case 8: return launch_lowp<RSC_BF16, 8, 32, kLowpQB>(a, gx, name, s);
+            case 9: return launch_lowp<RSC_BF16, 9, 32, kLowpQB>(a, gx, name, s);
             default: break;
         }
     } else if (p.resid > 0) {

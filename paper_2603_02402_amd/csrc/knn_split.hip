@@ -254,6 +254,7 @@ int split_collect(const CollectArgs &a, hipStream_t s) {
 template int scr::split_launch<16>(const scr::ScreenArgs &, const char *, hipStream_t);
 
 size_t split_packed_bytes(int d, int64_t nblk) { return (size_t)nblk * split_geom(d).chunks() * 1024; }
+size_t rounded_packed_bytes(int d, int64_t nblk) { return (size_t)nblk * scr::rounded_geom(d).chunks() * 1024; }
 
 int split_queries_per_group(int d, int half_width) {
     int qg = 0;

@@ -77,10 +77,16 @@ struct KnnCounters {
     int32_t flagged2;         // escalated rows whose second certificate failed
     int32_t rescanned;        // rows recomputed exhaustively
     uint32_t query_norm_bits; // float bits of the largest query norm (rectangular problem; else 0)
-    int32_t wide;             // nonzero: norms spread too far for the split screen, the FP32 chain runs
+    int32_t wide;             // nonzero: norms spread too far for the split screen; the FP32 chain runs (the
+                              // BF16 form: its plain screen)
+    int32_t verdict;          // BF16 form: 0 none yet, kPruned, kPlain (the plain screen answers)
+    int32_t sampled;          // BF16 form: sampled tiles that know their segments
     int32_t pad;
+    unsigned long long sampled_segments;  // those segments
     unsigned long long visited;  // pruned screen: segments screened, over all query tiles
 };
+
+constexpr int kPruned = 1, kPlain = 2;  // KnnCounters::verdict
 
 struct KnnPlan {
     int64_t nq, nr;
@@ -135,7 +141,7 @@ struct KnnBuffers {
     float *esc_key;
     double *esc_bound;  // flagged rows: bound of the m-th distance, candidates collected
     int32_t *esc_found;
-    float *qn, *rn;   // unit-normalised queries / references (cosine metric)
+    float *qn, *rn;   // the rows as screened: unit-normalised (cosine metric), rounded (large BF16 problems)
     // FP8 residual variant
     float *cent;          // partition centroids, resid x d
     int32_t *assign, *perm, *init, *map;
@@ -256,6 +262,7 @@ int split_collect(const CollectArgs &a, hipStream_t s);
 // tile (null: the queries are the references in their order).
 struct PrunedArgs;
 int split_screen_pruned(const PrunedArgs &a, int half_width, const char *name, hipStream_t s);
+size_t rounded_packed_bytes(int d, int64_t nblk);  // the BF16 form's rows
 double split_eps_coefficient(int d);
 double split_abs_coefficient(int d);
 // Reduced-precision screens (knn_lowp.hip).
@@ -264,8 +271,9 @@ int lowp_qb(int precision, int d);
 int lowp_queries_per_group(int precision, int d);
 size_t lowp_packed_bytes(int precision, int64_t nblk, int d);
 // Packs the references (rmap: packed slot -> row, or null for row order).
+// gate (BF16): only where the plain screen is to answer.
 int lowp_prepare(const KnnPlan &p, const float *Q, const float *R, void *packed, float *norms, float *scal,
-                 uint32_t *amax, const int32_t *rmap, hipStream_t stream);
+                 uint32_t *amax, const int32_t *rmap, hipStream_t stream, const KnnCounters *gate = nullptr);
 int lowp_screen(const KnnPlan &p, const scr::ScreenArgs &a, unsigned gx, hipStream_t s);
 // FP8 residual variant: partitions, residual scales and the partition-ordered
 // packing (into b.packed / b.norms, with b.map and b.blk_part); then, after
@@ -273,7 +281,8 @@ int lowp_screen(const KnnPlan &p, const scr::ScreenArgs &a, unsigned gx, hipStre
 int lowp_prepare_resid(const KnnPlan &p, const float *R, const KnnBuffers &b, hipStream_t stream);
 int lowp_unmap(const KnnPlan &p, const KnnBuffers &b, hipStream_t stream);
 // Candidates from packed slots to rows through the packing's row map.
-int lowp_unmap_rows(const KnnPlan &p, const KnnBuffers &b, const int32_t *rmap, hipStream_t stream);
+int lowp_unmap_rows(const KnnPlan &p, const KnnBuffers &b, const int32_t *rmap, hipStream_t stream,
+                    const KnnCounters *gate = nullptr);
 
 // Spatial order of query rows (query_order.hip): perm = the rows sorted by a
 // Morton code of their first three coordinates.

@@ -74,8 +74,9 @@ struct ScreenArgs {
     int rotate;             // one matrix whose references are packed in the queries' order: each query
                             // group starts its scan at its own block
     const int32_t *ref_map; // split screen: packed slot -> row (null: row order)
-    const KnnCounters *kc;  // exact path: the largest norms (the split screen's scale) and the range mark
+    const KnnCounters *kc;  // exact path and large BF16 problems: the largest norms (the split screen's scale) and the mark
     int only_wide;          // FP32 chain: run only on inputs marked wide
+    int only_plain;         // BF16 screen: run only where the pruned screen does not answer
     int32_t *cand_idx;
     float *cand_key;
 };

@@ -13,7 +13,9 @@ struct PrunedArgs {
     const int32_t *own;
     double eps;              // error coefficient of a split key
     bool rounded;            // BF16 rows: one FP16 part each (lists of 32)
-    unsigned long long *visited;  // statistics: segments screened, over all tiles
+    int samples;             // BF16 rows: tiles that tell whether the plain screen is to answer (none: it is not asked),
+    int plain_over;          // and the segments of a range, on their average, above which it is
+    KnnCounters *counters;   // statistics; the mark for the plain screen
 };
 
 namespace scr {
@@ -77,7 +79,37 @@ int split_launch_geom(const ScreenArgs &a, const char *name, hipStream_t s) {
 // With P ranges, range p holds the segments p, p + P, ..
 // ONE: the BF16 form's rounded rows, a chain of one product per dimension (500k
 // rows, d = 50: screen 40 -> 9 ms).
-template <int Q, int TC, int L, bool ONE>
+//
+// SAMPLE: rounded rows without clusters are answered by the plain BF16 screen,
+// which merges its lists at three waves per SIMD where this one has two: 200k
+// rows, d = 50, both screens: with every segment visited 19.3 ms pruned, 13.9
+// plain; with 0.50 of them 11.8 and 11.9; 0.30: 6.8 and 9.1.  The first workgroups
+// (PrunedArgs::samples) take tiles spread evenly over all; the last of these to
+// know its segments gives the verdict: plain where they are more than
+// PrunedArgs::plain_over on average.  A workgroup whose own last list is that long
+// waits for the verdict (those that start with the samples: they know theirs at
+// about the same time) and ends if it is plain.  The plain screen then takes all
+// queries, so the answer does not depend on who waited how long.
+// (Looking for the verdict during the last list instead: the loop around the ring
+// spills up to 77 registers more.  Leaving only the tiles with long lists to the
+// plain screen: a few of them run for as long as many, 500k rows 10.4 -> 13.5 ms.)
+constexpr int kSampleTiles = 64;
+constexpr int kWaitLooks = 4000;  // looks for the verdict, about a microsecond each
+
+// Tile of workgroup x: the samples i tiles / samples first, then the others in order.
+__device__ __forceinline__ int sampled_tile(int x, int tiles, int samples) {
+    if (samples == tiles) return x;
+    if (x < samples) return (int)((int64_t)x * tiles / samples);
+    // of the samples' runs (a sample, then the tiles to the next one): the last whose others start at or before x
+    int lo = 0, hi = samples - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) / 2;
+        if ((int64_t)mid * tiles / samples - mid <= x - samples) lo = mid; else hi = mid - 1;
+    }
+    return x - samples + lo + 1;
+}
+
+template <int Q, int TC, int L, bool ONE, bool SAMPLE>
 __global__ __launch_bounds__((SplitShape<Q, TC, L>::NW * kWave), (SplitShape<Q, TC, L>::W)) void k_split_pruned(
     PrunedArgs pa) {
     using S = SplitShape<Q, TC, L>;
@@ -91,14 +123,32 @@ __global__ __launch_bounds__((SplitShape<Q, TC, L>::NW * kWave), (SplitShape<Q, 
     __shared__ int count[NWORDS];
     __shared__ uint16_t list[kSegMax];
     __shared__ uint32_t tmin, tmax;    // float bits of the smallest and largest T
+    __shared__ int verdict;
     const ScreenArgs &a = pa.s;
     if (a.kc->wide) return;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6, h = lane >> 5;
+    // whether the verdict is plain, after at most `looks` looks: one answer for the workgroup
+    auto plain = [&](int looks) {
+        if (tid == 0) {
+            int v = 0;
+            for (int i = 0; i < looks; ++i) {
+                v = __hip_atomic_load(&pa.counters->verdict, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (v != 0) break;
+                __builtin_amdgcn_s_sleep(8);
+            }
+            verdict = v;
+        }
+        __syncthreads();
+        return verdict == kPlain;
+    };
+    if constexpr (SAMPLE)
+        if (plain(1)) return;
     const int p = blockIdx.y, P = a.P;
     const int nblk = (int)a.nblk, nseg = pa.nseg, sh = pa.seg_shift, nw = (nseg + 31) / 32;
     const int qg = blockDim.x / 2, qs = blockDim.x;
     const int64_t nslots = screen_slots(a);
-    const int64_t slot = (int64_t)blockIdx.x * qg + wave * 32 + (lane & 31);
+    const int64_t tile = SAMPLE ? sampled_tile(blockIdx.x, gridDim.x, pa.samples) : (int)blockIdx.x;
+    const int64_t slot = tile * qg + wave * 32 + (lane & 31);
     const int64_t row = slot < nslots ? (a.qlist ? (int64_t)a.qlist[slot] : slot) : -1;
     const float scale = ldexpf(1.f, split_exponent(a.kc));
 
@@ -118,9 +168,8 @@ __global__ __launch_bounds__((SplitShape<Q, TC, L>::NW * kWave), (SplitShape<Q, 
     const float slack = 1.5f * (float)pa.eps * (2.f * sqrtf(xx) * 16384.f + 268435456.f) + xx * 0x1p-18f;
 
     // first the range's segments around the tile's rows
-    const int first = pa.own ? pa.own[blockIdx.x] : (int)(((int64_t)blockIdx.x * qg / 32) >> sh);
-    const int last =
-        pa.own ? first : (int)(min((int64_t)nblk - 1, ((int64_t)(blockIdx.x + 1) * qg - 1) / 32) >> sh);
+    const int first = pa.own ? pa.own[tile] : (int)((tile * qg / 32) >> sh);
+    const int last = pa.own ? first : (int)(min((int64_t)nblk - 1, ((tile + 1) * qg - 1) / 32) >> sh);
     const int reach = max(1, kNearBlocks >> sh) * P;
     const int lo = max(0, first - reach), hi = min(nseg - 1, last + reach);
     const int near0 = lo + (p + P - lo % P) % P;
@@ -208,6 +257,21 @@ __global__ __launch_bounds__((SplitShape<Q, TC, L>::NW * kWave), (SplitShape<Q, 
                 break;
             }
         }
+        if constexpr (SAMPLE) {
+            if (final) {
+                if (p == 0 && (int)blockIdx.x < pa.samples && tid == 0) {
+                    KnnCounters *kc = pa.counters;
+                    atomicAdd(&kc->sampled_segments, (unsigned long long)(visited + total));
+                    __threadfence();
+                    if (atomicAdd(&kc->sampled, 1) == pa.samples - 1) {
+                        const double seen = (double)atomicAdd(&kc->sampled_segments, 0ull);
+                        const int v = seen > (double)pa.plain_over * pa.samples ? kPlain : kPruned;
+                        __hip_atomic_store(&kc->verdict, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                }
+                if (visited + total > pa.plain_over && plain(kWaitLooks)) return;
+            }
+        }
         int at = 0;
         for (int i = 0; i < nw; ++i) at += i < tid ? count[i] : 0;
         while (mine) {
@@ -216,15 +280,15 @@ __global__ __launch_bounds__((SplitShape<Q, TC, L>::NW * kWave), (SplitShape<Q, 
         }
     }
     if (row >= 0) top.store(a, slot, p, h, a.ref_map);
-    if (tid == 0) atomicAdd(pa.visited, (unsigned long long)visited);
+    if (tid == 0) atomicAdd(&pa.counters->visited, (unsigned long long)visited);
 }
 
-template <int Q, int TC, int L, bool ONE = false>
+template <int Q, int TC, int L, bool ONE = false, bool SAMPLE = false>
 int pruned_launch_geom(const PrunedArgs &a, const char *name, hipStream_t s) {
     using S = SplitShape<Q, TC, L>;
     ScopedTimer timer(name, s);
     const unsigned gx = (unsigned)((a.s.nq + S::QG - 1) / S::QG);
-    hipLaunchKernelGGL((k_split_pruned<Q, TC, L, ONE>), dim3(gx, (unsigned)a.s.P), dim3(S::NW * kWave), 0, s, a);
+    hipLaunchKernelGGL((k_split_pruned<Q, TC, L, ONE, SAMPLE>), dim3(gx, (unsigned)a.s.P), dim3(S::NW * kWave), 0, s, a);
     return launch_status(name);
 }
 
