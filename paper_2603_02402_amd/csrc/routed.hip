@@ -40,7 +40,7 @@ constexpr int kMaxParts = 8192;   // partitions of a probed search (LDS bitmap o
 constexpr int kMaxProbes = 64;    // probes per query (one per lane when sorting)
 constexpr int kTileQ = 32;        // queries per tile (one wave)
 constexpr int kBitmapWords = kMaxParts / 32;
-constexpr int64_t kExactSlack = 1024 * 512;  // see exact_plan
+constexpr int64_t kExactSlack = 131072;  // see exact_plan
 
 struct RoutedCounters {
     int32_t nconf;      // probed rows
@@ -81,18 +81,24 @@ int pick_dh_local(int d) {
 }
 
 // The exact search over the list of F rows: the plan of rsc_knn restricted to
-// the list.  Its workspace is bounded for every F <= n by the plan with
-// n + kExactSlack queries and one reference range (the range count of the
-// exact path is at most ceil(1024 / ceil(F / 128)), so F times it stays below
-// F + 131072).
-int exact_plan(int64_t F, int64_t n, int d, int k, KnnPlan *p) { return knn_plan(F, n, d, k, nullptr, true, p); }
+// the list (which is never pruned).  Its workspace is bounded for every F <= n by
+// the plan of n queries with one reference range and candidates (index and key) of
+// kExactSlack more rows.  What grows with the ranges is the candidates alone, F
+// times their number: knn_plan asks for at most 256 workgroups of at most 256
+// queries, which adds fewer than 256 * 256 + 256 rows to F; below 512 of them it
+// takes two ranges, which adds fewer than 512 * 256.  (A third rule, two ranges for more than 33 neighbours, has no such bound:
+// where its plan does not fit, one range does.)
+int exact_plan(int64_t F, int64_t n, int d, int k, KnnPlan *p) {
+    const int st = knn_plan(F, n, d, k, nullptr, true, p);
+    p->pruned = false;
+    return st;
+}
 
 size_t exact_bound_bytes(int64_t n, int d, int k) {
     KnnPlan p;
     if (exact_plan(n, n, d, k, &p) != RSC_OK) return 0;
-    p.nq = n + kExactSlack;
     p.splits = 1;
-    return knn_workspace(p, nullptr, nullptr);
+    return knn_workspace(p, nullptr, nullptr) + 2 * align_up((size_t)(kExactSlack * p.screen) * 4);
 }
 
 size_t carve_probed(int64_t n, int d, int k, int P, int probes, void *ws, RoutedBuffers *out) {
