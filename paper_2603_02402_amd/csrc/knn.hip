@@ -170,7 +170,9 @@ __global__ __launch_bounds__(256) void k_pack(const float *__restrict__ R, const
                                               int d, int DH, int S4, int folded, int64_t nblk,
                                               f32x4 *__restrict__ Ap, float *__restrict__ Np,
                                               const int32_t *__restrict__ blk_sample, const int64_t *__restrict__ boff,
-                                              const int64_t *__restrict__ soff, const int32_t *__restrict__ row_map) {
+                                              const int64_t *__restrict__ soff, const int32_t *__restrict__ row_map,
+                                              const KnnCounters *__restrict__ gate) {
+    if (gate && gate->wide == 0) return;  // the split screen answers
     const int64_t total = nblk * S4 * kWave;
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
          e += (int64_t)gridDim.x * blockDim.x) {
@@ -1031,21 +1033,23 @@ static int query_norms(const KnnPlan &p, const float *Q, const KnnBuffers &b, hi
     return launch_status("query norms");
 }
 
-int knn_prep_fp32(const KnnPlan &p, const float *R, const float *Q, const KnnBuffers &b, const int32_t *blk_sample,
-                  const int64_t *boff, const int64_t *soff, hipStream_t stream) {
-    const int s4 = packed_s4(p.dh);
+int knn_prep(const KnnPlan &p, const float *R, const float *Q, const KnnBuffers &b, hipStream_t stream) {
     ScopedTimer timer("prep_pack", stream);
-    hipLaunchKernelGGL(k_init_counters, dim3(1), dim3(64), 0, stream, b.counters);
-    hipLaunchKernelGGL(k_norms, dim3((unsigned)((p.nr + norm_rows(p.d) - 1) / norm_rows(p.d))), dim3(kNormThreads), 0,
-                       stream, R, p.nr, p.d, b.nrow,
-                       &b.counters->max_norm_bits);
-    const int64_t tot = p.nblk * s4 * kWave;
-    const unsigned g1 = (unsigned)std::min<int64_t>((tot + 255) / 256, 65536);
-    hipLaunchKernelGGL(k_pack, dim3(g1), dim3(256), 0, stream, R, b.nrow, p.nr, p.d, p.dh, s4,
-                       norm_folded(p.dh) ? 1 : 0, p.nblk, reinterpret_cast<f32x4 *>(b.packed), b.norms, blk_sample,
-                       boff, soff, nullptr);
-    if (Q && p.nq > 0) return query_norms(p, Q, b, stream);
-    return launch_status("prep_pack");
+    const int st = knn_norms(R, p.nr, p.d, b.nrow, b.counters, stream);
+    return st == RSC_OK && Q && p.nq > 0 ? query_norms(p, Q, b, stream) : st;
+}
+
+int knn_pack_fp32(int dh, const float *R, const float *nrow, int64_t nr, int d, int64_t nblk, float *packed,
+                  float *norms, const int32_t *blk_sample, const int64_t *boff, const int64_t *soff,
+                  const int32_t *row_map, const KnnCounters *gate, hipStream_t stream) {
+    const int s4 = packed_s4(dh);
+    ScopedTimer timer("pack_wide", stream);
+    const int64_t tot = nblk * s4 * kWave;
+    // (gated: most often idle)
+    const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>((tot + 255) / 256, gate ? 2048 : 65536));
+    hipLaunchKernelGGL(k_pack, dim3(g), dim3(256), 0, stream, R, nrow, nr, d, dh, s4, norm_folded(dh) ? 1 : 0, nblk,
+                       reinterpret_cast<f32x4 *>(packed), norms, blk_sample, boff, soff, row_map, gate);
+    return launch_status("pack_wide");
 }
 
 int knn_norms(const float *R, int64_t nr, int d, float *nrow, KnnCounters *counters, hipStream_t stream) {
@@ -1053,17 +1057,6 @@ int knn_norms(const float *R, int64_t nr, int d, float *nrow, KnnCounters *count
     hipLaunchKernelGGL(k_norms, dim3((unsigned)((nr + norm_rows(d) - 1) / norm_rows(d))), dim3(kNormThreads), 0, stream, R,
                        nr, d, nrow, &counters->max_norm_bits);
     return launch_status("norms");
-}
-
-int knn_pack_mapped(int dh, const float *R, const float *nrow, int64_t nr, int d, int64_t nblk, float *packed,
-                    float *norms, const int32_t *row_map, hipStream_t stream) {
-    const int s4 = packed_s4(dh);
-    ScopedTimer timer("prep_pack", stream);
-    const int64_t tot = nblk * s4 * kWave;
-    const unsigned g1 = (unsigned)std::max<int64_t>(1, std::min<int64_t>((tot + 255) / 256, 65536));
-    hipLaunchKernelGGL(k_pack, dim3(g1), dim3(256), 0, stream, R, nrow, nr, d, dh, s4, norm_folded(dh) ? 1 : 0, nblk,
-                       reinterpret_cast<f32x4 *>(packed), norms, nullptr, nullptr, nullptr, row_map);
-    return launch_status("prep_pack");
 }
 
 size_t knn_packed_floats(int dh, int64_t nblk) { return (size_t)nblk * packed_s4(dh) * kWave * 4; }
@@ -1236,19 +1229,29 @@ static int64_t query_tiles(const KnnPlan &p) {
     return (p.nq + qg - 1) / qg;
 }
 
+// Whether rows without a certificate collect their candidates (k_split_collect;
+// else the FP32 chain screens them again).
+static bool knn_collects(const KnnPlan &p) { return (p.self_mode ? p.k - 1 : p.k) <= kLeanAnswer; }
+
 size_t knn_workspace(const KnnPlan &p, void *ws, KnnBuffers *out) {
     Carver cv(ws);
     KnnBuffers b{};
     const bool fp32 = p.precision == RSC_FP32, rounded = !fp32 && p.pruned;
-    const int s4 = packed_s4(p.dh);
     const int64_t esc_rows = p.precision == RSC_FP32 ? std::min<int64_t>(p.nq, kEscalateCap) : 0;
     b.counters = cv.take<KnnCounters>(1);
     if (fp32) {
         b.nrow = cv.take<float>((size_t)p.nr);
-        b.packed = cv.take<float>((size_t)p.nblk * s4 * kWave * 4);
         b.norms = cv.take<float>(norm_folded(p.dh) ? 1 : (size_t)p.nblk * 32);
         // (the pruned screen loads whole segments: the last one may reach past the blocks)
-        b.split = cv.take<char>(split_packed_bytes(p.d, p.nblk + (p.pruned ? spatial_seg_blocks(p.nblk) : 0)));
+        const size_t split = split_packed_bytes(p.d, p.nblk + (p.pruned ? spatial_seg_blocks(p.nblk) : 0));
+        const size_t chain = knn_packed_floats(p.dh, p.nblk) * sizeof(float);
+        if (knn_collects(p)) {  // one or the other is read
+            b.split = cv.take<char>(std::max(split, chain));
+            b.packed = static_cast<float *>(b.split);
+        } else {
+            b.split = cv.take<char>(split);
+            b.packed = reinterpret_cast<float *>(cv.take<char>(chain));
+        }
     } else if (rounded) {
         b.nrow = cv.take<float>((size_t)p.nr);
         // one or the other screen's packing
@@ -1275,9 +1278,10 @@ size_t knn_workspace(const KnnPlan &p, void *ws, KnnBuffers *out) {
     }
     if (p.pruned) {
         b.qcount = cv.take<int32_t>(1);
-        const size_t need = spatial_carve(p.nq, p.nr, p.d, false, nullptr, nullptr);
+        // (a workspace serves the square and the rectangular form alike: with the queries' part)
+        const size_t need = spatial_carve(p.nq, p.nr, p.d, nullptr, nullptr);
         char *base = cv.take<char>(need);
-        spatial_carve(p.nq, p.nr, p.d, false, base, &b.sp);
+        spatial_carve(p.nq, p.nr, p.d, base, &b.sp);
     } else if (!fp32 && p.resid == 0 && p.nq > 0) {
         // spatial order of the queries (perm) and its sort
         b.perm = cv.take<int32_t>((size_t)p.nq);
@@ -1366,8 +1370,7 @@ int knn_run_rounded(const KnnPlan &p, const float *Q, const float *R, int32_t *o
     const bool cosine = p.metric == RSC_COSINE;
     if (cosine && (st = normalize_inputs(p, Q, R, b, stream)) != RSC_OK) return st;
     if ((st = round_inputs(p, cosine ? b.qn : Q, cosine ? b.rn : R, b, stream)) != RSC_OK) return st;
-    if ((st = knn_norms(b.rn, p.nr, p.d, b.nrow, b.counters, stream)) != RSC_OK) return st;
-    if (!p.self_mode && (st = query_norms(p, b.qn, b, stream)) != RSC_OK) return st;
+    if ((st = knn_prep(p, b.rn, p.self_mode ? nullptr : b.qn, b, stream)) != RSC_OK) return st;
     if ((st = order_rows(p, b.qn, b.rn, b, stream)) != RSC_OK) return st;
     {
         ScopedTimer timer("pack_split", stream);
@@ -1548,8 +1551,7 @@ int knn_run(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, 
     if (cosine && (st = normalize_inputs(p, Q, R, b, stream)) != RSC_OK) return st;
     const float *Qs = cosine ? b.qn : Q;  // what the screen sees
     const float *Rs = cosine ? b.rn : R;
-    if ((st = knn_prep_fp32(p, Rs, p.self_mode ? nullptr : Qs, b, nullptr, nullptr, nullptr, stream)) != RSC_OK)
-        return st;
+    if ((st = knn_prep(p, Rs, p.self_mode ? nullptr : Qs, b, stream)) != RSC_OK) return st;
     // Large problems are screened in a spatial order with its segments' bounds.
     // (Under stream capture every pair is screened instead.)
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
@@ -1597,6 +1599,11 @@ int knn_run(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, 
         st = split_screen(ss, p.half, "screen_fp32", stream);
     }
     if (st != RSC_OK) return st;
+    // (short answers read this packing on inputs marked wide alone, in the memory of the other)
+    const bool collect = knn_collects(p);
+    if ((st = knn_pack_fp32(p.dh, Rs, b.nrow, p.nr, p.d, p.nblk, b.packed, b.norms, nullptr, nullptr, nullptr, nullptr,
+                            collect ? b.counters : nullptr, stream)) != RSC_OK)
+        return st;
     sa.only_wide = 1;
     const unsigned gq = (unsigned)((p.nq + kQueriesPerGroup - 1) / kQueriesPerGroup);
     if ((st = screen(p.dh, sa, gq, p.half, false, "screen_wide", stream)) != RSC_OK) return st;
@@ -1628,7 +1635,6 @@ int knn_run(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, 
     ra.out_dist = out_dist;
     knn_split_bounds(ra);
     const int esc_cap = (int)std::min<int64_t>(p.nq, kEscalateCap);
-    const bool collect = (p.self_mode ? p.k - 1 : p.k) <= kLeanAnswer;
     if (collect) {
         ra.flag_bound = b.esc_bound;
         ra.flag_found = b.esc_found;

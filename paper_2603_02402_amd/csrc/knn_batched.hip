@@ -343,6 +343,13 @@ int launch_split_batched(const BatchArgs &ba, hipStream_t s) {
     return launch_status("screen_batched");
 }
 
+// The references for the FP32 chain, in the memory of the split screen's packing
+// once that is done with (gate: where it does not answer).
+int pack_chain(const BatchPlan &bp, const BatchBuffers &b, const float *X, const KnnCounters *gate, hipStream_t s) {
+    return knn_pack_fp32(bp.kp.dh, X, b.kb.nrow, bp.kp.nr, bp.kp.d, bp.kp.nblk, b.kb.packed, b.kb.norms, b.blk_sample,
+                         b.boff, b.soff, nullptr, gate, s);
+}
+
 // The batch's screen: the split screen, then (only where the inputs were
 // marked wide) the FP32 chain over the same items.
 int launch_screen(const BatchPlan &bp, BatchArgs ba, const BatchBuffers &b, hipStream_t s) {
@@ -361,6 +368,7 @@ int launch_screen(const BatchPlan &bp, BatchArgs ba, const BatchBuffers &b, hipS
 #undef X
         if (st != RSC_OK) return st;
     }
+    if ((st = pack_chain(bp, b, ba.base.Q, b.kb.counters, s)) != RSC_OK) return st;
     hipLaunchKernelGGL(k_batch_init, dim3(1), dim3(64), 0, s, ba.counter, nullptr, nullptr, (int64_t)0);
     ba.base.only_wide = 1;
     ba.tile_q = split_queries_per_group(bp.kp.d, bp.kp.half) / 128;
@@ -415,11 +423,11 @@ int screen_only(const BatchPlan &bp, const BatchBuffers &b, const float *X, hipS
     return launch_screen(bp, batch_args(bp, b, X), b, s);
 }
 
-// Row order, norms and packings (they do not depend on the tile shape).
+// Row order, norms and the split screen's packing (they do not depend on the tile shape).
 int prepare(const BatchPlan &bp, const BatchBuffers &b, const float *X, hipStream_t s) {
     int st = sample_order_run(X, bp.kp.nq, bp.kp.d, b.soff, bp.S, b.order_ws, b.order, s);
     if (st != RSC_OK) return st;
-    if ((st = knn_prep_fp32(bp.kp, X, nullptr, b.kb, b.blk_sample, b.boff, b.soff, s)) != RSC_OK) return st;
+    if ((st = knn_prep(bp.kp, X, nullptr, b.kb, s)) != RSC_OK) return st;
     return split_pack(X, b.kb.nrow, bp.kp.nr, bp.kp.d, bp.kp.nblk, b.kb.split, b.blk_sample, b.boff, b.soff, b.order,
                       bp.kp.nr, b.kb.counters, s);
 }
@@ -564,6 +572,7 @@ int escalate(const BatchPlan &bp, const BatchBuffers &b, const float *X, int32_t
         ba.items = b.esc_items;
         ba.n_items = (int)items.size();
         ba.rows = b.esc_rows;
+        if ((st = pack_chain(bp, b, X, nullptr, s)) != RSC_OK) return st;
         if ((st = launch_batched(bp, ba, s, kEscHalf, "screen_escalate")) != RSC_OK) return st;
         RerankArgs re = ra;
         re.qlist = b.esc_rows;

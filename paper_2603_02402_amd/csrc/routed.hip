@@ -113,9 +113,10 @@ size_t carve_probed(int64_t n, int d, int k, int P, int probes, void *ws, Routed
     b.nrow = cv.take<float>(n);
     b.pblk = cv.take<int64_t>(P + 1);
     b.map = cv.take<int32_t>((size_t)nblk * 32);
-    b.packed = cv.take<float>(knn_packed_floats(dh, nblk));
     b.norms = cv.take<float>((size_t)nblk * 32);
-    b.split = cv.take<char>(split_packed_bytes(d, nblk));
+    // one or the other screen's packing
+    b.split = cv.take<char>(std::max(split_packed_bytes(d, nblk), knn_packed_floats(dh, nblk) * sizeof(float)));
+    b.packed = static_cast<float *>(b.split);
     b.own = cv.take<int32_t>(n);
     b.probes = cv.take<int32_t>((size_t)n * probes);
     b.ccount = cv.take<int32_t>(P);
@@ -854,9 +855,10 @@ int probed_run(const float *X, int64_t n, int d, int k, const int64_t *offsets, 
         if ((st = launch_status("probed layout")) != RSC_OK) return st;
         // a partition layout inconsistent with n could overrun the packed
         // array: the pack covers the capacity, which every valid layout fits
-        if ((st = knn_pack_mapped(dh, X, b.nrow, n, d, nblk_cap, b.packed, b.norms, b.map, s)) != RSC_OK) return st;
         if ((st = split_pack(X, b.nrow, n, d, nblk_cap, b.split, nullptr, nullptr, nullptr, b.map, nblk_cap * 32, b.kc,
-                             s)) != RSC_OK)
+                             s)) != RSC_OK ||
+            (st = knn_pack_fp32(dh, X, b.nrow, n, d, nblk_cap, b.packed, b.norms, nullptr, nullptr, nullptr, b.map, b.kc,
+                                s)) != RSC_OK)
             return st;
         hipLaunchKernelGGL(k_sort_probes, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, probe_parts, n, probes, P,
                            b.probes, &b.rc->bad);

@@ -118,7 +118,7 @@ struct SpatialBuffers {
     size_t tmp_bytes;
 };
 int spatial_seg_blocks(int64_t nblk);
-size_t spatial_carve(int64_t nq, int64_t nr, int d, bool square, void *base, SpatialBuffers *out);
+size_t spatial_carve(int64_t nq, int64_t nr, int d, void *base, SpatialBuffers *out);
 // Orders the references (norms and their maximum known) and bounds the segments.
 // rounded: BF16 rows, whose segments are packed as one FP16 part.
 int spatial_refs(const float *R, const float *nrow, int64_t nr, int d, bool rounded, const SpatialBuffers &b,
@@ -200,11 +200,15 @@ int knn_run(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, 
 
 // Pieces of the exact path reused by the batched form (knn.hip).
 double knn_eps_coefficient(int d);
-// init counters, norms, FP32 packing (optionally per sample:
-// blk_sample, boff, soff device arrays).  Q: the queries of a rectangular
-// problem (their largest norm enters the split's scale), else null.
-int knn_prep_fp32(const KnnPlan &p, const float *R, const float *Q, const KnnBuffers &b, const int32_t *blk_sample,
-                  const int64_t *boff, const int64_t *soff, hipStream_t stream);
+// Counters and norms.  Q: the queries of a rectangular problem (their largest
+// norm enters the split's scale), else null.
+int knn_prep(const KnnPlan &p, const float *R, const float *Q, const KnnBuffers &b, hipStream_t stream);
+// Packs nblk blocks for the FP32 chain: rows in order, per sample (device tables
+// blk_sample, boff, soff) or by row_map (-1: padding).  gate: only where its
+// inputs were marked wide.
+int knn_pack_fp32(int dh, const float *R, const float *nrow, int64_t nr, int d, int64_t nblk, float *packed,
+                  float *norms, const int32_t *blk_sample, const int64_t *boff, const int64_t *soff,
+                  const int32_t *row_map, const KnnCounters *gate, hipStream_t stream);
 // The rerank's error bounds for keys of the split screen.
 void knn_split_bounds(RerankArgs &ra);
 int knn_launch_rerank(const RerankArgs &ra, int64_t slots, const char *name, hipStream_t stream);
@@ -222,13 +226,11 @@ struct ScreenArgs;
 int knn_norms(const float *R, int64_t nr, int d, float *nrow, KnnCounters *counters, hipStream_t stream);
 // FP32 packing of nblk blocks whose packed row 32b + c is row_map[32b + c]
 // of R (-1: padding with an infinite norm).
-int knn_pack_mapped(int dh, const float *R, const float *nrow, int64_t nr, int d, int64_t nblk, float *packed,
-                    float *norms, const int32_t *row_map, hipStream_t stream);
 size_t knn_packed_floats(int dh, int64_t nblk);
 // Split FP16 screen of the exact path (knn_split.hip).
 size_t split_packed_bytes(int d, int64_t nblk);
 int split_queries_per_group(int d, int half_width);
-// Packs nblk blocks (sample tables as knn_prep_fp32; row_map: the rows at
+// Packs nblk blocks (sample tables as knn_pack_fp32; row_map: the rows at
 // the first nmap positions, -1 and the positions past them padded)
 // and marks inputs whose norms spread too far; needs the norms of R.
 int split_pack(const float *R, const float *nrow, int64_t nr, int d, int64_t nblk, void *packed,

@@ -321,7 +321,7 @@ int spatial_seg_blocks(int64_t nblk) {
     return sb;
 }
 
-size_t spatial_carve(int64_t nq, int64_t nr, int d, bool square, void *base, SpatialBuffers *out) {
+size_t spatial_carve(int64_t nq, int64_t nr, int d, void *base, SpatialBuffers *out) {
     const int64_t nblk = (nr + 31) / 32;
     SpatialBuffers b{};
     b.seg_blocks = spatial_seg_blocks(nblk);
@@ -338,11 +338,9 @@ size_t spatial_carve(int64_t nq, int64_t nr, int d, bool square, void *base, Spa
     b.id = cv.take<int32_t>(most);
     b.rkey = cv.take<uint32_t>((size_t)nr);
     b.rperm = cv.take<int32_t>((size_t)nr);
-    if (!square) {
-        b.qkey = cv.take<uint32_t>((size_t)nq);
-        b.qperm = cv.take<int32_t>((size_t)nq);
-        b.own = cv.take<int32_t>((size_t)(nq + 127) / 128);
-    }
+    b.qkey = cv.take<uint32_t>((size_t)nq);
+    b.qperm = cv.take<int32_t>((size_t)nq);
+    b.own = cv.take<int32_t>((size_t)(nq + 127) / 128);
     b.centre = cv.take<float>((size_t)b.nseg * d);
     b.radius = cv.take<float>((size_t)b.nseg);
     b.seg_packed = cv.take<char>(split_packed_bytes(d, (b.nseg + 31) / 32));
