@@ -689,7 +689,6 @@ __global__ __launch_bounds__(256) void k_rerank_lean(RerankArgs a) {
     auto pass = [&]() {
         const int nc = min(waiting, G);
         double s2 = 0.0, yy = 0.0, sxy = 0.0;
-        float yf = 0.f;
         float *T = tile[g];
         const int ncw = PW == 1 ? nc : max(nc, __shfl_xor(nc, G & 63, kWave));  // either group's
         for (int k0 = 0; k0 < a.d; k0 += kLeanChunk) {
@@ -732,7 +731,7 @@ __global__ __launch_bounds__(256) void k_rerank_lean(RerankArgs a) {
                 auto step = [&](float xv, float yv) {
                     const double diff = __dsub_rn((double)xv, (double)yv);
                     s2 = __dadd_rn(s2, __dmul_rn(diff, diff));
-                    yf = fmaf(yv, yv, yf);
+                    yy = fma((double)yv, (double)yv, yy);
                 };
                 int t = 0;
                 for (; t + 1 < w; t += 2) {
@@ -756,9 +755,9 @@ __global__ __launch_bounds__(256) void k_rerank_lean(RerankArgs a) {
                 if (!zero) ratio = fmaxf(ratio, (float)(fabs(skey - (2.0 * d2 - 1.0)) / cosine_eps));
             } else {
                 d2 = s2;
-                const double yn = sqrt((double)yf);
+                const double yn = sqrt(yy);
                 const double err_bound =
-                    eps_coef * (2.0 * xn * yn + (double)yf) + eps_abs * (2.0 * xn + yn) + 1e-300;
+                    eps_coef * (2.0 * xn * yn + yy) + eps_abs * (2.0 * xn + yn) + 1e-300;
                 ratio = fmaxf(ratio, (float)(fabs(skey - (d2 - xx)) / err_bound));
             }
         }
