@@ -65,6 +65,11 @@ constexpr int kMaxKLowp = 63;
 // nothing from bounds; the BF16 form finds that out (knn_run_rounded).
 constexpr int64_t kPruneRows = 16384;
 constexpr double kPrunePairs = 2.5e8;
+// Foreign queries from which it is: fewer pay for ordering the references without
+// a gain (k = 15, in ms, not pruned and pruned: 600 of 1M rows, d = 20, 1.04, 2.88;
+// 2000 of 500k, d = 50, 1.15, 1.78; 5000 of 1M 3.63, 3.81; 12,000 1.0 to 1.35 times
+// as long without).
+constexpr int64_t kPruneQueries = 6000;
 // Foreign queries from which the BF16 form is pruned: fewer do not pay for ordering
 // the references.  In ms, plain and pruned, rows in 100 clusters: 2500 queries of
 // 100k rows 0.89, 1.05; 3500 1.24, 1.10; 3500 of 500k 2.27, 2.71; 5000 2.70, 2.70;
@@ -1193,7 +1198,7 @@ int knn_plan(int64_t nq, int64_t nr, int d, int k, const rsc_knn_opts *opts, boo
     plan->resid = resid;
     plan->pruned = (precision == RSC_FP32 || (precision == RSC_BF16 && lowp_ranges == 1)) && nr >= kPruneRows &&
                    (double)nq * (double)nr >= kPrunePairs;
-    if (precision == RSC_BF16 && !self_mode && nq < prune_queries_bf16(nr)) plan->pruned = false;
+    if (!self_mode && nq < (precision == RSC_BF16 ? prune_queries_bf16(nr) : kPruneQueries)) plan->pruned = false;
     const bool split = precision == RSC_FP32 || plan->pruned;
     // the split screen's workgroups of 8 waves fill a CU each; the others run four of 4 waves
     plan->splits = split
