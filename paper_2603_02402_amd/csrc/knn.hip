@@ -70,6 +70,10 @@ constexpr double kPrunePairs = 2.5e8;
 // 2000 of 500k, d = 50, 1.15, 1.78; 5000 of 1M 3.63, 3.81; 12,000 1.0 to 1.35 times
 // as long without).
 constexpr int64_t kPruneQueries = 6000;
+// Rows from which answers longer than 64 are: near rows crowd a range's lists, and
+// some rows are searched again (d = 50, k = 100, in ms, not pruned and pruned: 20k
+// rows 1.35, 2.55, in separate clusters 1.36, 1.57; 40k 3.55, 4.04 and 3.55, 2.34).
+constexpr int64_t kPruneRowsLong = 32768;
 // Foreign queries from which the BF16 form is pruned: fewer do not pay for ordering
 // the references.  In ms, plain and pruned, rows in 100 clusters: 2500 queries of
 // 100k rows 0.89, 1.05; 3500 1.24, 1.10; 3500 of 500k 2.27, 2.71; 5000 2.70, 2.70;
@@ -1199,6 +1203,9 @@ int knn_plan(int64_t nq, int64_t nr, int d, int k, const rsc_knn_opts *opts, boo
     plan->pruned = (precision == RSC_FP32 || (precision == RSC_BF16 && lowp_ranges == 1)) && nr >= kPruneRows &&
                    (double)nq * (double)nr >= kPrunePairs;
     if (!self_mode && nq < (precision == RSC_BF16 ? prune_queries_bf16(nr) : kPruneQueries)) plan->pruned = false;
+    const int m = self_mode ? k - 1 : k;
+    const bool long_answer = m > kLeanAnswer;
+    if (long_answer && nr < kPruneRowsLong) plan->pruned = false;
     const bool split = precision == RSC_FP32 || plan->pruned;
     // the split screen's workgroups of 8 waves fill a CU each; the others run four of 4 waves
     plan->splits = split
@@ -1229,9 +1236,12 @@ int knn_plan(int64_t nq, int64_t nr, int d, int k, const rsc_knn_opts *opts, boo
             plan->splits = 3 * tiles <= 2 * kCUs ? 3 : 2;
     }
     if (split) {
-        // enough (range, half) lists that the m nearest fill each to about half
-        const int m = self_mode ? k - 1 : k;
-        plan->splits = std::min(32, std::max(plan->splits, (m + plan->half - 1) / plan->half));
+        // enough (range, half) lists that the m nearest fill each to about half; rows in
+        // no order and more than 64 of them to four tenths, or a few of their lists
+        // overflow (4000 rows, k = 255, d = 50: 8 ranges and a second search 0.66 ms, 11
+        // ranges 0.39)
+        const int fill = long_answer && !plan->pruned ? plan->half * 25 / 32 : plan->half;
+        plan->splits = std::min(32, std::max(plan->splits, (m + fill - 1) / fill));
     } else {
         plan->splits = std::max(plan->splits, lowp_ranges);
     }
