@@ -408,7 +408,7 @@ __global__ __launch_bounds__(256) void k_rerank(RerankArgs a) {
     const double ymax = (double)__uint_as_float(a.counters->max_norm_bits) * (1.0 + 1e-6);
     const bool cosine = a.metric == RSC_COSINE;
     // units and error bound of the screened keys
-    const bool split = a.split && a.counters->wide == 0 && a.counters->verdict != kPlain;
+    const bool split = a.split && a.counters->wide == 0 && (a.split == 1 || a.counters->verdict != kPlain);
     const double kscale = split ? ldexp(1.0, -2 * scr::split_exponent(a.counters)) : 1.0;
     const double eps_coef = split ? a.split_eps : a.eps_coef;
     const double cosine_eps = split ? a.split_cosine_eps : a.cosine_eps;
@@ -621,7 +621,7 @@ __global__ __launch_bounds__(256) void k_rerank_lean(RerankArgs a) {
     const double xn = sqrt(xx) * (1.0 + 1e-12);
     const double ymax = (double)__uint_as_float(a.counters->max_norm_bits) * (1.0 + 1e-6);
     const bool cosine = a.metric == RSC_COSINE;
-    const bool split = a.split && a.counters->wide == 0 && a.counters->verdict != kPlain;
+    const bool split = a.split && a.counters->wide == 0 && (a.split == 1 || a.counters->verdict != kPlain);
     const double kscale = split ? ldexp(1.0, -2 * scr::split_exponent(a.counters)) : 1.0;
     const double eps_coef = split ? a.split_eps : a.eps_coef;
     const double cosine_eps = split ? a.split_cosine_eps : a.cosine_eps;
@@ -1379,6 +1379,39 @@ PrunedArgs pruned_args(const KnnPlan &p, const ScreenArgs &s, const KnnBuffers &
     pa.eps = split_eps_coefficient(p.d);
     pa.counters = b.counters;
     pa.rounded = p.precision == RSC_BF16;
+    // Whether bounds help is sampled where that pays.
+    // BF16 rows: with fewer than 256 blocks to a range a tile has screened most of
+    // them by the time the samples know (16.5k rows without clusters, 4 ranges of 129:
+    // 1.12 ms pruned, 1.23 with the verdict; 25k, 3 of 260: 1.71, 1.38); at 9 steps the
+    // plain screen has one workgroup per CU and gains nothing (d = 128, 200k rows: 44.6
+    // pruned, 46.4 plain; d = 126: 44.6, 25.1).
+    // Exact, lists of 32: the pruned loop spills 59 registers at 5 chunks to a row and
+    // 583 at 17, and the unpruned one is faster at the same work (100k rows without
+    // clusters, k = 30, pruned and plain: d = 35 14.1, 8.2 ms; d = 50 14.5, 8.8; d = 100
+    // 26.6, 18.1; d = 128 42.3, 16.6), but not without spills (d = 20, 3 chunks, 7.41,
+    // 7.21; d = 200, 29 chunks, 32.1, 29.7) or with short ranges in one round of
+    // workgroups.  With lists of 16 it gains at most a tenth, and the verdict costs more.
+    // Foreign queries in one round of workgroups gain nothing (BF16: 16,384 of 500k rows
+    // 5.09 and 5.20; 24,000 10.1 and 7.4; exact, k = 30: 24,000 16.7 and 10.6).
+    const int64_t tiles = query_tiles(p);
+    const int chunks = (int)(split_packed_bytes(p.d, 1) / 1024);
+    const double blocks = (double)p.nblk / p.splits;
+    const bool pays = pa.rounded ? blocks >= 256 && lowp_steps(p.precision, p.d) <= 8
+                                 : p.half == 32 && chunks >= 5 && chunks <= 25 &&
+                                       (blocks * chunks >= 1792 || tiles * p.splits >= 4 * scr::kCUs);
+    if (pays && (p.self_mode || 4 * tiles > scr::kCUs)) {
+        pa.samples = (int)std::min<int64_t>(scr::kSampleTiles, tiles);
+        // Both take the same time, BF16 at about half of the segments (200k rows, d = 50:
+        // 0.50 of them 11.8 ms pruned, 11.9 plain; 0.30 6.8 and 9.1); exact at 0.6 to 0.8
+        // (100k, d = 80, 0.65 of them 8.1, 8.2; 40k, d = 50, 0.83 of them 2.10, 1.77), with
+        // 15 chunks and more a quarter (d = 128, 100k, 0.33 of them 19.5, 13.2; 300k, 0.20
+        // 48.6, 70.9).  Foreign queries' tiles span several clusters, but their lists settle
+        // early: 24,000 of 500k BF16 rows in 100 clusters 4.8 pruned, 6.0 plain.
+        const bool late = p.self_mode && !pa.rounded && chunks < 15;
+        const double share = late ? 0.75 : !p.self_mode ? 0.95 : pa.rounded ? 0.55 : 0.25;
+        pa.plain_over = (int)(share * b.sp.nseg / p.splits);
+        pa.wait_over = late ? pa.plain_over / 2 : pa.plain_over;
+    }
     return pa;
 }
 
@@ -1421,20 +1454,6 @@ int knn_run_rounded(const KnnPlan &p, const float *Q, const float *R, int32_t *o
         ScreenArgs ss = sa;
         ss.ref_map = b.sp.rperm;
         PrunedArgs pa = pruned_args(p, ss, b);
-        // Whether bounds help is sampled where that pays: with fewer than 256 blocks
-        // to a range a tile has screened most of them by the time the samples know
-        // (16.5k rows without clusters, 4 ranges of 129: 1.12 ms pruned, 1.23 with the
-        // verdict; 25k, 3 of 260: 1.71, 1.38); foreign queries in one round of
-        // workgroups the same (16,384 of 500k rows: 5.09 and 5.20; 24,000: 10.1 and
-        // 7.4); at 9 steps the plain screen has one workgroup per CU and gains nothing
-        // (d = 128, 200k rows: 44.6 pruned, 46.4 plain; d = 126: 44.6, 25.1).
-        // Foreign queries' tiles span several clusters, but their lists settle early:
-        // 24,000 of 500k rows in 100 clusters 4.8 ms pruned, 6.0 plain.
-        const int64_t tiles = query_tiles(p);
-        if (p.nblk / p.splits >= 256 && lowp_steps(p.precision, p.d) <= 8 && (p.self_mode || 4 * tiles > scr::kCUs)) {
-            pa.samples = (int)std::min<int64_t>(scr::kSampleTiles, tiles);
-            pa.plain_over = (int)((p.self_mode ? 0.55 : 0.95) * b.sp.nseg / p.splits);
-        }
         if ((st = split_screen_pruned(pa, p.half, "screen_bf16_pruned", stream)) != RSC_OK) return st;
         // (as in knn_run_lowp, references in the queries' order for a single range of one matrix)
         const int32_t *rmap = p.self_mode && p.splits == 1 ? b.sp.rperm : nullptr;
@@ -1468,7 +1487,7 @@ int knn_run_rounded(const KnnPlan &p, const float *Q, const float *R, int32_t *o
     ra.flag_count = &b.counters->flagged;
     ra.out_idx = out_idx;
     ra.out_dist = out_dist;
-    ra.split = 1;  // (keys times the squared scale, unless marked)
+    ra.split = 2;
     ra.eps_coef = ra.cosine_eps = ra.split_eps = ra.split_cosine_eps = 1.0;
     return knn_launch_rerank(ra, p.nq, "rerank", stream);
 }
@@ -1619,7 +1638,16 @@ int knn_run(const KnnPlan &p, const float *Q, const float *R, int32_t *out_idx, 
     ss.Ap = b.split;
     ss.ref_map = ref_map;
     if (pruned) {
-        st = split_screen_pruned(pruned_args(p, ss, b), p.half, "screen_fp32", stream);
+        PrunedArgs pa = pruned_args(p, ss, b);
+        ScopedTimer timer("screen_fp32", stream);
+        if ((st = split_screen_pruned(pa, p.half, "screen_pruned", stream)) != RSC_OK) return st;
+        if (pa.samples > 0) {
+            ss.only_plain = ss.rotate = 1;
+            ss.own = pa.own;
+            ss.own_q = split_queries_per_group(p.d, p.half);
+            ss.own_shift = pa.seg_shift;
+            st = split_screen(ss, p.half, "screen_plain", stream);
+        }
     } else {
         st = split_screen(ss, p.half, "screen_fp32", stream);
     }

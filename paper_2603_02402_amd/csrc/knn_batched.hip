@@ -108,7 +108,7 @@ __global__ __launch_bounds__((SplitShape<Q, TC, L>::NW * kWave), (SplitShape<Q, 
         const int span = (int)(I.b1 - I.b0);
         // packed position of the tile's first query: ref_base = soff - 32 boff
         const int own = (int)((I.q0 - I.ref_base) / 32 - I.b0);
-        screen_split_tile<Q, TC, L>(ba.base, slot, row, (int)I.b0, span, max(0, min(own, span - 1)), I.p,
+        screen_split_tile<Q, TC, L>(ba.base, slot, row, (int)I.b0, span, 1, max(0, min(own, span - 1)), I.p,
                                     I.ref_base, ring0, ring1, qbuf);
     }
 }

@@ -9,10 +9,8 @@ namespace rsc {
 
 int scr::rounded_launch(const PrunedArgs &a, const char *name, hipStream_t s) {
     switch (rounded_geom(a.s.d).tc) {
-#define X(TC)                                                                        \
-    case TC:                                                                         \
-        return a.samples > 0 ? pruned_launch_geom<0, TC, 32, true, true>(a, name, s) \
-                             : pruned_launch_geom<0, TC, 32, true>(a, name, s);
+#define X(TC) \
+    case TC: return pruned_launch_geom<0, TC, 32, true>(a, name, s);
         RSC_ROUNDED_CHUNKS(X)
 #undef X
     }

@@ -79,8 +79,8 @@ struct KnnCounters {
     uint32_t query_norm_bits; // float bits of the largest query norm (rectangular problem; else 0)
     int32_t wide;             // nonzero: norms spread too far for the split screen; the FP32 chain runs (the
                               // BF16 form: its plain screen)
-    int32_t verdict;          // BF16 form: 0 none yet, kPruned, kPlain (the plain screen answers)
-    int32_t sampled;          // BF16 form: sampled tiles that know their segments
+    int32_t verdict;          // pruned screen: 0 none yet, kPruned, kPlain (a plain screen answers)
+    int32_t sampled;          // sampled tiles that know their segments
     int32_t pad;
     unsigned long long sampled_segments;  // those segments
     unsigned long long visited;  // pruned screen: segments screened, over all query tiles
@@ -170,8 +170,8 @@ struct RerankArgs {
     const float *cand_key;
     double eps_coef;
     // keys of the split FP16 screen (times its squared scale, unless the
-    // inputs were marked wide): its error bound in place of eps_coef /
-    // cosine_eps
+    // inputs were marked wide; 2: nor where the plain BF16 screen answered): its
+    // error bound in place of eps_coef / cosine_eps
     int split;
     double split_eps, split_abs, split_cosine_eps;
     KnnCounters *counters;

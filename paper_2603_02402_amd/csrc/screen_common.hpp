@@ -71,12 +71,14 @@ struct ScreenArgs {
     int64_t nblk;
     int d;
     int P;                  // reference ranges (gridDim.y)
-    int rotate;             // one matrix whose references are packed in the queries' order: each query
-                            // group starts its scan at its own block
+    int rotate;             // references packed in the queries' order (or one that `own` relates to it): each
+                            // query group starts its scan at its own block
+    const int32_t *own;     // split screen: that block for every own_q queries, in units of 1 << own_shift (null:
+    int own_q, own_shift;   // the queries are the references)
     const int32_t *ref_map; // split screen: packed slot -> row (null: row order)
     const KnnCounters *kc;  // exact path and large BF16 problems: the largest norms (the split screen's scale) and the mark
     int only_wide;          // FP32 chain: run only on inputs marked wide
-    int only_plain;         // BF16 screen: run only where the pruned screen does not answer
+    int only_plain;         // split and BF16 screen: run only where the pruned screen does not answer
     int32_t *cand_idx;
     float *cand_key;
 };

@@ -256,13 +256,13 @@ __device__ __forceinline__ void split_stream(const char *Ab, int count, Phys phy
     }
 }
 
-// One tile of 32 queries per wave over the `span` packed blocks from b0 on,
-// starting at the `rot`-th and around: every wave of the workgroup calls this
+// One tile of 32 queries per wave over `span` packed blocks, every `stride`-th from
+// b0 on, starting at the `rot`-th and around: every wave of the workgroup calls this
 // together.  slot / row: this lane's output slot and query row (or -1);
 // ref_base: reference row of packed row 0.
 template <int Q, int TC, int L>
 __device__ __forceinline__ void screen_split_tile(const ScreenArgs &a, int64_t slot, int64_t row, int b0, int span,
-                                                  int rot, int p, int64_t ref_base, char *ring0, char *ring1,
+                                                  int stride, int rot, int p, int64_t ref_base, char *ring0, char *ring1,
                                                   double *qbuf) {
     using S = SplitShape<Q, TC, L>;
     const int h = (threadIdx.x & (kWave - 1)) >> 5;
@@ -277,7 +277,7 @@ __device__ __forceinline__ void screen_split_tile(const ScreenArgs &a, int64_t s
         [&](int i) {  // packed block of position i of the scan
             int j = rot + i;
             if (j >= span) j -= span;
-            return b0 + j;
+            return b0 + j * stride;
         },
         ring0, ring1, [&](const f16x8(&A)[2 * Q + TC], int blk) {
             top.offer(split_keys(A, qop), (int)(ref_base + (int64_t)blk * 32) + 4 * h, q, qs);

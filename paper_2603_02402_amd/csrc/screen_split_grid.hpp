@@ -13,8 +13,9 @@ struct PrunedArgs {
     const int32_t *own;
     double eps;              // error coefficient of a split key
     bool rounded;            // BF16 rows: one FP16 part each (lists of 32)
-    int samples;             // BF16 rows: tiles that tell whether the plain screen is to answer (none: it is not asked),
+    int samples;             // tiles that tell whether a plain screen is to answer (none: it is not asked),
     int plain_over;          // and the segments of a range, on their average, above which it is
+    int wait_over;           // a tile with more of them waits for the verdict
     KnnCounters *counters;   // statistics; the mark for the plain screen
 };
 
@@ -37,19 +38,26 @@ __global__ __launch_bounds__((SplitShape<Q, TC, L>::NW * kWave), (SplitShape<Q, 
     __shared__ __attribute__((aligned(16))) char ring0[S::RING];
     __shared__ __attribute__((aligned(16))) char ring1[S::RING];
     __shared__ double qbuf[S::QCAP * S::NW * kWave];
-    if (a.kc->wide) return;
+    if (a.kc->wide || (a.only_plain && a.kc->verdict != kPlain)) return;
     const int tid = threadIdx.x;
     const int wave = tid >> 6, c = tid & 31;
     const int p = blockIdx.y;
-    const int nblk = (int)a.nblk, per = (nblk + a.P - 1) / a.P, b0 = p * per;  // range p: a run of blocks
-    const int span = max(0, min(per, nblk - b0));
+    // range p: a run of blocks; rotated: every P-th block, as near rows follow each other
+    const int nblk = (int)a.nblk, per = (nblk + a.P - 1) / a.P;
+    const int b0 = a.rotate ? p : p * per, stride = a.rotate ? a.P : 1;
+    const int span = a.rotate ? (nblk - p + a.P - 1) / a.P : max(0, min(per, nblk - b0));
     const int64_t nslots = screen_slots(a);
     const int qg = blockDim.x / 2;  // queries of the workgroup
     for (int64_t qblk = blockIdx.x; qblk * qg < nslots; qblk += gridDim.x) {
         const int64_t slot = qblk * qg + wave * 32 + c;
         int64_t row = -1;
         if (slot < nslots) row = a.qlist ? (int64_t)a.qlist[slot] : slot;
-        screen_split_tile<Q, TC, L>(a, slot < nslots ? slot : -1, row, b0, span, 0, p, 0, ring0, ring1, qbuf);
+        int rot = 0;
+        if (a.rotate) {
+            const int64_t own = a.own ? (int64_t)a.own[qblk * qg / a.own_q] << a.own_shift : qblk * qg / 32;
+            rot = max(0, min((int)(own / a.P), span - 1));
+        }
+        screen_split_tile<Q, TC, L>(a, slot < nslots ? slot : -1, row, b0, span, stride, rot, p, 0, ring0, ring1, qbuf);
     }
 }
 
@@ -80,25 +88,25 @@ int split_launch_geom(const ScreenArgs &a, const char *name, hipStream_t s) {
 // ONE: the BF16 form's rounded rows, a chain of one product per dimension (500k
 // rows, d = 50: screen 40 -> 9 ms).
 //
-// SAMPLE: rounded rows without clusters are answered by the plain BF16 screen,
-// which merges its lists at three waves per SIMD where this one has two: 200k
-// rows, d = 50, both screens: with every segment visited 19.3 ms pruned, 13.9
-// plain; with 0.50 of them 11.8 and 11.9; 0.30: 6.8 and 9.1.  The first workgroups
-// (PrunedArgs::samples) take tiles spread evenly over all; the last of these to
-// know its segments gives the verdict: plain where they are more than
-// PrunedArgs::plain_over on average.  A workgroup whose own last list is that long
-// waits for the verdict (those that start with the samples: they know theirs at
-// about the same time) and ends if it is plain.  The plain screen then takes all
-// queries, so the answer does not depend on who waited how long.
+// Rows without clusters are answered by a plain screen: the BF16 form's, which
+// merges its lists at three waves per SIMD where this one has two, or the exact
+// form's unpruned one in the same order, without this one's spills (lists of 32).
+// The first workgroups (PrunedArgs::samples) take tiles spread evenly over all;
+// the last of these to know its segments gives the verdict: plain where they are
+// more than PrunedArgs::plain_over on average.  A workgroup whose own last list is
+// long (PrunedArgs::wait_over) waits for the verdict (those that start with the samples: they know
+// theirs at about the same time) and ends if it is plain.  The plain screen then
+// takes all queries, so the answer does not depend on who waited how long.
 // (Looking for the verdict during the last list instead: the loop around the ring
 // spills up to 77 registers more.  Leaving only the tiles with long lists to the
-// plain screen: a few of them run for as long as many, 500k rows 10.4 -> 13.5 ms.)
+// plain screen: a few of them run for as long as many, 500k BF16 rows 10.4 -> 13.5
+// ms.)
 constexpr int kSampleTiles = 64;
 constexpr int kWaitLooks = 4000;  // looks for the verdict, about a microsecond each
 
 // Tile of workgroup x: the samples i tiles / samples first, then the others in order.
 __device__ __forceinline__ int sampled_tile(int x, int tiles, int samples) {
-    if (samples == tiles) return x;
+    if (samples == 0 || samples == tiles) return x;
     if (x < samples) return (int)((int64_t)x * tiles / samples);
     // of the samples' runs (a sample, then the tiles to the next one): the last whose others start at or before x
     int lo = 0, hi = samples - 1;
@@ -109,7 +117,7 @@ __device__ __forceinline__ int sampled_tile(int x, int tiles, int samples) {
     return x - samples + lo + 1;
 }
 
-template <int Q, int TC, int L, bool ONE, bool SAMPLE>
+template <int Q, int TC, int L, bool ONE>
 __global__ __launch_bounds__((SplitShape<Q, TC, L>::NW * kWave), (SplitShape<Q, TC, L>::W)) void k_split_pruned(
     PrunedArgs pa) {
     using S = SplitShape<Q, TC, L>;
@@ -141,13 +149,12 @@ __global__ __launch_bounds__((SplitShape<Q, TC, L>::NW * kWave), (SplitShape<Q, 
         __syncthreads();
         return verdict == kPlain;
     };
-    if constexpr (SAMPLE)
-        if (plain(1)) return;
+    if (pa.samples > 0 && plain(1)) return;
     const int p = blockIdx.y, P = a.P;
     const int nblk = (int)a.nblk, nseg = pa.nseg, sh = pa.seg_shift, nw = (nseg + 31) / 32;
     const int qg = blockDim.x / 2, qs = blockDim.x;
     const int64_t nslots = screen_slots(a);
-    const int64_t tile = SAMPLE ? sampled_tile(blockIdx.x, gridDim.x, pa.samples) : (int)blockIdx.x;
+    const int64_t tile = sampled_tile(blockIdx.x, gridDim.x, pa.samples);
     const int64_t slot = tile * qg + wave * 32 + (lane & 31);
     const int64_t row = slot < nslots ? (a.qlist ? (int64_t)a.qlist[slot] : slot) : -1;
     const float scale = ldexpf(1.f, split_exponent(a.kc));
@@ -257,20 +264,18 @@ __global__ __launch_bounds__((SplitShape<Q, TC, L>::NW * kWave), (SplitShape<Q, 
                 break;
             }
         }
-        if constexpr (SAMPLE) {
-            if (final) {
-                if (p == 0 && (int)blockIdx.x < pa.samples && tid == 0) {
-                    KnnCounters *kc = pa.counters;
-                    atomicAdd(&kc->sampled_segments, (unsigned long long)(visited + total));
-                    __threadfence();
-                    if (atomicAdd(&kc->sampled, 1) == pa.samples - 1) {
-                        const double seen = (double)atomicAdd(&kc->sampled_segments, 0ull);
-                        const int v = seen > (double)pa.plain_over * pa.samples ? kPlain : kPruned;
-                        __hip_atomic_store(&kc->verdict, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    }
+        if (pa.samples > 0 && final) {
+            if (p == 0 && (int)blockIdx.x < pa.samples && tid == 0) {
+                KnnCounters *kc = pa.counters;
+                atomicAdd(&kc->sampled_segments, (unsigned long long)(visited + total));
+                __threadfence();
+                if (atomicAdd(&kc->sampled, 1) == pa.samples - 1) {
+                    const double seen = (double)atomicAdd(&kc->sampled_segments, 0ull);
+                    const int v = seen > (double)pa.plain_over * pa.samples ? kPlain : kPruned;
+                    __hip_atomic_store(&kc->verdict, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
-                if (visited + total > pa.plain_over && plain(kWaitLooks)) return;
             }
+            if (visited + total > pa.wait_over && plain(kWaitLooks)) return;
         }
         int at = 0;
         for (int i = 0; i < nw; ++i) at += i < tid ? count[i] : 0;
@@ -283,12 +288,12 @@ __global__ __launch_bounds__((SplitShape<Q, TC, L>::NW * kWave), (SplitShape<Q, 
     if (tid == 0) atomicAdd(&pa.counters->visited, (unsigned long long)visited);
 }
 
-template <int Q, int TC, int L, bool ONE = false, bool SAMPLE = false>
+template <int Q, int TC, int L, bool ONE = false>
 int pruned_launch_geom(const PrunedArgs &a, const char *name, hipStream_t s) {
     using S = SplitShape<Q, TC, L>;
     ScopedTimer timer(name, s);
     const unsigned gx = (unsigned)((a.s.nq + S::QG - 1) / S::QG);
-    hipLaunchKernelGGL((k_split_pruned<Q, TC, L, ONE, SAMPLE>), dim3(gx, (unsigned)a.s.P), dim3(S::NW * kWave), 0, s, a);
+    hipLaunchKernelGGL((k_split_pruned<Q, TC, L, ONE>), dim3(gx, (unsigned)a.s.P), dim3(S::NW * kWave), 0, s, a);
     return launch_status(name);
 }
 
