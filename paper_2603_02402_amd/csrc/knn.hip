@@ -1400,7 +1400,7 @@ PrunedArgs pruned_args(const KnnPlan &p, const ScreenArgs &s, const KnnBuffers &
                                  : p.half == 32 && chunks >= 5 && chunks <= 25 &&
                                        (blocks * chunks >= 1792 || tiles * p.splits >= 4 * scr::kCUs);
     if (pays && (p.self_mode || 4 * tiles > scr::kCUs)) {
-        pa.samples = (int)std::min<int64_t>(scr::kSampleTiles, tiles);
+        pa.samples = (int)std::min<int64_t>(pa.rounded ? 64 : 16, tiles);
         // Both take the same time, BF16 at about half of the segments (200k rows, d = 50:
         // 0.50 of them 11.8 ms pruned, 11.9 plain; 0.30 6.8 and 9.1); exact at 0.6 to 0.8
         // (100k, d = 80, 0.65 of them 8.1, 8.2; 40k, d = 50, 0.83 of them 2.10, 1.77), with

@@ -97,11 +97,13 @@ int split_launch_geom(const ScreenArgs &a, const char *name, hipStream_t s) {
 // long (PrunedArgs::wait_over) waits for the verdict (those that start with the samples: they know
 // theirs at about the same time) and ends if it is plain.  The plain screen then
 // takes all queries, so the answer does not depend on who waited how long.
+// Samples far from each other share no segments in the caches: 64 of the exact
+// form's 782 workgroups of 100k rows (d = 35, 20 clusters) cost 9% of the call, 16
+// of them 4.
 // (Looking for the verdict during the last list instead: the loop around the ring
 // spills up to 77 registers more.  Leaving only the tiles with long lists to the
 // plain screen: a few of them run for as long as many, 500k BF16 rows 10.4 -> 13.5
 // ms.)
-constexpr int kSampleTiles = 64;
 constexpr int kWaitLooks = 4000;  // looks for the verdict, about a microsecond each
 
 // Tile of workgroup x: the samples i tiles / samples first, then the others in order.
