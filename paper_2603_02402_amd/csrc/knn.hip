@@ -1224,16 +1224,15 @@ int knn_plan(int64_t nq, int64_t nr, int d, int k, const rsc_knn_opts *opts, boo
     }
     // (two ranges even out tiles of different cost while each CU gets about one)
     if (plan->pruned && nq < 512 * split_queries_per_group(d, plan->half)) plan->splits = std::max(plan->splits, 2);
-    // One workgroup a CU at a time: few tiles take as many ranges as fill one round,
-    // and three of them two rounds where two would leave the second nearly empty
-    // (20k rows, 79 tiles, d = 10, k = 15: 4 ranges 0.76 ms, 3 0.54; 42k, 165 tiles,
-    // 2 ranges 1.54, 3 1.29).
+    // One workgroup a CU at a time: few tiles take as many ranges as fill one round
+    // (20k rows, 79 tiles, d = 10, k = 15, without clusters: 4 ranges 0.76 ms, 3 0.54;
+    // in 78 clusters, d = 60, k = 30, 0.67, 0.51).  Two ranges beyond: three would fill
+    // the second round of 129 to 170 tiles (42k rows without clusters 1.54 -> 1.29), but
+    // in clusters, where the tiles differ, they cost up to a quarter (33k, d = 38, k = 50,
+    // 0.60 -> 0.76).
     if (plan->pruned && self_mode && precision == RSC_FP32) {
         const int64_t qg = split_queries_per_group(d, plan->half), tiles = (nq + qg - 1) / qg;
-        if (tiles <= kCUs / 2)
-            plan->splits = (int)(kCUs / tiles);
-        else if (tiles <= kCUs)
-            plan->splits = 3 * tiles <= 2 * kCUs ? 3 : 2;
+        if (tiles <= kCUs / 2) plan->splits = (int)(kCUs / tiles);
     }
     if (split) {
         // enough (range, half) lists that the m nearest fill each to about half; rows in
