@@ -66,14 +66,17 @@ constexpr int kMaxKLowp = 63;
 constexpr int64_t kPruneRows = 16384;
 constexpr double kPrunePairs = 2.5e8;
 // Foreign queries from which it is: fewer pay for ordering the references without
-// a gain (k = 15, in ms, not pruned and pruned: 600 of 1M rows, d = 20, 1.04, 2.88;
-// 2000 of 500k, d = 50, 1.15, 1.78; 5000 of 1M 3.63, 3.81; 12,000 1.0 to 1.35 times
-// as long without).
-constexpr int64_t kPruneQueries = 6000;
+// a gain (in ms, not pruned and pruned, rows in 5 to 100 clusters: 600 of 1M rows,
+// d = 20, k = 15, 1.04, 2.88; 2000 of 500k, d = 50, 1.15, 1.78; 4500 of 300k, d = 50,
+// k = 30, 1.89, 1.80 to 2.39; of 800k, d = 90, 4.28, 4.70 to 4.94, d = 20 2.19, 1.86 to
+// 2.13; 12,000 1.0 to 1.35 times as long without).
+constexpr int64_t kPruneQueries = 4000;
 // Rows from which answers longer than 64 are: near rows crowd a range's lists, and
-// some rows are searched again (d = 50, k = 100, in ms, not pruned and pruned: 20k
-// rows 1.35, 2.55, in separate clusters 1.36, 1.57; 40k 3.55, 4.04 and 3.55, 2.34).
-constexpr int64_t kPruneRowsLong = 32768;
+// some rows are searched again (in ms, not pruned and pruned, rows in 5, 30 and 78
+// clusters: 20k rows, d = 50, k = 100, 1.35; 1.74, 1.54, 1.02; d = 90, k = 100, 2.06;
+// 2.60, 2.09, 2.25; 25k, d = 50, k = 255, 2.97; 2.68, 2.50, 2.67; d = 90, k = 100 32k
+// 3.28; 3.72, 2.69, 2.64).
+constexpr int64_t kPruneRowsLong = 20480;
 // Foreign queries from which the BF16 form is pruned: fewer do not pay for ordering
 // the references.  In ms, plain and pruned, rows in 100 clusters: 2500 queries of
 // 100k rows 0.89, 1.05; 3500 1.24, 1.10; 3500 of 500k 2.27, 2.71; 5000 2.70, 2.70;

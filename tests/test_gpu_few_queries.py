@@ -29,12 +29,12 @@ def rows(n, d, seed):
         torch.randint(0, 30, (n,), generator=gen, device="cuda")]
 
 
-@pytest.mark.parametrize("nq,n,d,k", [(300, 1000000, 20, 15), (2000, 500000, 50, 15), (5999, 60000, 50, 30),
-                                      (6000, 60000, 50, 30), (5999, 60001, 9, 100)])
+@pytest.mark.parametrize("nq,n,d,k", [(300, 1000000, 20, 15), (2000, 500000, 50, 15), (3999, 70000, 50, 30),
+                                      (4000, 70000, 50, 30), (3999, 70001, 9, 100)])
 def test_queries(nq, n, d, k):
     X, Q = rows(n, d, 1), rows(nq, d, 2)
     ws = rsc.Workspace("cuda")
-    assert ordered(lambda: rsc.knn(X, k, Q=Q, workspace=ws)) == (nq >= 6000)
+    assert ordered(lambda: rsc.knn(X, k, Q=Q, workspace=ws)) == (nq >= 4000)
     idx, dist = rsc.knn(X, k, Q=Q, workspace=ws)
     Xn = X.cpu().numpy()
     for i in (0, 1, nq // 2, nq - 1):

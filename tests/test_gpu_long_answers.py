@@ -25,7 +25,7 @@ def test_lists_suffice(oracle_mod, n, d, k):
     assert res["exact_rows"] + res["near_tie_rows"] == at.size
 
 
-@pytest.mark.parametrize("n,k,order", [(20000, 65, True), (20000, 66, False), (32767, 66, False), (32768, 66, True)])
+@pytest.mark.parametrize("n,k,order", [(20000, 65, True), (20000, 66, False), (20479, 66, False), (20480, 66, True)])
 def test_order(oracle_mod, n, k, order):
     X = rows(n, 50, 3)
     ws = rsc.Workspace("cuda")
