@@ -1207,7 +1207,7 @@ int knn_plan(int64_t nq, int64_t nr, int d, int k, const rsc_knn_opts *opts, boo
                    (double)nq * (double)nr >= kPrunePairs;
     if (!self_mode && nq < (precision == RSC_BF16 ? prune_queries_bf16(nr) : kPruneQueries)) plan->pruned = false;
     const int m = self_mode ? k - 1 : k;
-    const bool long_answer = m > kLeanAnswer;
+    const bool long_answer = k > kLeanAnswer + 1;  // (either mode: one workspace serves both)
     if (long_answer && nr < kPruneRowsLong) plan->pruned = false;
     const bool split = precision == RSC_FP32 || plan->pruned;
     // the split screen's workgroups of 8 waves fill a CU each; the others run four of 4 waves
