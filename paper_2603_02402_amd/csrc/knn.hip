@@ -1235,7 +1235,7 @@ int knn_plan(int64_t nq, int64_t nr, int d, int k, const rsc_knn_opts *opts, boo
     // 0.60 -> 0.76).
     if (plan->pruned && self_mode && precision == RSC_FP32) {
         const int64_t qg = split_queries_per_group(d, plan->half), tiles = (nq + qg - 1) / qg;
-        if (tiles <= kCUs / 2) plan->splits = (int)(kCUs / tiles);
+        if (tiles <= kCUs / 2) plan->splits = (int)std::min<int64_t>(plan->splits, kCUs / tiles);
     }
     if (split) {
         // enough (range, half) lists that the m nearest fill each to about half; rows in

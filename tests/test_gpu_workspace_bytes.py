@@ -25,3 +25,24 @@ def test_square_and_rectangular(n, precision):
         assert lib.rsc_knn_opt(ptr(X), n, d, k, ctypes.byref(o), ptr(idx), ptr(dist), ptr(ws), need, stream) == 0, (k, need)
         assert lib.rsc_knn_ex(ptr(X), n, ptr(X), n, d, k, ctypes.byref(o), ptr(idx), ptr(dist), ptr(ws), need, stream) == 0
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("n,listed", [(300000, 900), (300000, 20000), (20000, 15000)])
+def test_listed_rows(n, listed):
+    """The exact rows of a probed search, few of many: their plan keeps to 32 ranges, and the answers to the exact search's."""
+    import numpy as np
+
+    gen = torch.Generator().manual_seed(n)
+    X = torch.randn((n, 20), generator=gen).cuda()
+    label = torch.randint(0, 64, (n,), generator=gen).numpy()
+    perm = np.argsort(label, kind="stable").astype(np.int32)
+    off = np.concatenate([[0], np.cumsum(np.bincount(label, minlength=64))]).astype(np.int64)
+    probes = np.stack([label, (label + 1) % 64], 1).astype(np.int32)
+    mark = torch.zeros((n,), dtype=torch.uint8)
+    mark[torch.randperm(n, generator=gen)[:listed]] = 1
+    idx, dist, route, _ = rsc.knn_probed(X, 15, *[torch.from_numpy(a).cuda() for a in (off, perm, probes)],
+                                         exact_rows=mark.cuda())
+    want, wdist = rsc.knn(X, 15)
+    rows = route != 0
+    assert int(rows.sum()) >= listed
+    assert torch.equal(idx[rows], want[rows]) and torch.equal(dist[rows], wdist[rows])
