@@ -209,8 +209,9 @@ size_t rsc_knn_batched_workspace_bytes(const int64_t *offsets, int32_t S, int32_
 
 /* Exact kNN of every sample (same output layout and exactness as rsc_knn,
  * neighbours drawn from the row's own sample).  Uses the scheduling policy
- * the autotuner chose for this batch shape, else a default.  Synchronises
- * `stream` once (to upload the work list into the workspace). */
+ * the autotuner chose for this batch shape, else a default; batches too small
+ * to fill the device split their samples' references where nothing is tuned.
+ * Synchronises `stream` once (to upload the work list into the workspace). */
 int rsc_knn_batched(const float *X, const int64_t *offsets, int32_t S, int32_t d, int32_t k, int32_t *out_idx,
                     float *out_dist, void *workspace, size_t workspace_bytes, void *stream);
 

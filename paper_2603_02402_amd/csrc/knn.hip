@@ -7,31 +7,27 @@
 //
 //   key_ij = ||y_j||^2 - 2 x_i . y_j      (= d_ij - ||x_i||^2, same order per row)
 //
-// Data path of the screen (one wave = 32 queries, one workgroup = 4 waves):
-//   * the query operand (-2 x) stays in VGPRs for the whole launch;
-//   * references are repacked once into the MFMA A-operand order (one
-//     float4 per lane per four contraction steps, 1 KiB per wave load, fully
-//     coalesced) and streamed HBM/MALL/L2 -> VGPR, each float4 of the next
-//     block loaded as soon as the current one has been consumed; no LDS and
-//     no workgroup barrier;
-//   * when the half-width leaves a spare contraction slot, ||y||^2 rides in
-//     it (times 1 on the query side), so the MFMA chain produces the key;
-//     otherwise the norm is added in the epilogue;
-//   * each lane keeps, in registers, the sorted 16 (or 32) smallest keys of
-//     the references its contraction half sees (every other group of four
-//     rows); a key below the lane's current 16th enters by an unrolled
-//     compare-and-shift, so the common case costs one compare per pair.
-// A launch may split the references into P ranges (blockIdx.y) to give
-// small problems enough workgroups; each range keeps its own heap.
+// The screen.  Operands are split into two FP16 parts and the keys accumulated in
+// float32 (screen_split.hpp): the references are packed once in MFMA operand
+// order and pass through an LDS ring that a workgroup of 8 waves, 32 queries
+// each, shares; a lane keeps, in registers, the 16 or 32 smallest keys of the
+// half of the rows its contraction half sees.  Large problems are searched in a
+// spatial order whose segments carry bounds (k_split_pruned); where bounds do
+// not help, lists of 32 and the BF16 form go to a scan of everything.  Inputs
+// whose norms spread too far for FP16 parts are marked, and the FP32 chain
+// (screen_fp32.hpp) answers them: both are launched, one returns at once.
+// A launch may split the references into P ranges (blockIdx.y) to give small
+// problems enough workgroups and long answers enough lists.
 //
-// The float32 screen is not the answer.  Its rounding error is bounded per
-// query, every candidate is re-ranked with float64 distances summed from
-// direct differences in dimension order, and a row is certified exact when
-// its m-th re-ranked distance is below the smallest key any range could
-// have rejected, minus the bound.  Rows that fail go through a second,
-// wider screen over many reference ranges (escalation) and, if they fail
-// again, an exhaustive float64 scan.  Ties are broken towards the lower
-// index throughout.
+// The screen is not the answer.  Its rounding error is bounded per query, every
+// candidate is re-ranked with float64 distances summed from direct differences
+// in dimension order, and a row is certified exact when its m-th re-ranked
+// distance is below the smallest key any range could have rejected, minus the
+// bound.  Rows that fail collect every reference whose key can lie below the
+// distance found (answers to 64; k_split_collect) or go through a wider FP32
+// screen over many ranges (longer ones), and an exhaustive float64 scan where
+// that does not settle them either.  Ties are broken towards the lower index
+// throughout.
 
 #include <hip/hip_runtime.h>
 
@@ -62,7 +58,7 @@ constexpr int kMaxKLowp = 63;
 // the pairs of that square.  The BF16 form's rows (64 candidates a query) take
 // the same path from there: 16.5k rows 1.40 -> 0.72 ms, 40k 2.25 -> 1.02, 500k
 // 44.4 -> 14.6 (100 clusters, with their graph).  Rows without clusters gain
-// nothing from bounds; the BF16 form finds that out (knn_run_rounded).
+// nothing from bounds: a sample of the tiles finds that out (pruned_args).
 constexpr int64_t kPruneRows = 16384;
 constexpr double kPrunePairs = 2.5e8;
 // Foreign queries from which it is: fewer pay for ordering the references without

@@ -7,9 +7,10 @@
 // fill together and fewer merges and fewer blocks with any key below a
 // threshold occur.  The order is a Morton (Z-order) code of the first three
 // coordinates, each quantised to 10 bits over its range, sorted by rocPRIM's
-// radix sort; the rows' results are written back in row order, so the order
-// changes which candidates a screen keeps only through the threshold
-// history, never the rows of the answer.
+// radix sort (in pieces while a stream is recorded, order_sort.hpp); the rows'
+// results are written back in row order, so the order changes which candidates
+// a screen keeps only through the threshold history, never the rows of the
+// answer.
 
 #include <hip/hip_runtime.h>
 

@@ -1,8 +1,8 @@
 // Probed and routed kNN: each query is compared with the cells of the
-// partitions it probes, on the same FP32 MFMA screen, float64 rerank and
-// certificate as the exact path, and rows that are marked (or whose screen
-// cannot be certified inside their partitions) are answered by the exact
-// path over all cells.
+// partitions it probes, on the exact path's split FP16 screen (the FP32 chain for
+// inputs marked wide), float64 rerank and certificate, and rows that are marked
+// (or whose screen cannot be certified inside their partitions) are answered by
+// the exact path over all cells.
 //
 // Layout.  The cells are packed once in partition order: partition p owns
 // the 32-row blocks [pblk[p], pblk[p+1]) of one packed array (its last block
@@ -10,13 +10,15 @@
 //
 // Work.  Probed queries are grouped by their own partition (cells of one
 // partition probe nearly the same partitions) and cut into tiles of 32
-// queries.  A persistent grid pops tiles from an atomic counter; a wave
-// builds the union of its 32 queries' probe lists as a bitmap in LDS, walks
-// the union's partitions in ascending order and streams their blocks through
-// the MFMA chain once for all 32 queries.  Each lane walks its own query's
-// sorted probe list alongside, and keys of partitions the query did not
-// probe are dropped before selection, so a query's answer is exactly the
-// nearest cells among its own probed partitions, whatever tile it lands in.
+// queries, a wave each.  A persistent grid pops workgroups' tiles from an atomic
+// counter; a workgroup builds the union of its queries' probe lists as a bitmap
+// in LDS and passes the union's blocks through an LDS ring once for all of them,
+// its own partition first and around.  A wave sits out the partitions none of its
+// queries probed; each lane walks its own query's sorted probe list alongside,
+// and keys of partitions the query did not probe are dropped before selection,
+// so a query's answer is exactly the nearest cells among its own probed
+// partitions, whatever tile it lands in.  (The FP32 chain takes one tile per wave
+// and streams the blocks without a ring.)
 
 #include <hip/hip_runtime.h>
 
@@ -86,8 +88,9 @@ int pick_dh_local(int d) {
 // kExactSlack more rows.  What grows with the ranges is the candidates alone, F
 // times their number: knn_plan asks for at most 256 workgroups of at most 256
 // queries, which adds fewer than 256 * 256 + 256 rows to F; below 512 of them it
-// takes two ranges, which adds fewer than 512 * 256.  (A third rule, two ranges for more than 33 neighbours, has no such bound:
-// where its plan does not fit, one range does.)
+// takes two ranges, which adds fewer than 512 * 256.  (A third rule, two ranges for
+// more than 33 neighbours, has no such bound: where its plan does not fit, one
+// range does.)
 int exact_plan(int64_t F, int64_t n, int d, int k, KnnPlan *p) {
     const int st = knn_plan(F, n, d, k, nullptr, true, p);
     p->pruned = false;

@@ -29,7 +29,7 @@ def test_square_and_rectangular(n, precision):
 
 @pytest.mark.parametrize("n,listed", [(300000, 900), (300000, 20000), (20000, 15000)])
 def test_listed_rows(n, listed):
-    """The exact rows of a probed search, few of many: their plan keeps to 32 ranges, and the answers to the exact search's."""
+    """The exact rows of a probed search, few of many: the answers are the exact search's."""
     import numpy as np
 
     gen = torch.Generator().manual_seed(n)
