@@ -148,6 +148,8 @@ def screened_pairs(ws, n: int):
     seg = 1
     while (blocks + seg - 1) // seg > 8192:
         seg *= 2
+    if int(ws.buf[28:32].view(torch.int32)[0]) == 2:  # a plain screen answered
+        return float(n) * n
     visited = int(ws.buf[32:40].view(torch.int64)[0])
     return visited * seg * 32 * 256
 

@@ -80,10 +80,10 @@ struct KnnCounters {
     int32_t wide;             // nonzero: norms spread too far for the split screen; the FP32 chain runs (the
                               // BF16 form: its plain screen)
     int32_t verdict;          // pruned screen: 0 none yet, kPruned, kPlain (a plain screen answers)
+    unsigned long long visited;  // pruned screen: segments screened, over all query tiles (bench.py reads it here)
     int32_t sampled;          // sampled tiles that know their segments
     int32_t pad;
     unsigned long long sampled_segments;  // those segments
-    unsigned long long visited;  // pruned screen: segments screened, over all query tiles
 };
 
 constexpr int kPruned = 1, kPlain = 2;  // KnnCounters::verdict
