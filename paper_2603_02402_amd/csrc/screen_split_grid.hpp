@@ -14,6 +14,7 @@ struct PrunedArgs {
     double eps;              // error coefficient of a split key
     bool rounded;            // BF16 rows: one FP16 part each (lists of 32)
     int samples;             // tiles that tell whether a plain screen is to answer (none: it is not asked),
+    int sample_step;         // every so many tiles from the first on (0: the samples come first, from all tiles),
     int plain_over;          // and the segments of a range, on their average, above which it is
     int wait_over;           // a tile with more of them waits for the verdict
     KnnCounters *counters;   // statistics; the mark for the plain screen
@@ -99,7 +100,7 @@ int split_launch_geom(const ScreenArgs &a, const char *name, hipStream_t s) {
 // takes all queries, so the answer does not depend on who waited how long.
 // Samples far from each other share no segments in the caches: 64 of the exact
 // form's 782 workgroups of 100k rows (d = 35, 20 clusters) cost 9% of the call, 16
-// of them 4.
+// of them 4.  Up to two rounds of tiles the exact form's stay in their place.
 // (Looking for the verdict during the last list instead: the loop around the ring
 // spills up to 77 registers more.  Leaving only the tiles with long lists to the
 // plain screen: a few of them run for as long as many, 500k BF16 rows 10.4 -> 13.5
@@ -156,7 +157,7 @@ __global__ __launch_bounds__((SplitShape<Q, TC, L>::NW * kWave), (SplitShape<Q, 
     const int nblk = (int)a.nblk, nseg = pa.nseg, sh = pa.seg_shift, nw = (nseg + 31) / 32;
     const int qg = blockDim.x / 2, qs = blockDim.x;
     const int64_t nslots = screen_slots(a);
-    const int64_t tile = sampled_tile(blockIdx.x, gridDim.x, pa.samples);
+    const int64_t tile = pa.sample_step ? (int)blockIdx.x : sampled_tile(blockIdx.x, gridDim.x, pa.samples);
     const int64_t slot = tile * qg + wave * 32 + (lane & 31);
     const int64_t row = slot < nslots ? (a.qlist ? (int64_t)a.qlist[slot] : slot) : -1;
     const float scale = ldexpf(1.f, split_exponent(a.kc));
@@ -267,7 +268,8 @@ __global__ __launch_bounds__((SplitShape<Q, TC, L>::NW * kWave), (SplitShape<Q, 
             }
         }
         if (pa.samples > 0 && final) {
-            if (p == 0 && (int)blockIdx.x < pa.samples && tid == 0) {
+            const int x = blockIdx.x, step = pa.sample_step;
+            if (p == 0 && tid == 0 && (step ? x % step == 0 && x / step < pa.samples : x < pa.samples)) {
                 KnnCounters *kc = pa.counters;
                 atomicAdd(&kc->sampled_segments, (unsigned long long)(visited + total));
                 __threadfence();
